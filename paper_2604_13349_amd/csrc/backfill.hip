@@ -8,7 +8,7 @@
 //                certified).
 //   del_stats  : for heads that still need it, one streaming pass over V accumulating the Gram
 //                matrix V_del^T V_del, the mass-weighted sum of deleted values and ||V_del||_F^2
-//                (del_stats_mfma.hip for bf16 head_dim-128 caches, k_bf_del_stats below otherwise).
+//                (del_stats_mfma.hip for bf16 head_dim-128 caches, del_stats_generic.hip otherwise).
 //                R itself (Eq. 3) is never materialised: R^T R = P (V_del^T V_del) P and
 //                sum_j w_j R_j = P sum_j w_j V_j with P = I - Q Q^T.
 //   finalize   : per head, an orthonormal basis Z of the complement of the retained span, the eigenpairs of
@@ -488,86 +488,6 @@ __global__ __launch_bounds__(KB_THREADS) void k_bf_plain_state(const float* __re
     s.active = (rank > 0 && n > 0 && N - n > 0) ? 1 : 0;
     s.k_used = 0; s.pad = 0; s.rcr = 0.f; s.ivn = 0.f;
     state[head] = s;
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// del_stats: partial V_del^T V_del, sum_j A_j v_j and ||V_del||^2 over one chunk of tokens
-constexpr int DS_THREADS = 256;
-constexpr int DS_TOK = 32;
-
-template <typename T>
-__global__ __launch_bounds__(DS_THREADS) void k_bf_del_stats(const T* __restrict__ V, const float* __restrict__ scores,
-                                                             const int32_t* __restrict__ idx, int N, int d,
-                                                             int max_budget, int nstat,
-                                                             const HeadState* __restrict__ state,
-                                                             const int32_t* __restrict__ n_keep /*non-null: do not read the head states*/,
-                                                             float* __restrict__ gram_part, int scs, int kvs) {
-  const int head = blockIdx.y, chunk = blockIdx.x;
-  const int n = n_keep ? n_keep[head] : state[head].n_keep;
-  if (n_keep ? !(n > 0 && n < N) : !state[head].active) return;
-  extern __shared__ float Vs[];              // [DS_TOK][d], retained rows zeroed
-  __shared__ float wt[DS_TOK];               // score of the token (0 for rows that are not deleted)
-  __shared__ int isdel[DS_TOK];              // 1: deleted row of this chunk
-  const int32_t* id = idx + (size_t)head * max_budget;
-  const T* Vh = V + (size_t)head * kvs * d;
-  const float* sc = scores + (size_t)head * scs;
-  const int t0 = chunk * kStatChunk, t1 = min(N, t0 + kStatChunk);
-  const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-  const int bs = d / 16;
-  float acc[8][8];
-  for (int a = 0; a < 8; ++a) for (int b = 0; b < 8; ++b) acc[a][b] = 0.f;
-  float u = 0.f, su = 0.f, nn = 0.f;         // threads < d: weighted and plain column sums, squared norm share
-
-  for (int tt = t0; tt < t1; tt += DS_TOK) {
-    __syncthreads();
-    if (threadIdx.x < DS_TOK) {
-      const int j = tt + threadIdx.x;
-      float wgt = 0.f;
-      int del = 0;
-      if (j < t1) {
-        int lo = 0, hi = n;                  // is j in the ascending retained list?
-        while (lo < hi) { const int mid = (lo + hi) >> 1; if (id[mid] < j) lo = mid + 1; else hi = mid; }
-        del = !(lo < n && id[lo] == j);
-        wgt = del ? sc[j] : 0.f;
-      }
-      wt[threadIdx.x] = wgt;
-      isdel[threadIdx.x] = del;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < DS_TOK * d; e += DS_THREADS) {
-      const int i = e / d, c = e - i * d;
-      Vs[e] = isdel[i] ? Elem<T>::load(Vh + (size_t)(tt + i) * d + c) : 0.f;
-    }
-    __syncthreads();
-    for (int i = 0; i < DS_TOK; ++i) {
-      float av[8], bv[8];
-      for (int a = 0; a < bs; ++a) av[a] = Vs[i * d + ty * bs + a];
-      for (int b = 0; b < bs; ++b) bv[b] = Vs[i * d + tx * bs + b];
-      for (int a = 0; a < bs; ++a) for (int b = 0; b < bs; ++b) acc[a][b] = fmaf(av[a], bv[b], acc[a][b]);
-    }
-    if ((int)threadIdx.x < d) {
-      for (int i = 0; i < DS_TOK; ++i) {
-        const float x = Vs[i * d + threadIdx.x];
-        const float wgt = wt[i];
-        u = fmaf(wgt, x, u);
-        su += x;
-        nn = fmaf(x, x, nn);
-      }
-    }
-  }
-  float* out = gram_part + ((size_t)head * nstat + chunk) * gram_stride(d);
-  for (int a = 0; a < bs; ++a) for (int b = 0; b < bs; ++b) out[(ty * bs + a) * d + tx * bs + b] = acc[a][b];
-  if ((int)threadIdx.x < d) { out[d * d + threadIdx.x] = u; out[d * d + d + threadIdx.x] = su; }
-  // ||V_del||^2 of the chunk: sum over the d column shares, fixed order
-  __shared__ float nsh[128];
-  __syncthreads();
-  if ((int)threadIdx.x < d) nsh[threadIdx.x] = nn;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int c = 0; c < d; ++c) s += (double)nsh[c];
-    out[d * d + 2 * d] = (float)s;
   }
 }
 
@@ -1669,9 +1589,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     const bool few_active = min_budget > m.d && m.N > m.d && !var.skips_basis();
     if (launch_del_stats_mfma(m, w, V, scores, idx, max_budget, state, nk_stats, gram_part, st, few_active) != OBF_OK) return OBF_ERR_HIP;
   } else if (rank > 0) {
-    { ProfScope prof_(ST_DEL_STATS, st); hipLaunchKernelGGL(k_bf_del_stats<T>, dim3(w.nstat, m.heads), dim3(DS_THREADS), sizeof(float) * DS_TOK * m.d, st,
-                       (const T*)V, scores, idx, m.N, m.d, max_budget, w.nstat, state, nk_stats, gram_part, m.scs, m.kvs); }
-    if (check_launch("backfill del_stats") != OBF_OK) return OBF_ERR_HIP;
+    if (launch_del_stats_generic(m, w, V, scores, idx, max_budget, state, nk_stats, gram_part, st) != OBF_OK) return OBF_ERR_HIP;
   }
   if (join.now() != OBF_OK) return OBF_ERR_HIP;
   {

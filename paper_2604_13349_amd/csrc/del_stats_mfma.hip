@@ -4,7 +4,7 @@
 // deleted rows of the chunk.  Retained rows enter as zeros.  The two sums are matrix products as well: the weight of
 // a token, split into three bf16 parts that add up to it exactly, and the constant one are four more "columns" next
 // to the 128 value columns, and the squared norm is the trace of the Gram matrix - the vector ALU only moves data.
-// Output format and meaning are those of the reference-precision kernel it replaces:
+// Output format and meaning are those of the kernel for the other shapes (del_stats_generic.hip):
 // gram_part[head][chunk] = { G [d][d], u [d], s [d], ||V_del||^2, pad[3] }.
 #include "common.hpp"
 #include "gram_stage.hpp"

@@ -144,6 +144,13 @@ def test_small_budget_basis_variants(gpu, d, dtype, budgets):
     assert sum(r.skipped == 0 for r in reps) >= len(budgets) // 2
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("N", [14, 17, 65, 129, 1023, 1024, 1025, 2050])     # pairs of tokens per wave, load batches, chunks of 1024
+def test_deleted_row_statistics_of_fp32_and_half_width_heads(gpu, dtype, d, N):
+    cfg = si.RelayConfig("delstats", 13, 1, 2, 1, d, N, 4, min(12, N - 1), 2, dtype, "structured", outlier_frac=0.01)
+    _check_cfg(gpu, cfg, expect_active=True if N > 14 else None)
+
+
 @pytest.mark.parametrize("budget", [48, 300])
 def test_rank_deficient_retained_rows(gpu, budget):
     """Values that repeat 24 distinct rows (plus a few free tokens): the retained span has rank far below both the

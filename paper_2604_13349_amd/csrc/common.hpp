@@ -72,8 +72,7 @@ struct Workspace {
   size_t inv_norm;     // float   [heads][max_budget]     reciprocal norms of the retained keys (cache merging)
   size_t route;        // int32   [heads][N]              retained slot of every deleted token (cache merging, when not an output)
   size_t total;
-  int nchunk;          // score chunks per head
-  int chunk_tokens;    // tokens per score chunk
+  int nchunk;          // most chunks per head of the double-precision score path
   int rgroups, tiles_per_head, tiles_per_range, nranges, nslot;   // matrix-core score partition
   int nstat;           // statistics chunks per head
 };
@@ -104,9 +103,8 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 inline Workspace carve(const Dims& m, int max_budget, int rank) {
   Workspace w;
-  // reference-precision score path: fixed chunks of 512 tokens
-  w.chunk_tokens = 512;
-  w.nchunk = (m.N + w.chunk_tokens - 1) / w.chunk_tokens;
+  // double-precision score path: at most one chunk per 512 tokens (or nslot below, whichever is more)
+  w.nchunk = (m.N + 511) / 512;
   w.nstat = (m.N + kStatChunk - 1) / kStatChunk;
   // matrix-core score path: the flattened (head, 32-token tile) space is cut into one range per
   // persistent workgroup; a head is covered by at most nslot ranges

@@ -1,173 +1,224 @@
-// Attention-mass scores (Eq. 1), reference-precision path: every logit, exponential and sum is
-// carried in double on the vector ALU.  Used for fp32 I/O and for shapes the MFMA path does not
-// take.  Two passes over K because a column sum of softmax rows needs every row's normaliser
-// first: pass A gives per-row log-sum-exp, pass B the column sums.
+// Attention-mass scores (Eq. 1) for fp32 caches and head_dim 64: every logit, exponential and sum is carried in double.  Two passes
+// over K because a column sum of softmax rows needs every row's normaliser first: pass A gives per-row log-sum-exp, pass B the column
+// sums.
+//
+// The logits are products of the double-precision matrix instruction v_mfma_f64_16x16x4_f64 on 16 x 16 tiles (16 tokens against 16
+// query rows).  Its operands hold, in lane l, row l % 16 and one k of four, picked by l / 16; which k that is does not matter as long
+// as both operands agree, so lane l takes the head_dim entries (l/16) * d/4 ..  of its row: consecutive in memory, loaded straight into
+// registers in 16-byte pieces, converted to double once per tile.  Entry i of lane l of the result is row l/16 + 4 i, column l % 16.
+//   pass A: a wave keeps the operand of 16 query rows and walks the tiles of its chunk of tokens (tokens x rows: a lane owns one
+//           query row and keeps its running maximum and sum);
+//   pass B: a wave keeps the operand of 16 tokens and walks all query rows (rows x tokens: a lane owns one token).
+// Bound by the double-precision matrix rate (64 multiply-adds per clock and compute unit: 43 us a pass at the first shape below) and
+// the exponentials, which the same units compute.  96 heads x 2048 tokens x 128 rows at head_dim 64: 102 and 88 us; 2 heads x 512
+// tokens x 32 rows: 12 and 8 us.  With the products as scalar multiply-adds fed from LDS: 975 and 853 us, 224 and 215 us.
 #include "common.hpp"
 
 namespace obf {
 
-constexpr int GS_ROWS = 32;     // query rows per tile
-constexpr int GS_TOK = 64;      // tokens per tile
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
+
 constexpr int GS_THREADS = 256;
+constexpr int GS_WAVES = GS_THREADS / 64;
+constexpr int GS_T = 16;                 // tokens and query rows per tile
+constexpr int GS_MIN_TILES = 2;          // shortest chunk of pass A, in tiles
+constexpr int GS_TARGET_WAVES = 4096;    // waves of pass A that fill the chip (four per SIMD); fewer, longer chunks beyond
+constexpr int GS_FOLD = 1024;            // partials per head up to which pass B folds them itself (each of its workgroups reads them all;
+                                         // a launch of its own costs 5 us)
 
-template <typename T>
-__device__ __forceinline__ void load_tile(float* dst, int ld, const T* src, int rows_valid, int rows_total, int d) {
-  // dst[r][c] = src[r*d + c] for r < rows_valid, zero otherwise
-  for (int e = threadIdx.x; e < rows_total * d; e += GS_THREADS) {
-    int r = e / d, c = e - r * d;
-    dst[r * ld + c] = (r < rows_valid) ? Elem<T>::load(src + (size_t)r * d + c) : 0.0f;
+// the head_dim entries (lane / 16) * D/4 .. of one row, as they lie in memory
+template <typename T, int D>
+struct RowPart {
+  static constexpr int NV = D / 4 * (int)sizeof(T) / 16;     // 16-byte pieces
+  uint4 v[NV];
+  __device__ __forceinline__ void load(const T* __restrict__ row, int lane) {
+    const uint4* p = (const uint4*)(row + (lane >> 4) * (D / 4));
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = p[i];
+  }
+  __device__ __forceinline__ double at(int s) const {         // entry s; s is a compile-time constant after unrolling
+    if constexpr (sizeof(T) == 2) {
+      const uint4& q = v[s >> 3];
+      const int k = s & 7;
+      const uint32_t w = (k >> 1) == 0 ? q.x : (k >> 1) == 1 ? q.y : (k >> 1) == 2 ? q.z : q.w;
+      return (double)__uint_as_float((k & 1) ? (w & 0xffff0000u) : (w << 16));
+    } else {
+      const uint4& q = v[s >> 2];
+      const int k = s & 3;
+      return (double)__uint_as_float(k == 0 ? q.x : k == 1 ? q.y : k == 2 ? q.z : q.w);
+    }
+  }
+};
+
+// 16 x 16 tile of dot products: `moving`, the operand a wave streams, gives the rows of the result, `fixed`, the one it keeps, the
+// columns.  Two chains, so that an instruction does not wait for the one before it.
+template <typename T, int D>
+__device__ __forceinline__ f64x4 tile_product(const double (&fixed)[D / 4], const RowPart<T, D>& moving) {
+  f64x4 a = {0.0, 0.0, 0.0, 0.0}, b = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < D / 4; s += 2) {
+    a = __builtin_amdgcn_mfma_f64_16x16x4f64(moving.at(s), fixed[s], a, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f64_16x16x4f64(moving.at(s + 1), fixed[s + 1], b, 0, 0, 0);
+  }
+  return a + b;
+}
+
+// Pass A: partial (max, sum exp(logit - max)) per query row over one chunk of tokens.  Wave w of the grid's first dimension takes row
+// block w % nrb and chunk w / nrb of head blockIdx.y.
+template <typename T, int D>
+__global__ __launch_bounds__(GS_THREADS, 2) void k_score_stats_f64(const T* __restrict__ K, const T* __restrict__ Q,
+                                                                   double* __restrict__ stats_part, int N, int R, int nrb, int nchunk,
+                                                                   int chunk_tokens, int kvs) {
+  const int head = blockIdx.y, lane = threadIdx.x & 63;
+  const int w = blockIdx.x * GS_WAVES + (threadIdx.x >> 6);
+  const int chunk = w / nrb, row = (w - chunk * nrb) * GS_T + (lane & 15);
+  if (chunk >= nchunk) return;                                // whole wave; there is no barrier
+  const int t0 = chunk * chunk_tokens, t1 = min(N, t0 + chunk_tokens);
+  const T* Kh = K + (size_t)head * kvs * D;
+  const double scale = 1.0 / sqrt((double)D);
+  double q[D / 4];
+  {
+    RowPart<T, D> p;
+    p.load(Q + ((size_t)head * R + min(row, R - 1)) * D, lane);     // rows past R: the last one again, not written
+#pragma unroll
+    for (int s = 0; s < D / 4; ++s) q[s] = p.at(s);
+  }
+  double m = -INFINITY, l = 0.0;
+  RowPart<T, D> cur, nxt;
+  cur.load(Kh + (size_t)min(t0 + (lane & 15), N - 1) * D, lane);
+  for (int tt = t0; tt < t1; tt += GS_T) {
+    nxt.load(Kh + (size_t)min(tt + GS_T + (lane & 15), N - 1) * D, lane);      // clamped: masked below
+    const f64x4 acc = tile_product<T, D>(q, cur);
+    double x[4];
+    bool ok[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ok[i] = tt + (lane >> 4) + 4 * i < t1;
+      x[i] = ok[i] ? acc[i] * scale : -INFINITY;
+    }
+    const double mx = fmax(fmax(x[0], x[1]), fmax(x[2], x[3]));
+    if (__ballot(mx > m)) {                                   // rare after the first tiles: the sum is rescaled only when a maximum moved
+      const double mn = fmax(m, mx);
+      if (mn > m) l *= exp(m - mn);
+      m = mn;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) l += ok[i] ? exp(x[i] - m) : 0.0;
+    cur = nxt;
+  }
+  // the four lanes of a row
+#pragma unroll
+  for (int off = 16; off < 64; off <<= 1) {
+    const double m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
+    const double M = fmax(m, m2);
+    const double a = (m == -INFINITY) ? 0.0 : l * exp(m - M);
+    const double b = (m2 == -INFINITY) ? 0.0 : l2 * exp(m2 - M);
+    m = M; l = a + b;
+  }
+  if (lane < 16 && row < R) {
+    double* o = stats_part + (((size_t)head * nchunk + chunk) * R + row) * 2;
+    o[0] = m; o[1] = l;
   }
 }
 
-// Pass A: partial (max, sum exp(logit - max)) per query row over one chunk of tokens.
-template <typename T>
-__global__ __launch_bounds__(GS_THREADS) void k_score_stats_generic(const T* __restrict__ K, const T* __restrict__ Q,
-                                                                    double* __restrict__ stats_part, int N, int d, int R,
-                                                                    int nchunk, int chunk_tokens, int kvs) {
-  extern __shared__ float smem[];
-  const int ld = d + 1;
-  float* Qs = smem;                   // [GS_ROWS][ld]
-  float* Ks = smem + GS_ROWS * ld;    // [GS_TOK][ld]
-  const int head = blockIdx.y, chunk = blockIdx.x;
-  const int t0 = chunk * chunk_tokens;
-  const int t1 = min(N, t0 + chunk_tokens);
-  const T* Kh = K + (size_t)head * kvs * d;
-  const T* Qh = Q + (size_t)head * R * d;
-  const int rr = threadIdx.x >> 3, tl = threadIdx.x & 7;
-  const double scale = 1.0 / sqrt((double)d);
-
-  for (int r0 = 0; r0 < R; r0 += GS_ROWS) {
-    __syncthreads();
-    load_tile<T>(Qs, ld, Qh + (size_t)r0 * d, min(GS_ROWS, R - r0), GS_ROWS, d);
-    double m = -INFINITY, l = 0.0;
-    for (int tt = t0; tt < t1; tt += GS_TOK) {
-      __syncthreads();
-      const int tv = min(GS_TOK, t1 - tt);
-      load_tile<T>(Ks, ld, Kh + (size_t)tt * d, tv, GS_TOK, d);
-      __syncthreads();
-      for (int i = 0; i < GS_TOK / 8; ++i) {
-        const int t = tl + 8 * i;
-        if (t < tv) {
-          double acc = 0.0;
-          const float* q = Qs + rr * ld;
-          const float* k = Ks + t * ld;
-          for (int c = 0; c < d; ++c) acc = fma((double)q[c], (double)k[c], acc);
-          const double s = acc * scale;
-          if (s > m) { l = l * exp(m - s) + 1.0; m = s; }
-          else l += exp(s - m);
-        }
-      }
-    }
-    // combine the 8 token lanes of a row (consecutive lanes)
-    for (int off = 1; off < 8; off <<= 1) {
-      const double m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
-      const double M = fmax(m, m2);
-      const double a = (m == -INFINITY) ? 0.0 : l * exp(m - M);
-      const double b = (m2 == -INFINITY) ? 0.0 : l2 * exp(m2 - M);
-      m = M; l = a + b;
-    }
-    const int row = r0 + rr;
-    if (tl == 0 && row < R) {
-      double* o = stats_part + (((size_t)head * nchunk + chunk) * R + row) * 2;
-      o[0] = m; o[1] = l;
-    }
-  }
+// log-sum-exp of one query row from its chunk partials (p: the first chunk's, `step` doubles between chunks)
+__device__ __forceinline__ double fold_lse(const double* __restrict__ p, int nchunk, size_t step) {
+  double M = -INFINITY;
+  for (int c = 0; c < nchunk; ++c) M = fmax(M, p[c * step]);
+  double L = 0.0;
+  for (int c = 0; c < nchunk; ++c)
+    if (p[c * step] != -INFINITY) L += p[c * step + 1] * exp(p[c * step] - M);
+  return M + log(L);
 }
 
-// log-sum-exp of every query row from the chunk partials.
+// ... of every query row, where pass B does not do it itself
 __global__ void k_score_lse(const double* __restrict__ stats_part, double* __restrict__ row_lse, int R, int nchunk,
                             int total_rows) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total_rows) return;
   const int head = i / R, row = i - head * R;
-  double M = -INFINITY;
-  for (int c = 0; c < nchunk; ++c) M = fmax(M, stats_part[(((size_t)head * nchunk + c) * R + row) * 2]);
-  double L = 0.0;
-  for (int c = 0; c < nchunk; ++c) {
-    const double* p = stats_part + (((size_t)head * nchunk + c) * R + row) * 2;
-    if (p[0] != -INFINITY) L += p[1] * exp(p[0] - M);
-  }
-  row_lse[i] = M + log(L);
+  row_lse[i] = fold_lse(stats_part + ((size_t)head * nchunk * R + row) * 2, nchunk, (size_t)R * 2);
 }
 
-// Pass B: scores[j] = sum_rows exp(logit - lse[row]).
-template <typename T>
-__global__ __launch_bounds__(GS_THREADS) void k_score_mass_generic(const T* __restrict__ K, const T* __restrict__ Q,
-                                                                   const double* __restrict__ row_lse,
-                                                                   float* __restrict__ scores, int N, int d, int R, int chunk_tokens, int kvs) {
-  extern __shared__ float smem[];
-  const int ld = d + 1;
-  float* Qs = smem;
-  float* Ks = smem + GS_ROWS * ld;
-  double* red = (double*)(smem + (GS_ROWS + GS_TOK) * ld + ((GS_ROWS + GS_TOK) * ld & 1));   // [GS_ROWS][GS_TOK]
-  const int head = blockIdx.y, chunk = blockIdx.x;
-  const int t0 = chunk * chunk_tokens;
-  const int t1 = min(N, t0 + chunk_tokens);
-  const T* Kh = K + (size_t)head * kvs * d;
-  const T* Qh = Q + (size_t)head * R * d;
-  const double* lse = row_lse + (size_t)head * R;
-  const int rr = threadIdx.x >> 3, tl = threadIdx.x & 7;
-  const double scale = 1.0 / sqrt((double)d);
-
-  for (int tt = t0; tt < t1; tt += GS_TOK) {
-    const int tv = min(GS_TOK, t1 - tt);
-    __syncthreads();
-    load_tile<T>(Ks, ld, Kh + (size_t)tt * d, tv, GS_TOK, d);
-    double col[GS_TOK / 8];
-    for (int i = 0; i < GS_TOK / 8; ++i) col[i] = 0.0;
-    for (int r0 = 0; r0 < R; r0 += GS_ROWS) {
-      __syncthreads();
-      load_tile<T>(Qs, ld, Qh + (size_t)r0 * d, min(GS_ROWS, R - r0), GS_ROWS, d);
-      __syncthreads();
-      const int row = r0 + rr;
-      if (row < R) {
-        const double L = lse[row];
-        const float* q = Qs + rr * ld;
-        for (int i = 0; i < GS_TOK / 8; ++i) {
-          const int t = tl + 8 * i;
-          if (t < tv) {
-            double acc = 0.0;
-            const float* k = Ks + t * ld;
-            for (int c = 0; c < d; ++c) acc = fma((double)q[c], (double)k[c], acc);
-            col[i] += exp(acc * scale - L);
-          }
-        }
+// Pass B: scores[j] = sum_rows exp(logit - lse[row]).  A workgroup takes 64 tokens of a head, a wave sixteen.  With stats_part the
+// head's row normalisers are folded here first, by every workgroup alike; the first one writes them out.
+template <typename T, int D>
+__global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __restrict__ K, const T* __restrict__ Q,
+                                                                  const double* __restrict__ stats_part /*nullable*/, int nchunk,
+                                                                  double* __restrict__ row_lse, float* __restrict__ scores, int N,
+                                                                  int R, int kvs) {
+  extern __shared__ double s_lse[];                           // [R rounded up to 16]
+  const int head = blockIdx.y, lane = threadIdx.x & 63;
+  const int tok = (blockIdx.x * GS_WAVES + (threadIdx.x >> 6)) * GS_T + (lane & 15);
+  const T* Qh = Q + (size_t)head * R * D;
+  const double scale = 1.0 / sqrt((double)D);
+  RowPart<T, D> kp, cur, nxt;
+  kp.load(K + ((size_t)head * kvs + min(tok, N - 1)) * D, lane);        // tokens past the end: the last one again, not written
+  cur.load(Qh + (size_t)min(lane & 15, R - 1) * D, lane);
+  for (int r = threadIdx.x; r < (R + GS_T - 1) / GS_T * GS_T; r += GS_THREADS) {
+    double lse = INFINITY;                                    // rows past R add exp(-inf) = 0
+    if (r < R) {
+      if (stats_part) {
+        lse = fold_lse(stats_part + ((size_t)head * nchunk * R + r) * 2, nchunk, (size_t)R * 2);
+        if (blockIdx.x == 0) row_lse[(size_t)head * R + r] = lse;
+      } else {
+        lse = row_lse[(size_t)head * R + r];
       }
     }
-    for (int i = 0; i < GS_TOK / 8; ++i) red[rr * GS_TOK + tl + 8 * i] = col[i];
-    __syncthreads();
-    if (threadIdx.x < tv) {
-      double s = 0.0;
-      for (int r = 0; r < GS_ROWS; ++r) s += red[r * GS_TOK + threadIdx.x];
-      scores[(size_t)head * N + tt + threadIdx.x] = (float)s;
-    }
+    s_lse[r] = lse;
   }
+  __syncthreads();
+  double k[D / 4];
+#pragma unroll
+  for (int s = 0; s < D / 4; ++s) k[s] = kp.at(s);
+  double col = 0.0;
+  for (int r0 = 0; r0 < R; r0 += GS_T) {
+    nxt.load(Qh + (size_t)min(r0 + GS_T + (lane & 15), R - 1) * D, lane);
+    const f64x4 acc = tile_product<T, D>(k, cur);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) col += exp(acc[i] * scale - s_lse[r0 + (lane >> 4) + 4 * i]);
+    cur = nxt;
+  }
+  col += __shfl_xor(col, 16);
+  col += __shfl_xor(col, 32);
+  if (lane < 16 && tok < N) scores[(size_t)head * N + tok] = (float)col;
 }
 
-template <typename T>
+template <typename T, int D>
 static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void* K, const void* Q, float* scores,
                         double* row_lse, hipStream_t st) {
   double* stats_part = (double*)(ws + w.stats_part);
-  const size_t ld = m.d + 1;
-  const size_t smemA = sizeof(float) * (GS_ROWS + GS_TOK) * ld;
-  const size_t smemB = smemA + 8 + sizeof(double) * GS_ROWS * GS_TOK;
-  dim3 grid(w.nchunk, m.heads);
-  { ProfScope prof_(ST_SCORE_STATS, st); hipLaunchKernelGGL(k_score_stats_generic<T>, grid, dim3(GS_THREADS), smemA, st, (const T*)K, (const T*)Q, stats_part,
-                     m.N, m.d, m.R, w.nchunk, w.chunk_tokens, m.kvs); }
-  if (check_launch("score stats (generic)") != OBF_OK) return OBF_ERR_HIP;
-  const int total_rows = m.heads * m.R;
-  { ProfScope prof_(ST_SCORE_LSE, st); hipLaunchKernelGGL(k_score_lse, dim3((total_rows + 255) / 256), dim3(256), 0, st, stats_part, row_lse, m.R, w.nchunk,
-                     total_rows); }
-  if (check_launch("score lse") != OBF_OK) return OBF_ERR_HIP;
-  { ProfScope prof_(ST_SCORE_MASS, st); hipLaunchKernelGGL(k_score_mass_generic<T>, grid, dim3(GS_THREADS), smemB, st, (const T*)K, (const T*)Q, row_lse, scores,
-                     m.N, m.d, m.R, w.chunk_tokens, m.kvs); }
-  return check_launch("score mass (generic)");
+  // chunks of pass A: enough waves for the chip, within the slots the workspace has per query row
+  const int nrb = (m.R + GS_T - 1) / GS_T, tiles = (m.N + GS_T - 1) / GS_T, slots = w.nchunk > w.nslot ? w.nchunk : w.nslot;
+  const long units = (long)m.heads * nrb;
+  int nchunk = (int)((GS_TARGET_WAVES + units - 1) / units);
+  if (nchunk > slots) nchunk = slots;
+  const int per = (tiles + nchunk - 1) / nchunk > GS_MIN_TILES ? (tiles + nchunk - 1) / nchunk : GS_MIN_TILES;
+  nchunk = (tiles + per - 1) / per;
+  { ProfScope prof_(ST_SCORE_STATS, st);
+    hipLaunchKernelGGL((k_score_stats_f64<T, D>), dim3((unsigned)(((long)nrb * nchunk + GS_WAVES - 1) / GS_WAVES), m.heads), dim3(GS_THREADS), 0, st,
+                       (const T*)K, (const T*)Q, stats_part, m.N, m.R, nrb, nchunk, per * GS_T, m.kvs); }
+  if (check_launch("score stats (f64)") != OBF_OK) return OBF_ERR_HIP;
+  const bool fold = (long)nchunk * m.R <= GS_FOLD;
+  if (!fold) {
+    const int total_rows = m.heads * m.R;
+    ProfScope prof_(ST_SCORE_LSE, st);
+    hipLaunchKernelGGL(k_score_lse, dim3((total_rows + 255) / 256), dim3(256), 0, st, stats_part, row_lse, m.R, nchunk, total_rows);
+    if (check_launch("score lse") != OBF_OK) return OBF_ERR_HIP;
+  }
+  { ProfScope prof_(ST_SCORE_MASS, st);
+    hipLaunchKernelGGL((k_score_mass_f64<T, D>), dim3((m.N + GS_WAVES * GS_T - 1) / (GS_WAVES * GS_T), m.heads), dim3(GS_THREADS),
+                       sizeof(double) * nrb * GS_T, st, (const T*)K, (const T*)Q, fold ? (const double*)stats_part : (const double*)nullptr,
+                       nchunk, row_lse, scores, m.N, m.R, m.kvs); }
+  return check_launch("score mass (f64)");
 }
 
 obf_status_t launch_score_generic(const Dims& m, const Workspace& w, char* ws, const void* K, const void* Q,
                                   float* scores, double* row_lse, hipStream_t st) {
-  if (m.dtype == OBF_BF16) return run<uint16_t>(m, w, ws, K, Q, scores, row_lse, st);
-  return run<float>(m, w, ws, K, Q, scores, row_lse, st);
+  // (bf16 caches of head_dim 128 are score_mfma.hip's)
+  if (m.dtype == OBF_BF16) return run<uint16_t, 64>(m, w, ws, K, Q, scores, row_lse, st);
+  if (m.d == 64) return run<float, 64>(m, w, ws, K, Q, scores, row_lse, st);
+  return run<float, 128>(m, w, ws, K, Q, scores, row_lse, st);
 }
 
 }  // namespace obf

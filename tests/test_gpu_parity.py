@@ -145,6 +145,28 @@ def test_small_budget_basis_variants(gpu, d, dtype, budgets):
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("N,g,W", [(1, 1, 1), (15, 1, 17), (16, 1, 16), (17, 3, 5), (33, 1, 33), (64, 2, 16), (65, 1, 1), (257, 1, 3),
+                                   (4200, 4, 40)])        # tiles of 16 tokens and rows, one and several chunks, normalisers folded apart
+def test_scores_of_fp32_and_half_width_heads(gpu, dtype, d, N, g, W):
+    """Masses and row normalisers against the oracle: both sides are double until the mass is stored as a float, so half a unit in
+    its last place (6e-8 of it) and nothing else is left."""
+    import torch
+    from paper_2604_13349_amd import binding as B
+    cfg = si.RelayConfig("scores64", 17, 1, 2, g, d, N, W, 1, 0, dtype, "structured", outlier_frac=0.01)
+    K, V, Q = si.make_cache(cfg, 0)
+    sc, lse = B.score(gpu.to_dev(K, dtype), gpu.to_dev(Q, dtype))
+    torch.cuda.synchronize()
+    sc, lse = sc.cpu().numpy(), lse.cpu().numpy()
+    for h in range(2):
+        k, q = O.decode(K[0, h], dtype), O.decode(Q[0, h * g:(h + 1) * g], dtype).reshape(-1, d)
+        A = O.attention_mass(k, q)
+        np.testing.assert_allclose(sc[0, h], A, rtol=6.1e-8, atol=1e-38)
+        S = q @ k.T / np.sqrt(d)
+        ref = S.max(1) + np.log(np.exp(S - S.max(1, keepdims=True)).sum(1))
+        np.testing.assert_allclose(lse[0, h], ref, rtol=1e-13, atol=1e-13)
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
 @pytest.mark.parametrize("N", [14, 17, 65, 129, 1023, 1024, 1025, 2050])     # pairs of tokens per wave, load batches, chunks of 1024
 def test_deleted_row_statistics_of_fp32_and_half_width_heads(gpu, dtype, d, N):
     cfg = si.RelayConfig("delstats", 13, 1, 2, 1, d, N, 4, min(12, N - 1), 2, dtype, "structured", outlier_frac=0.01)

@@ -1,7 +1,7 @@
 // Leading eigenpairs of a small symmetric matrix, for a workgroup of 512 threads: the direct route for
 // the case "a few leading right singular vectors of the residual" (Sec. 4.4: k = pca_rank is small against the
 // width of the complement), in place of a full Jacobi diagonalisation:
-//   1. Householder tridiagonalisation T = H S H^T (m - 2 reflectors, four barriers each);
+//   1. Householder tridiagonalisation T = H S H^T (m - 2 reflectors, one barrier each);
 //   2. the k largest eigenvalues of the tridiagonal S by multisection on Sturm counts (every thread evaluates one
 //      shift per round; three or four rounds shrink an eigenvalue's bracket below single-precision resolution);
 //   3. their eigenvectors by inverse iteration on S - theta I (tridiagonal elimination with row exchanges, one lane
@@ -15,11 +15,12 @@
 
 namespace obf {
 
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_te;
+
 constexpr int TE_THREADS = 512;
 constexpr int TE_WAVES = TE_THREADS / 64;
 constexpr int TE_MAXK = 16;              // most eigenpairs
 constexpr int TE_BATCH = 8;              // eigenvectors per pass of the inverse iteration and the back-transformation (one wave each)
-constexpr int TE_CPT = 32;               // columns per thread of the register-resident matrix (128 rows x 4 groups)
 
 // floats of LDS scratch tri_top_eigs needs for an m x m matrix and k eigenpairs
 __host__ __device__ inline int tri_lane_stride(int k) { return k <= 4 ? 4 : 8; }
@@ -98,6 +99,159 @@ __device__ __forceinline__ float te_backward(const float* __restrict__ f, const 
   return big;
 }
 
+// Tridiagonalisation of the m x m symmetric matrix Tsrc (row stride ls), 32 (MB - 1) < m <= 32 MB: the diagonal to dv, the
+// sub-diagonal to ev, reflector j (I - bet[j] v v^T) to column j of Rf below the diagonal.  cbuf and ybuf [2][128] are LDS, 16-byte
+// aligned.  All threads call; ends with a barrier.
+//
+// The matrix lives in registers as 32 x 32 tiles in the result layout of the matrix instructions (entry i of lane l: row
+// (i/4)*8 + (l/32)*4 + i%4, column l%32); wave b < MB holds the tiles of row block b.  With x the column to be reduced, c the next
+// one (both below the diagonal, before the step's update), v = x - alpha e and T v = T x - alpha c, a step is
+//   every wave: |x| and its 32 entries of T x (a lane sums over its column of every tile, a reduce-scatter over the lanes of a
+//               half-wave leaves each with one row) to LDS;                                     -- barrier --
+//   every wave: p = beta (T x - alpha c), w = p - (beta/2 p.v) v, all entries, two per lane; the update T - v w^T - w v^T is one
+//               v_mfma_f32_32x32x2_f32 per tile whose operands are lane swaps of v and w; the next x is c less its share of the
+//               update; the tiles that hold the next c publish it.
+// Repeating the vector work in every wave leaves one barrier and one LDS round trip per reflector (none of the waves' barriers once
+// the trailing matrix fits one block); it is why only MB waves take part: two waves on a SIMD share its instruction issue, and two
+// tiles on each of eight waves took as long (2900 cycles a step at m = 96) as the same work on the vector ALU with four barriers.
+// Bound by the dependent chain of a step: 0.85 us at m = 96 and 0.55 at m = 32 (1.3 us before); 2 directions of 288 complements 96
+// wide in a 256-token call: 514 -> 445 us for the whole call.
+template <int MB>
+__device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const int ls, float* Rf, const int lt, const int m,
+                                           float* dv, float* ev, float* bet, float* cbuf, float* ybuf) {
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr bool TWO = MB > 2;                                 // a lane holds two entries of a vector
+  auto lane_val = [](const float x, const int l) -> float {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), l));
+  };
+  if (tid < 128) cbuf[tid] = (m > 1 && tid < m) ? Tsrc[(size_t)ls + tid] : 0.f;    // column 1, read as row 1
+  if (tid == 0) dv[0] = Tsrc[0];
+  f32x16_te tile[MB];
+  float xa = 0.f, xb = 0.f;                                    // entries lane and lane + 64 of x
+  if (wave < MB) {
+#pragma unroll
+    for (int cb = 0; cb < MB; ++cb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = wave * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), c = cb * 32 + lr;
+        tile[cb][i] = (r < m && c < m) ? Tsrc[(size_t)r * ls + c] : 0.f;
+      }
+    xa = (lane > 0 && lane < m) ? Tsrc[lane] : 0.f;            // column 0
+    xb = (TWO && lane + 64 < m) ? Tsrc[lane + 64] : 0.f;
+  }
+  __syncthreads();
+  // the row this lane is left with: entry 8 b4 + 4 b3 + 2 b2 + b1 of the tile's sixteen (b: the bits of the lane number)
+  const bool l3 = (lane & 8) != 0, l2 = (lane & 4) != 0, l1 = (lane & 2) != 0;
+  const int my_row = wave * 32 + ((lane >> 4) & 1) * 16 + ((lane >> 3) & 1) * 8 + lh * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
+  auto step = [&](const int j, const bool alone) {
+    const int b0 = (j + 1) >> 5, par = j & 1;                  // the block in which the trailing matrix starts
+    const bool live = wave < MB && wave >= b0;                 // uniform over the wave
+    float alpha = 0.f, beta = 0.f, head = 0.f;
+    if (live) {
+      const auto X0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(xa), __float_as_uint(xa), false, false);   // blocks 0 and 1 of x,
+      const auto X1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(xb), __float_as_uint(xb), false, false);   // 2 and 3, in both half-waves
+      const float ss = te_wave_sum(TWO ? fmaf(xa, xa, xb * xb) : xa * xa);
+      head = lane_val((TWO && j + 1 >= 64) ? xb : xa, (j + 1) & 63);
+      float s[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+      for (int cb = 0; cb < MB; ++cb)
+        if (cb >= b0) {
+          const float xc = __uint_as_float((cb == 0) ? X0[0] : (cb == 1) ? X0[1] : (cb == 2) ? X1[0] : X1[1]);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[i] = fmaf(tile[cb][i], xc, s[i]);
+        }
+      // reduce-scatter over the 32 lanes of the half-wave: partners differ in bit 4, then in bits 3 - 0, 2 - 0, 1 and 0
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[i]), __float_as_uint(s[i + 8]), false, false);
+        s[i] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float keep = l3 ? s[i + 4] : s[i], give = l3 ? s[i] : s[i + 4];
+        s[i] = keep + __uint_as_float(OBF_DPP_MOV(__float_as_uint(give), 0x140));
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float keep = l2 ? s[i + 2] : s[i], give = l2 ? s[i] : s[i + 2];
+        s[i] = keep + __uint_as_float(OBF_DPP_MOV(__float_as_uint(give), 0x141));
+      }
+      {
+        const float keep = l1 ? s[1] : s[0], give = l1 ? s[0] : s[1];
+        s[0] = keep + __uint_as_float(OBF_DPP_MOV(__float_as_uint(give), 0x4E));
+      }
+      s[0] += __uint_as_float(OBF_DPP_MOV(__float_as_uint(s[0]), 0xB1));
+      ybuf[par * 128 + my_row] = s[0];                         // the same value from two lanes
+      // Single-instruction square root and reciprocal (1 ulp): the reflector only has to be orthogonal to rounding.
+      const float sigma = __builtin_amdgcn_sqrtf(ss);
+      if (sigma > 0.f) {
+        alpha = (head >= 0.f) ? -sigma : sigma;
+        beta = __builtin_amdgcn_rcpf(sigma * (sigma + fabsf(head)));
+      }
+    }
+    if (alone) __builtin_amdgcn_wave_barrier(); else lds_barrier();
+    if (live) {
+      const float* yr = ybuf + par * 128;
+      const float* cr = cbuf + par * 128;
+      const float ya = yr[lane], yb = TWO ? yr[lane + 64] : 0.f, ca = cr[lane], cb_ = TWO ? cr[lane + 64] : 0.f;
+      const bool ina = lane > j && lane < m, inb = TWO && lane + 64 > j && lane + 64 < m;
+      const float v1 = head - alpha;
+      const float va = (lane == j + 1) ? v1 : xa, vb = (lane + 64 == j + 1) ? v1 : xb;       // zero outside j < i < m
+      const float pa = ina ? beta * fmaf(-alpha, ca, ya) : 0.f, pb = inb ? beta * fmaf(-alpha, cb_, yb) : 0.f;
+      const float K = 0.5f * beta * te_wave_sum(TWO ? fmaf(pa, va, pb * vb) : pa * va);
+      const float wa = fmaf(-K, va, pa), wb = fmaf(-K, vb, pb);
+      // operands of the update: k = 0 in the lower half-wave, k = 1 in the upper; block b of a vector sits in half b % 2 of entry b / 2
+      const bool hi = TWO && wave >= 2;
+      const auto A = __builtin_amdgcn_permlane32_swap(__float_as_uint(hi ? vb : va), __float_as_uint(hi ? wb : wa), false, false);
+      const auto B0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(wa), __float_as_uint(va), false, false);
+      const auto B1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(wb), __float_as_uint(vb), false, false);
+      const float a = -__uint_as_float((wave & 1) ? A[1] : A[0]);
+#pragma unroll
+      for (int cb = 0; cb < MB; ++cb)
+        if (cb >= b0) {
+          const uint32_t bo = (cb == 0) ? B0[0] : (cb == 1) ? B0[1] : (cb == 2) ? B1[0] : B1[1];
+          tile[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, __uint_as_float(bo), tile[cb], 0, 0, 0);
+        }
+      // column j + 1 after the update: its diagonal entry is final, the rest is the next x
+      const float w1 = lane_val((TWO && j + 1 >= 64) ? wb : wa, (j + 1) & 63);
+      const float na = fmaf(-va, w1, fmaf(-wa, v1, ca)), nb = fmaf(-vb, w1, fmaf(-wb, v1, cb_));
+      if (wave == MB - 1) {                                    // the wave that stays to the end keeps the books
+        if (ina) Rf[lane * lt + j] = va;
+        if (inb) Rf[(lane + 64) * lt + j] = vb;
+        if (lane == 0) { bet[j] = beta; ev[j] = alpha; }
+        if (lane == ((j + 1) & 63)) dv[j + 1] = (TWO && j + 1 >= 64) ? nb : na;
+      }
+      xa = (lane > j + 1 && lane < m) ? na : 0.f;
+      xb = (TWO && lane + 64 > j + 1 && lane + 64 < m) ? nb : 0.f;
+      const int cn = j + 2;                                    // the next raw column
+#pragma unroll
+      for (int cb = 0; cb < MB; ++cb)
+        if (cb == (cn >> 5)) {
+          if (lr == (cn & 31)) {
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4)
+              *(float4*)&cbuf[(par ^ 1) * 128 + wave * 32 + i4 * 8 + lh * 4] =
+                  make_float4(tile[cb][4 * i4], tile[cb][4 * i4 + 1], tile[cb][4 * i4 + 2], tile[cb][4 * i4 + 3]);
+          }
+        }
+    }
+  };
+  int j = 0;
+  for (; j + 2 < m && ((j + 1) >> 5) < MB - 1; ++j) step(j, false);
+  lds_barrier();                                               // the other row blocks' last column is published
+  if (wave == MB - 1) {
+    for (; j + 2 < m; ++j) step(j, true);
+    // the last 2 x 2 block: x is column m - 2, the published column is m - 1
+    const float last = lane_val((TWO && m - 1 >= 64) ? xb : xa, (m - 1) & 63);
+    __builtin_amdgcn_wave_barrier();
+    if (m >= 2 && lane == 0) { ev[m - 2] = last; dv[m - 1] = cbuf[(m & 1) * 128 + m - 1]; }
+  }
+  __syncthreads();
+}
+
 // Tsrc: the m x m symmetric matrix (row stride ls; global or LDS, read once).  Rf: LDS, m rows of stride lt (odd), receives
 // the reflectors (column j below the sub-diagonal).  m <= 128.
 // work: LDS scratch of tri_work_floats(m, k) floats, 16-byte aligned.  1 <= k <= min(m, TE_MAXK); KS = tri_lane_stride(k).
@@ -110,9 +264,8 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
                                              const int k, float* work, const float** theta, const float** W) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float* vv = work;                   // [128] reflector, zero outside the trailing block and past the matrix (work is 16-byte aligned)
-  float* pv = vv + 128;               // [128] beta T v, likewise
-  float* dv = pv + 128;               // diagonal of S
+  float* cbuf = work;                 // [2][128] tridiagonalisation: the raw next column, by step parity (work is 16-byte aligned)
+  float* dv = cbuf + 256;             // diagonal of S
   float* ev = dv + m;                 // sub-diagonal of S: ev[j] = S[j+1][j]
   float* e2 = ev + m;
   float* bet = e2 + m;                // reflector j is I - bet[j] v v^T, v in column j of Rf
@@ -125,120 +278,11 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
   float* lu = scal + 32;              // [5][m][KS] factors of S - theta I per eigenvector + [m][KS] second iteration vector; later W [k][m]
   float* zz = lu + 6 * m * KS;        // [m][KS] iteration vectors
 
-  // ---- 1. tridiagonalisation.  The matrix lives in registers: thread (a, g) = (tid % 128, tid / 128) owns row a, columns
-  // g, g + 4, ..., g + 124 (absolute numbering throughout; vv and pv are zero in front of the trailing block, so no
-  // column needs masking).  The cyclic deal keeps the four column groups equally busy while the trailing block shrinks:
-  // a group's columns come in four blocks of eight, and a block that lies in front of the trailing block (or past the
-  // matrix) is skipped by the whole wave, as is a wave all of whose 64 rows do.  Per reflector: wave 0 forms v from the
-  // column the owners published, all threads form their share of T v, the rows add the four shares, and the symmetric
-  // rank-two update stays in registers.  LDS carries only vectors and receives the reflectors.
-  const int ra = tid & 127;
-  const int rg = __builtin_amdgcn_readfirstlane(tid >> 7);
-  const int row_lo = (wave & 1) * 64;                          // the rows of this wave: row_lo .. row_lo + 63
-  float* part = (float*)cnt;                                   // [4][128] shares of T v (the counts come later)
-  float* xcol = e2;                                            // the published column (e2 is free until the form is complete)
-  float tr[TE_CPT];
-#pragma unroll
-  for (int c = 0; c < TE_CPT; ++c)                              // symmetric: entry (ra, col) is read as (col, ra), lanes along a row
-    tr[c] = (ra < m && rg + 4 * c < m) ? Tsrc[(size_t)(rg + 4 * c) * ls + ra] : 0.f;
-  if (tid < 128) { vv[tid] = 0.f; pv[tid] = 0.f; }
-  if (rg == 0 && ra < m) xcol[ra] = tr[0];                     // column 0
-  if (tid == 0) dv[0] = tr[0];
-  __syncthreads();
-  // A wave's threads share their 32 columns (rg is the same for all of them): each lane fetches one entry of v and of
-  // p, and the others' entries arrive as scalar operands through lane reads - no LDS broadcast traffic.
-  const int cmine = rg + 4 * (lane & 31);
-  auto lane_val = [](const float x, const int l) -> float {
-    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), l));
-  };
-  for (int j = 0; j + 2 < m; ++j) {
-    // wave 0 forms the reflector from the published column.  Single-instruction square root and reciprocal (1 ulp): the
-    // reflector only has to be orthogonal to rounding.
-    if (wave == 0) {
-      const int i0 = j + 1 + lane, i1 = i0 + 64;               // absolute rows of the column below the diagonal
-      const float x0 = (i0 < m) ? xcol[i0] : 0.f, x1 = (i1 < m) ? xcol[i1] : 0.f;
-      const float sigma = __builtin_amdgcn_sqrtf(te_wave_sum(fmaf(x0, x0, x1 * x1)));
-      const float head = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x0)));
-      const float alpha = (head >= 0.f) ? -sigma : sigma;
-      const float v0 = (lane == 0) ? x0 - alpha : x0;
-      if (i0 < m) { vv[i0] = v0; Rf[i0 * lt + j] = v0; }        // the reflector, kept for the back-transformation
-      if (i1 < m) { vv[i1] = x1; Rf[i1 * lt + j] = x1; }
-      if (lane == 0) {
-        vv[j] = 0.f; pv[j] = 0.f;                              // row / column j have left the trailing block
-        bet[j] = (sigma > 0.f) ? __builtin_amdgcn_rcpf(sigma * (sigma + fabsf(head))) : 0.f;
-        ev[j] = (sigma > 0.f) ? alpha : 0.f;
-      }
-    }
-    __syncthreads();
-    const float beta = bet[j];
-    const bool rows_live = row_lo + 63 > j && row_lo < m;      // uniform over the wave
-    if (beta != 0.f) {                                         // uniform
-      const float vmine = vv[cmine];
-      if (rows_live) {
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;           // four independent chains
-#pragma unroll
-        for (int b = 0; b < TE_CPT / 8; ++b) {
-          if (rg + 32 * b + 28 > j && rg + 32 * b < m) {        // uniform: the block reaches into the trailing block
-#pragma unroll
-            for (int c = 8 * b; c < 8 * b + 8; c += 4) {
-              s0 = fmaf(tr[c], lane_val(vmine, c), s0); s1 = fmaf(tr[c + 1], lane_val(vmine, c + 1), s1);
-              s2 = fmaf(tr[c + 2], lane_val(vmine, c + 2), s2); s3 = fmaf(tr[c + 3], lane_val(vmine, c + 3), s3);
-            }
-          }
-        }
-        if (ra > j && ra < m) part[rg * 128 + ra] = (s0 + s1) + (s2 + s3);
-      }
-      __syncthreads();
-      if (tid > j && tid < m) pv[tid] = beta * ((part[tid] + part[128 + tid]) + (part[256 + tid] + part[384 + tid]));
-      __syncthreads();
-      const float K = 0.5f * beta * te_wave_sum(fmaf(pv[lane], vv[lane], pv[lane + 64] * vv[lane + 64]));   // the same in every wave
-      if (rows_live) {
-        // rows outside the trailing block (and past the matrix) have v = p = 0: their registers do not change
-        const float va = vv[ra], wa = fmaf(-K, va, pv[ra]);
-        const float wmine = fmaf(-K, vmine, pv[cmine]);      // w = p - K v of this lane's column
-#pragma unroll
-        for (int b = 0; b < TE_CPT / 8; ++b) {
-          if (rg + 32 * b + 28 > j && rg + 32 * b < m) {
-#pragma unroll
-            for (int c = 8 * b; c < 8 * b + 8; ++c) tr[c] -= fmaf(va, lane_val(wmine, c), wa * lane_val(vmine, c));
-          }
-        }
-      }
-    }
-    // the owners publish column j + 1 of the updated block (and its diagonal entry, final from here on); the column's
-    // position in the register array is the same for the whole workgroup: a jump, not a chain of selects
-    if (rg == ((j + 1) & 3) && ra > j && ra < m) {
-      float xv = 0.f;
-      switch ((j + 1) >> 2) {
-#define OBF_TE_CASE(q) case q: xv = tr[q]; break;
-        OBF_TE_CASE(0) OBF_TE_CASE(1) OBF_TE_CASE(2) OBF_TE_CASE(3) OBF_TE_CASE(4) OBF_TE_CASE(5) OBF_TE_CASE(6) OBF_TE_CASE(7)
-        OBF_TE_CASE(8) OBF_TE_CASE(9) OBF_TE_CASE(10) OBF_TE_CASE(11) OBF_TE_CASE(12) OBF_TE_CASE(13) OBF_TE_CASE(14) OBF_TE_CASE(15)
-        OBF_TE_CASE(16) OBF_TE_CASE(17) OBF_TE_CASE(18) OBF_TE_CASE(19) OBF_TE_CASE(20) OBF_TE_CASE(21) OBF_TE_CASE(22) OBF_TE_CASE(23)
-        OBF_TE_CASE(24) OBF_TE_CASE(25) OBF_TE_CASE(26) OBF_TE_CASE(27) OBF_TE_CASE(28) OBF_TE_CASE(29) OBF_TE_CASE(30) OBF_TE_CASE(31)
-#undef OBF_TE_CASE
-        default: break;
-      }
-      xcol[ra] = xv;
-      if (ra == j + 1) dv[j + 1] = xv;
-    }
-    __syncthreads();
-  }
-  // the last 2 x 2 block: its diagonal entries and the sub-diagonal entry between them
-  if (m >= 2) {
-    if (rg == ((m - 1) & 3) && ra == m - 1) {
-      float xv = 0.f;
-#pragma unroll
-      for (int c = 0; c < TE_CPT; ++c) if (c == (m - 1) >> 2) xv = tr[c];
-      dv[m - 1] = xv;
-    }
-    if (rg == ((m - 2) & 3) && ra == m - 1) {
-      float xv = 0.f;
-#pragma unroll
-      for (int c = 0; c < TE_CPT; ++c) if (c == (m - 2) >> 2) xv = tr[c];
-      ev[m - 2] = xv;
-    }
-  }
-  __syncthreads();
+  // ---- 1. tridiagonalisation (the counts come later)
+  if (m <= 32) tri_reduce<1>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
+  else if (m <= 64) tri_reduce<2>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
+  else if (m <= 96) tri_reduce<3>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
+  else tri_reduce<4>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
   if (wave == 0) {
     // Gershgorin interval of S and its largest squared sub-diagonal entry: lane l looks at rows l and l + 64
     float lo = INFINITY, hi = -INFINITY, me2 = 0.f;

@@ -144,6 +144,18 @@ def test_small_budget_basis_variants(gpu, d, dtype, budgets):
     assert sum(r.skipped == 0 for r in reps) >= len(budgets) // 2
 
 
+@pytest.mark.parametrize("dtype,d,rank,iters,budgets", [
+    ("bf16", 128, 3, 0, [108, 97, 96, 95, 65, 64, 63, 33, 32, 31]),     # complements 20 to 97 wide: edges of the 32-wide tiles
+    ("bf16", 128, 12, 0, [100, 96, 64, 40]),                            # more than eight eigenpairs
+    ("f32", 64, 2, 0, [44, 33, 32, 31, 17, 16]),
+    ("bf16", 128, 2, 3, [127, 126, 125, 96, 95, 64, 1]),                # the fast path reports its distance from the direct route: any width
+])
+def test_leading_eigenpairs_at_tile_edges(gpu, dtype, d, rank, iters, budgets):
+    cfg = si.RelayConfig("tileedges", 19, 1, len(budgets), 1, d, 900, 8, 0, rank, dtype, "structured", outlier_frac=0.01)
+    variant = O.Variant(subspace_iters=iters) if iters else None
+    _check_cfg(gpu, cfg, budgets=budgets, max_budget=max(budgets), expect_active=True, variant=variant)
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
 @pytest.mark.parametrize("N,g,W", [(1, 1, 1), (15, 1, 17), (16, 1, 16), (17, 3, 5), (33, 1, 33), (64, 2, 16), (65, 1, 1), (257, 1, 3),
                                    (4200, 4, 40)])        # tiles of 16 tokens and rows, one and several chunks, normalisers folded apart

@@ -1290,21 +1290,31 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
   float* Rf = sm;
   float* work = sm + ((m * lt + 3) & ~3);                      // 16-byte aligned
   const int kq = min(rank, m);
-  if (tid < d) uvec[tid] = delta[(size_t)head * d + tid];      // u
-  __syncthreads();
-  for (int t0 = wave; t0 < m; t0 += 4 * TE_WAVES) {            // y = Z u (Eq. 4 in complement coordinates), a wave per row,
-    float z0[4], z1[4];                                        // four rows' loads in flight
+  // y = Z u (Eq. 4 in complement coordinates), a wave per row, four rows' loads in flight (the first four beside u's)
+  float z0[4], z1[4];
+  auto fetch_rows = [&](const int t0) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int t = min(t0 + q * TE_WAVES, m - 1);
       z0[q] = (lane < d) ? Zg[(size_t)t * d + lane] : 0.f;
       z1[q] = (lane + 64 < d) ? Zg[(size_t)t * d + lane + 64] : 0.f;
     }
+  };
+  fetch_rows(wave);
+  if (tid < d) uvec[tid] = delta[(size_t)head * d + tid];      // u
+  __syncthreads();
+  {
     const float u0 = (lane < d) ? uvec[lane] : 0.f, u1 = (lane + 64 < d) ? uvec[lane + 64] : 0.f;
+    for (int t0 = wave; t0 < m; t0 += 4 * TE_WAVES) {
+      float sy[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float sy = te_wave_sum(fmaf(z1[q], u1, z0[q] * u0));
-      if (lane == 0 && t0 + q * TE_WAVES < m) rbar[t0 + q * TE_WAVES] = sy;
+      for (int q = 0; q < 4; ++q) sy[q] = fmaf(z1[q], u1, z0[q] * u0);
+      fetch_rows(t0 + 4 * TE_WAVES);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float y = te_wave_sum(sy[q]);
+        if (lane == 0 && t0 + q * TE_WAVES < m) rbar[t0 + q * TE_WAVES] = y;
+      }
     }
   }
   // Delta in complement coordinates (times a_del + eps) from kk orthonormal rows Cb [kk][m]: Eq. 5
@@ -1469,17 +1479,31 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
   int skipped = 1;
   float ivn = 0.f;
   if (k_used > 0) {
-    float dl = 0.f;
-    if (tid < d) {
+    // Delta back in head_dim coordinates: four groups of 128 threads share the complement's rows, their sums meet in LDS (the
+    // reflectors are done with)
+    __syncthreads();                                           // (a narrow complement's subspace may lie in that range: its last readers)
+    {
+      const int g = tid >> 7, c = tid & 127;
       float s = 0.f;
-      for (int t = 0; t < m; ++t) s = fmaf(Zg[(size_t)t * d + tid], dcomp[t], s);
-      const double alpha = (vflags & VF_NO_SCALING) ? 1.0 : st.a_del / (st.a_keep + kEps);          // Eq. 6
-      dl = (float)(alpha * ((double)s / (st.a_del + kEps)));
+      if (c < d) {
+#pragma unroll 8
+        for (int t = g; t < m; t += TE_THREADS / 128) s = fmaf(Zg[(size_t)t * d + c], dcomp[t], s);
+      }
+      sm[tid] = s;
     }
-    __syncthreads();                                           // every thread has read u
-    if (tid < d) uvec[tid] = dl;
+    __syncthreads();                                           // (and every thread has read u)
+    if (tid < d) {
+      const float s = (sm[tid] + sm[128 + tid]) + (sm[256 + tid] + sm[384 + tid]);
+      const double alpha = (vflags & VF_NO_SCALING) ? 1.0 : st.a_del / (st.a_keep + kEps);          // Eq. 6
+      uvec[tid] = (float)(alpha * ((double)s / (st.a_del + kEps)));
+    }
     __syncthreads();
-    if (tid == 0) { double s = 0.0; for (int c = 0; c < d; ++c) s += (double)uvec[c] * uvec[c]; s_off = (float)sqrt(s); }
+    if (wave == 0) {
+      double s = (lane < d) ? (double)uvec[lane] * uvec[lane] : 0.0;
+      if (lane + 64 < d) s += (double)uvec[lane + 64] * uvec[lane + 64];
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      if (lane == 0) s_off = (float)sqrt(s);
+    }
     __syncthreads();
     ivn = s_off;
     skipped = 0;

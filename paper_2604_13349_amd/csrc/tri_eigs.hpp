@@ -5,7 +5,7 @@
 //   2. the k largest eigenvalues of the tridiagonal S by multisection on Sturm counts (every thread evaluates one
 //      shift per round; three or four rounds shrink an eigenvalue's bracket below single-precision resolution);
 //   3. their eigenvectors by inverse iteration on S - theta I (tridiagonal elimination with row exchanges, one lane
-//      per eigenvector, three solves from a fixed pseudo-random start), eight at a time;
+//      per eigenvector, two solves from a fixed pseudo-random start), eight at a time;
 //   4. back-transformation through the reflectors (one wave per eigenvector) and a final Gram-Schmidt pass over the
 //      k vectors (eigenvalues that agree to rounding give vectors that only span the right subspace together).
 // All arithmetic is single precision; nothing here depends on convergence of an iteration.
@@ -41,18 +41,37 @@ __device__ __forceinline__ float te_wave_sum(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// The sums over the wave of three values at once, uniform: two lane swaps leave a value in each 16-lane row (p in row 0, r in row 1,
+// q in row 2), four in-row steps finish all of them together.
+__device__ __forceinline__ void te_wave_sum3(const float p, const float q, const float r, float& sp, float& sq, float& sr) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);
+  const float pq = __uint_as_float(a[0]) + __uint_as_float(a[1]), rr = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(pq), __float_as_uint(rr), false, false);
+  float v = __uint_as_float(c[0]) + __uint_as_float(c[1]);
+  v += __uint_as_float(OBF_DPP_MOV(__float_as_uint(v), 0xB1));
+  v += __uint_as_float(OBF_DPP_MOV(__float_as_uint(v), 0x4E));
+  v += __uint_as_float(OBF_DPP_MOV(__float_as_uint(v), 0x141));
+  v += __uint_as_float(OBF_DPP_MOV(__float_as_uint(v), 0x140));
+  sp = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 0));
+  sr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 16));
+  sq = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 32));
+}
+
 // Inverse iteration on the tridiagonal S - theta I for one eigenvector per lane.  Arrays of the factorisation live at
 // f[(q * m + j) * KS] for q = 0 .. 4: the upper triangle's three diagonals (the first as its reciprocal), the
 // multiplier and the row-exchange flag of step j (elimination with partial pivoting).  KS, the lane stride, is a
-// compile-time constant so that the compiler can tell the entries apart and keep the loads ahead of the stores.
+// compile-time constant.  The three passes are chains through one or two registers; what they read comes from LDS in batches of
+// TE_AHEAD steps, so that the chain does not wait for it step by step.
+constexpr int TE_AHEAD = 8;
+
 template <int KS>
 __device__ __forceinline__ void te_factor(const float* __restrict__ dv, const float* __restrict__ ev, const int m,
                                           const float theta, const float tiny, float* __restrict__ f) {
   float* i0 = f; float* a1 = f + m * KS; float* a2 = a1 + m * KS; float* mu = a2 + m * KS; float* sw = mu + m * KS;
   float r0 = dv[0] - theta, r1 = (m > 1) ? ev[0] : 0.f, r2 = 0.f;
-#pragma unroll 4
-  for (int j = 0; j + 1 < m; ++j) {
-    float n0 = ev[j], n1 = dv[j + 1] - theta, n2 = (j + 2 < m) ? ev[j + 1] : 0.f;
+  auto step = [&](const int j, float n0, const float d1, float n2) {
+    float n1 = d1 - theta;
     const bool swap = fabsf(n0) > fabsf(r0);
     if (swap) { float t; t = r0; r0 = n0; n0 = t; t = r1; r1 = n1; n1 = t; t = r2; r2 = n2; n2 = t; }
     if (r0 == 0.f) r0 = tiny;
@@ -61,7 +80,17 @@ __device__ __forceinline__ void te_factor(const float* __restrict__ dv, const fl
     const float g = n0 * inv;
     i0[j * KS] = inv; a1[j * KS] = r1; a2[j * KS] = r2; mu[j * KS] = g; sw[j * KS] = swap ? 1.f : 0.f;
     r0 = fmaf(-g, r1, n1); r1 = fmaf(-g, r2, n2); r2 = 0.f;
+  };
+  int j0 = 0;
+  for (; j0 + TE_AHEAD + 1 < m; j0 += TE_AHEAD) {
+    float d[TE_AHEAD], e[TE_AHEAD + 1];
+#pragma unroll
+    for (int u = 0; u < TE_AHEAD; ++u) { d[u] = dv[j0 + u + 1]; e[u] = ev[j0 + u]; }
+    e[TE_AHEAD] = ev[j0 + TE_AHEAD];
+#pragma unroll
+    for (int u = 0; u < TE_AHEAD; ++u) step(j0 + u, e[u], d[u], e[u + 1]);
   }
+  for (; j0 + 1 < m; ++j0) step(j0, ev[j0], dv[j0 + 1], (j0 + 2 < m) ? ev[j0 + 1] : 0.f);
   i0[(m - 1) * KS] = 1.f / ((fabsf(r0) > 1e-3f * tiny) ? r0 : tiny);
   a1[(m - 1) * KS] = 0.f; a2[(m - 1) * KS] = 0.f;
 }
@@ -72,14 +101,22 @@ __device__ __forceinline__ void te_forward(const float* __restrict__ f, const in
                                            float* __restrict__ out, const float scale) {
   const float* mu = f + 3 * m * KS; const float* sw = mu + m * KS;
   float carry = in[0] * scale;
-#pragma unroll 4
-  for (int j = 0; j + 1 < m; ++j) {
-    const float nx = in[(j + 1) * KS] * scale, g = mu[j * KS];
-    const bool swap = sw[j * KS] != 0.f;
+  auto step = [&](const int j, const float x, const float g, const float s) {
+    const float nx = x * scale;
+    const bool swap = s != 0.f;
     const float bj = swap ? nx : carry, bn = swap ? carry : nx;
     out[j * KS] = bj;
     carry = fmaf(-g, bj, bn);
+  };
+  int j0 = 0;
+  for (; j0 + TE_AHEAD < m; j0 += TE_AHEAD) {
+    float x[TE_AHEAD], g[TE_AHEAD], s[TE_AHEAD];
+#pragma unroll
+    for (int u = 0; u < TE_AHEAD; ++u) { x[u] = in[(j0 + u + 1) * KS]; g[u] = mu[(j0 + u) * KS]; s[u] = sw[(j0 + u) * KS]; }
+#pragma unroll
+    for (int u = 0; u < TE_AHEAD; ++u) step(j0 + u, x[u], g[u], s[u]);
   }
+  for (; j0 + 1 < m; ++j0) step(j0, in[(j0 + 1) * KS], mu[j0 * KS], sw[j0 * KS]);
   out[(m - 1) * KS] = carry;
 }
 
@@ -89,13 +126,21 @@ __device__ __forceinline__ float te_backward(const float* __restrict__ f, const 
                                              float* __restrict__ out) {
   const float* i0 = f; const float* a1 = f + m * KS; const float* a2 = a1 + m * KS;
   float z1 = 0.f, z2 = 0.f, big = 0.f;
-#pragma unroll 4
-  for (int j = m - 1; j >= 0; --j) {
-    const float v = (in[j * KS] - a1[j * KS] * z1 - a2[j * KS] * z2) * i0[j * KS];
+  auto step = [&](const int j, const float x, const float c1, const float c2, const float iv) {
+    const float v = fmaf(-c1, z1, fmaf(-c2, z2, x)) * iv;
     out[j * KS] = v;
     z2 = z1; z1 = v;
     big = fmaxf(big, fabsf(v));
+  };
+  int j0 = m - 1;
+  for (; j0 >= TE_AHEAD - 1; j0 -= TE_AHEAD) {
+    float x[TE_AHEAD], c1[TE_AHEAD], c2[TE_AHEAD], iv[TE_AHEAD];
+#pragma unroll
+    for (int u = 0; u < TE_AHEAD; ++u) { x[u] = in[(j0 - u) * KS]; c1[u] = a1[(j0 - u) * KS]; c2[u] = a2[(j0 - u) * KS]; iv[u] = i0[(j0 - u) * KS]; }
+#pragma unroll
+    for (int u = 0; u < TE_AHEAD; ++u) step(j0 - u, x[u], c1[u], c2[u], iv[u]);
   }
+  for (; j0 >= 0; --j0) step(j0, in[j0 * KS], a1[j0 * KS], a2[j0 * KS], i0[j0 * KS]);
   return big;
 }
 
@@ -279,13 +324,14 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
   float* zz = lu + 6 * m * KS;        // [m][KS] iteration vectors
 
   // ---- 1. tridiagonalisation (the counts come later)
+  for (int e = tid; e < m * lt; e += TE_THREADS) Rf[e] = 0.f;  // (the reduction starts with a barrier before it writes there)
   if (m <= 32) tri_reduce<1>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
   else if (m <= 64) tri_reduce<2>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
   else if (m <= 96) tri_reduce<3>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
   else tri_reduce<4>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
   if (wave == 0) {
-    // Gershgorin interval of S and its largest squared sub-diagonal entry: lane l looks at rows l and l + 64
-    float lo = INFINITY, hi = -INFINITY, me2 = 0.f;
+    // Gershgorin interval of S and its squared sub-diagonal entries: lane l looks at rows l and l + 64
+    float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int i = lane + 64 * h;
@@ -293,33 +339,36 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
         const float below = (i + 1 < m) ? ev[i] : 0.f, above = (i > 0) ? ev[i - 1] : 0.f;
         const float r = fabsf(above) + fabsf(below);
         lo = fminf(lo, dv[i] - r); hi = fmaxf(hi, dv[i] + r);
-        me2 = fmaxf(me2, below * below);
-        e2[i] = below * below;
+        e2[i] = fmaxf(below * below, 1e-36f);                    // never 0: see the Sturm recurrence
       }
     }
     for (int off = 32; off > 0; off >>= 1) {
-      lo = fminf(lo, __shfl_xor(lo, off)); hi = fmaxf(hi, __shfl_xor(hi, off)); me2 = fmaxf(me2, __shfl_xor(me2, off));
+      lo = fminf(lo, __shfl_xor(lo, off)); hi = fmaxf(hi, __shfl_xor(hi, off));
     }
     if (lane == 0) {
       const float span = hi - lo;
       scal[0] = lo - (1e-3f * span + 1e-30f);
       scal[1] = hi + (1e-3f * span + 1e-30f);
-      scal[2] = 1e-30f * fmaxf(1.f, me2);                        // smallest pivot magnitude of the Sturm recurrence
       scal[3] = 1.2e-7f * fmaxf(fabsf(lo), fabsf(hi));           // pivot perturbation of the inverse iteration
     }
   }
   __syncthreads();
 
   // ---- 2. eigenvalues: number of eigenvalues below x = number of negative terms of the Sturm recurrence
-  const float pivmin = scal[2];
+  // (a pivot that vanishes gives an infinite term and the next step forgets it: the count is right without a guard as long as no
+  // off-diagonal entry is an exact zero; two dependent instructions per step, the rest is read ahead)
   auto sturm = [&](const float x) -> int {
     float q = dv[0] - x;
     int c = q < 0.f;
-    for (int i = 1; i < m; ++i) {
-      if (fabsf(q) < pivmin) q = (q < 0.f) ? -pivmin : pivmin;
-      q = dv[i] - x - e2[i - 1] * __builtin_amdgcn_rcpf(q);
-      c += q < 0.f;
+    int i = 1;
+    for (; i + TE_AHEAD <= m; i += TE_AHEAD) {
+      float d[TE_AHEAD], e[TE_AHEAD];
+#pragma unroll
+      for (int u = 0; u < TE_AHEAD; ++u) { d[u] = dv[i + u] - x; e[u] = e2[i + u - 1]; }
+#pragma unroll
+      for (int u = 0; u < TE_AHEAD; ++u) { q = fmaf(-e[u], __builtin_amdgcn_rcpf(q), d[u]); c += q < 0.f; }
     }
+    for (; i < m; ++i) { q = fmaf(-e2[i - 1], __builtin_amdgcn_rcpf(q), dv[i] - x); c += q < 0.f; }
     return c;
   };
   {
@@ -374,21 +423,23 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
   float* Wv = (k > TE_BATCH) ? zz + m * KS : lu;               // [k][m]; a single pass leaves it where the factors were
   for (int b0 = 0; b0 < k; b0 += TE_BATCH) {
     const int kb = min(TE_BATCH, k - b0);
+    // start: a fixed pseudo-random right-hand side of the first back substitution
+    for (int e = tid; e < m * KS; e += TE_THREADS) {
+      const uint32_t h = ((uint32_t)(e / KS) * 2654435761u + (uint32_t)(b0 + e % KS) * 40503u + 12345u) >> 8;
+      lu[5 * m * KS + e] = (float)(h & 0xffffu) * (1.f / 65536.f) - 0.5f;
+    }
+    __syncthreads();
     if (wave == 0 && lane < kb) {
       float* za = zz + lane;
       float* zb = lu + 5 * m * KS + lane;                      // second vector buffer (behind the factors)
       te_factor<KS>(dv, ev, m, th[b0 + lane], scal[3], lu + lane);
-      for (int j = 0; j < m; ++j) {
-        const uint32_t h = ((uint32_t)j * 2654435761u + (uint32_t)(b0 + lane) * 40503u + 12345u) >> 8;
-        za[j * KS] = (float)(h & 0xffffu) * (1.f / 65536.f) - 0.5f;
-      }
-      // Three solves.  Between them the iterate is only rescaled by its largest magnitude (folded into the next solve's
-      // first pass: the squares of the last normalisation cannot overflow, and nothing else depends on the length).
-      float big = 1.f;
-      for (int it = 0; it < 3; ++it) {
-        te_forward<KS>(lu + lane, m, za, zb, (big > 0.f && big < INFINITY) ? 1.f / big : 1.f);
-        big = te_backward<KS>(lu + lane, m, zb, za);
-      }
+      // Two solves, the first one without its row operations (a random right-hand side is one as well as the other): theta is within
+      // 1e-7 of the spectrum's extent of the eigenvalue, so a solve shrinks the rest of the vector by the gap over that, and two
+      // leave nothing that single precision could tell.  Between them the iterate is only rescaled by its largest magnitude (the
+      // squares of the last normalisation cannot overflow, and nothing else depends on the length).
+      float big = te_backward<KS>(lu + lane, m, zb, za);
+      te_forward<KS>(lu + lane, m, za, zb, (big > 0.f && big < INFINITY) ? 1.f / big : 1.f);
+      big = te_backward<KS>(lu + lane, m, zb, za);
       scal[8 + lane] = big;                                    // the waves of the back-transformation bring it to unit length
     }
     __syncthreads();
@@ -409,17 +460,29 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
         if (fabsf(w0) < 1e-12f) w0 = 0.f;
         if (fabsf(w1) < 1e-12f) w1 = 0.f;
       }
-      // reflector j - 1 is fetched while reflector j is applied (the chain through w is all that is sequential)
-      const float* r0p = Rf + min(lane, m - 1) * lt;
-      const float* r1p = Rf + min(lane + 64, m - 1) * lt;
-      float nb = (m >= 3) ? bet[m - 3] : 0.f, n0 = (m >= 3) ? r0p[m - 3] : 0.f, n1 = (m >= 3) ? r1p[m - 3] : 0.f;
-      for (int j = m - 3; j >= 0; --j) {
-        const float beta = nb;
-        const float v0 = (lane > j && lane < m) ? n0 : 0.f;
-        const float v1 = (lane + 64 > j && lane + 64 < m) ? n1 : 0.f;
-        if (j > 0) { nb = bet[j - 1]; n0 = r0p[j - 1]; n1 = r1p[j - 1]; }
-        const float s = beta * te_wave_sum(fmaf(v0, w0, v1 * w1));   // beta = 0: an identity reflector
-        w0 = fmaf(-s, v0, w0); w1 = fmaf(-s, v1, w1);
+      // Two reflectors at a time: (I - b2 v2 v2^T)(I - b1 v1 v1^T) w needs v1.w, v2.w and v1.v2, three sums that go through the wave
+      // together; the next pair is fetched meanwhile.  Entries on and above the diagonal of Rf are zero (so is its row 0, which
+      // stands in for rows past the matrix).
+      const float* r0p = Rf + (lane < m ? lane : 0) * lt;
+      const float* r1p = Rf + (lane + 64 < m ? lane + 64 : 0) * lt;
+      int j = m - 3;
+      float p0 = 0.f, p1 = 0.f, q0 = 0.f, q1 = 0.f, bp = 0.f, bq = 0.f;
+      auto fetch = [&](const int jj) {                         // reflectors jj and jj - 1
+        const int a = max(jj, 0), b = max(jj - 1, 0);
+        p0 = r0p[a]; p1 = r1p[a]; q0 = r0p[b]; q1 = r1p[b]; bp = bet[a]; bq = bet[b];
+      };
+      fetch(j);
+      for (; j >= 1; j -= 2) {
+        const float v0 = p0, v1 = p1, u0 = q0, u1 = q1, b1 = bp, b2 = bq;
+        fetch(j - 2);
+        float g1, g2, c;
+        te_wave_sum3(fmaf(v0, w0, v1 * w1), fmaf(u0, w0, u1 * w1), fmaf(v0, u0, v1 * u1), g1, g2, c);
+        const float s1 = b1 * g1, s2 = b2 * fmaf(-s1, c, g2);  // beta = 0: an identity reflector
+        w0 = fmaf(-s2, u0, fmaf(-s1, v0, w0)); w1 = fmaf(-s2, u1, fmaf(-s1, v1, w1));
+      }
+      if (j == 0) {
+        const float s = bp * te_wave_sum(fmaf(p0, w0, p1 * w1));
+        w0 = fmaf(-s, p0, w0); w1 = fmaf(-s, p1, w1);
       }
     }
     __syncthreads();                                           // every wave has read its column of zz / lu is free

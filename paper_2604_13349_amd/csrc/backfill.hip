@@ -1262,11 +1262,64 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
 }
 
 // ------------------------------------------------------------------------------------------------
+// orth of App. H's iteration for one wave: Gram-Schmidt over the kk <= KQ rows of Yb (128 floats apart, m entries) in order, two passes
+// each; a row left with at most 1e-5 of the first row's norm depends on the rows before it and is dropped.  The kept rows go to Ya;
+// returns their number.  All rows are in registers, a pass takes the coefficients on all earlier rows at once (a dropped row is zero).
+template <int KQ>
+__device__ __forceinline__ int lead_orth(float* __restrict__ Ya, const float* __restrict__ Yb, const int m, const int kk) {
+  const int lane = threadIdx.x & 63;
+  float x0[KQ], x1[KQ];
+#pragma unroll
+  for (int i = 0; i < KQ; ++i) {
+    x0[i] = (i < kk && lane < m) ? Yb[i * 128 + lane] : 0.f;
+    x1[i] = (i < kk && lane + 64 < m) ? Yb[i * 128 + lane + 64] : 0.f;
+  }
+  int nk = 0;
+  float first = -1.f;
+#pragma unroll
+  for (int i = 0; i < KQ; ++i) {
+    if (i < kk) {
+#pragma unroll
+      for (int pass = 0; pass < 2; ++pass) {
+        float g[KQ + 2];
+#pragma unroll
+        for (int j = 0; j < i; j += 3) {
+          const int j1 = (j + 1 < i) ? j + 1 : j, j2 = (j + 2 < i) ? j + 2 : j;
+          te_wave_sum3(fmaf(x0[i], x0[j], x1[i] * x1[j]), fmaf(x0[i], x0[j1], x1[i] * x1[j1]), fmaf(x0[i], x0[j2], x1[i] * x1[j2]),
+                       g[j], g[j + 1], g[j + 2]);
+        }
+#pragma unroll
+        for (int j = 0; j < i; ++j) { x0[i] = fmaf(-g[j], x0[j], x0[i]); x1[i] = fmaf(-g[j], x1[j], x1[i]); }
+      }
+      const float nn = sqrtf(te_wave_sum(fmaf(x0[i], x0[i], x1[i] * x1[i])));
+      if (first < 0.f) first = nn;
+      const bool kept = first > 0.f && nn > 1e-5f * first;
+      const float rn = kept ? 1.f / nn : 0.f;
+      x0[i] = kept ? x0[i] * rn : 0.f; x1[i] = kept ? x1[i] * rn : 0.f;
+      if (kept) {
+        if (lane < m) Ya[nk * 128 + lane] = x0[i];
+        if (lane + 64 < m) Ya[nk * 128 + lane + 64] = x1[i];
+        ++nk;
+      }
+    }
+  }
+  return nk;
+}
+
+// ------------------------------------------------------------------------------------------------
 // The heads the finalisation handed over: leading eigenpairs of T by the direct route, then Eq. 4-7 as there.
 // iters > 0 selects the fast path of App. H instead: `iters` steps of C <- orth(C G) from a fixed orthonormal start,
 // carried out in complement coordinates (G = Z^T T Z, so a row c of C is followed as its coordinates c Z^T and
 // C G becomes Y T); the direct route then runs only when diagnostics are wanted, to report how far the fast path's
 // Delta is from it.
+// Floats of dynamic LDS of that kernel for complements up to mmax wide and kq directions; d != 0: the fast path at that head_dim
+// (start rows behind the scratch of the direct route; the rows, their images and the partial sums take 128 floats a row).
+inline size_t lead_lds_floats(int mmax, int kq, int d) {
+  const size_t mat = (size_t)mmax * (mmax | 1) + 4, direct = tri_work_floats(mmax, kq) + (size_t)kq * d;
+  const size_t fast = d ? (size_t)128 * (2 * kq + 4 * (kq < 4 ? kq : 4)) : 0;
+  return mat + (direct > fast ? direct : fast);
+}
+
 template <typename T>
 __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, HeadState* __restrict__ state, float* __restrict__ mats,
                                                           float* __restrict__ delta, float* __restrict__ delta_out,
@@ -1317,31 +1370,31 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
       }
     }
   }
-  // Delta in complement coordinates (times a_del + eps) from kk orthonormal rows Cb [kk][m]: Eq. 5
-  auto project = [&](const float* Cb, const int kk) {
+  // Delta in complement coordinates (times a_del + eps) from kk orthonormal rows, `cs` floats apart in Cb: Eq. 5
+  auto project = [&](const float* Cb, const int cs, const int kk) {
     for (int v = wave; v < kk; v += TE_WAVES) {
-      float sc = (lane < m) ? rbar[lane] * Cb[v * m + lane] : 0.f;
-      if (lane + 64 < m) sc = fmaf(rbar[lane + 64], Cb[v * m + lane + 64], sc);
+      float sc = (lane < m) ? rbar[lane] * Cb[v * cs + lane] : 0.f;
+      if (lane + 64 < m) sc = fmaf(rbar[lane + 64], Cb[v * cs + lane + 64], sc);
       sc = te_wave_sum(sc);
       if (lane == 0) dvec[v] = sc;
     }
     __syncthreads();
     if (tid < m) {
       float sd = 0.f;
-      for (int i = 0; i < kk; ++i) sd = fmaf(dvec[i], Cb[i * m + tid], sd);
+      for (int i = 0; i < kk; ++i) sd = fmaf(dvec[i], Cb[i * cs + tid], sd);
       dcomp[tid] = sd;
     }
     __syncthreads();
   };
   // Per-token alternative (App. D): the subspace goes to the head's second scratch matrix in head_dim coordinates
   // (row i: sum_t Cb[i][t] Z[t][:]) for the kernel that forms the per-slot directions.
-  auto export_basis = [&](const float* Cb, const int kk) {
+  auto export_basis = [&](const float* Cb, const int cs, const int kk) {
     if (!(vflags & VF_PER_TOKEN)) return;
     float* Cg = mats + ((size_t)head * 3 + 1) * d * d;
     for (int e = tid; e < kk * d; e += TE_THREADS) {
       const int i = e / d, c = e - i * d;
       float s = 0.f;
-      for (int t = 0; t < m; ++t) s = fmaf(Cb[i * m + t], Zg[(size_t)t * d + c], s);
+      for (int t = 0; t < m; ++t) s = fmaf(Cb[i * cs + t], Zg[(size_t)t * d + c], s);
       Cg[e] = s;
     }
   };
@@ -1368,45 +1421,77 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
     k_used = s_k;
     revr = (k_used > 0) ? s_off : 0.f;
     __syncthreads();
-    project(Wk, k_used);
-    if (iters <= 0) export_basis(Wk, k_used);
+    project(Wk, m, k_used);
+    if (iters <= 0) export_basis(Wk, m, k_used);
   }
   if (iters > 0) {
     if (diag != nullptr && tid < m) dex[tid] = dcomp[tid];     // the direct route's Delta, for the error report
     __syncthreads();                                           // the direct route's LDS is free
-    float* Tl = sm;                                            // [m][lt]
-    float* Ya = work;                                          // [TE_MAXK][m] the current rows
-    float* Yb = Ya + TE_MAXK * m;                              // [TE_MAXK][m] their images under T
+    // T lives in registers: thread (t, g) = (tid % 128, tid / 128) holds T[s][t] for the rp rows s = rp g + u
+    const int t = tid & 127, grp = tid >> 7, rp = ((m + 15) >> 4) << 2;
+    float tr[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) tr[u] = (u < rp && grp * rp + u < m && t < m) ? Tg[(size_t)(grp * rp + u) * m + t] : 0.f;
+    float* Ya = work;                                          // [kq][128] the current rows, zero past m
+    float* Yb = Ya + kq * 128;                                 // [kq][128] their images under T
+    float* psum = Yb + kq * 128;                               // [4 groups][4 rows][128], once the start rows are done with
     float* c0 = work + tri_work_floats(m, kq);                 // [k][d] start rows (the host sized the LDS for them)
     const int k0 = min(min(rank, m), st.n_del);
-    for (int e = tid; e < m * m; e += TE_THREADS) { const int a = e / m; Tl[a * lt + (e - a * m)] = Tg[e]; }
+    for (int e = tid; e < kq * 128; e += TE_THREADS) Ya[e] = 0.f;
     // C_0: the first rows of the orthonormal cosine basis, C_0[i][c] = sqrt(2/d) cos(pi (i + 1/2)(c + 1/2) / d)
     for (int e = tid; e < k0 * d; e += TE_THREADS) {
       const int i = e / d, c = e - i * d;
       c0[e] = sqrtf(2.f / (float)d) * cospif((float)((2 * i + 1) * (2 * c + 1)) / (float)(4 * d));
     }
     __syncthreads();
-    for (int v = wave; v < k0; v += TE_WAVES) {
-      for (int t = lane; t < m; t += 64) {
-        float sy = 0.f;
-        for (int c = 0; c < d; ++c) sy = fmaf(c0[v * d + c], Zg[(size_t)t * d + c], sy);
-        Ya[v * m + t] = sy;
+    // Y_0 = C_0 Z^T, a wave per complement row as for y above, three start rows' sums at a time
+    fetch_rows(wave);
+    for (int t0 = wave; t0 < m; t0 += 4 * TE_WAVES) {
+      float c0v[4], c1v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { c0v[q] = z0[q]; c1v[q] = z1[q]; }
+      fetch_rows(t0 + 4 * TE_WAVES);
+      for (int v = 0; v < k0; v += 3) {
+        float x0[3], x1[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          const float* cr = c0 + min(v + i, k0 - 1) * d;
+          x0[i] = (lane < d) ? cr[lane] : 0.f; x1[i] = (lane + 64 < d) ? cr[lane + 64] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float g[3];
+          te_wave_sum3(fmaf(c1v[q], x1[0], c0v[q] * x0[0]), fmaf(c1v[q], x1[1], c0v[q] * x0[1]), fmaf(c1v[q], x1[2], c0v[q] * x0[2]),
+                       g[0], g[1], g[2]);
+          const int t = t0 + q * TE_WAVES;
+          if (lane < 3 && v + lane < k0 && t < m) Ya[(v + lane) * 128 + t] = (lane == 0) ? g[0] : (lane == 1) ? g[1] : g[2];
+        }
       }
     }
     if (tid == 0) s_k = k0;
     __syncthreads();
-    auto times_T = [&](const int kk) {                         // Yb = Ya T (T is symmetric: row s is read as column s)
-      for (int v = wave; v < kk; v += TE_WAVES) {
-        float a0 = 0.f, a1 = 0.f;
-        for (int s = 0; s < m; ++s) {
-          const float ys = Ya[v * m + s];
-          a0 = fmaf(ys, (lane < m) ? Tl[s * lt + lane] : 0.f, a0);
-          a1 = fmaf(ys, (lane + 64 < m) ? Tl[s * lt + lane + 64] : 0.f, a1);
+    auto times_T = [&](const int kk) {                         // Yb = Ya T (T is symmetric), four rows at a time
+      for (int v0 = 0; v0 < kk; v0 += 4) {
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 32; u += 4) {
+          if (u < rp) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float4 y = *(const float4*)&Ya[min(v0 + i, kk - 1) * 128 + grp * rp + u];
+              acc[i] = fmaf(y.w, tr[u + 3], fmaf(y.z, tr[u + 2], fmaf(y.y, tr[u + 1], fmaf(y.x, tr[u], acc[i]))));
+            }
+          }
         }
-        if (lane < m) Yb[v * m + lane] = a0;
-        if (lane + 64 < m) Yb[v * m + lane + 64] = a1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) if (v0 + i < kk) psum[(grp * min(kk, 4) + i) * 128 + t] = acc[i];
+        __syncthreads();
+        if (v0 + grp < kk) {                                   // group g adds row v0 + g
+          const int n = min(kk, 4);
+          Yb[(v0 + grp) * 128 + t] = (psum[grp * 128 + t] + psum[(n + grp) * 128 + t]) + (psum[(2 * n + grp) * 128 + t] + psum[(3 * n + grp) * 128 + t]);
+        }
+        __syncthreads();
       }
-      __syncthreads();
     };
     for (int it = 0; it < iters; ++it) {
       const int kk = s_k;
@@ -1414,27 +1499,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
       if (kk == 0) break;                                      // uniform
       times_T(kk);
       if (wave == 0) {
-        // orth: Gram-Schmidt over the rows in order, two passes each; a row left with at most 1e-5 of the first row's
-        // norm depends on the rows before it and is dropped
-        int nk = 0;
-        float first = -1.f;
-        for (int i = 0; i < kk; ++i) {
-          float x0 = (lane < m) ? Yb[i * m + lane] : 0.f, x1 = (lane + 64 < m) ? Yb[i * m + lane + 64] : 0.f;
-          for (int pass = 0; pass < 2; ++pass) {
-            for (int j = 0; j < nk; ++j) {
-              const float y0 = (lane < m) ? Ya[j * m + lane] : 0.f, y1 = (lane + 64 < m) ? Ya[j * m + lane + 64] : 0.f;
-              const float dt = te_wave_sum(fmaf(x0, y0, x1 * y1));
-              x0 = fmaf(-dt, y0, x0); x1 = fmaf(-dt, y1, x1);
-            }
-          }
-          const float nn = sqrtf(te_wave_sum(fmaf(x0, x0, x1 * x1)));
-          if (first < 0.f) first = nn;
-          if (!(first > 0.f) || !(nn > 1e-5f * first)) continue;
-          const float rn = 1.f / nn;
-          if (lane < m) Ya[nk * m + lane] = x0 * rn;
-          if (lane + 64 < m) Ya[nk * m + lane + 64] = x1 * rn;
-          ++nk;
-        }
+        const int nk = (kk <= 4) ? lead_orth<4>(Ya, Yb, m, kk) : lead_orth<TE_MAXK>(Ya, Yb, m, kk);
         if (lane == 0) s_k = nk;
       }
       __syncthreads();
@@ -1445,8 +1510,8 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
     if (k_used > 0) {
       times_T(k_used);                                         // explained share: sum_i c_i T c_i^T over the trace
       for (int v = wave; v < k_used; v += TE_WAVES) {
-        float sc = (lane < m) ? Ya[v * m + lane] * Yb[v * m + lane] : 0.f;
-        if (lane + 64 < m) sc = fmaf(Ya[v * m + lane + 64], Yb[v * m + lane + 64], sc);
+        float sc = (lane < m) ? Ya[v * 128 + lane] * Yb[v * 128 + lane] : 0.f;
+        if (lane + 64 < m) sc = fmaf(Ya[v * 128 + lane + 64], Yb[v * 128 + lane + 64], sc);
         sc = te_wave_sum(sc);
         if (lane == 0) dvec[v] = sc;
       }
@@ -1459,8 +1524,8 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
       __syncthreads();
       revr = s_off;
       __syncthreads();
-      project(Ya, k_used);
-      export_basis(Ya, k_used);
+      project(Ya, 128, k_used);
+      export_basis(Ya, 128, k_used);
     } else {
       if (tid < m) dcomp[tid] = 0.f;
       __syncthreads();
@@ -1557,7 +1622,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     (void)hipFuncSetAttribute((const void*)k_bf_keep_gram_part<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 128 * 8);
     (void)hipFuncSetAttribute((const void*)k_bf_finalize<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 129 * 4);
     (void)hipFuncSetAttribute((const void*)k_bf_lead<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)sizeof(float) * (128 * 129 + 4 + tri_work_floats(128, TE_MAXK) + TE_MAXK * 128));
+                              (int)(sizeof(float) * lead_lds_floats(128, TE_MAXK, 128)));
   });
   if (var.subspace_iters > 0 && !(var.flags & VF_NAIVE) &&
       (rank > TE_MAXK || (var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) || m.d > 128)) {
@@ -1645,8 +1710,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     if (check_launch("backfill finalize") != OBF_OK) return OBF_ERR_HIP;
     if (lead) {
       const int kq = rank < TE_MAXK ? rank : TE_MAXK;
-      const size_t lds = sizeof(float) * ((size_t)m_direct_max * (m_direct_max | 1) + 4 + tri_work_floats(m_direct_max, kq) +
-                                          (iters > 0 ? (size_t)kq * m.d : 0));
+      const size_t lds = sizeof(float) * lead_lds_floats(m_direct_max, kq, iters > 0 ? m.d : 0);
       hipLaunchKernelGGL(k_bf_lead<T>, dim3(m.heads), dim3(TE_THREADS), lds, st, m.d, rank, state, mats, delta, delta_out, diag,
                          (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, scores, idx, var.flags, m.scs,
                          (const LeadJob*)lead, iters);

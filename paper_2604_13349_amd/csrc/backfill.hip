@@ -593,6 +593,113 @@ __device__ __forceinline__ void fn_emit(const int head, const int d, const int r
   }
 }
 
+// ---- An orthonormal basis Z of the complement of at most FN_FEW orthonormal rows Q [r][d], m = d - r.
+// Householder reconstruction (Ballard, Demmel, Grigori, Jacquelin, Nguyen, Solomonik: "Reconstructing Householder vectors from
+// tall-skinny QR"): with Q1 = Q[:, :r], Q2 = Q[:, r:] and signs S = diag(+-1), M = Q1^T - S factors without pivoting when
+// S_k is minus the sign of the k-th diagonal entry at its turn (every pivot is at least 1), and the orthogonal matrix
+// I - Y T Y^T whose first columns are Q^T S has as its others Z = [0 | I] + W (S Q - [I | 0]), W = Q2^T M^-1.  So instead of a
+// pivoted factorisation of the d x d projector with m sequential pivots there are r <= 32 sequential pivots on an r x r matrix, and
+// two thin matrix products.  For more rows the pivots' number turns against it and the projector route stays.
+constexpr int FN_FEW = 32;
+constexpr int FN_LDN = FN_FEW + 1;       // row stride of the small matrices in LDS
+
+// One wave: N = M^-1 S (rows and columns past r zero) to LDS, the signs to sg.  In-place Gauss-Jordan, lane c holds column c; the rows
+// move up by one register per step so that the pivot row is always the first and the loop stays rolled.
+__device__ __forceinline__ void fn_invert_block(const float* __restrict__ Qb, const int r, const int d, float* __restrict__ N,
+                                                float* __restrict__ sg) {
+  const int lane = threadIdx.x & 63;
+  float a[FN_FEW];
+  {
+    const float4* q = (const float4*)(Qb + (size_t)(lane < r ? lane : 0) * d);     // column c of Q1^T is the head of row c of Q
+#pragma unroll
+    for (int i = 0; i < FN_FEW; i += 4) {
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (lane < r) v = q[i >> 2];
+      a[i] = v.x; a[i + 1] = v.y; a[i + 2] = v.z; a[i + 3] = v.w;
+    }
+#pragma unroll
+    for (int i = 0; i < FN_FEW; ++i) if (i >= r || lane >= r) a[i] = (i == lane) ? 1.f : 0.f;      // padding: an identity block
+  }
+  float sign = 1.f;
+#pragma unroll 1
+  for (int k = 0; k < FN_FEW; ++k) {
+    auto of_column_k = [&](const float x) -> float { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), k)); };
+    const float f0 = of_column_k(a[0]);
+    const float s = (f0 >= 0.f) ? -1.f : 1.f, p = f0 - s;
+    float ip = __builtin_amdgcn_rcpf(p);
+    ip = fmaf(fmaf(-p, ip, 1.f), ip, ip);
+    const bool mine = lane == k;
+    if (mine) sign = s;
+    const float row = mine ? ip : a[0] * ip;
+    const float sub = mine ? ip + 1.f : row;                   // the pivot column becomes -f ip: f - f (ip + 1)
+#pragma unroll
+    for (int i = 1; i < FN_FEW; i += 4) {                      // four lane reads ahead of the four uses (a use must wait for its read)
+      float f[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) f[u] = (i + u < FN_FEW) ? of_column_k(a[i + u]) : 0.f;
+      asm volatile("" : "+s"(f[0]), "+s"(f[1]), "+s"(f[2]), "+s"(f[3]));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) if (i + u < FN_FEW) a[i + u - 1] = fmaf(-f[u], sub, a[i + u]);
+    }
+    a[FN_FEW - 1] = row;
+  }
+  if (lane < FN_FEW) {
+#pragma unroll
+    for (int i = 0; i < FN_FEW; ++i) N[i * FN_LDN + lane] = (i < r && lane < r) ? a[i] * sign : 0.f;
+    sg[lane] = (lane < r) ? sign : 0.f;
+  }
+}
+
+// The whole workgroup, after a barrier behind fn_invert_block (N at sm + m (d + 1)) and the staging of Q (sm, FN_FEW rows, row stride
+// d + 1): Z in Q's place and in global memory.  Ends with a barrier.
+__device__ __forceinline__ void fn_complement(const int r, const int d, const int m, float* sm, const float* __restrict__ sg,
+                                              float* __restrict__ Zg) {
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ld = d + 1, MB = (m + 31) >> 5, TD = d >> 5;
+  float* N = sm + m * ld;                                      // then V = W S, in the same place
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  if (wave < MB) {                                             // V = Q2^T N
+    const float* qp = sm + r + min(wave * 32 + l31, m - 1);    // rows past m: the last one again, not stored
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(qp[(2 * u + lh) * ld], N[(2 * u + lh) * FN_LDN + l31], acc, 0, 0, 0);
+  }
+  // operands of the wave's tile of Z meanwhile: rows of S Q - [I | 0], that is (with V = W S) of Q - [S | 0]
+  const int tb = wave / TD, cb = wave % TD;
+  const bool ztile = wave < MB * TD;
+  const int col = cb * 32 + l31;
+  float bv[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) { const int k = 2 * u + lh; bv[u] = ztile ? sm[k * ld + col] - (col == k ? sg[k] : 0.f) : 0.f; }
+  __syncthreads();                                             // N and Q are read
+  if (wave < MB) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int t = wave * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
+      if (t < m) N[t * FN_LDN + l31] = acc[i];
+    }
+  }
+  __syncthreads();
+  if (ztile) {
+    const int t0 = tb * 32;
+    const float* vp = N + min(t0 + l31, m - 1) * FN_LDN;
+    f32x16 z;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = (col == r + t0 + (i >> 2) * 8 + lh * 4 + (i & 3)) ? 1.f : 0.f;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) z = __builtin_amdgcn_mfma_f32_32x32x2f32(vp[2 * u + lh], bv[u], z, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int t = t0 + (i >> 2) * 8 + lh * 4 + (i & 3);
+      if (t < m) { sm[t * ld + col] = z[i]; Zg[(size_t)t * d + col] = z[i]; }
+    }
+  }
+  __syncthreads();
+}
+
 template <typename T>
 __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int nstat, int rank,
                                                             HeadState* __restrict__ state,
@@ -615,6 +722,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
   __shared__ float uvec[128], svec[128], rbar[128], dvec[128], lamv[128];
   __shared__ int order[128];
   __shared__ float fred[FN_WAVES];
+  __shared__ double dred[4];
   __shared__ int s_k;
   __shared__ float s_off;
   __shared__ __attribute__((aligned(16))) float xcol[128], xcol2[128];
@@ -660,44 +768,61 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     float* Yg = Zg + (size_t)d * d;                            // [m][d] Z G
     float* Gg = Yg + (size_t)d * d;                            // [d][d] G summed over the chunk partials
 
-    // G = sum of chunk partials (fixed order), u, ||V_del||^2
-    // only the 32 x 32 tiles on and below the diagonal of a partial are defined; the sum is mirrored
-    for (int e = tid * 4; e < d * d; e += FN_THREADS * 4) {
-      const int row = e / d, col = e - row * d;
-      if ((row >> 5) < (col >> 5)) continue;
-      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 8
-      for (int c = 0; c < nstat; ++c) {
-        const float4 q = *(const float4*)(gp + c * pstride + e);
-        s.x += q.x; s.y += q.y; s.z += q.z; s.w += q.w;
+    const int lane = tid & 63, l31 = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lgd = (d == 128) ? 7 : 6;
+    // Few retained rows: Z comes from the r x r leading block of Q (fn_complement below) instead of the projector.  The last wave inverts
+    // that block while the others sum G.  At r = 32, head_dim 128: 11k cycles more than the sum alone and 12k for the products, where P
+    // and its factorisation took 11k and 136k (whole kernel 228k -> 92k cycles, a 256-token call 415 -> 340 us).
+    const bool few = r <= FN_FEW;                              // uniform
+    const bool inverting = few && wave == FN_WAVES - 1;
+    if (inverting) {
+      fn_invert_block(Qb, r, d, sm + m * ld, dvec);
+    } else {
+      if (few) {                                               // Q to LDS, rows past r zero (where Z will be)
+        for (int e = tid; e < FN_FEW * d; e += FN_THREADS - 64) sm[(e >> lgd) * ld + (e & (d - 1))] = ((e >> lgd) < r) ? Qb[e] : 0.f;
       }
-      *(float4*)(Gg + e) = s;                                  // read back (through L2) when X = G Z^T is formed
-      if ((row >> 5) > (col >> 5)) {
-        Gg[(col + 0) * d + row] = s.x; Gg[(col + 1) * d + row] = s.y;
-        Gg[(col + 2) * d + row] = s.z; Gg[(col + 3) * d + row] = s.w;
+      // G = sum of chunk partials (fixed order), u, ||V_del||^2
+      // only the 32 x 32 tiles on and below the diagonal of a partial are defined; the sum is mirrored
+      const int step = 4 * (few ? FN_THREADS - 64 : FN_THREADS);
+      for (int e = tid * 4; e < d * d; e += step) {
+        const int row = e >> lgd, col = e & (d - 1);
+        if ((row >> 5) < (col >> 5)) continue;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+        for (int c = 0; c < nstat; ++c) {
+          const float4 q = *(const float4*)(gp + c * pstride + e);
+          s.x += q.x; s.y += q.y; s.z += q.z; s.w += q.w;
+        }
+        *(float4*)(Gg + e) = s;                                // read back (through L2) when X = G Z^T is formed
+        if ((row >> 5) > (col >> 5)) {
+          Gg[(col + 0) * d + row] = s.x; Gg[(col + 1) * d + row] = s.y;
+          Gg[(col + 2) * d + row] = s.z; Gg[(col + 3) * d + row] = s.w;
+        }
       }
-    }
-    if (tid < d) {
-      float s = 0.f;
+      if (tid < d) {
+        float s = 0.f;
 #pragma unroll 8
-      for (int c = 0; c < nstat; ++c) s += gp[c * pstride + d * d + tid];
-      uvec[tid] = s;
-      float s2 = 0.f;
+        for (int c = 0; c < nstat; ++c) s += gp[c * pstride + d * d + tid];
+        uvec[tid] = s;
+        float s2 = 0.f;
 #pragma unroll 8
-      for (int c = 0; c < nstat; ++c) s2 += gp[c * pstride + d * d + d + tid];
-      svec[tid] = s2;
+        for (int c = 0; c < nstat; ++c) s2 += gp[c * pstride + d * d + d + tid];
+        svec[tid] = s2;
+      }
     }
     float vd2 = 0.f;
 #pragma unroll 8
     for (int c = 0; c < nstat; ++c) vd2 += gp[c * pstride + d * d + 2 * d];
 
     __syncthreads();                                           // G is in global scratch for every thread of the workgroup
+    const int TD = d >> 5;
+    if (few) {
+      fn_complement(r, d, m, sm, dvec, Zg);
+    } else {
     // P = I - Q^T Q (projector onto the complement of the retained span, Eq. 3) on the matrix cores: wave (rb, cb)
     // holds the 32 x 32 tile of P in 16 registers per lane, entry i of lane l being
     // P[rb*32 + (i/4)*8 + (l/32)*4 + i%4][cb*32 + l%32].
-    const int lane = tid & 63, l31 = lane & 31, lh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int TD = d >> 5;
     // P is symmetric: only the tiles on and below the diagonal are formed and deflated (10 of 16 at d = 128; the waves
     // of the others stay out of the way), and a column's entries above the diagonal block are read off as the row of
     // the mirrored tile
@@ -841,10 +966,12 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
       }
     }
     __syncthreads();
+    for (int e = tid; e < m * d; e += FN_THREADS) Zg[e] = U[(e >> lgd) * ld + (e & (d - 1))];   // Z to global scratch (for the last phase)
+    }
 
-    // projection cosine (App. K.2): with s the column sum of V_del, the column sum of V_par is s - Z^T Z s, and
+    // projection cosine (App. K.2; diagnostics only): with s the column sum of V_del, the column sum of V_par is s - Z^T Z s, and
     // their cosine is |s_par| / |s| = sqrt(1 - |Z s|^2 / |s|^2)
-    {
+    if (diag) {
       float zs2 = 0.f, sd2 = 0.f;
       if (tid < m) { float z = 0.f; for (int c = 0; c < d; ++c) z = fmaf(U[tid * ld + c], svec[c], z); zs2 = z * z; }
       if (tid < d) sd2 = svec[tid] * svec[tid];
@@ -855,10 +982,9 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
       pc = (s2 > 0.f) ? sqrtf(fmaxf(s2 - z2, 0.f) / s2) : 0.f;
       __syncthreads();
     }
-    // Z to global scratch (for the last phase), X = G Z^T (d x m) and T = Z X (m x m) on the matrix cores.
+    // X = G Z^T (d x m) and T = Z X (m x m) on the matrix cores.
     // T is the residual Gram matrix R^T R = P G P restricted to the complement; its eigenpairs (lambda, w) give
     // those of P G P as (lambda, Z^T w).
-    for (int e = tid; e < m * d; e += FN_THREADS) Zg[e] = U[(e / d) * ld + (e % d)];
     const int MB = (m + 31) >> 5, MP = MB << 5;
     float* Xg = Yg;                                              // [d][MP]
     if (wave < TD * MB) {
@@ -907,32 +1033,19 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
         for (int u = 0; u < 8; ++u) ta = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], bv[u], ta, 0, 0, 0);
       }
     }
-    __syncthreads();                                             // Z (in LDS) is dead from here on
-    U = (2 * mm * lt <= fn_small_floats(d)) ? sm + mm * lt : sm + d * ld;   // W next to T, or in the second buffer of the large launch
-    if (ttile) {
+    {                                                            // trace(T) = ||R||_F^2, summed in double: the diagonal tiles' shares
+      double tr = 0.0;
+      if (ttile && sblk == tblk2) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int srow = sblk * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), t = tblk2 * 32 + l31;
-        if (srow < m && t < m) M[srow * lt + t] = ta[i];
+        for (int i = 0; i < 16; ++i) if ((i >> 2) * 8 + lh * 4 + (i & 3) == l31) tr = (double)ta[i];     // rows past m are zero
+        for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
+        if (lane == 0) dred[sblk] = tr;
       }
     }
-    if (mm > m) for (int e = tid; e < mm; e += FN_THREADS) { M[m * lt + e] = 0.f; M[e * lt + m] = 0.f; }
-    __syncthreads();
-    // symmetrise, W = I, trace
-    for (int e = tid; e < mm * mm; e += FN_THREADS) {
-      const int a = e / mm, b = e - a * mm;
-      if (a < b) M[a * lt + b] = M[b * lt + a];                  // the upper triangle mirrors the computed lower one
-      U[a * lt + b] = (a == b) ? 1.f : 0.f;
-    }
-    __syncthreads();
-    if (wave == 0) {                                             // trace(T) = ||R||_F^2, summed in double
-      double tr = (lane < m) ? (double)M[lane * lt + lane] : 0.0;
-      if (lane + 64 < m) tr += (double)M[(lane + 64) * lt + lane + 64];
-      for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
-      if (lane == 0) s_off = (float)tr;
-    }
-    __syncthreads();
-    const float res2 = s_off;
+    __syncthreads();                                             // Z (in LDS) is dead from here on
+    double tr = 0.0;
+    for (int b = 0; b < MB; ++b) tr += dred[b];
+    const float res2 = (float)tr;
     rcr = res2 / (vd2 + 1e-12f);
     pcr = fmaxf(vd2 - res2, 0.f) / (vd2 + 1e-12f);
     const bool negligible = !(res2 > kRcrSkip * vd2) || m <= 0;
@@ -945,7 +1058,13 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
                         kq <= TE_MAXK && m >= m_direct_min && m <= m_direct_max;
     if (direct) {
       float* Tg = Gg;                                            // G itself is no longer needed
-      for (int e = tid; e < m * m; e += FN_THREADS) { const int a = e / m; Tg[e] = M[a * lt + (e - a * m)]; }
+      if (ttile) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int srow = sblk * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), t = tblk2 * 32 + l31;
+          if (srow < m && t <= srow) { Tg[srow * m + t] = ta[i]; Tg[t * m + srow] = ta[i]; }    // the upper triangle mirrors the lower one
+        }
+      }
       if (tid < d) delta[(size_t)head * d + tid] = uvec[tid];    // u = sum_j A_j v_j; the other kernel replaces it by delta
       if (tid == 0) {
         LeadJob jb;
@@ -954,7 +1073,24 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
       }
       return;
     }
-    if (!negligible && !direct) {
+    U = (2 * mm * lt <= fn_small_floats(d)) ? sm + mm * lt : sm + d * ld;   // W next to T, or in the second buffer of the large launch
+    if (ttile) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int srow = sblk * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), t = tblk2 * 32 + l31;
+        if (srow < m && t < m) M[srow * lt + t] = ta[i];
+      }
+    }
+    if (mm > m) for (int e = tid; e < mm; e += FN_THREADS) { M[m * lt + e] = 0.f; M[e * lt + m] = 0.f; }
+    __syncthreads();
+    // symmetrise, W = I
+    for (int e = tid; e < mm * mm; e += FN_THREADS) {
+      const int a = e / mm, b = e - a * mm;
+      if (a < b) M[a * lt + b] = M[b * lt + a];                  // the upper triangle mirrors the computed lower one
+      U[a * lt + b] = (a == b) ? 1.f : 0.f;
+    }
+    __syncthreads();
+    if (!negligible) {
       // cyclic Jacobi with a round-robin ordering: mm/2 disjoint rotations per round
       const int half = mm / 2;
       // Wide complements: only W_k W_k^T y is needed of the eigenvectors (y = Z u, W_k the k_used leading ones), and

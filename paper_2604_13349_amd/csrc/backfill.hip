@@ -712,7 +712,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
                                                             const int32_t* __restrict__ idx, int vflags, float evr_tau,
                                                             int scs, float* __restrict__ rot /*nullable*/,
                                                             LeadJob* __restrict__ lead /*nullable: no leading-eigenpair kernel follows*/,
-                                                            int m_direct_min, int m_direct_max) {
+                                                            int m_direct_min) {
   extern __shared__ float sm[];
   const int head = blockIdx.x;
   const int ld = d + 1;
@@ -733,12 +733,23 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
   int k_used = 0;
   const int tid = threadIdx.x;
   const bool naive = (vflags & VF_NAIVE) != 0;
+  // Only a few leading eigenpairs wanted (the method itself: k = pca_rank, no Max-P / EVR rule) from a wide enough complement: the head
+  // goes to the leading-eigenpair kernel (tridiagonalisation + bisection + inverse iteration, with a register budget of its own)
+  // instead of having all of T diagonalised here.
+  const int m_span = d - st.r_keep;
+  const bool direct_ok = lead != nullptr && !(vflags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) && min(rank, m_span) >= 1 &&
+                         min(rank, m_span) <= TE_MAXK && m_span >= m_direct_min;
   {
-    // Two launches share the heads: the first has fn_small_floats(d) floats of LDS (two workgroups per CU) and takes
-    // every head whose complement is small enough for T and W to fit there, the second takes the rest.
-    const int m0 = (st.active && !naive) ? d - st.r_keep : 0;
-    const int mm0 = m0 + (m0 & 1);
-    const int big = 2 * mm0 * (mm0 + 1) > fn_small_floats(d);
+    // Two launches share the heads: the first has fn_small_floats(d) floats of LDS (two workgroups per CU) and takes every head that
+    // fits there, the second takes the rest.  A head needs room for Z and, by its route, the small matrices of fn_complement or the
+    // projector's columns; one that is diagonalised here also for T and W.
+    int need = 0;
+    if (st.active && !naive) {
+      const int mm0 = m_span + (m_span & 1);
+      need = m_span * (ld + (st.r_keep <= FN_FEW ? FN_LDN : 0));
+      if (!direct_ok) need = max(need, 2 * mm0 * (mm0 + 1));
+    }
+    const int big = need > fn_small_floats(d);
     if (cls >= 0 && big != cls) return;                        // cls < 0: one launch with the large LDS takes every head
   }
   if (lead && tid == 0) lead[head].pending = 0;
@@ -1050,12 +1061,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     pcr = fmaxf(vd2 - res2, 0.f) / (vd2 + 1e-12f);
     const bool negligible = !(res2 > kRcrSkip * vd2) || m <= 0;
 
-    // Only a few leading eigenpairs wanted (the method itself: k = pca_rank, no Max-P / EVR rule) from a wide enough
-    // complement: the head is handed to the leading-eigenpair kernel (tridiagonalisation + bisection + inverse iteration,
-    // with a register budget of its own) instead of diagonalising all of T here.
-    const int kq = min(rank, m);
-    const bool direct = lead != nullptr && !negligible && !(vflags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) && kq >= 1 &&
-                        kq <= TE_MAXK && m >= m_direct_min && m <= m_direct_max;
+    const bool direct = direct_ok && !negligible;
     if (direct) {
       float* Tg = Gg;                                            // G itself is no longer needed
       if (ttile) {
@@ -1073,24 +1079,24 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
       }
       return;
     }
-    U = (2 * mm * lt <= fn_small_floats(d)) ? sm + mm * lt : sm + d * ld;   // W next to T, or in the second buffer of the large launch
-    if (ttile) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int srow = sblk * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), t = tblk2 * 32 + l31;
-        if (srow < m && t < m) M[srow * lt + t] = ta[i];
-      }
-    }
-    if (mm > m) for (int e = tid; e < mm; e += FN_THREADS) { M[m * lt + e] = 0.f; M[e * lt + m] = 0.f; }
-    __syncthreads();
-    // symmetrise, W = I
-    for (int e = tid; e < mm * mm; e += FN_THREADS) {
-      const int a = e / mm, b = e - a * mm;
-      if (a < b) M[a * lt + b] = M[b * lt + a];                  // the upper triangle mirrors the computed lower one
-      U[a * lt + b] = (a == b) ? 1.f : 0.f;
-    }
-    __syncthreads();
     if (!negligible) {
+      U = (2 * mm * lt <= fn_small_floats(d)) ? sm + mm * lt : sm + d * ld;   // W next to T, or in the second buffer of the large launch
+      if (ttile) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int srow = sblk * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), t = tblk2 * 32 + l31;
+          if (srow < m && t < m) M[srow * lt + t] = ta[i];
+        }
+      }
+      if (mm > m) for (int e = tid; e < mm; e += FN_THREADS) { M[m * lt + e] = 0.f; M[e * lt + m] = 0.f; }
+      __syncthreads();
+      // symmetrise, W = I
+      for (int e = tid; e < mm * mm; e += FN_THREADS) {
+        const int a = e / mm, b = e - a * mm;
+        if (a < b) M[a * lt + b] = M[b * lt + a];                  // the upper triangle mirrors the computed lower one
+        U[a * lt + b] = (a == b) ? 1.f : 0.f;
+      }
+      __syncthreads();
       // cyclic Jacobi with a round-robin ordering: mm/2 disjoint rotations per round
       const int half = mm / 2;
       // Wide complements: only W_k W_k^T y is needed of the eigenvectors (y = Z u, W_k the k_used leading ones), and
@@ -1451,7 +1457,7 @@ __device__ __forceinline__ int lead_orth(float* __restrict__ Ya, const float* __
 // Floats of dynamic LDS of that kernel for complements up to mmax wide and kq directions; d != 0: the fast path at that head_dim
 // (start rows behind the scratch of the direct route; the rows, their images and the partial sums take 128 floats a row).
 inline size_t lead_lds_floats(int mmax, int kq, int d) {
-  const size_t mat = (size_t)mmax * (mmax | 1) + 4, direct = tri_work_floats(mmax, kq) + (size_t)kq * d;
+  const size_t mat = (size_t)tri_refl_floats(mmax) + 4, direct = tri_work_floats(mmax, kq) + (size_t)kq * d;
   const size_t fast = d ? (size_t)128 * (2 * kq + 4 * (kq < 4 ? kq : 4)) : 0;
   return mat + (direct > fast ? direct : fast);
 }
@@ -1473,11 +1479,10 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const HeadState st = state[head];
   const int m = jb.m, r = st.r_keep;
-  const int lt = m | 1;                                        // odd row stride: column accesses without bank conflicts
   const float* Zg = mats + (size_t)head * 3 * d * d;           // [m][d] basis of the complement
   const float* Tg = Zg + 2 * (size_t)d * d;                    // [m][m]
   float* Rf = sm;
-  float* work = sm + ((m * lt + 3) & ~3);                      // 16-byte aligned
+  float* work = sm + ((tri_refl_floats(m) + 3) & ~3);          // 16-byte aligned
   const int kq = min(rank, m);
   // y = Z u (Eq. 4 in complement coordinates), a wave per row, four rows' loads in flight (the first four beside u's)
   float z0[4], z1[4];
@@ -1539,8 +1544,8 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
   if (iters <= 0 || diag != nullptr) {
     const float* th;
     const float* Wk;
-    if (kq <= 4) tri_top_eigs<4>(Tg, m, Rf, lt, m, kq, work, &th, &Wk);
-    else tri_top_eigs<8>(Tg, m, Rf, lt, m, kq, work, &th, &Wk);
+    if (kq <= 4) tri_top_eigs<4>(Tg, m, Rf, m, kq, work, &th, &Wk);
+    else tri_top_eigs<8>(Tg, m, Rf, m, kq, work, &th, &Wk);
     if (tid == 0) {
       const float lmax = th[0];
       const float srel = (float)max(st.n_del, d) * (float)kRankEps;
@@ -1821,8 +1826,8 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     ProfScope prof_(ST_FINALIZE, st);
     const size_t one = sizeof(float) * m.d * (m.d + 1);
     // Heads that only need a few leading eigenpairs of a wide enough complement go to k_bf_lead after the finalisation
-    // (not under the Max-P / EVR rules, which need the whole spectrum).  Its LDS is sized for complements up to 3d/4 wide
-    // (two workgroups per CU); without the projection every complement is all of R^d, and it is sized for that.
+    // (not under the Max-P / EVR rules, which need the whole spectrum).  Its LDS holds the reflectors packed, 52 KB for up to four
+    // directions at head_dim 128, so that complements of every width take that route with two workgroups per CU.
     // The fast path of App. H lives in that kernel too and then takes every head that reaches Eq. 4.
     // So does the Per-token alternative (it needs the subspace itself, which only that kernel exports).
     const int iters = (var.flags & VF_NAIVE) ? 0 : var.subspace_iters;
@@ -1830,7 +1835,6 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     const bool lead_ok = rank > 0 && rank <= TE_MAXK && !(var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE)) &&
                          (all_lead || !(min_budget > m.d && m.N > m.d && !var.skips_basis()));
     LeadJob* lead = lead_ok ? (LeadJob*)(ws + w.lead_job) : (LeadJob*)nullptr;
-    const int m_direct_max = ((var.flags & VF_NO_PROJECTION) || all_lead) ? m.d : 3 * m.d / 4;
     const int m_direct_min = all_lead ? 1 : FN_DIRECT_MIN;
     // every budget above head_dim: heads that need the finalisation are rare (the certificate settles the others), so one
     // launch with the large LDS size serves both classes instead of two launches that mostly exit at once
@@ -1841,12 +1845,12 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
                          w.nstat, rank, state, basis, gram_part, mats, delta, delta_out, diag,
                          (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, cls, scores, idx,
                          var.flags, var.evr_tau, m.scs, (max_budget < m.d && rank > 0) ? (float*)(ws + w.rot) : (float*)nullptr,
-                         lead, m_direct_min, m_direct_max);
+                         lead, m_direct_min);
     }
     if (check_launch("backfill finalize") != OBF_OK) return OBF_ERR_HIP;
     if (lead) {
       const int kq = rank < TE_MAXK ? rank : TE_MAXK;
-      const size_t lds = sizeof(float) * lead_lds_floats(m_direct_max, kq, iters > 0 ? m.d : 0);
+      const size_t lds = sizeof(float) * lead_lds_floats(m.d, kq, iters > 0 ? m.d : 0);
       hipLaunchKernelGGL(k_bf_lead<T>, dim3(m.heads), dim3(TE_THREADS), lds, st, m.d, rank, state, mats, delta, delta_out, diag,
                          (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, scores, idx, var.flags, m.scs,
                          (const LeadJob*)lead, iters);

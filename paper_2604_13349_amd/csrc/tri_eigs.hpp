@@ -28,6 +28,10 @@ __host__ __device__ inline int tri_work_floats(int m, int k) {
   return 4 * m + 256 + TE_THREADS + 96 + 7 * tri_lane_stride(k) * m + (k > TE_BATCH ? k * m : 0);
 }
 
+// floats of LDS of the packed reflectors, and where entry i of reflector j lies: tri_refl_off(m, j) + i
+__host__ __device__ inline int tri_refl_floats(int m) { return m * (m - 1) / 2; }
+__device__ __forceinline__ int tri_refl_off(const int m, const int j) { return __mul24(j, m - 2) - (__mul24(j, j - 1) >> 1) - 1; }
+
 // sum over the 64 lanes, the result in every lane: four in-row DPP steps, then the rows and the halves meet through
 // lane swaps (no LDS traffic, a fixed order of additions)
 __device__ __forceinline__ float te_wave_sum(float v) {
@@ -145,7 +149,7 @@ __device__ __forceinline__ float te_backward(const float* __restrict__ f, const 
 }
 
 // Tridiagonalisation of the m x m symmetric matrix Tsrc (row stride ls), 32 (MB - 1) < m <= 32 MB: the diagonal to dv, the
-// sub-diagonal to ev, reflector j (I - bet[j] v v^T) to column j of Rf below the diagonal.  cbuf and ybuf [2][128] are LDS, 16-byte
+// sub-diagonal to ev, reflector j (I - bet[j] v v^T), entries j + 1 .. m - 1, to Rf packed column behind column.  cbuf and ybuf [2][128] are LDS, 16-byte
 // aligned.  All threads call; ends with a barrier.
 //
 // The matrix lives in registers as 32 x 32 tiles in the result layout of the matrix instructions (entry i of lane l: row
@@ -162,8 +166,8 @@ __device__ __forceinline__ float te_backward(const float* __restrict__ f, const 
 // Bound by the dependent chain of a step: 0.85 us at m = 96 and 0.55 at m = 32 (1.3 us before); 2 directions of 288 complements 96
 // wide in a 256-token call: 514 -> 445 us for the whole call.
 template <int MB>
-__device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const int ls, float* Rf, const int lt, const int m,
-                                           float* dv, float* ev, float* bet, float* cbuf, float* ybuf) {
+__device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const int ls, float* Rf, const int m, float* dv, float* ev,
+                                           float* bet, float* cbuf, float* ybuf) {
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr bool TWO = MB > 2;                                 // a lane holds two entries of a vector
@@ -264,8 +268,9 @@ __device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const
       const float w1 = lane_val((TWO && j + 1 >= 64) ? wb : wa, (j + 1) & 63);
       const float na = fmaf(-va, w1, fmaf(-wa, v1, ca)), nb = fmaf(-vb, w1, fmaf(-wb, v1, cb_));
       if (wave == MB - 1) {                                    // the wave that stays to the end keeps the books
-        if (ina) Rf[lane * lt + j] = va;
-        if (inb) Rf[(lane + 64) * lt + j] = vb;
+        const int off = tri_refl_off(m, j);
+        if (ina) Rf[off + lane] = va;
+        if (inb) Rf[off + lane + 64] = vb;
         if (lane == 0) { bet[j] = beta; ev[j] = alpha; }
         if (lane == ((j + 1) & 63)) dv[j + 1] = (TWO && j + 1 >= 64) ? nb : na;
       }
@@ -297,15 +302,15 @@ __device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const
   __syncthreads();
 }
 
-// Tsrc: the m x m symmetric matrix (row stride ls; global or LDS, read once).  Rf: LDS, m rows of stride lt (odd), receives
-// the reflectors (column j below the sub-diagonal).  m <= 128.
+// Tsrc: the m x m symmetric matrix (row stride ls; global or LDS, read once).  Rf: LDS, tri_refl_floats(m) floats, with `work` behind
+// it (masked lanes read past it).  m <= 128.
 // work: LDS scratch of tri_work_floats(m, k) floats, 16-byte aligned.  1 <= k <= min(m, TE_MAXK); KS = tri_lane_stride(k).
 // More than TE_BATCH eigenpairs are found in passes of TE_BATCH (the eigenvalues' multisection, the inverse iteration and
 // the back-transformation each run once per pass on the same scratch).
 // On return (after its own final barrier) *theta points at the k eigenvalues, largest first, and *W at the k unit
 // eigenvectors, W[i * m + t].  Every thread of the workgroup must call.
 template <int KS>
-__device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, const int ls, float* Rf, const int lt, const int m,
+__device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, const int ls, float* Rf, const int m,
                                              const int k, float* work, const float** theta, const float** W) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -324,11 +329,10 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
   float* zz = lu + 6 * m * KS;        // [m][KS] iteration vectors
 
   // ---- 1. tridiagonalisation (the counts come later)
-  for (int e = tid; e < m * lt; e += TE_THREADS) Rf[e] = 0.f;  // (the reduction starts with a barrier before it writes there)
-  if (m <= 32) tri_reduce<1>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
-  else if (m <= 64) tri_reduce<2>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
-  else if (m <= 96) tri_reduce<3>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
-  else tri_reduce<4>(Tsrc, ls, Rf, lt, m, dv, ev, bet, cbuf, (float*)cnt);
+  if (m <= 32) tri_reduce<1>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
+  else if (m <= 64) tri_reduce<2>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
+  else if (m <= 96) tri_reduce<3>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
+  else tri_reduce<4>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
   if (wave == 0) {
     // Gershgorin interval of S and its squared sub-diagonal entries: lane l looks at rows l and l + 64
     float lo = INFINITY, hi = -INFINITY;
@@ -461,15 +465,15 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
         if (fabsf(w1) < 1e-12f) w1 = 0.f;
       }
       // Two reflectors at a time: (I - b2 v2 v2^T)(I - b1 v1 v1^T) w needs v1.w, v2.w and v1.v2, three sums that go through the wave
-      // together; the next pair is fetched meanwhile.  Entries on and above the diagonal of Rf are zero (so is its row 0, which
-      // stands in for rows past the matrix).
-      const float* r0p = Rf + (lane < m ? lane : 0) * lt;
-      const float* r1p = Rf + (lane + 64 < m ? lane + 64 : 0) * lt;
+      // together; the next pair is fetched meanwhile.
+      const int ia = lane < m ? lane : -1, ib = lane + 64 < m ? lane + 64 : -1;      // entries of this lane; -1: none
       int j = m - 3;
       float p0 = 0.f, p1 = 0.f, q0 = 0.f, q1 = 0.f, bp = 0.f, bq = 0.f;
       auto fetch = [&](const int jj) {                         // reflectors jj and jj - 1
-        const int a = max(jj, 0), b = max(jj - 1, 0);
-        p0 = r0p[a]; p1 = r1p[a]; q0 = r0p[b]; q1 = r1p[b]; bp = bet[a]; bq = bet[b];
+        const int a = max(jj, 0), b = max(jj - 1, 0), oa = tri_refl_off(m, a) + lane, ob = tri_refl_off(m, b) + lane;
+        const float a0 = Rf[max(oa, 0)], a1 = Rf[oa + 64], b0 = Rf[max(ob, 0)], b1 = Rf[ob + 64];
+        p0 = (ia > a) ? a0 : 0.f; p1 = (ib > a) ? a1 : 0.f; q0 = (ia > b) ? b0 : 0.f; q1 = (ib > b) ? b1 : 0.f;
+        bp = bet[a]; bq = bet[b];
       };
       fetch(j);
       for (; j >= 1; j -= 2) {

@@ -148,6 +148,8 @@ def test_small_budget_basis_variants(gpu, d, dtype, budgets):
     ("bf16", 128, 3, 0, [108, 97, 96, 95, 65, 64, 63, 33, 32, 31]),     # complements 20 to 97 wide: edges of the 32-wide tiles
     ("bf16", 128, 12, 0, [100, 96, 64, 40]),                            # more than eight eigenpairs
     ("f32", 64, 2, 0, [44, 33, 32, 31, 17, 16]),
+    ("bf16", 128, 4, 0, [30, 17, 16, 15, 14, 13, 5, 2]),                # complements above 96, both sizes of the finalisation's LDS
+    ("f32", 64, 10, 0, [15, 8, 3]),
     ("bf16", 128, 2, 3, [127, 126, 125, 96, 95, 64, 1]),                # the fast path reports its distance from the direct route: any width
 ])
 def test_leading_eigenpairs_at_tile_edges(gpu, dtype, d, rank, iters, budgets):

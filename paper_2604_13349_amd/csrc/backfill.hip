@@ -496,7 +496,6 @@ __global__ __launch_bounds__(KB_THREADS) void k_bf_plain_state(const float* __re
 constexpr int FN_THREADS = 1024;
 constexpr int FN_WAVES = FN_THREADS / 64;
 constexpr int FN_SWEEPS = kJacobiSweeps;
-constexpr int FN_DIRECT_MIN = 20;         // complements at least this wide take the direct leading-eigenpair route when it applies
 constexpr int FN_REPLAY_MIN = 64;        // complements at least this wide do not accumulate eigenvectors (see the Jacobi phase)
 // Floats of dynamic LDS of the first finalisation launch: room for the d x (d+1) projector and for T and W of every
 // complement up to three quarters of d wide (74.5 KB at d = 128, so that two workgroups still share a CU).
@@ -711,8 +710,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
                                                             const float* __restrict__ scores,
                                                             const int32_t* __restrict__ idx, int vflags, float evr_tau,
                                                             int scs, float* __restrict__ rot /*nullable*/,
-                                                            LeadJob* __restrict__ lead /*nullable: no leading-eigenpair kernel follows*/,
-                                                            int m_direct_min) {
+                                                            LeadJob* __restrict__ lead /*nullable: no leading-eigenpair kernel follows*/) {
   extern __shared__ float sm[];
   const int head = blockIdx.x;
   const int ld = d + 1;
@@ -733,12 +731,12 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
   int k_used = 0;
   const int tid = threadIdx.x;
   const bool naive = (vflags & VF_NAIVE) != 0;
-  // Only a few leading eigenpairs wanted (the method itself: k = pca_rank, no Max-P / EVR rule) from a wide enough complement: the head
-  // goes to the leading-eigenpair kernel (tridiagonalisation + bisection + inverse iteration, with a register budget of its own)
-  // instead of having all of T diagonalised here.
+  // Only a few leading eigenpairs wanted (the method itself: k = pca_rank, no Max-P / EVR rule): the head goes to the leading-eigenpair
+  // kernel (tridiagonalisation + bisection + inverse iteration, with a register budget of its own) instead of having all of T
+  // diagonalised here.  At every width: 288 heads of 256 tokens take 501 against 558 us at 18, 514 against 519 at 4.
   const int m_span = d - st.r_keep;
   const bool direct_ok = lead != nullptr && !(vflags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) && min(rank, m_span) >= 1 &&
-                         min(rank, m_span) <= TE_MAXK && m_span >= m_direct_min;
+                         min(rank, m_span) <= TE_MAXK;
   {
     // Two launches share the heads: the first has fn_small_floats(d) floats of LDS (two workgroups per CU) and takes every head that
     // fits there, the second takes the rest.  A head needs room for Z and, by its route, the small matrices of fn_complement or the
@@ -1835,7 +1833,6 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     const bool lead_ok = rank > 0 && rank <= TE_MAXK && !(var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE)) &&
                          (all_lead || !(min_budget > m.d && m.N > m.d && !var.skips_basis()));
     LeadJob* lead = lead_ok ? (LeadJob*)(ws + w.lead_job) : (LeadJob*)nullptr;
-    const int m_direct_min = all_lead ? 1 : FN_DIRECT_MIN;
     // every budget above head_dim: heads that need the finalisation are rare (the certificate settles the others), so one
     // launch with the large LDS size serves both classes instead of two launches that mostly exit at once
     const bool single = min_budget > m.d && m.N > m.d && !var.skips_basis();
@@ -1845,7 +1842,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
                          w.nstat, rank, state, basis, gram_part, mats, delta, delta_out, diag,
                          (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, cls, scores, idx,
                          var.flags, var.evr_tau, m.scs, (max_budget < m.d && rank > 0) ? (float*)(ws + w.rot) : (float*)nullptr,
-                         lead, m_direct_min);
+                         lead);
     }
     if (check_launch("backfill finalize") != OBF_OK) return OBF_ERR_HIP;
     if (lead) {

@@ -1161,3 +1161,28 @@ def test_relay_row_codes_are_bit_exact(gpu, dtype, d, bits):
     assert np.array_equal(got, want), f"{int((got != want).sum())} codes differ"
     ref_back = O.round_to_io(O.dequantize_rows(q_ref, s_ref, z_ref), dtype)
     assert np.array_equal(gpu.to_host(back, dtype), ref_back)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 128), ("bf16", 64), ("f32", 64)])
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("rows,offset", [(1, 0), (31, 0), (33, 1), (64, 3), (65, 0)])      # ends of a workgroup's rows; arrays off their alignment
+def test_relay_row_codes_at_workgroup_edges(gpu, dtype, d, bits, rows, offset):
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    r = np.random.default_rng(7 * rows + bits + d)
+    X_io = O.round_to_io((r.standard_normal((rows, d)) * np.exp(r.standard_normal((rows, 1)))).astype(np.float32), dtype)
+    q_ref, s_ref, z_ref = O.quantize_rows(X_io, dtype, bits)
+    flat = gpu.to_dev(X_io, dtype).reshape(-1)
+    held = torch.zeros(flat.numel() + offset, dtype=flat.dtype, device="cuda")
+    held[offset:] = flat
+    codes, scale, zero = Bd.quantize_rows(held[offset:].view(rows, d), bits)
+    want = q_ref if bits == 8 else (q_ref[:, 0::2] | (q_ref[:, 1::2] << 4)).astype(np.uint8)
+    torch.cuda.synchronize()
+    assert np.array_equal(codes.cpu().numpy(), want)
+    assert np.array_equal(scale.cpu().numpy().view(np.uint16), s_ref.view(np.uint16))
+    assert np.array_equal(zero.cpu().numpy().view(np.uint16), z_ref.view(np.uint16))
+    chold = torch.zeros(codes.numel() + offset, dtype=torch.uint8, device="cuda")
+    chold[offset:] = codes.reshape(-1)
+    back = Bd.dequantize_rows(chold[offset:].view(codes.shape), scale, zero, d, flat.dtype, bits)
+    torch.cuda.synchronize()
+    assert np.array_equal(gpu.to_host(back, dtype), O.round_to_io(O.dequantize_rows(q_ref, s_ref, z_ref), dtype))

@@ -16,12 +16,10 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 constexpr int MG_THREADS = 256;
 constexpr int MG_D = 128;
 constexpr int MG_KK = MG_D / 16;
-constexpr int MG_SLOTS_PER_WAVE = 8;     // merge: retained slots whose sums one wave carries
-constexpr int MG_SLOTS_PER_WG = 4 * MG_SLOTS_PER_WAVE;
 
 union MgFrag { uint4 u; bf16x8 v; };
 
-// 1 / |K_t| of every retained key (0 for a zero key), from the gathered keys: one wave per slot.
+// 1 / |K_t| of every retained key (0 for a zero key), from the gathered keys, for the routing on the vector ALU: one wave per slot.
 template <typename T>
 __global__ __launch_bounds__(MG_THREADS) void k_mg_inv_norm(const T* __restrict__ K_out, const int32_t* __restrict__ n_keep,
                                                             int d, int max_budget, float* __restrict__ inv_norm) {
@@ -37,64 +35,117 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_inv_norm(const T* __restrict_
   if (lane == 0) inv_norm[(size_t)head * max_budget + slot] = s > 0.f ? 1.0f / sqrtf(s) : 0.f;
 }
 
-// Routing on the matrix cores.  One wave owns 32 tokens (lane l and lane l + 32 both hold token l % 32, the two halves
-// of head_dim's 16-element MFMA steps); it walks the retained slots 32 at a time: the 32 x 32 tile of dot products has,
-// in entry i of lane l, slot s0 + (i/4)*8 + (l/32)*4 + i%4 against token l%32, so the running maximum is kept per lane
-// over slots in ascending order and the two lanes of a token are combined at the end.
-__global__ __launch_bounds__(MG_THREADS) void k_mg_route_mfma(const uint16_t* __restrict__ K, const uint16_t* __restrict__ K_out,
-                                                              const float* __restrict__ inv_norm,
-                                                              const int32_t* __restrict__ n_keep, int N, int kvs,
-                                                              int max_budget, int32_t* __restrict__ route) {
-  const int head = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Routing on the matrix cores.  A workgroup owns 256 tokens, a wave two blocks of 32 whose keys stay in registers (lane l and lane
+// l + 32 both hold token l % 32, the two halves of head_dim's 16-element MFMA steps); it walks the retained slots 32 at a time, staged
+// in LDS once for the four waves (the next tile's rows travel meanwhile) together with their reciprocal norms: the 32 x 32 tile of dot
+// products has, in entry i of lane l, slot s0 + (i/4)*8 + (l/32)*4 + i%4 against token l%32, so the running maximum is kept per lane
+// over slots in ascending order and the two lanes of a token are combined at the end.  Retained tokens are written as -1 here.
+// Bound by the vector work on the tiles (multiply, compare, two selects per entry) beside one pass over K.
+// 58 us on 288 heads x 2048 tokens x 205 slots; 423 us with the slots' rows and norms read from memory by every wave, and two more
+// launches (19 us) for the norms and the retained tokens.
+constexpr int MG_TOK = 256;              // tokens per workgroup
+constexpr int MG_LDB = MG_D * 2 + 16;    // LDS bytes per staged slot row: 16-byte reads of eight consecutive rows use different banks
+
+__global__ __launch_bounds__(MG_THREADS, 3) void k_mg_route_mfma(const uint16_t* __restrict__ K, const uint16_t* __restrict__ K_out,
+                                                                 const int32_t* __restrict__ idx, const int32_t* __restrict__ n_keep,
+                                                                 int N, int kvs, int max_budget, int32_t* __restrict__ route) {
+  __shared__ __attribute__((aligned(16))) uint8_t stage[2][32 * MG_LDB];
+  __shared__ __attribute__((aligned(16))) float inv[2][32];
+  __shared__ uint32_t kept[MG_TOK / 32];
+  const int head = blockIdx.y, tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 31, lh = lane >> 5;
-  const int tok = blockIdx.x * 128 + wave * 32 + lr;
-  const int nk = n_keep[head];
+  const int base = blockIdx.x * MG_TOK, tok = base + wave * 64 + lr;       // and tok + 32
+  const int nk = min(n_keep[head], max_budget);
   int32_t* rt = route + (size_t)head * N;
-  if (nk <= 0) { if (lh == 0 && tok < N) rt[tok] = -1; return; }
+  if (nk <= 0) { if (base + tid < N) rt[base + tid] = -1; return; }
   const uint16_t* Kh = K + (size_t)head * kvs * MG_D;
   const uint16_t* Ko = K_out + (size_t)head * max_budget * MG_D;
-  const float* inv = inv_norm + (size_t)head * max_budget;
-  MgFrag tf[MG_KK];
-  {
-    const uint4* p = (const uint4*)(Kh + (size_t)min(tok, N - 1) * MG_D + lh * 8);
+  const int32_t* id = idx + (size_t)head * max_budget;
+  MgFrag tf[2][MG_KK];
 #pragma unroll
-    for (int kk = 0; kk < MG_KK; ++kk) tf[kk].u = p[kk * 2];
+  for (int b = 0; b < 2; ++b) {
+    const uint4* p = (const uint4*)(Kh + (size_t)min(tok + 32 * b, N - 1) * MG_D + lh * 8);
+#pragma unroll
+    for (int kk = 0; kk < MG_KK; ++kk) tf[b][kk].u = p[kk * 2];
   }
-  float best = -INFINITY;
-  int bslot = 0;
-  MgFrag sf[2][MG_KK];
-  auto load_slots = [&](MgFrag (&dst)[MG_KK], int s0) {
-    const uint4* p = (const uint4*)(Ko + (size_t)min(s0 + lr, nk - 1) * MG_D + lh * 8);      // rows past the list: clamped, masked below
-#pragma unroll
-    for (int kk = 0; kk < MG_KK; ++kk) dst[kk].u = p[kk * 2];
+  // thread t moves 32 bytes of slot row t / 8
+  const int srow = tid >> 3, spart = tid & 7;
+  uint4 pre[2];
+  auto fetch = [&](const int s0) {
+    const uint4* p = (const uint4*)(Ko + (size_t)min(s0 + srow, nk - 1) * MG_D + spart * 16);    // rows past the list: the last one again
+    pre[0] = p[0]; pre[1] = p[1];
   };
-  load_slots(sf[0], 0);
+  auto put = [&](const int s0, const int buf) {
+    uint4* o = (uint4*)(stage[buf] + srow * MG_LDB + spart * 32);
+    o[0] = pre[0]; o[1] = pre[1];
+    float s = 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t w[4] = {pre[h].x, pre[h].y, pre[h].z, pre[h].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float a = __uint_as_float(w[i] << 16), b = __uint_as_float(w[i] & 0xffff0000u);
+        s = fmaf(a, a, s); s = fmaf(b, b, s);
+      }
+    }
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) s += __shfl_xor(s, off);
+    // 0 for a zero key; a slot past the list compares as not a number: never the maximum
+    if (spart == 0) inv[buf][srow] = (s0 + srow >= nk) ? __uint_as_float(0x7fc00000u) : s > 0.f ? 1.0f / sqrtf(s) : 0.f;
+  };
+  fetch(0);
+  if (tid < MG_TOK / 32) kept[tid] = 0u;
+  put(0, 0);
+  if (nk > 32) fetch(32);
+  __syncthreads();
+  for (int i = tid; i < nk; i += MG_THREADS) {                 // the retained tokens of the workgroup's range
+    const unsigned j = (unsigned)(id[i] - base);
+    if (j < (unsigned)MG_TOK) atomicOr(&kept[j >> 5], 1u << (j & 31));
+  }
+  float best[2] = {-INFINITY, -INFINITY};
+  int bslot[2] = {0, 0};
   int buf = 0;
   for (int s0 = 0; s0 < nk; s0 += 32, buf ^= 1) {
-    if (s0 + 32 < nk) load_slots(sf[buf ^ 1], s0 + 32);
-    f32x16 acc;
+    f32x16 acc[2];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int kk = 0; kk < MG_KK; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sf[buf][kk].v, tf[kk].v, acc, 0, 0, 0);
+      for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < MG_KK; ++kk) {
+      MgFrag sf;
+      sf.u = *(const uint4*)(stage[buf] + lr * MG_LDB + kk * 32 + lh * 16);
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sf.v, tf[0][kk].v, acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sf.v, tf[1][kk].v, acc[1], 0, 0, 0);
+    }
+    if (s0 + 32 < nk) {                                        // uniform
+      put(s0 + 32, buf ^ 1);
+      if (s0 + 64 < nk) fetch(s0 + 64);
+    }
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
-      const int sb = s0 + i4 * 8 + lh * 4;                      // this lane's four consecutive slots of the group
+      const float4 iv = *(const float4*)&inv[buf][i4 * 8 + lh * 4];           // this lane's four consecutive slots of the group
+      const float iw[4] = {iv.x, iv.y, iv.z, iv.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int s = sb + e;
-        if (s < nk) {
-          const float c = acc[i4 * 4 + e] * inv[s];
-          if (c > best) { best = c; bslot = s; }               // strict: the first maximum wins
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const float c = acc[b][i4 * 4 + e] * iw[e];
+          if (c > best[b]) { best[b] = c; bslot[b] = s0 + i4 * 8 + lh * 4 + e; }    // strict: the first maximum wins
         }
       }
     }
+    __syncthreads();
   }
-  const float ob = __shfl_xor(best, 32);
-  const int os = __shfl_xor(bslot, 32);
-  if (ob > best || (ob == best && os < bslot)) { best = ob; bslot = os; }
-  if (lh == 0 && tok < N) rt[tok] = bslot;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const float ob = __shfl_xor(best[b], 32);
+    const int os = __shfl_xor(bslot[b], 32);
+    if (ob > best[b] || (ob == best[b] && os < bslot[b])) bslot[b] = os;
+    const int t = tok + 32 * b;
+    if (lh == 0 && t < N) rt[t] = ((kept[(t - base) >> 5] >> ((t - base) & 31)) & 1u) ? -1 : bslot[b];
+  }
 }
 
 // Routing on the vector ALU (fp32 caches, head_dim 64): one thread per token, the retained keys staged through LDS
@@ -146,6 +197,41 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_unroute_kept(const int32_t* _
   if (t < n_keep[head] && t < max_budget) route[(size_t)head * N + idx[(size_t)head * max_budget + t]] = -1;
 }
 
+// Deleted tokens sorted by slot, one workgroup per head: offs[slot] .. offs[slot + 1] of `order` lists the tokens of a slot, in no
+// particular order within it (the merge sorts its own, short, list).
+constexpr int MB_THREADS = 1024;
+__global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restrict__ route, const int32_t* __restrict__ n_keep, int N,
+                                                          int max_budget, int32_t* __restrict__ order /*[heads][hstride]*/,
+                                                          size_t hstride) {
+  extern __shared__ int cnt[];                                 // [n_keep] counts, then running positions
+  __shared__ int wsum[MB_THREADS / 64];
+  const int head = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nk = min(n_keep[head], max_budget);
+  if (nk <= 0) return;
+  const int32_t* rt = route + (size_t)head * N;
+  int32_t* ord = order + (size_t)head * hstride;
+  int32_t* offs = ord + N;                                     // [n_keep + 1]
+  for (int i = tid; i < nk; i += MB_THREADS) cnt[i] = 0;
+  __syncthreads();
+  for (int j = tid; j < N; j += MB_THREADS) { const int r = rt[j]; if (r >= 0) atomicAdd(&cnt[r], 1); }
+  __syncthreads();
+  int carry = 0;
+  for (int i0 = 0; i0 < nk; i0 += MB_THREADS) {                // exclusive prefix sums, a stretch of MB_THREADS slots at a time
+    const int i = i0 + tid, c = (i < nk) ? cnt[i] : 0;
+    int inc = c;
+    for (int off = 1; off < 64; off <<= 1) { const int x = __shfl_up(inc, off); if (lane >= off) inc += x; }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    int before = carry, tot = 0;
+    for (int w = 0; w < MB_THREADS / 64; ++w) { const int x = wsum[w]; if (w < wave) before += x; tot += x; }
+    if (i < nk) { cnt[i] = before + inc - c; offs[i] = before + inc - c; }
+    carry += tot;
+    __syncthreads();
+  }
+  if (tid == 0) offs[nk] = carry;
+  for (int j = tid; j < N; j += MB_THREADS) { const int r = rt[j]; if (r >= 0) ord[atomicAdd(&cnt[r], 1)] = j; }
+}
+
 // The same per-slot sums serve the Per-token alternative of App. D (PER_TOKEN; the reading: the deleted tokens are shared
 // out among the slots by the routing above, slot t's direction is B a_del / (a_keep + eps) times the projection of
 // sum_{pi(j) = t} A_j v_j / (a_del + eps) onto the residual subspace C of Eq. 5 - C's rows lie in the complement of
@@ -153,21 +239,34 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_unroute_kept(const int32_t* _
 // There the weights are the attention masses themselves, the sums are projected with the k_used rows of C that the
 // back-fill kernel left in the head's scratch, and the result is added to the slot's value.
 //
-// Merge.  A workgroup owns 32 consecutive retained slots, a wave eight of them.  Every wave scans the head's route list
-// 64 tokens at a time and, for each token routed to one of its slots, in ascending token order, adds the weighted value
-// row into that slot's running sum (LDS, one lane per pair of columns): the order of the additions is fixed, so the
-// result is the same on every run.  Slots that received nothing are left as the bit copies the gather wrote.
-template <typename T, bool PER_TOKEN>
+// Merge.  A wave per retained slot takes the slot's tokens in ascending order and adds their weighted value rows into a running
+// sum in registers (a lane owns D / 64 columns): the order of the additions is fixed, so the result is the same on every run.  A list of
+// up to MG_LIST tokens is put in order first (every entry counts the smaller ones); a longer one is not: the head's routes are scanned
+// instead, which finds the slot's tokens in order.  Eight rows are in flight at a time.  Slots that received nothing are left as the
+// bit copies the gather wrote.  Bound by the chain offsets - list - masses - rows of a wave (nine tokens a slot here), then by the
+// pass over V: 99 us on 288 heads x 2048 tokens x 205 slots, and 7 for the lists; 247 with eight slots per wave, each wave scanning
+// all routes and waiting for every row by itself.
+constexpr int MG_LIST = 256;
+constexpr int MG_AHEAD = 8;
+
+template <typename T, int CPL> struct LaneCols;                // CPL consecutive elements of a row
+template <> struct LaneCols<uint16_t, 2> { typedef uint32_t type; static __device__ __forceinline__ void get(uint32_t v, float (&o)[2]) { o[0] = __uint_as_float(v << 16); o[1] = __uint_as_float(v & 0xffff0000u); } };
+template <> struct LaneCols<uint16_t, 1> { typedef uint16_t type; static __device__ __forceinline__ void get(uint16_t v, float (&o)[1]) { o[0] = bf16_bits_to_float(v); } };
+template <> struct LaneCols<float, 2> { typedef float2 type; static __device__ __forceinline__ void get(float2 v, float (&o)[2]) { o[0] = v.x; o[1] = v.y; } };
+template <> struct LaneCols<float, 1> { typedef float type; static __device__ __forceinline__ void get(float v, float (&o)[1]) { o[0] = v; } };
+
+template <typename T, int D, bool PER_TOKEN>
 __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V, const float* __restrict__ scores,
                                                          const int32_t* __restrict__ idx, const int32_t* __restrict__ n_keep,
-                                                         const int32_t* __restrict__ route, int N, int d, int kvs, int scs,
-                                                         int max_budget, T* __restrict__ V_out,
+                                                         const int32_t* __restrict__ route, const int32_t* __restrict__ order,
+                                                         size_t hstride, int N, int kvs, int scs, int max_budget,
+                                                         T* __restrict__ V_out,
                                                          const HeadState* __restrict__ state /*PER_TOKEN*/,
                                                          const float* __restrict__ mats /*PER_TOKEN: [heads][3][d*d], C in the second matrix*/,
                                                          int no_scaling) {
-  __shared__ float acc[4][MG_SLOTS_PER_WAVE][MG_D];
-  __shared__ float a_slot[4][MG_SLOTS_PER_WAVE];
-  __shared__ int cnt[4][MG_SLOTS_PER_WAVE];
+  constexpr int CPL = D / 64;
+  typedef LaneCols<T, CPL> LC;
+  __shared__ int list[MG_THREADS / 64][MG_LIST];
   __shared__ float cb[PER_TOKEN ? 16 : 1][MG_D];               // the rows of C
   const int head = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -178,57 +277,89 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V
     const HeadState hs = state[head];
     if (!hs.active || hs.k_used <= 0) return;                  // no injection for this head (uniform over the workgroup)
     kc = min(hs.k_used, 16);
-    const float* Cg = mats + ((size_t)head * 3 + 1) * d * d;
-    for (int e = threadIdx.x; e < kc * d; e += MG_THREADS) cb[e / d][e % d] = Cg[e];
+    const float* Cg = mats + ((size_t)head * 3 + 1) * D * D;
+    for (int e = threadIdx.x; e < kc * D; e += MG_THREADS) cb[e / D][e % D] = Cg[e];
     pt_scale = (float)((double)hs.n_keep * (no_scaling ? 1.0 : hs.a_del / (hs.a_keep + kEps)) / (hs.a_del + kEps));
     __syncthreads();
   }
-  const int slot0 = blockIdx.x * MG_SLOTS_PER_WG + wave * MG_SLOTS_PER_WAVE;
-  if (slot0 >= nk) return;                                     // whole wave: nothing to own (no barrier below)
+  const int slot = blockIdx.x * (MG_THREADS / 64) + wave;
+  if (slot >= nk) return;                                      // whole wave (no barrier below)
+  const int32_t* ord = order + (size_t)head * hstride;
+  const int off = ord[N + slot], len = ord[N + slot + 1] - off;
+  if (len <= 0) return;
   const float* sc = scores + (size_t)head * scs;
-  const int32_t* rt = route + (size_t)head * N;
-  const T* Vh = V + (size_t)head * kvs * d;
-  for (int e = lane; e < MG_SLOTS_PER_WAVE * MG_D; e += 64) acc[wave][e / MG_D][e % MG_D] = 0.f;
-  if (lane < MG_SLOTS_PER_WAVE) {
-    cnt[wave][lane] = 0;
-    a_slot[wave][lane] = (slot0 + lane < nk) ? sc[idx[(size_t)head * max_budget + slot0 + lane]] : 0.f;
-  }
-  __builtin_amdgcn_wave_barrier();
-  for (int base = 0; base < N; base += 64) {
-    const int j = base + lane;
-    const int r = (j < N) ? rt[j] : -1;
-    const unsigned local = (unsigned)(r - slot0);
-    uint64_t mask = __ballot(r >= 0 && local < (unsigned)MG_SLOTS_PER_WAVE);
-    while (mask) {
-      const int l = __builtin_ctzll(mask);
-      mask &= mask - 1;
-      const int sl = __shfl((int)local, l);
-      const int jj = base + l;
-      const float w = PER_TOKEN ? sc[jj] : (float)((double)sc[jj] / ((double)a_slot[wave][sl] + kEps));
-      const T* vr = Vh + (size_t)jj * d;
-      for (int c = lane; c < d; c += 64) acc[wave][sl][c] = fmaf(w, Elem<T>::load(vr + c), acc[wave][sl][c]);
-      if (lane == 0) cnt[wave][sl] += 1;
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-  for (int sl = 0; sl < MG_SLOTS_PER_WAVE; ++sl) {
-    if (slot0 + sl >= nk || cnt[wave][sl] == 0) continue;
-    T* o = V_out + ((size_t)head * max_budget + slot0 + sl) * d;
-    if (PER_TOKEN) {
-      // lane l holds columns l and l + 64 of the slot's sum; its coefficient on every row of C, then the combination
-      const float u0 = (lane < d) ? acc[wave][sl][lane] : 0.f, u1 = (lane + 64 < d) ? acc[wave][sl][lane + 64] : 0.f;
-      float d0 = 0.f, d1 = 0.f;
-      for (int i = 0; i < kc; ++i) {
-        const float c0 = (lane < d) ? cb[i][lane] : 0.f, c1 = (lane + 64 < d) ? cb[i][lane + 64] : 0.f;
-        float g = fmaf(u0, c0, u1 * c1);
-        for (int off = 32; off > 0; off >>= 1) g += __shfl_xor(g, off);
-        d0 = fmaf(g, c0, d0); d1 = fmaf(g, c1, d1);
+  const T* Vh = V + (size_t)head * kvs * D + lane * CPL;
+  const double a_slot = PER_TOKEN ? 0.0 : (double)sc[idx[(size_t)head * max_budget + slot]] + kEps;
+  float acc[CPL];
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
+  // the rows of the tokens that the first `n` lanes hold, added in lane order
+  auto add_rows = [&](const int n, const int tok) {
+    float w = 0.f;
+    if (lane < n) w = PER_TOKEN ? sc[tok] : (float)((double)sc[tok] / a_slot);
+    for (int i0 = 0; i0 < n; i0 += MG_AHEAD) {
+      typename LC::type v[MG_AHEAD];
+#pragma unroll
+      for (int u = 0; u < MG_AHEAD; ++u) {
+        const int j = __builtin_amdgcn_readlane(tok, min(i0 + u, n - 1));
+        __builtin_memcpy(&v[u], Vh + (size_t)j * D, sizeof(v[u]));       // one load; V need only be aligned to its elements
       }
-      if (lane < d) Elem<T>::store(o + lane, fmaf(pt_scale, d0, Elem<T>::load(o + lane)));
-      if (lane + 64 < d) Elem<T>::store(o + lane + 64, fmaf(pt_scale, d1, Elem<T>::load(o + lane + 64)));
-    } else {
-      for (int c = lane; c < d; c += 64) Elem<T>::store(o + c, Elem<T>::load(o + c) + acc[wave][sl][c]);
+#pragma unroll
+      for (int u = 0; u < MG_AHEAD; ++u) {
+        if (i0 + u < n) {
+          const float wu = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(w), i0 + u));
+          float x[CPL];
+          LC::get(v[u], x);
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) acc[c] = fmaf(wu, x[c], acc[c]);
+        }
+      }
     }
+  };
+  if (len <= MG_LIST) {
+    const int32_t* src = ord + off;
+    int* dst = list[wave];
+    for (int i0 = 0; i0 < len; i0 += 64) {
+      const int mine = (i0 + lane < len) ? src[i0 + lane] : 0x7fffffff;
+      int rank = 0;
+      for (int q0 = 0; q0 < len; q0 += 64) {
+        const int other = (q0 + lane < len) ? src[q0 + lane] : 0x7fffffff;
+        const int n = min(64, len - q0);
+        for (int q = 0; q < n; ++q) rank += (__builtin_amdgcn_readlane(other, q) < mine) ? 1 : 0;
+      }
+      if (i0 + lane < len) dst[rank] = mine;
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int i0 = 0; i0 < len; i0 += 64) add_rows(min(64, len - i0), dst[min(i0 + lane, len - 1)]);
+  } else {
+    const int32_t* rt = route + (size_t)head * N;
+    for (int base = 0; base < N; base += 64) {
+      const int j = base + lane;
+      uint64_t mask = __ballot(j < N && rt[min(j, N - 1)] == slot);
+      const int n = __popcll(mask);
+      int tok = 0;
+      for (int i = 0; i < n; ++i) { const int b = __builtin_ctzll(mask); mask &= mask - 1; if (lane == i) tok = base + b; }
+      if (n) add_rows(n, tok);
+    }
+  }
+  T* o = V_out + ((size_t)head * max_budget + slot) * D + lane * CPL;
+  if (PER_TOKEN) {
+    float dsum[CPL];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) dsum[c] = 0.f;
+    for (int i = 0; i < kc; ++i) {                             // the sum's coefficient on every row of C, then the combination
+      float g = 0.f;
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) g = fmaf(acc[c], cb[i][lane * CPL + c], g);
+      for (int of = 32; of > 0; of >>= 1) g += __shfl_xor(g, of);
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) dsum[c] = fmaf(g, cb[i][lane * CPL + c], dsum[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) Elem<T>::store(o + c, fmaf(pt_scale, dsum[c], Elem<T>::load(o + c)));
+  } else {
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) Elem<T>::store(o + c, Elem<T>::load(o + c) + acc[c]);
   }
 }
 
@@ -248,32 +379,46 @@ static obf_status_t run_merge(const Dims& m, const Workspace& w, char* ws, const
   }
   float* inv_norm = (float*)(ws + w.inv_norm);
   int32_t* route = route_out ? route_out : (int32_t*)(ws + w.route);
+  // the tokens by slot and the slots' offsets, N + n_keep + 1 <= 2 N + 1 numbers a head, lie where the statistics of the deleted values
+  // are during a back-fill (over 4 N a head): done with by now
+  int32_t* order = (int32_t*)(ws + w.gram_part);
+  const size_t hstride = (size_t)w.nstat * gram_stride(m.d);
   const bool bf = m.dtype == OBF_BF16;
-  dim3 gn((max_budget + 3) / 4, m.heads);
-  if (bf) hipLaunchKernelGGL(k_mg_inv_norm<uint16_t>, gn, dim3(MG_THREADS), 0, st, (const uint16_t*)K_out, n_keep, m.d, max_budget, inv_norm);
-  else hipLaunchKernelGGL(k_mg_inv_norm<float>, gn, dim3(MG_THREADS), 0, st, (const float*)K_out, n_keep, m.d, max_budget, inv_norm);
-  if (check_launch("merge inv_norm") != OBF_OK) return OBF_ERR_HIP;
   if (bf && m.d == MG_D) {
-    hipLaunchKernelGGL(k_mg_route_mfma, dim3((m.N + 127) / 128, m.heads), dim3(MG_THREADS), 0, st, (const uint16_t*)K,
-                       (const uint16_t*)K_out, inv_norm, n_keep, m.N, m.kvs, max_budget, route);
-  } else if (bf) {
-    hipLaunchKernelGGL(k_mg_route_generic<uint16_t>, dim3((m.N + MG_THREADS - 1) / MG_THREADS, m.heads), dim3(MG_THREADS), 0, st,
-                       (const uint16_t*)K, (const uint16_t*)K_out, inv_norm, n_keep, m.N, m.d, m.kvs, max_budget, route);
+    hipLaunchKernelGGL(k_mg_route_mfma, dim3((m.N + MG_TOK - 1) / MG_TOK, m.heads), dim3(MG_THREADS), 0, st, (const uint16_t*)K,
+                       (const uint16_t*)K_out, idx, n_keep, m.N, m.kvs, max_budget, route);
+    if (check_launch("merge route") != OBF_OK) return OBF_ERR_HIP;
   } else {
-    hipLaunchKernelGGL(k_mg_route_generic<float>, dim3((m.N + MG_THREADS - 1) / MG_THREADS, m.heads), dim3(MG_THREADS), 0, st,
-                       (const float*)K, (const float*)K_out, inv_norm, n_keep, m.N, m.d, m.kvs, max_budget, route);
+    dim3 gn((max_budget + 3) / 4, m.heads), gr((m.N + MG_THREADS - 1) / MG_THREADS, m.heads);
+    if (bf) {
+      hipLaunchKernelGGL(k_mg_inv_norm<uint16_t>, gn, dim3(MG_THREADS), 0, st, (const uint16_t*)K_out, n_keep, m.d, max_budget, inv_norm);
+      hipLaunchKernelGGL(k_mg_route_generic<uint16_t>, gr, dim3(MG_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)K_out, inv_norm,
+                         n_keep, m.N, m.d, m.kvs, max_budget, route);
+    } else {
+      hipLaunchKernelGGL(k_mg_inv_norm<float>, gn, dim3(MG_THREADS), 0, st, (const float*)K_out, n_keep, m.d, max_budget, inv_norm);
+      hipLaunchKernelGGL(k_mg_route_generic<float>, gr, dim3(MG_THREADS), 0, st, (const float*)K, (const float*)K_out, inv_norm, n_keep,
+                         m.N, m.d, m.kvs, max_budget, route);
+    }
+    if (check_launch("merge route") != OBF_OK) return OBF_ERR_HIP;
+    hipLaunchKernelGGL(k_mg_unroute_kept, dim3((max_budget + MG_THREADS - 1) / MG_THREADS, m.heads), dim3(MG_THREADS), 0, st, idx,
+                       n_keep, m.N, max_budget, route);
+    if (check_launch("merge unroute") != OBF_OK) return OBF_ERR_HIP;
   }
-  if (check_launch("merge route") != OBF_OK) return OBF_ERR_HIP;
-  hipLaunchKernelGGL(k_mg_unroute_kept, dim3((max_budget + MG_THREADS - 1) / MG_THREADS, m.heads), dim3(MG_THREADS), 0, st, idx,
-                     n_keep, m.N, max_budget, route);
-  if (check_launch("merge unroute") != OBF_OK) return OBF_ERR_HIP;
-  dim3 gm((max_budget + MG_SLOTS_PER_WG - 1) / MG_SLOTS_PER_WG, m.heads);
-#define OBF_MG_LAUNCH(T, PT) hipLaunchKernelGGL((k_mg_merge<T, PT>), gm, dim3(MG_THREADS), 0, st, (const T*)V, scores, idx, n_keep, \
-                                               route, m.N, m.d, m.kvs, m.scs, max_budget, (T*)V_out, state, mats, no_scaling)
-  if (bf && per_token) OBF_MG_LAUNCH(uint16_t, true);
-  else if (bf) OBF_MG_LAUNCH(uint16_t, false);
-  else if (per_token) OBF_MG_LAUNCH(float, true);
-  else OBF_MG_LAUNCH(float, false);
+  static std::mutex attr_mu;
+  static uint64_t attr_seen = 0;
+  once_per_device(attr_mu, attr_seen, [] {
+    (void)hipFuncSetAttribute((const void*)k_mg_bucket, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(int) * kMaxTokens);
+  });
+  hipLaunchKernelGGL(k_mg_bucket, dim3(m.heads), dim3(MB_THREADS), sizeof(int) * (size_t)(max_budget < m.N ? max_budget : m.N), st, route,
+                     n_keep, m.N, max_budget, order, hstride);
+  if (check_launch("merge bucket") != OBF_OK) return OBF_ERR_HIP;
+  dim3 gm((max_budget + MG_THREADS / 64 - 1) / (MG_THREADS / 64), m.heads);
+#define OBF_MG_LAUNCH(T, D, PT) hipLaunchKernelGGL((k_mg_merge<T, D, PT>), gm, dim3(MG_THREADS), 0, st, (const T*)V, scores, idx, n_keep, \
+                                                  route, order, hstride, m.N, m.kvs, m.scs, max_budget, (T*)V_out, state, mats, no_scaling)
+  if (bf && m.d == 128) { if (per_token) OBF_MG_LAUNCH(uint16_t, 128, true); else OBF_MG_LAUNCH(uint16_t, 128, false); }
+  else if (bf) { if (per_token) OBF_MG_LAUNCH(uint16_t, 64, true); else OBF_MG_LAUNCH(uint16_t, 64, false); }
+  else if (m.d == 128) { if (per_token) OBF_MG_LAUNCH(float, 128, true); else OBF_MG_LAUNCH(float, 128, false); }
+  else { if (per_token) OBF_MG_LAUNCH(float, 64, true); else OBF_MG_LAUNCH(float, 64, false); }
 #undef OBF_MG_LAUNCH
   return check_launch("merge values");
 }

@@ -981,6 +981,44 @@ def test_cache_merging_fp32_and_head_dim_64(gpu):
     assert _check_merge(gpu, cfg, 2, [40, 0, 1000, 333]) > 250
 
 
+@pytest.mark.parametrize("dtype,d,N,B,dup", [
+    ("bf16", 128, 255, 31, 0), ("bf16", 128, 257, 33, 0), ("bf16", 128, 700, 64, 0),     # tiles of 32 slots, workgroups of 256 tokens
+    ("bf16", 128, 600, 3, 0), ("f32", 64, 600, 2, 0), ("f32", 128, 333, 40, 0), ("bf16", 64, 130, 1, 0),    # lists past 256 tokens; one slot
+    ("bf16", 128, 400, 20, 1),                                                          # equal keys: the first slot wins everything
+])
+def test_cache_merging_at_tile_and_list_edges(gpu, dtype, d, N, B, dup):
+    """Routes against the oracle's where its two best cosines are apart, merged values (sums in ascending token order) on the device's
+    own routes."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    cfg = si.RelayConfig("mergeedges", 23, 1, 2, 1, d, N, 4, B, 0, dtype, "structured", outlier_frac=0.01)
+    K, V, Q = si.make_cache(cfg, 0)
+    if dup:
+        K[:] = K[:, :, :1]
+    o = Bd.compress_relay_merge(gpu.to_dev(K, dtype), gpu.to_dev(V, dtype), gpu.to_dev(Q, dtype), budget=B, want_scores=True, want_route=True)
+    torch.cuda.synchronize()
+    idx, route, sc = (o[k].cpu().numpy() for k in ("idx", "route", "scores"))
+    for h in range(2):
+        ref = O.merge_head(K[0, h], V[0, h], Q[0, h:h + 1], B, dtype)
+        assert np.array_equal(idx[0, h], ref.idx)
+        clear = (ref.cos_gap > 2e-5) | (ref.route < 0)
+        assert np.array_equal(route[0, h][clear], ref.route[clear])
+        if dup:
+            assert set(route[0, h][route[0, h] >= 0]) == {0}
+        v32 = O.decode(V[0, h], dtype).astype(np.float32)
+        want = O.decode(V[0, h], dtype)[idx[0, h]].astype(np.float32)
+        for t in range(B):
+            acc = np.zeros(d, np.float64)
+            for j in np.nonzero(route[0, h] == t)[0]:
+                w = np.float32(np.float64(sc[0, h, j]) / (np.float64(sc[0, h, idx[0, h, t]]) + 1e-12))
+                acc = (np.float64(w) * v32[j] + acc).astype(np.float32).astype(np.float64)      # the device's fused multiply-add
+            want[t] = want[t] + acc.astype(np.float32)
+        got = O.decode(gpu.to_host(o["V_out"], dtype)[0, h], dtype)
+        # the emulated multiply-add rounds twice now and then (once to double): one single-precision rounding of the sum per addition
+        bound = 2.0 ** -23 * (N + 1) * np.abs(want).max()
+        np.testing.assert_allclose(got, O.decode(O.round_to_io(want, dtype), dtype), rtol=2.0 ** -7 if dtype == "bf16" else 0, atol=bound)
+
+
 def test_cache_merging_ragged_token_count_on_the_matrix_cores(gpu):
     cfg = si.RelayConfig("merge-tail", 24, 1, 3, 2, 128, 4099, 16, 0, 0, "bf16", "structured", outlier_frac=0.01)
     assert _check_merge(gpu, cfg, 3, [130, 1, 615]) > 600

@@ -1,7 +1,8 @@
 // Retained-span basis (Eq. 2) for heads with at most head_dim retained rows: the budget is below the
 // head dimension, so the span always leaves a complement and Orthogonal BackFill (Sec. 4.4) is active.
 //
-// Per head (one workgroup of 16 x 32 threads), everything in double precision:
+// Per head one workgroup, everything in double precision.  Ordinary heads take a blocked factorisation (ks_chol_head below); heads whose
+// rows are dependent or nearly so take the pivoted loop (ks_head; 16 x 32 threads):
 //   C = A A^T, the n x n Gram matrix of the retained rows A (entries of A are exact in float; products and
 //       sums are taken in double), kept in registers (thread (ty, tx) owns C[ty + 16a][tx + 32b]; a single-precision
 //       copy in LDS serves the power iteration only);
@@ -264,6 +265,244 @@ __device__ __forceinline__ int ks_head(const T* __restrict__ Vh, const int32_t* 
   return r;
 }
 
+// ---- The ordinary head: well conditioned, n independent rows.  Q = L^-1 A with C = A A^T = L L^T factored in order, no pivot search, in
+// blocks of 16 rows on the double-precision matrix instructions (v_mfma_f64_16x16x4_f64: operands row l % 16, k = l / 16; result entry r of
+// lane l is row l/16 + 4 r, column l % 16 - which is also how it serves as the right operand of the next product, k-step by k-step).
+//   C       tiles on and below the diagonal, one per wave at a time, from A staged as floats; then kept in LDS as 16 x 16 tiles;
+//   panel k one row per lane: lanes 0 - 15 of waves 0 - 2 carry the diagonal block (each wave for itself), the other lanes the rows
+//           below it and, in wave 0, an identity that becomes the inverse of the diagonal block's factor; sixteen pivots as unscaled
+//           rank-one steps (a reciprocal each), the square roots at the end;
+//   trail   C_ij -= L_ik L_jk^T, a tile per wave;
+//   solve   wave w owns 16 columns of A in registers: Q_k = L_kk^-1 A_k, A_i -= L_ik Q_k.  Waves 3 - 7 do it beside the next panel,
+//           waves 0 - 2 at the end (head_dim 64: waves 4 - 7 have all of it).
+// Whether the rows really are independent by the rank rule is settled there too: wave 3 solves for sixteen fixed vectors of signs z at
+// the end, whose mean |L^-1 z|^2 estimates trace(C^-1) >= 1 / lambda_min(C).  A head passes when that times trace(C) is below 1e7: then every
+// pivot in any order is above the rank threshold ((max(n, d) 2^-23)^2 lambda_max, 4e-10 of the trace at most) with a factor of 100 to
+// spare for the estimate - sixteen chi-square draws fall short of a hundredth of their mean once in 1e11 - and L^-1 A is orthonormal to
+// better than its single-precision storage.  Any other head takes the pivoted loop above, one row at a time.
+// Bound by the chain of pivots inside the panels.  288 heads, d = 128, the kernel alone: 65 us at n = 96 and 17 at n = 32; the pivoted loop
+// takes 224 and 56.
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double ks_f64x4;
+constexpr int KS_LT = 17;                // row stride of an LDS tile in doubles: operand reads (16 rows, one column) without bank conflicts
+constexpr int KS_TILE = 16 * KS_LT;
+constexpr double kCholLimit = 1.0e7;     // largest trace(C) trace(C^-1) (estimated) of a head that is settled here
+
+__host__ __device__ inline int ks_tile(int i, int j) { return i * (i + 1) / 2 + j; }
+
+__device__ __forceinline__ double ks_lane_f64(const double x, const int l) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// number t of a triangle walked by rows: (i, j), j <= i
+__device__ __forceinline__ void ks_untri(const int t, int& i, int& j) {
+  i = 0;
+  while ((i + 1) * (i + 2) / 2 <= t) ++i;
+  j = t - i * (i + 1) / 2;
+}
+
+// 16 x 16 product a b^T (or with the sign of `neg`) added to acc; both operands 16 x 16 tiles in LDS
+__device__ __forceinline__ ks_f64x4 ks_mul_bt(const double* a, const double* b, const int lane, ks_f64x4 acc) {
+  const int o = (lane & 15) * KS_LT + (lane >> 4);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[o + 4 * s], b[o + 4 * s], acc, 0, 0, 0);
+  return acc;
+}
+
+// LDS of a head of n rows: the rows as they are stored (row stride KS_SLD elements: 16 rows, 4 consecutive entries each, on different
+// banks), then the tiles.
+template <typename T> __host__ __device__ constexpr int ks_row_elems(int d) { return d + 16 / (int)sizeof(T); }
+template <typename T> __host__ __device__ constexpr size_t ks_tiles_off(int nb, int d) { return (size_t)16 * nb * ks_row_elems<T>(d) * sizeof(T); }
+
+__device__ __forceinline__ void ks_load4(const uint16_t* p, double (&o)[4]) {
+  const uint2 q = *(const uint2*)p;
+  o[0] = (double)__uint_as_float(q.x << 16); o[1] = (double)__uint_as_float(q.x & 0xffff0000u);
+  o[2] = (double)__uint_as_float(q.y << 16); o[3] = (double)__uint_as_float(q.y & 0xffff0000u);
+}
+__device__ __forceinline__ void ks_load4(const float* p, double (&o)[4]) {
+  const float4 q = *(const float4*)p;
+  o[0] = (double)q.x; o[1] = (double)q.y; o[2] = (double)q.z; o[3] = (double)q.w;
+}
+
+// NBM: most 16-row blocks (n <= 16 NBM).  True when the head was settled: its n basis rows are in bh.  All threads call.
+template <typename T, int D, int NBM>
+__device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int32_t* __restrict__ id, const int n, float* __restrict__ bh,
+                                             double* lds, KsShared& sh) {
+  constexpr int GT = (NBM * (NBM + 1) / 2 + KS_WAVES - 1) / KS_WAVES;        // Gram tiles per wave
+  constexpr int SLD = ks_row_elems<T>(D);
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int NB = (n + 15) >> 4;
+  T* stg = (T*)lds;
+  double* Lt = (double*)((char*)lds + ks_tiles_off<T>(NB, D));
+  {
+    constexpr int EPP = 16 / (int)sizeof(T), PPR = D / EPP;
+#pragma unroll 4
+    for (int e = tid; e < 16 * NB * PPR; e += KS_THREADS) {
+      const int i = e / PPR, pc = e - i * PPR;
+      uint4 q = *(const uint4*)(Vh + (size_t)id[min(i, n - 1)] * D + pc * EPP);
+      if (i >= n) q = make_uint4(0u, 0u, 0u, 0u);
+      *(uint4*)(stg + i * SLD + pc * EPP) = q;
+    }
+  }
+  __syncthreads();
+  double tr = 0.0;
+#pragma unroll 1
+  for (int q = 0; q < GT; ++q) {
+    const int t = wave + KS_WAVES * q;
+    if (t >= NB * (NB + 1) / 2) break;
+    int i, j;
+    ks_untri(t, i, j);
+    ks_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    const T* pa = stg + (16 * i + r16) * SLD + 4 * g;
+    const T* pb = stg + (16 * j + r16) * SLD + 4 * g;
+#pragma unroll 4
+    for (int c = 0; c < D; c += 16) {
+      double a[4], b[4];
+      ks_load4(pa + c, a);
+      ks_load4(pb + c, b);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], acc, 0, 0, 0);
+    }
+    double* o = Lt + ks_tile(i, j) * KS_TILE;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = g + 4 * r;
+      double v = acc[r];
+      if (i == j && row == r16) {
+        if (16 * i + row < n) tr += v; else v = 1.0;           // rows past n: an identity
+      }
+      o[row * KS_LT + r16] = v;
+    }
+  }
+  const double trace = ks_block_sum(tr, sh.red);               // (its barriers also publish the tiles)
+
+  // trailing tiles after panel k, a tile per wave
+  auto trail = [&](const int k) {
+    const int mt = (NB - 1 - k) * (NB - k) / 2;
+    for (int t = wave; t < mt; t += KS_WAVES) {
+      int i, j;
+      ks_untri(t, i, j);
+      i += k + 1; j += k + 1;
+      double* o = Lt + ks_tile(i, j) * KS_TILE + g * KS_LT + r16;
+      ks_f64x4 acc = {o[0], o[4 * KS_LT], o[8 * KS_LT], o[12 * KS_LT]};
+      acc = ks_mul_bt(Lt + ks_tile(i, k) * KS_TILE, Lt + ks_tile(j, k) * KS_TILE, lane, acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[4 * r * KS_LT] = acc[r];
+    }
+  };
+  double ss = 0.0;                                             // wave 3: squares of its solution for the sign vectors
+  // The solve for 16 right-hand sides per wave: entry r of block i is row 16 i + g + 4 r.  cb: the columns of A, < 0: the sign vectors
+  auto solve = [&](const int cb, auto&& before_step, auto&& after_last) {
+    ks_f64x4 at[NBM];
+#pragma unroll
+    for (int i = 0; i < NBM; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * i + g + 4 * r;
+        if (cb >= 0) at[i][r] = (i < NB) ? (double)Elem<T>::load(stg + row * SLD + cb * 16 + r16) : 0.0;
+        else {
+          const uint32_t h = ((uint32_t)row * 2654435761u) ^ ((uint32_t)(r16 + 1) * 0x9e3779b9u);
+          at[i][r] = (row < n) ? (((h * 0x85ebca6bu) >> 31) ? 1.0 : -1.0) : 0.0;
+        }
+      }
+    for (int k = 0; k < NB; ++k) {
+      before_step(k);
+      const int o = r16 * KS_LT + g;
+      const double* iv = Lt + ks_tile(k, k) * KS_TILE + o;
+      ks_f64x4 b = {0.0, 0.0, 0.0, 0.0}, q = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < NBM; ++i) if (i == k) b = at[i];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) q = __builtin_amdgcn_mfma_f64_16x16x4f64(iv[4 * s], b[s], q, 0, 0, 0);
+#pragma unroll
+      for (int i = 1; i < NBM; ++i)
+        if (i > k && i < NB) {
+          const double* l = Lt + ks_tile(i, k) * KS_TILE + o;
+#pragma unroll
+          for (int s = 0; s < 4; ++s) at[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(-l[4 * s], q[s], at[i], 0, 0, 0);
+        }
+      if (cb >= 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * k + g + 4 * r;
+          if (row < n) bh[(size_t)row * D + cb * 16 + r16] = (float)q[r];
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ss = fma(q[r], q[r], ss);
+      }
+    }
+    after_last();
+  };
+  const int cblk = (D == 128) ? wave : wave - 4;               // this wave's columns of A
+  // Three barriers per panel for every wave, whatever it does between them: rows read - panel written - trailing tiles written.
+  if (wave < 3) {
+#pragma unroll 1
+    for (int k = 0; k < NB; ++k) {
+      // panel k, a row per lane
+      double a[16];
+      const bool diag = lane < 16, unit = wave == 0 && lane >= 16 && lane < 32;
+      const int p = diag ? 16 * k + lane : 16 * (k + 1) + (wave == 0 ? lane - 32 : 32 + (wave - 1) * 48 + lane - 16);
+      const bool have = !unit && p < 16 * NB;
+      const bool used = wave == 0 || 16 * (k + 1) + 32 + (wave - 1) * 48 < 16 * NB;      // uniform
+      double* prow = Lt + (have ? ks_tile(p >> 4, k) * KS_TILE + (p & 15) * KS_LT : 0);
+      if (used) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) a[c] = have ? prow[c] : (unit && c == lane - 16) ? 1.0 : 0.0;
+      }
+      lds_barrier();                                           // the diagonal block is read by all three waves
+      if (used) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          const double d = ks_lane_f64(a[c], c);
+          double rc = __builtin_amdgcn_rcp(d);
+          const double e = fma(-d, rc, 1.0);
+          rc = fma(rc, fma(e, e, e), rc);
+          rc = fma(fma(-d, rc, 1.0), rc, rc);
+          const double t = -(a[c] * rc);
+#pragma unroll
+          for (int j = c + 1; j < 16; ++j) a[j] = fma(t, ks_lane_f64(a[c], j), a[j]);
+        }
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          const double d = ks_lane_f64(a[c], c);               // the c-th pivot: lane c's own entry
+          double y = __builtin_amdgcn_rsq(d);
+          y = fma(fma(-d * y, y, 1.0), 0.5 * y, y);
+          y = fma(fma(-d * y, y, 1.0), 0.5 * y, y);
+          a[c] *= y;
+        }
+        if (have && !diag) {
+#pragma unroll
+          for (int c = 0; c < 16; ++c) prow[c] = a[c];
+        }
+        if (unit) {                                            // row i of L_kk^-T: column i of the inverse
+          double* o = Lt + ks_tile(k, k) * KS_TILE + lane - 16;
+#pragma unroll
+          for (int c = 0; c < 16; ++c) o[c * KS_LT] = a[c];
+        }
+      }
+      lds_barrier();
+      trail(k);
+      lds_barrier();
+    }
+    if (cblk >= 0) solve(cblk, [](int) {}, [] {});
+  } else {
+    // step k of the solve runs beside panel k + 1
+    solve(cblk >= 0 ? cblk : 0, [&](const int k) {
+      if (k == 0) lds_barrier();                               // (the rows of panel 0 are read)
+      lds_barrier();
+      trail(k);
+      lds_barrier();
+      if (k + 1 < NB) lds_barrier();
+    }, [] {});
+    if (wave == 3) solve(-1, [](int) {}, [] {});
+  }
+  const double est = ks_block_sum(ss, sh.red) * (1.0 / 16.0);  // (wave 3's alone)
+  return trace * est < kCholLimit;                             // false also when a pivot was not positive
+}
+
 template <typename T, bool BIG>
 __global__ __launch_bounds__(KS_THREADS, BIG ? 2 : 4) void k_bf_keep_basis_small(const T* __restrict__ V, const float* __restrict__ scores,
                                                                     const int32_t* __restrict__ idx,
@@ -282,30 +521,48 @@ __global__ __launch_bounds__(KS_THREADS, BIG ? 2 : 4) void k_bf_keep_basis_small
   const T* Vh = V + (size_t)head * kvs * d;
   const int tid = threadIdx.x;
 
-  // demand sums of Eq. 6, in double, fixed summation order
+  // demand sums of Eq. 6, in double, fixed summation order: this thread's shares, added up over the workgroup at the end
   double pk = 0.0, pt = 0.0;
   for (int i = tid; i < n; i += KS_THREADS) pk += (double)sc[id[i]];
-  for (int i = tid; i < N; i += KS_THREADS) pt += (double)sc[i];
-  const double a_keep = ks_block_sum(pk, sh.red);
-  const double a_tot = ks_block_sum(pt, sh.red);
-  double a_del = a_tot - a_keep;
-  if (a_del < 0.0) a_del = 0.0;
+  for (int i0 = tid; i0 < N; i0 += 8 * KS_THREADS) {           // eight loads in flight
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = (i0 + u * KS_THREADS < N) ? sc[i0 + u * KS_THREADS] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) pt += (double)v[u];
+  }
 
   int r_keep = 0, active = 0;
   if (rank > 0 && n > 0 && n_del > 0) {
     float* bh = basis + (size_t)head * d * d;
-    if constexpr (BIG) {
-      r_keep = ks_head<T, 8, 4>(Vh, id, n, bh, Cs, sh);        // n > 96 implies d = 128
+    bool done;
+    if constexpr (BIG) {                                       // n > 96 implies d = 128
+      done = ks_chol_head<T, 128, 8>(Vh, id, n, bh, Cs, sh);
     } else if (d == 128) {
-      if (n <= 32) r_keep = ks_head<T, 2, 4>(Vh, id, n, bh, Cs, sh);
-      else if (n <= 64) r_keep = ks_head<T, 4, 4>(Vh, id, n, bh, Cs, sh);
-      else r_keep = ks_head<T, 6, 4>(Vh, id, n, bh, Cs, sh);
+      if (n <= 32) done = ks_chol_head<T, 128, 2>(Vh, id, n, bh, Cs, sh);
+      else done = ks_chol_head<T, 128, 6>(Vh, id, n, bh, Cs, sh);
     } else {
-      if (n <= 32) r_keep = ks_head<T, 2, 2>(Vh, id, n, bh, Cs, sh);
-      else r_keep = ks_head<T, 4, 2>(Vh, id, n, bh, Cs, sh);
+      done = ks_chol_head<T, 64, 4>(Vh, id, n, bh, Cs, sh);
+    }
+    r_keep = n;
+    if (!done) {
+      if constexpr (BIG) {
+        r_keep = ks_head<T, 8, 4>(Vh, id, n, bh, Cs, sh);
+      } else if (d == 128) {
+        if (n <= 32) r_keep = ks_head<T, 2, 4>(Vh, id, n, bh, Cs, sh);
+        else if (n <= 64) r_keep = ks_head<T, 4, 4>(Vh, id, n, bh, Cs, sh);
+        else r_keep = ks_head<T, 6, 4>(Vh, id, n, bh, Cs, sh);
+      } else {
+        if (n <= 32) r_keep = ks_head<T, 2, 2>(Vh, id, n, bh, Cs, sh);
+        else r_keep = ks_head<T, 4, 2>(Vh, id, n, bh, Cs, sh);
+      }
     }
     active = (r_keep < d) ? 1 : 0;
   }
+  const double a_keep = ks_block_sum(pk, sh.red);
+  const double a_tot = ks_block_sum(pt, sh.red);
+  double a_del = a_tot - a_keep;
+  if (a_del < 0.0) a_del = 0.0;
   if (tid == 0) {
     HeadState s;
     s.a_keep = a_keep; s.a_del = a_del; s.n_keep = n; s.n_del = n_del; s.r_keep = r_keep; s.active = active;
@@ -314,10 +571,13 @@ __global__ __launch_bounds__(KS_THREADS, BIG ? 2 : 4) void k_bf_keep_basis_small
   }
 }
 
-// dynamic LDS of a launch whose heads keep at most nmax rows: the padded Gram matrix or the row staging
+// dynamic LDS of a launch whose heads keep at most nmax rows: the padded Gram matrix or the row staging of the pivoted loop, the rows and
+// the tiles of the blocked factorisation
+template <typename T>
 static size_t ks_smem(size_t nmax, int d) {
-  const size_t np = (nmax + 31) / 32 * 32;
-  return max(np * np * sizeof(float), nmax * (size_t)(d + 1) * sizeof(float));
+  const size_t np = (nmax + 31) / 32 * 32, nb = (nmax + 15) / 16;
+  return max(max(np * np * sizeof(float), nmax * (size_t)(d + 1) * sizeof(float)),
+             ks_tiles_off<T>((int)nb, d) + nb * (nb + 1) / 2 * KS_TILE * sizeof(double));
 }
 
 template <typename T>
@@ -327,15 +587,15 @@ static obf_status_t run_small(const Dims& m, const void* V, const float* scores,
   static std::mutex attr_mu;
   static uint64_t attr_seen = 0;
   once_per_device(attr_mu, attr_seen, [] {
-    (void)hipFuncSetAttribute((const void*)k_bf_keep_basis_small<T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 129 * 4);
-    (void)hipFuncSetAttribute((const void*)k_bf_keep_basis_small<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 129 * 4);
+    (void)hipFuncSetAttribute((const void*)k_bf_keep_basis_small<T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_smem<T>(96, 128));
+    (void)hipFuncSetAttribute((const void*)k_bf_keep_basis_small<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_smem<T>(128, 128));
   });
   const size_t nmax = (size_t)min(max_budget, m.d);
-  hipLaunchKernelGGL((k_bf_keep_basis_small<T, false>), dim3(m.heads), dim3(KS_THREADS), ks_smem(min(nmax, (size_t)96), m.d), st,
+  hipLaunchKernelGGL((k_bf_keep_basis_small<T, false>), dim3(m.heads), dim3(KS_THREADS), ks_smem<T>(min(nmax, (size_t)96), m.d), st,
                      (const T*)V, scores, idx, n_keep, m.N, m.d, max_budget, rank, state, basis, m.scs, m.kvs);
   if (check_launch("backfill keep_basis_small") != OBF_OK) return OBF_ERR_HIP;
   if (nmax > 96) {
-    hipLaunchKernelGGL((k_bf_keep_basis_small<T, true>), dim3(m.heads), dim3(KS_THREADS), ks_smem(nmax, m.d), st,
+    hipLaunchKernelGGL((k_bf_keep_basis_small<T, true>), dim3(m.heads), dim3(KS_THREADS), ks_smem<T>(nmax, m.d), st,
                        (const T*)V, scores, idx, n_keep, m.N, m.d, max_budget, rank, state, basis, m.scs, m.kvs);
     if (check_launch("backfill keep_basis_small (wide)") != OBF_OK) return OBF_ERR_HIP;
   }

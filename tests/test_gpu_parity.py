@@ -187,6 +187,31 @@ def test_deleted_row_statistics_of_fp32_and_half_width_heads(gpu, dtype, d, N):
     _check_cfg(gpu, cfg, expect_active=True if N > 14 else None)
 
 
+@pytest.mark.parametrize("d,dtype,budgets", [
+    (128, "bf16", [1, 2, 15, 17, 31, 32, 47, 48, 49, 79, 80, 81, 95, 111, 113, 126]),     # blocks of 16 rows, panels on one to three waves
+    (128, "f32", [16, 31, 65, 96, 128]),
+    (64, "bf16", [1, 16, 17, 48, 63]),
+])
+def test_small_budget_basis_block_edges(gpu, d, dtype, budgets):
+    cfg = si.RelayConfig("blockedges", 29, 1, len(budgets), 1, d, 800, 8, 0, 3, dtype, "structured", outlier_frac=0.01)
+    _check_cfg(gpu, cfg, budgets=budgets, max_budget=max(budgets), expect_active=True)
+
+
+@pytest.mark.parametrize("noise", [1e-1, 1e-2])
+def test_nearly_dependent_retained_rows(gpu, noise):
+    """Retained rows that repeat 20 distinct ones up to a small difference: trace(C) trace(C^-1) is about 2e3 / noise^2, so the blocked
+    factorisation settles the first case (limit 1e7) and hands the second to the pivoted loop.  (Differences of 1e-3 bring singular values
+    within a decade of the rank rule's threshold, where the checks compare nothing.)"""
+    cfg = si.RelayConfig("nearlydep", 31, 1, 3, 1, 128, 600, 8, 40, 2, "f32", "structured", outlier_frac=0.0)
+    def edit(K, V, Q):
+        r = np.random.default_rng(5)
+        for h in range(3):
+            base = V[0, h, :20].copy()
+            V[0, h] = base[np.arange(600) % 20] + noise * r.standard_normal((600, 128)).astype(np.float32)
+    reps = _check_cfg(gpu, cfg, edit=edit)
+    assert any(r.skipped == 0 for r in reps)
+
+
 @pytest.mark.parametrize("budget", [48, 300])
 def test_rank_deficient_retained_rows(gpu, budget):
     """Values that repeat 24 distinct rows (plus a few free tokens): the retained span has rank far below both the

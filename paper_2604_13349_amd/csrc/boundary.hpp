@@ -1,49 +1,69 @@
 // Exact re-decision of the tokens at the selection threshold, shared by the standalone refinement kernel and by the
 // fused select+refine kernel so that both take bit-identical decisions.
 #pragma once
-#include "common.hpp"
+#include "f64_tile.hpp"
 
 namespace obf {
 
-// eight consecutive elements as floats, one 16-byte (bf16) or two 16-byte (fp32) loads; p must be 16-byte aligned
-__device__ __forceinline__ void load8(const uint16_t* p, float (&o)[8]) {
-  const uint4 v = *(const uint4*)p;
-  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+// Exact (double) attention mass of each band token, sixteen tokens against sixteen query rows at a time on the double-precision matrix
+// instructions: a wave takes every WAVES-th block of rows, leaves the block's sixteen column sums in LDS, and a thread per token adds
+// the blocks in order - the order of the additions does not depend on the number of waves, and tokens with equal keys get equal masses.
+// With a wave per token and the products as scalar double-precision multiply-adds this was 46k of the 103k cycles of a selection
+// workgroup on 16384 tokens x 320 rows.  All threads call; `part` is LDS scratch; ends with a barrier.
+constexpr int kRescoreBlocks = 32;       // row blocks per round of the scratch
+struct RescoreScratch { double part[kRescoreBlocks][16]; };
+
+template <typename T, int WAVES, int D>
+__device__ __forceinline__ void rescore_band_d(const T* __restrict__ Kh, const T* __restrict__ Qh, const double* __restrict__ lse, int R,
+                                               const int* band, int nband, double* band_score, RescoreScratch& rs) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double scale = 1.0 / sqrt((double)D);
+  const int nblk = (R + 15) >> 4;
+  for (int b0 = 0; b0 < nband; b0 += 16) {
+    RowPart<T, D> kp;
+    kp.load(Kh + (size_t)band[min(b0 + (lane & 15), nband - 1)] * D, lane);        // tokens past the band: the last one again, not written
+    double sum = 0.0;
+    for (int c0 = 0; c0 < nblk; c0 += kRescoreBlocks) {
+      const int nc = min(kRescoreBlocks, nblk - c0);
+      for (int c = wave; c < nc; c += WAVES) {
+        const int r0 = (c0 + c) * 16;
+        RowPart<T, D> qp;
+        qp.load(Qh + (size_t)min(r0 + (lane & 15), R - 1) * D, lane);
+        double l[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) { o[2 * i] = __uint_as_float(w[i] << 16); o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
-}
-__device__ __forceinline__ void load8(const float* p, float (&o)[8]) {
-  const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-  o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
+        for (int i = 0; i < 4; ++i) { const int r = r0 + (lane >> 4) + 4 * i; l[i] = (r < R) ? lse[r] : 0.0; }
+        // (the token's entries are converted again for every block: kept as doubles they would take D / 2 registers)
+#pragma unroll
+        for (int i = 0; i < RowPart<T, D>::NV; ++i) asm volatile("" : "+v"(kp.v[i].x), "+v"(kp.v[i].y), "+v"(kp.v[i].z), "+v"(kp.v[i].w));
+        f64x4 x = {0.0, 0.0, 0.0, 0.0}, y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < D / 4; s += 2) {
+          x = __builtin_amdgcn_mfma_f64_16x16x4f64(qp.at(s), kp.at(s), x, 0, 0, 0);
+          y = __builtin_amdgcn_mfma_f64_16x16x4f64(qp.at(s + 1), kp.at(s + 1), y, 0, 0, 0);
+          if ((s & 7) == 6) __builtin_amdgcn_sched_barrier(0);           // conversions stay near their use
+        }
+        x += y;
+        double col = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) if (r0 + (lane >> 4) + 4 * i < R) col += exp(x[i] * scale - l[i]);
+        col += __shfl_xor(col, 16);
+        col += __shfl_xor(col, 32);
+        if (lane < 16) rs.part[c][lane] = col;
+      }
+      __syncthreads();
+      if (threadIdx.x < 16) for (int c = 0; c < nc; ++c) sum += rs.part[c][threadIdx.x];
+      __syncthreads();
+    }
+    if (threadIdx.x < 16 && b0 + (int)threadIdx.x < nband) band_score[b0 + threadIdx.x] = sum;
+  }
+  __syncthreads();
 }
 
-// Exact (double) attention mass of each band token: one wave per token, lanes over the query rows, fixed
-// summation order (row stride 64 per lane, then a butterfly over the lanes).
 template <typename T, int WAVES>
-__device__ __forceinline__ void rescore_band(const T* __restrict__ Kh, const T* __restrict__ Qh,
-                                             const double* __restrict__ lse, int d, int R, const int* band, int nband,
-                                             double* band_score) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const double scale = 1.0 / sqrt((double)d);
-  for (int b = wave; b < nband; b += WAVES) {
-    const T* kr = Kh + (size_t)band[b] * d;
-    double part = 0.0;
-    for (int r = lane; r < R; r += 64) {
-      const T* qr = Qh + (size_t)r * d;
-      double acc = 0.0;
-#pragma unroll 4
-      for (int c = 0; c < d; c += 8) {                  // head_dim is a multiple of 8; same element order as a scalar loop
-        float qv[8], kv[8];
-        load8(qr + c, qv);
-        load8(kr + c, kv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc = fma((double)qv[e], (double)kv[e], acc);
-      }
-      part += exp(acc * scale - lse[r]);
-    }
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-    if (lane == 0) band_score[b] = part;
-  }
+__device__ __forceinline__ void rescore_band(const T* __restrict__ Kh, const T* __restrict__ Qh, const double* __restrict__ lse, int d, int R,
+                                             const int* band, int nband, double* band_score, RescoreScratch& rs) {
+  if (d == 128) rescore_band_d<T, WAVES, 128>(Kh, Qh, lse, R, band, nband, band_score, rs);
+  else rescore_band_d<T, WAVES, 64>(Kh, Qh, lse, R, band, nband, band_score, rs);
 }
 
 // Thread u < nband: is band token u among the nkb best (exact score descending, index ascending; band[] is ascending)?

@@ -32,6 +32,7 @@ struct RfShared {
   int band[kBandCap];
   double band_score[kBandCap];
   int keep_new[kBandCap];
+  RescoreScratch rescore;
   int wsum[NT / 64];
   float wred[NT / 64];
   int s_changed;
@@ -145,8 +146,7 @@ __global__ __launch_bounds__(NT) void k_refine(const T* __restrict__ K, const T*
   if (!rf_find_band<NT>(sh, sc, out, n, N, nband, nkb, kb)) return;
   // 4. exact scores of the band tokens
   rescore_band<T, NT / 64>(K + (size_t)head * kvs * d, Q + (size_t)head * R * d, row_lse + (size_t)head * R, d, R, sh.band,
-                           nband, sh.band_score);
-  __syncthreads();
+                           nband, sh.band_score, sh.rescore);
   rf_apply<NT>(sh, out, N, nband, nkb, kb);
 }
 
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(NT) void k_refine_layer_part(const T* __restrict__ 
   int nband, nkb, kb;
   if (!rf_find_band<NT>(sh, layer_scores + (size_t)l * N, idx_layer + (size_t)l * max_budget, n, N, nband, nkb, kb)) return;
   rescore_band<T, NT / 64>(K + (size_t)head * kvs * d, Q + (size_t)head * R * d, row_lse + (size_t)head * R, d, R, sh.band,
-                           nband, part + (size_t)head * kBandCap);
+                           nband, part + (size_t)head * kBandCap, sh.rescore);
 }
 
 // Second launch: one workgroup per layer finds the band again, adds the heads' exact masses in head order and

@@ -3,20 +3,16 @@
 // sums.
 //
 // The logits are products of the double-precision matrix instruction v_mfma_f64_16x16x4_f64 on 16 x 16 tiles (16 tokens against 16
-// query rows).  Its operands hold, in lane l, row l % 16 and one k of four, picked by l / 16; which k that is does not matter as long
-// as both operands agree, so lane l takes the head_dim entries (l/16) * d/4 ..  of its row: consecutive in memory, loaded straight into
-// registers in 16-byte pieces, converted to double once per tile.  Entry i of lane l of the result is row l/16 + 4 i, column l % 16.
+// query rows; operand layout in f64_tile.hpp).
 //   pass A: a wave keeps the operand of 16 query rows and walks the tiles of its chunk of tokens (tokens x rows: a lane owns one
 //           query row and keeps its running maximum and sum);
 //   pass B: a wave keeps the operand of 16 tokens and walks all query rows (rows x tokens: a lane owns one token).
 // Bound by the double-precision matrix rate (64 multiply-adds per clock and compute unit: 43 us a pass at the first shape below) and
 // the exponentials, which the same units compute.  96 heads x 2048 tokens x 128 rows at head_dim 64: 102 and 88 us; 2 heads x 512
 // tokens x 32 rows: 12 and 8 us.  With the products as scalar multiply-adds fed from LDS: 975 and 853 us, 224 and 215 us.
-#include "common.hpp"
+#include "f64_tile.hpp"
 
 namespace obf {
-
-typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
 
 constexpr int GS_THREADS = 256;
 constexpr int GS_WAVES = GS_THREADS / 64;
@@ -25,30 +21,6 @@ constexpr int GS_MIN_TILES = 2;          // shortest chunk of pass A, in tiles
 constexpr int GS_TARGET_WAVES = 4096;    // waves of pass A that fill the chip (four per SIMD); fewer, longer chunks beyond
 constexpr int GS_FOLD = 1024;            // partials per head up to which pass B folds them itself (each of its workgroups reads them all;
                                          // a launch of its own costs 5 us)
-
-// the head_dim entries (lane / 16) * D/4 .. of one row, as they lie in memory
-template <typename T, int D>
-struct RowPart {
-  static constexpr int NV = D / 4 * (int)sizeof(T) / 16;     // 16-byte pieces
-  uint4 v[NV];
-  __device__ __forceinline__ void load(const T* __restrict__ row, int lane) {
-    const uint4* p = (const uint4*)(row + (lane >> 4) * (D / 4));
-#pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = p[i];
-  }
-  __device__ __forceinline__ double at(int s) const {         // entry s; s is a compile-time constant after unrolling
-    if constexpr (sizeof(T) == 2) {
-      const uint4& q = v[s >> 3];
-      const int k = s & 7;
-      const uint32_t w = (k >> 1) == 0 ? q.x : (k >> 1) == 1 ? q.y : (k >> 1) == 2 ? q.z : q.w;
-      return (double)__uint_as_float((k & 1) ? (w & 0xffff0000u) : (w << 16));
-    } else {
-      const uint4& q = v[s >> 2];
-      const int k = s & 3;
-      return (double)__uint_as_float(k == 0 ? q.x : k == 1 ? q.y : k == 2 ? q.z : q.w);
-    }
-  }
-};
 
 // 16 x 16 tile of dot products: `moving`, the operand a wave streams, gives the rows of the result, `fixed`, the one it keeps, the
 // columns.  Two chains, so that an instruction does not wait for the one before it.

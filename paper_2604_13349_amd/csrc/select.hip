@@ -41,13 +41,19 @@ __device__ __forceinline__ void block_exscan2(int a, int b, int& ea, int& eb, in
   __syncthreads();
 }
 
-// Thread t owns the SEG consecutive tokens starting at t*SEG (keys stay in registers).  The key of rank B is
-// found by bisection on the 32 key bits, most significant first: T is the largest value with
-// count(key >= T) >= B.  Counting is one ballot + population count per owned token and one workgroup sum per bit.
+// Thread t owns the SEG consecutive tokens starting at t*SEG (keys stay in registers).  The key of rank B is found by counting: a
+// histogram of the keys between the smallest and the largest one (SEL_BINS bins of equal width in the integer image, that is
+// logarithmic in the score), a scan from the top for the bin that holds rank B, and again inside that bin until it is one key wide
+// or its keys fit a list, whose entries then count the larger ones among themselves.  One histogram and a list of some tens of keys as a
+// rule.  With a bisection on the key bits (a ballot and a population count per owned token and bit) and the scalar re-decision the whole
+// kernel took 36, 113 and 158 us on 288, 320 and 288 heads of 8192, 16384 and 32768 tokens; it takes 25, 59 to 74 and 98.
 // With REFINE the tokens whose score lies in the relative band around the threshold are re-decided in double from K, Q
 // and the row log-sum-exp before the list is written (same decisions as select followed by the refinement kernel).
+constexpr int SEL_BINS = 2048;
+constexpr int SEL_LIST = 256;
+
 template <int SEG, int SEL_THREADS, bool REFINE, typename ET>
-__global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict__ scores, int N, int head0,
+__global__ __launch_bounds__(SEL_THREADS, 4) void k_select(const float* __restrict__ scores, int N, int head0,
                                                         int uniform_budget, BudgetBatch per_head, int use_per_head,
                                                         int max_budget, int32_t* __restrict__ idx,
                                                         int32_t* __restrict__ n_keep, const ET* __restrict__ K,
@@ -55,11 +61,14 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
                                                         int d, int R, int scs, int kvs,
                                                         int32_t* __restrict__ sel_flags /*nullable; written with REFINE only*/) {
   constexpr int SEL_WAVES = SEL_THREADS / 64;
-  __shared__ int band[REFINE ? kBandCap : 1];
+  __shared__ __attribute__((aligned(16))) int hist[SEL_BINS];
+  __shared__ uint32_t list[SEL_LIST];
+  __shared__ int band[REFINE ? kBandCap : 1], band_raw[REFINE ? kBandCap : 1];
   __shared__ double band_score[REFINE ? kBandCap : 1];
   __shared__ int keep_new[REFINE ? kBandCap : 1];
-  __shared__ int s_changed;
-  __shared__ int wcnt[2][SEL_WAVES];
+  __shared__ int s_changed, s_bin, s_above, s_nlist, s_nband, s_nkb;
+  __shared__ uint32_t s_T;
+  __shared__ uint32_t wmin[SEL_WAVES], wmax[SEL_WAVES];
   __shared__ int wsum[2 * SEL_WAVES];
   const int head = head0 + blockIdx.x;
   const float* sc = scores + (size_t)head * scs;
@@ -86,49 +95,80 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
 #pragma unroll
     for (int i = 0; i < SEG; ++i) key[i] = (i < nvalid) ? order_key(sc[base + i]) : 0u;
   }
+  if (tid == 0) { s_nlist = 0; s_changed = 0; s_nband = 0; s_nkb = 0; }
 
-  // tokens outside the head carry key 0 and every candidate is >= 1, so they never count
-  auto count_ge = [&](uint32_t cand, int buf) -> int {
-    int c = 0;
+  // the keys' range
+  {
+    uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
-    for (int i = 0; i < SEG; ++i) c += __popcll(__ballot(key[i] >= cand));
-    if (lane == 0) wcnt[buf][wave] = c;
-    __syncthreads();
-    int tot = 0;
-#pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) tot += wcnt[buf][w];
-    return tot;
-  };
-
-  // Bisection, most significant bit first.  As soon as exactly B keys are >= the candidate, the retained set is
-  // known and the rank-B key is the smallest of them (one more workgroup reduction) - the remaining bits are skipped.
-  uint32_t T = 0u;
-  int buf = 0;
-  bool exact = false;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t cand = T | (1u << bit);
-    const int c = count_ge(cand, buf);
-    buf ^= 1;
-    if (c >= B) T = cand;
-    if (c == B) { exact = true; break; }
+    for (int i = 0; i < SEG; ++i) if (i < nvalid) { mn = min(mn, key[i]); mx = max(mx, key[i]); }
+    for (int off = 32; off > 0; off >>= 1) { mn = min(mn, (uint32_t)__shfl_xor((int)mn, off)); mx = max(mx, (uint32_t)__shfl_xor((int)mx, off)); }
+    if (lane == 0) { wmin[wave] = mn; wmax[wave] = mx; }
   }
-  if (exact) {
-    uint32_t mn = 0xffffffffu;
-#pragma unroll
-    for (int i = 0; i < SEG; ++i) if (i < nvalid && key[i] >= T) mn = min(mn, key[i]);
-    for (int off = 32; off > 0; off >>= 1) mn = min(mn, (uint32_t)__shfl_xor((int)mn, off));
-    if (lane == 0) wcnt[buf][wave] = (int)mn;
+  __syncthreads();
+  uint32_t lo_key = 0xffffffffu, hi_key = 0u;
+  for (int w = 0; w < SEL_WAVES; ++w) { lo_key = min(lo_key, wmin[w]); hi_key = max(hi_key, wmax[w]); }
+  int need = B;                                                // rank wanted among the keys of [lo_key, hi_key]
+  int n_gt = 0;                                                // keys above hi_key; at the end: above T
+  uint32_t T = lo_key;
+  for (;;) {                                                   // uniform
+    const uint32_t span = hi_key - lo_key;
+    if (span == 0u) { T = lo_key; break; }
+    const int shift = max(0, 32 - __clz((int)span) - 11);      // span >> shift < SEL_BINS = 2^11
+    for (int i = tid; i < SEL_BINS; i += SEL_THREADS) hist[i] = 0;
     __syncthreads();
-    uint32_t t = 0xffffffffu;
 #pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) t = min(t, (uint32_t)wcnt[buf][w]);
-    T = t;
-    buf ^= 1;
+    for (int i = 0; i < SEG; ++i) {
+      const uint32_t o = key[i] - lo_key;                      // keys below the range wrap to above the span
+      if (i < nvalid && o <= span) atomicAdd(&hist[o >> shift], 1);
+    }
+    __syncthreads();
+    // from the top: this thread's bins are hb - 1 .. hb - PER
+    constexpr int PER = SEL_BINS / SEL_THREADS;
+    const int hb = SEL_BINS - tid * PER;
+    int c[PER], mine = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) { c[i] = hist[hb - 1 - i]; mine += c[i]; }
+    int inc = mine;
+    for (int off = 1; off < 64; off <<= 1) { const int x = __shfl_up(inc, off); if (lane >= off) inc += x; }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    int before = inc - mine;
+    for (int w = 0; w < wave; ++w) before += wsum[w];
+    if (before < need && need <= before + mine) {
+      int above = before;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        if (above < need && need <= above + c[i]) { s_bin = hb - 1 - i; s_above = above; }
+        above += c[i];
+      }
+    }
+    __syncthreads();
+    const int bin = s_bin, above = s_above, inside = hist[bin];
+    n_gt += above; need -= above;
+    const uint64_t top = (uint64_t)lo_key + (((uint64_t)bin + 1u) << shift) - 1u;
+    if (top < (uint64_t)hi_key) hi_key = (uint32_t)top;        // (the last bin may run past the largest key)
+    lo_key += (uint32_t)bin << shift;
+    if (shift == 0) { T = lo_key; break; }
+    if (inside <= SEL_LIST) {
+      const uint32_t w = hi_key - lo_key;
+#pragma unroll
+      for (int i = 0; i < SEG; ++i) if (i < nvalid && key[i] - lo_key <= w) list[atomicAdd(&s_nlist, 1)] = key[i];
+      __syncthreads();
+      for (int t = tid; t < inside; t += SEL_THREADS) {
+        const uint32_t k = list[t];
+        int gt = 0, ge = 0;
+        for (int j = 0; j < inside; ++j) { gt += list[j] > k; ge += list[j] >= k; }
+        if (gt < need && need <= ge) { s_T = k; s_above = gt; }                // the same from every copy of the key
+      }
+      __syncthreads();
+      T = s_T;
+      n_gt += s_above;
+      break;
+    }
+    __syncthreads();                                           // hist is cleared again
   }
   // keys greater than T are all kept; of the keys equal to T the lowest indices fill the rest
-  int n_gt = 0;
-  if (T != 0xffffffffu) n_gt = count_ge(T + 1u, buf);
-  buf ^= 1;
   const int need_eq = B - n_gt;
   int cg = 0, ce = 0;
 #pragma unroll
@@ -136,14 +176,13 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
   int eg, ee, tg, te;
   block_exscan2<SEL_WAVES>(cg, ce, eg, ee, tg, te, wsum);
   bool refined = false;
-  int bpos0 = 0;
+  int nband = 0;
   float lo = 0.f, hi = 0.f;
   if (REFINE) {
     // band around the threshold score, in the same float arithmetic as the standalone refinement
     const float tau = key_to_float(T);
     const float half = kBandRel * fabsf(tau);
     lo = tau - half; hi = tau + half;
-    int cb = 0, ckb = 0;
     {
       int er = ee;                                      // running count of keys equal to T before this token
 #pragma unroll
@@ -153,31 +192,29 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
           const float s = key_to_float(k);
           const bool kept = (k > T) || (k == T && er < need_eq);
           er += (k == T);
-          if (s >= lo && s <= hi) { ++cb; ckb += kept; }
+          if (s >= lo && s <= hi) {                     // few: collected as they come, put in index order below
+            const int p = atomicAdd(&s_nband, 1);
+            if (kept) atomicAdd(&s_nkb, 1);
+            if (p < kBandCap) band_raw[p] = ((base + i) << 1) | (kept ? 1 : 0);
+          }
         }
       }
     }
-    int ebk, nband, nkb;
-    block_exscan2<SEL_WAVES>(cb, ckb, bpos0, ebk, nband, nkb, wsum);
-    if (tid == 0) s_changed = 0;
+    __syncthreads();
+    nband = s_nband;
+    const int nkb = s_nkb;
     // a band that straddles the threshold but is too large to re-score keeps the single-precision order: say so
     if (sel_flags && tid == 0) sel_flags[head] = (nband > kBandCap && nkb > 0 && nkb < nband) ? OBF_SELECT_BAND_OVERFLOW : 0;
     if (nband > 1 && nband <= kBandCap && nkb > 0 && nkb < nband) {       // uniform
-      int bp = bpos0, er = ee;
-#pragma unroll
-      for (int i = 0; i < SEG; ++i) {
-        if (i < nvalid) {
-          const uint32_t k = key[i];
-          const float s = key_to_float(k);
-          const bool kept = (k > T) || (k == T && er < need_eq);
-          er += (k == T);
-          if (s >= lo && s <= hi) { band[bp] = base + i; keep_new[bp] = kept; ++bp; }
-        }
+      for (int t = tid; t < nband; t += SEL_THREADS) {
+        const int raw = band_raw[t];
+        int rank = 0;
+        for (int j = 0; j < nband; ++j) rank += band_raw[j] < raw;
+        band[rank] = raw >> 1; keep_new[rank] = raw & 1;
       }
       __syncthreads();
       rescore_band<ET, SEL_WAVES>(K + (size_t)head * kvs * d, Q + (size_t)head * R * d, row_lse + (size_t)head * R, d, R,
-                                 band, nband, band_score);
-      __syncthreads();
+                                 band, nband, band_score, *(RescoreScratch*)hist);
       int keep = 0, was = 0;
       if (tid < nband) { was = keep_new[tid]; keep = band_keeps(band_score, nband, nkb, tid); if (keep != was) s_changed = 1; }
       __syncthreads();
@@ -200,7 +237,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
     uint32_t flags = 0u;
     int cnt = 0;
     {
-      int bp = bpos0, er = ee;
+      int er = ee;
 #pragma unroll
       for (int i = 0; i < SEG; ++i) {
         if (i < nvalid) {
@@ -208,7 +245,11 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select(const float* __restrict_
           const float s = key_to_float(k);
           bool kept = (k > T) || (k == T && er < need_eq);
           er += (k == T);
-          if (s >= lo && s <= hi) { kept = keep_new[bp] != 0; ++bp; }
+          if (s >= lo && s <= hi) {
+            int bp = 0;
+            while (band[bp] != base + i) ++bp;          // it is one of the nband tokens listed
+            kept = keep_new[bp] != 0;
+          }
           if (kept) { flags |= 1u << i; ++cnt; }
         }
       }
@@ -248,12 +289,14 @@ template <bool REFINE, typename T>
 static obf_status_t dispatch_select(const Dims& m, const float* scores, const int32_t* budgets_host, int32_t budget,
                                     int32_t max_budget, int32_t* idx, int32_t* n_keep, const void* K, const void* Q,
                                     const double* row_lse, hipStream_t st, int32_t* sel_flags) {
-  // per bit every wave counts its keys and the workgroup adds the counts: 16 keys per thread up to 8192 tokens, 32 above
+  // a workgroup's time is its scans and barriers, which a larger one pays more for, and its keys in LDS atomics: 16 keys per thread up
+  // to 8192 tokens, 32 above (288 heads x 8192: 26 us, 32 with (32, 256), 33 with (8, 1024); 320 x 16384: 59 us, 70 with (16, 1024);
+  // 288 x 2048: 13 us, 13 with (4, 512), 20 with (2, 1024))
 #define OBF_SEL(SEG, THR) launch_select_seg<SEG, THR, REFINE, T>(m, scores, budgets_host, budget, max_budget, idx, n_keep, K, Q, row_lse, st, sel_flags)
   if (m.N <= 4 * 256) return OBF_SEL(4, 256);
   if (m.N <= 8 * 256) return OBF_SEL(8, 256);
   if (m.N <= 16 * 256) return OBF_SEL(16, 256);
-  if (m.N <= 16 * 512) return OBF_SEL(16, 512);      // 8192 tokens: 37 us against 42 with (32, 256) and 48 with (8, 1024)
+  if (m.N <= 16 * 512) return OBF_SEL(16, 512);
   if (m.N <= 32 * 512) return OBF_SEL(32, 512);
   return OBF_SEL(32, 1024);
 #undef OBF_SEL

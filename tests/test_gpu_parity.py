@@ -381,6 +381,39 @@ def test_select_stage_is_exact_on_given_scores(gpu):
             assert np.all(idx[0, h, b:] == -1)
 
 
+@pytest.mark.parametrize("N", [1, 2, 63, 1024, 1025, 2048, 2049, 4097, 8192, 8193, 16384, 16385, 32768])
+def test_select_stage_over_key_ranges_and_sizes(gpu, N):
+    """The threshold is found by a histogram over the keys' range and a list of one bin's keys: one key value only, one outlier that
+    leaves all others in one bin, clusters a few ulps wide with more ties than the list holds, both signs with zeros and infinities,
+    and a head's first and last ranks, at the sizes where the keys per thread change."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    rng = np.random.default_rng(N)
+    s = np.empty((1, 6, N), dtype=np.float32)
+    s[0, 0] = np.exp(3 * rng.standard_normal(N)).astype(np.float32)
+    s[0, 1] = 0.25
+    s[0, 2] = (1 + 1e-3 * rng.random(N)).astype(np.float32)
+    s[0, 2, N // 2] = 3e38                                                   # every other key in one bin
+    s[0, 3] = (np.float32(0.7).view(np.int32) + rng.integers(0, 3, N).astype(np.int32)).view(np.float32)
+    s[0, 4] = (np.where(rng.random(N) < 0.5, -1, 1) * np.exp(40 * rng.standard_normal(N).clip(-2, 2))).astype(np.float32)
+    s[0, 4, ::5] = 0.0
+    s[0, 4, 1::5] = -0.0
+    s[0, 4, 2::11] = np.inf
+    s[0, 4, 3::11] = -np.inf
+    s[0, 5] = rng.integers(0, 2 ** 31 - 2 ** 23, N).astype(np.int32).view(np.float32)      # uniform in the integer image
+    sh = Bd.make_shape(1, 6, 1, 64, N, 1, "bf16")
+    bits = s.view(np.uint32)
+    order = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31)).astype(np.float64)      # the integer image, exact in double
+    for b in sorted({1, (N + 2) // 3, N // 2 + 1, N - 1} - {0}):
+        if b > N:
+            continue
+        idx, n_keep = Bd.select_topk(sh, torch.from_numpy(s).cuda(), budget=b, max_budget=b)
+        torch.cuda.synchronize()
+        idx, n_keep = idx.cpu().numpy(), n_keep.cpu().numpy()
+        for h in range(6):
+            assert n_keep[0, h] == b and np.array_equal(idx[0, h], O.select_topk(order[0, h], b)), f"head {h} budget {b}"
+
+
 # --------------------------------------------------------------------------- full sizes, sampled heads
 def _full_size(gpu, name, seed, sample, expect_active):
     """The whole named config through the fused call (the launch configuration bench.py times);

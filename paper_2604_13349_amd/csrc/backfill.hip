@@ -601,6 +601,15 @@ __device__ __forceinline__ void fn_emit(const int head, const int d, const int r
 // two thin matrix products.  For more rows the pivots' number turns against it and the projector route stays.
 constexpr int FN_FEW = 32;
 constexpr int FN_LDN = FN_FEW + 1;       // row stride of the small matrices in LDS
+__host__ __device__ inline int fn_few_floats(int r, int d) { return (d - r) * (d + 1 + FN_LDN); }
+
+// Does a head of r retained directions, n retained rows take that route?  Below 14 directions (head_dim 128; 16 at 64) it needs the large
+// LDS of the finalisation's second launch: taken only where n says so too, so that a rank-deficient head of a larger budget (whose Z then
+// comes from the projector, which always fits) cannot ask for that launch.
+__host__ __device__ inline bool fn_few(int r, int n, int d) {
+  const int small = fn_small_floats(d);
+  return r <= FN_FEW && (fn_few_floats(r, d) <= small || (n <= FN_FEW && fn_few_floats(n, d) > small));
+}
 
 // One wave: N = M^-1 S (rows and columns past r zero) to LDS, the signs to sg.  In-place Gauss-Jordan, lane c holds column c; the rows
 // move up by one register per step so that the pivot row is always the first and the loop stays rolled.
@@ -737,18 +746,19 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
   const int m_span = d - st.r_keep;
   const bool direct_ok = lead != nullptr && !(vflags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) && min(rank, m_span) >= 1 &&
                          min(rank, m_span) <= TE_MAXK;
+  const int n_few = (vflags & VF_NO_PROJECTION) ? 0 : st.n_keep;       // (without the projection r = 0 whatever n is)
   {
     // Two launches share the heads: the first has fn_small_floats(d) floats of LDS (two workgroups per CU) and takes every head that
     // fits there, the second takes the rest.  A head needs room for Z and, by its route, the small matrices of fn_complement or the
-    // projector's columns; one that is diagonalised here also for T and W.
+    // projector's columns; one that is diagonalised here also for T and W.  cls < 0: one launch with the large LDS takes every head.
     int need = 0;
     if (st.active && !naive) {
       const int mm0 = m_span + (m_span & 1);
-      need = m_span * (ld + (st.r_keep <= FN_FEW ? FN_LDN : 0));
+      need = fn_few(st.r_keep, n_few, d) ? fn_few_floats(st.r_keep, d) : m_span * ld;
       if (!direct_ok) need = max(need, 2 * mm0 * (mm0 + 1));
     }
     const int big = need > fn_small_floats(d);
-    if (cls >= 0 && big != cls) return;                        // cls < 0: one launch with the large LDS takes every head
+    if (cls >= 0 && big != cls) return;
   }
   if (lead && tid == 0) lead[head].pending = 0;
 
@@ -783,7 +793,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     // Few retained rows: Z comes from the r x r leading block of Q (fn_complement below) instead of the projector.  The last wave inverts
     // that block while the others sum G.  At r = 32, head_dim 128: 11k cycles more than the sum alone and 12k for the products, where P
     // and its factorisation took 11k and 136k (whole kernel 228k -> 92k cycles, a 256-token call 415 -> 340 us).
-    const bool few = r <= FN_FEW;                              // uniform
+    const bool few = fn_few(r, n_few, d);                      // uniform
     const bool inverting = few && wave == FN_WAVES - 1;
     if (inverting) {
       fn_invert_block(Qb, r, d, sm + m * ld, dvec);
@@ -1836,7 +1846,11 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     // every budget above head_dim: heads that need the finalisation are rare (the certificate settles the others), so one
     // launch with the large LDS size serves both classes instead of two launches that mostly exit at once
     const bool single = min_budget > m.d && m.N > m.d && !var.skips_basis();
-    for (int cls = single ? -1 : 0; cls < (single ? 0 : 2); ++cls) {
+    // every head leaves its eigenpairs to the leading-eigenpair kernel and none has few enough rows to need the large LDS: the second
+    // launch, 5 us with every workgroup leaving at once, is not made 
+    // (256 tokens, budget 32: 302 -> 297 us; eight agents in lanes: 2215 -> 2074)
+    const bool small_only = !single && lead_ok && !var.skips_basis() && (min_budget > FN_FEW || fn_few_floats(max(min_budget, 0), m.d) <= fn_small_floats(m.d));
+    for (int cls = single ? -1 : 0; cls < (single ? 0 : small_only ? 1 : 2); ++cls) {
       const size_t lds = (cls == 0) ? sizeof(float) * (size_t)fn_small_floats(m.d) : 2 * one;
       hipLaunchKernelGGL(k_bf_finalize<T>, dim3(m.heads), dim3(FN_THREADS), lds, st, m.N, m.d,
                          w.nstat, rank, state, basis, gram_part, mats, delta, delta_out, diag,

@@ -230,6 +230,23 @@ def test_rank_deficient_retained_rows(gpu, budget):
     assert all(r.r_keep < 128 for r in reps)
 
 
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "f32")])
+@pytest.mark.parametrize("budgets", [(16, 24, 32, 40), (13, 15, 5, 24)])
+def test_very_rank_deficient_retained_rows(gpu, d, dtype, budgets):
+    """Values that repeat 6 distinct rows under budgets that would allow many more directions: such heads take the complement's
+    basis from the projector.  Every budget of the first set keeps the finalisation to one launch; the second needs both."""
+    cfg = si.RelayConfig("fewdirs", 12, 1, 4, 2, d, 300, 8, 24, 2, dtype, "structured")
+
+    def edit(K, V, Q):
+        N = V.shape[2]
+        for h in range(V.shape[1]):
+            free = (np.arange(N) % 37 == 5) & (np.arange(N) > 200)       # a few deleted tokens keep their own value row
+            V[0, h] = np.where(free[:, None], V[0, h], V[0, h, :6][np.arange(N) % 6])
+
+    reps = _check_cfg(gpu, cfg, budgets=list(budgets), edit=edit)
+    assert any(r.r_keep <= 12 for r in reps)
+
+
 def test_rank_deficient_large_budget_uses_partial_gram_sums(gpu):
     """More than 2048 retained rows of rank-deficient values on ten heads (two plain ones among them): the certificate
     cannot settle the eight-plus deficient heads, the first eight of them get their double-precision Gram matrix as

@@ -1847,7 +1847,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     // launch with the large LDS size serves both classes instead of two launches that mostly exit at once
     const bool single = min_budget > m.d && m.N > m.d && !var.skips_basis();
     // every head leaves its eigenpairs to the leading-eigenpair kernel and none has few enough rows to need the large LDS: the second
-    // launch, 5 us with every workgroup leaving at once, is not made 
+    // launch, 5 us with every workgroup leaving at once, is not made
     // (256 tokens, budget 32: 302 -> 297 us; eight agents in lanes: 2215 -> 2074)
     const bool small_only = !single && lead_ok && !var.skips_basis() && (min_budget > FN_FEW || fn_few_floats(max(min_budget, 0), m.d) <= fn_small_floats(m.d));
     for (int cls = single ? -1 : 0; cls < (single ? 0 : small_only ? 1 : 2); ++cls) {

@@ -7,6 +7,7 @@
 // fp32.  The cosine of token j with slot t is <K_j, K_t> / (|K_j| |K_t|); 1 / |K_j| is the same for every slot, so the
 // arg-max only needs <K_j, K_t> / |K_t| (sign and order preserved), and an all-zero K_j routes to slot 0.
 #include "common.hpp"
+#include "wave_ops.hpp"
 
 namespace obf {
 
@@ -69,28 +70,50 @@ __global__ __launch_bounds__(MG_THREADS, 3) void k_mg_route_mfma(const uint16_t*
 #pragma unroll
     for (int kk = 0; kk < MG_KK; ++kk) tf[b][kk].u = p[kk * 2];
   }
-  // thread t moves 32 bytes of slot row t / 8
-  const int srow = tid >> 3, spart = tid & 7;
+  // a thread moves 2 x 16 bytes of slot row tid / 8: columns c .. c + 7 and c + 64 .. c + 71, c = 8 spart; spart is numbered so that the
+  // threads whose sparts differ in one bit are each other's mirror image of eight, or neighbours in four (single-instruction exchanges)
+  const int srow = tid >> 3, spart = (tid & 7) ^ ((tid & 4) ? 3 : 0);
   uint4 pre[2];
   auto fetch = [&](const int s0) {
-    const uint4* p = (const uint4*)(Ko + (size_t)min(s0 + srow, nk - 1) * MG_D + spart * 16);    // rows past the list: the last one again
-    pre[0] = p[0]; pre[1] = p[1];
+    const uint4* p = (const uint4*)(Ko + (size_t)min(s0 + srow, nk - 1) * MG_D + spart * 8);     // rows past the list: the last one again
+    pre[0] = p[0]; pre[1] = p[8];
   };
   auto put = [&](const int s0, const int buf) {
-    uint4* o = (uint4*)(stage[buf] + srow * MG_LDB + spart * 32);
-    o[0] = pre[0]; o[1] = pre[1];
-    float s = 0.f;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t w[4] = {pre[h].x, pre[h].y, pre[h].z, pre[h].w};
+    uint4* o = (uint4*)(stage[buf] + srow * MG_LDB + spart * 16);
+    o[0] = pre[0]; o[8] = pre[1];
+    // The squared norm is added as k_mg_inv_norm does, a lane per two columns c and c + 64 and a butterfly from the high bit down: routes
+    // between nearly equal cosines depend on it.  Column 8 spart + i: the three high bits are the thread's, exchanged by halves.
+    float q[8];
+    {
+      const uint32_t wa[4] = {pre[0].x, pre[0].y, pre[0].z, pre[0].w}, wb[4] = {pre[1].x, pre[1].y, pre[1].z, pre[1].w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float a = __uint_as_float(w[i] << 16), b = __uint_as_float(w[i] & 0xffff0000u);
-        s = fmaf(a, a, s); s = fmaf(b, b, s);
+        const float a0 = __uint_as_float(wa[i] << 16), a1 = __uint_as_float(wa[i] & 0xffff0000u);
+        const float b0 = __uint_as_float(wb[i] << 16), b1 = __uint_as_float(wb[i] & 0xffff0000u);
+        q[2 * i] = fmaf(b0, b0, a0 * a0); q[2 * i + 1] = fmaf(b1, b1, a1 * a1);
       }
     }
+    const bool p4 = (spart & 4) != 0, p2 = (spart & 2) != 0, p1 = (spart & 1) != 0;
+#define OBF_MG_EXCH(x, ctrl) __uint_as_float(OBF_DPP_MOV(__float_as_uint(x), ctrl))      /* 0x141: spart ^ 4, 0x4E: ^ 2, 0xB1: ^ 1 */
 #pragma unroll
-    for (int off = 1; off < 8; off <<= 1) s += __shfl_xor(s, off);
+    for (int i = 0; i < 4; ++i) {
+      const float keep = p4 ? q[i + 4] : q[i], give = p4 ? q[i] : q[i + 4];
+      q[i] = keep + OBF_MG_EXCH(give, 0x141);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float keep = p2 ? q[i + 2] : q[i], give = p2 ? q[i] : q[i + 2];
+      q[i] = keep + OBF_MG_EXCH(give, 0x4E);
+    }
+    float s;                                                   // column sum i = spart
+    {
+      const float keep = p1 ? q[1] : q[0], give = p1 ? q[0] : q[1];
+      s = keep + OBF_MG_EXCH(give, 0xB1);
+    }
+    s += OBF_MG_EXCH(s, 0x141);
+    s += OBF_MG_EXCH(s, 0x4E);
+    s += OBF_MG_EXCH(s, 0xB1);
+#undef OBF_MG_EXCH
     // 0 for a zero key; a slot past the list compares as not a number: never the maximum
     if (spart == 0) inv[buf][srow] = (s0 + srow >= nk) ? __uint_as_float(0x7fc00000u) : s > 0.f ? 1.0f / sqrtf(s) : 0.f;
   };
@@ -242,12 +265,12 @@ __global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restr
 // Merge.  A wave per retained slot takes the slot's tokens in ascending order and adds their weighted value rows into a running
 // sum in registers (a lane owns D / 64 columns): the order of the additions is fixed, so the result is the same on every run.  A list of
 // up to MG_LIST tokens is put in order first (every entry counts the smaller ones); a longer one is not: the head's routes are scanned
-// instead, which finds the slot's tokens in order.  Eight rows are in flight at a time.  Slots that received nothing are left as the
-// bit copies the gather wrote.  Bound by the chain offsets - list - masses - rows of a wave (nine tokens a slot here), then by the
-// pass over V: 99 us on 288 heads x 2048 tokens x 205 slots, and 7 for the lists; 247 with eight slots per wave, each wave scanning
-// all routes and waiting for every row by itself.
+// instead, which finds the slot's tokens in order.  Sixteen rows are in flight at a time.  Slots that received nothing are left as the
+// bit copies the gather wrote.  Bound by a wave's instructions per token and its chain offsets - list - masses - rows (nine tokens a
+// slot here), then by the pass over V: 77 us on 288 heads x 2048 tokens x 205 slots, and 7 for the lists; 99 with eight rows ahead and
+// every lane read waited for by itself, 157 with four slots per wave, 247 with each wave scanning all routes.
 constexpr int MG_LIST = 256;
-constexpr int MG_AHEAD = 8;
+constexpr int MG_AHEAD = 16;
 
 template <typename T, int CPL> struct LaneCols;                // CPL consecutive elements of a row
 template <> struct LaneCols<uint16_t, 2> { typedef uint32_t type; static __device__ __forceinline__ void get(uint32_t v, float (&o)[2]) { o[0] = __uint_as_float(v << 16); o[1] = __uint_as_float(v & 0xffff0000u); } };
@@ -325,7 +348,13 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V
       for (int q0 = 0; q0 < len; q0 += 64) {
         const int other = (q0 + lane < len) ? src[q0 + lane] : 0x7fffffff;
         const int n = min(64, len - q0);
-        for (int q = 0; q < n; ++q) rank += (__builtin_amdgcn_readlane(other, q) < mine) ? 1 : 0;
+        for (int q = 0; q < n; q += 8) {                       // lane reads ahead of their uses; past the end the entries are never smaller
+          int k[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) k[u] = __builtin_amdgcn_readlane(other, q + u);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) rank += (k[u] < mine) ? 1 : 0;
+        }
       }
       if (i0 + lane < len) dst[rank] = mine;
     }

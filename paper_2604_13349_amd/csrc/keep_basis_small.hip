@@ -275,17 +275,18 @@ __device__ __forceinline__ int ks_head(const T* __restrict__ Vh, const int32_t* 
 //   trail   C_ij -= L_ik L_jk^T, a tile per wave;
 //   solve   wave w owns 16 columns of A in registers: Q_k = L_kk^-1 A_k, A_i -= L_ik Q_k.  Waves 3 - 7 do it beside the next panel,
 //           waves 0 - 2 at the end (head_dim 64: waves 4 - 7 have all of it).
-// Whether the rows really are independent by the rank rule is settled there too: wave 3 solves for sixteen fixed vectors of signs z at
-// the end, whose mean |L^-1 z|^2 estimates trace(C^-1) >= 1 / lambda_min(C).  A head passes when that times trace(C) is below 1e7: then every
-// pivot in any order is above the rank threshold ((max(n, d) 2^-23)^2 lambda_max, 4e-10 of the trace at most) with a factor of 100 to
-// spare for the estimate - sixteen chi-square draws fall short of a hundredth of their mean once in 1e11 - and L^-1 A is orthonormal to
-// better than its single-precision storage.  Any other head takes the pivoted loop above, one row at a time.
+// Whether the rows really are independent by the rank rule is settled there too: waves 3 - 7 solve for the columns of the identity at the
+// end, a block of sixteen at a time, and |L^-1|_F^2 = trace(C^-1) >= 1 / lambda_min(C).  A head passes when that times trace(C) is below
+// 1e7: then every pivot in any order is at least 1e-7 of the trace, the rank threshold is (max(n, d) 2^-23)^2 lambda_max, 4e-10 of it at
+// most (the computed factor is that of C + E, |E| <= n 2^-52 trace), and L^-1 A is orthonormal to better than its single-precision
+// storage.  An estimate from sign vectors instead of the identity takes as long (those waves have nothing else to do) and misses
+// dependences whose coefficients are orthogonal to all of them.  Any other head takes the pivoted loop above, one row at a time.
 // Bound by the chain of pivots inside the panels.  288 heads, d = 128, the kernel alone: 65 us at n = 96 and 17 at n = 32; the pivoted loop
 // takes 224 and 56.
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double ks_f64x4;
 constexpr int KS_LT = 17;                // row stride of an LDS tile in doubles: operand reads (16 rows, one column) without bank conflicts
 constexpr int KS_TILE = 16 * KS_LT;
-constexpr double kCholLimit = 1.0e7;     // largest trace(C) trace(C^-1) (estimated) of a head that is settled here
+constexpr double kCholLimit = 1.0e7;     // largest trace(C) trace(C^-1) of a head that is settled here
 
 __host__ __device__ inline int ks_tile(int i, int j) { return i * (i + 1) / 2 + j; }
 
@@ -392,9 +393,10 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
       for (int r = 0; r < 4; ++r) o[4 * r * KS_LT] = acc[r];
     }
   };
-  double ss = 0.0;                                             // wave 3: squares of its solution for the sign vectors
-  // The solve for 16 right-hand sides per wave: entry r of block i is row 16 i + g + 4 r.  cb: the columns of A, < 0: the sign vectors
-  auto solve = [&](const int cb, auto&& before_step, auto&& after_last) {
+  double ss = 0.0;                                             // waves 3 - 7: squares of their columns of L^-1
+  // The solve for 16 right-hand sides per wave: entry r of block i is row 16 i + g + 4 r.  cb: the columns of A, < 0: those of the
+  // identity's block column k0, which is zero above row block k0
+  auto solve = [&](const int cb, const int k0, auto&& before_step) {
     ks_f64x4 at[NBM];
 #pragma unroll
     for (int i = 0; i < NBM; ++i)
@@ -402,12 +404,9 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
       for (int r = 0; r < 4; ++r) {
         const int row = 16 * i + g + 4 * r;
         if (cb >= 0) at[i][r] = (i < NB) ? (double)Elem<T>::load(stg + row * SLD + cb * 16 + r16) : 0.0;
-        else {
-          const uint32_t h = ((uint32_t)row * 2654435761u) ^ ((uint32_t)(r16 + 1) * 0x9e3779b9u);
-          at[i][r] = (row < n) ? (((h * 0x85ebca6bu) >> 31) ? 1.0 : -1.0) : 0.0;
-        }
+        else at[i][r] = (i == k0 && row == 16 * i + r16) ? 1.0 : 0.0;
       }
-    for (int k = 0; k < NB; ++k) {
+    for (int k = k0; k < NB; ++k) {
       before_step(k);
       const int o = r16 * KS_LT + g;
       const double* iv = Lt + ks_tile(k, k) * KS_TILE + o;
@@ -431,10 +430,9 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
         }
       } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ss = fma(q[r], q[r], ss);
+        for (int r = 0; r < 4; ++r) ss += (16 * k + g + 4 * r < n) ? q[r] * q[r] : 0.0;      // (rows past n: the padding's identity)
       }
     }
-    after_last();
   };
   const int cblk = (D == 128) ? wave : wave - 4;               // this wave's columns of A
   // Three barriers per panel for every wave, whatever it does between them: rows read - panel written - trailing tiles written.
@@ -487,20 +485,22 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
       trail(k);
       lds_barrier();
     }
-    if (cblk >= 0) solve(cblk, [](int) {}, [] {});
+    if (cblk >= 0) solve(cblk, 0, [](int) {});
   } else {
     // step k of the solve runs beside panel k + 1
-    solve(cblk >= 0 ? cblk : 0, [&](const int k) {
+    solve(cblk >= 0 ? cblk : 0, 0, [&](const int k) {
       if (k == 0) lds_barrier();                               // (the rows of panel 0 are read)
       lds_barrier();
       trail(k);
       lds_barrier();
       if (k + 1 < NB) lds_barrier();
-    }, [] {});
-    if (wave == 3) solve(-1, [](int) {}, [] {});
+    });
+    // block columns of the identity: wave w takes w - 3, and of the last three, which are the shortest, number 12 - w: eight steps at most
+#pragma unroll 1
+    for (int b = wave - 3; b < NB; b = (b < 5 && 12 - wave > b) ? 12 - wave : NB) solve(-1, b, [](int) {});
   }
-  const double est = ks_block_sum(ss, sh.red) * (1.0 / 16.0);  // (wave 3's alone)
-  return trace * est < kCholLimit;                             // false also when a pivot was not positive
+  const double inv_trace = ks_block_sum(ss, sh.red);
+  return trace * inv_trace < kCholLimit;                       // false also when a pivot was not positive
 }
 
 template <typename T, bool BIG>

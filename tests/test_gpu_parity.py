@@ -212,6 +212,27 @@ def test_nearly_dependent_retained_rows(gpu, noise):
     assert any(r.skipped == 0 for r in reps)
 
 
+@pytest.mark.parametrize("slots", [(1, 18, 22, 32), (15, 16, 31, 47)])
+def test_four_retained_rows_that_sum_to_zero(gpu, slots):
+    """One exact dependence among the retained rows, small whole numbers otherwise: the last of the four pivots is a rounding error of
+    either sign, and it is only that dependence that makes the inverse of the Gram matrix large.  (The slots of the first set have signs
+    that cancel in each of sixteen vectors of a hash once used to estimate the trace of that inverse.)"""
+    heads, B = 16, 48
+    cfg = si.RelayConfig("zerosum", 37, 1, heads, 1, 128, 300, 8, B, 2, "bf16", "structured", outlier_frac=0.0)
+
+    def edit(K, V, Q):
+        r = np.random.default_rng(sum(slots))
+        for h in range(heads):
+            A = O.attention_mass(O.decode(K[0, h], "bf16"), O.decode(Q[0, h], "bf16").reshape(-1, 128))
+            idx = O.select_topk(A, B)
+            rows = r.integers(-8, 9, (300, 128)).astype(np.float32)
+            rows[idx[slots[3]]] = -(rows[idx[slots[0]]] + rows[idx[slots[1]]] + rows[idx[slots[2]]])
+            V[0, h] = O.round_to_io(rows, "bf16")
+
+    reps = _check_cfg(gpu, cfg, edit=edit, expect_active=True)
+    assert sum(r.r_keep == B - 1 for r in reps) == heads
+
+
 @pytest.mark.parametrize("budget", [48, 300])
 def test_rank_deficient_retained_rows(gpu, budget):
     """Values that repeat 24 distinct rows (plus a few free tokens): the retained span has rank far below both the

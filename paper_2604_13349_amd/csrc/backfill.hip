@@ -1072,17 +1072,21 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     const bool direct = direct_ok && !negligible;
     if (direct) {
       float* Tg = Gg;                                            // G itself is no longer needed
+      // scaled by the power of two that brings the trace to [1, 2): squares and reciprocals of its entries then stay in the range of
+      // single precision whatever the values' own scale is (unscaled they left it for values below 1e-10 or above 1e7)
+      const int ex = min(max((int)(__float_as_uint(res2) >> 23) - 127, -126), 126);
+      const float down = __uint_as_float((uint32_t)(127 - ex) << 23);
       if (ttile) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int srow = sblk * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), t = tblk2 * 32 + l31;
-          if (srow < m && t <= srow) { Tg[srow * m + t] = ta[i]; Tg[t * m + srow] = ta[i]; }    // the upper triangle mirrors the lower one
+          if (srow < m && t <= srow) { Tg[srow * m + t] = ta[i] * down; Tg[t * m + srow] = ta[i] * down; }    // the upper triangle mirrors the lower one
         }
       }
       if (tid < d) delta[(size_t)head * d + tid] = uvec[tid];    // u = sum_j A_j v_j; the other kernel replaces it by delta
       if (tid == 0) {
         LeadJob jb;
-        jb.pending = 1; jb.m = m; jb.res2 = res2; jb.vd2 = vd2; jb.pc = pc; jb.pcr = pcr; jb.rcr = rcr; jb.pad = 0;
+        jb.pending = 1; jb.m = m; jb.res2 = res2; jb.vd2 = vd2; jb.pc = pc; jb.pcr = pcr; jb.rcr = rcr; jb.unit = __uint_as_float((uint32_t)(127 + ex) << 23);
         lead[head] = jb;
       }
       return;
@@ -1488,7 +1492,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
   const HeadState st = state[head];
   const int m = jb.m, r = st.r_keep;
   const float* Zg = mats + (size_t)head * 3 * d * d;           // [m][d] basis of the complement
-  const float* Tg = Zg + 2 * (size_t)d * d;                    // [m][m]
+  const float* Tg = Zg + 2 * (size_t)d * d;                    // [m][m], over jb.unit
   float* Rf = sm;
   float* work = sm + ((tri_refl_floats(m) + 3) & ~3);          // 16-byte aligned
   const int kq = min(rank, m);
@@ -1564,7 +1568,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
       s_k = min(rank, rankR);
       double top = 0.0;
       for (int j = 0; j < s_k; ++j) top += (double)th[j];
-      s_off = (float)(top / ((double)jb.res2 + 1e-12));
+      s_off = (float)(top * (double)jb.unit / ((double)jb.res2 + 1e-12));
     }
     __syncthreads();
     k_used = s_k;
@@ -1668,7 +1672,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, Head
       if (tid == 0) {
         double top = 0.0;
         for (int i = 0; i < k_used; ++i) top += (double)dvec[i];
-        s_off = (float)(top / ((double)jb.res2 + 1e-12));
+        s_off = (float)(top * (double)jb.unit / ((double)jb.res2 + 1e-12));
       }
       __syncthreads();
       revr = s_off;

@@ -89,10 +89,10 @@ struct HeadState {
 
 // What the finalisation hands to the leading-eigenpair kernel for a head it does not diagonalise itself.
 struct LeadJob {
-  int32_t pending;      // 1: the residual Gram matrix T (m x m, complement coordinates) waits in the head's scratch
+  int32_t pending;      // 1: the residual Gram matrix T (m x m, complement coordinates) over `unit` waits in the head's scratch
   int32_t m;
   float res2, vd2, pc, pcr, rcr;
-  int32_t pad;
+  float unit;           // power of two
 };
 
 // One chunk's statistics of the deleted values: G [d][d] (tiles on and below the diagonal), u = sum_j A_j v_j [d],

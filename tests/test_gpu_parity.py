@@ -158,6 +158,22 @@ def test_leading_eigenpairs_at_tile_edges(gpu, dtype, d, rank, iters, budgets):
     _check_cfg(gpu, cfg, budgets=budgets, max_budget=max(budgets), expect_active=True, variant=variant)
 
 
+@pytest.mark.parametrize("budget,rank,iters", [(16, 2, 0), (32, 4, 0), (115, 2, 0), (24, 10, 0), (32, 2, 3)])
+def test_offset_follows_the_scale_of_the_values(gpu, budget, rank, iters):
+    """Values times a power of two give the offset times that power, bit for bit: no step rounds differently unless a square or a
+    reciprocal of the residual Gram matrix leaves the range of single precision.  (2^36 takes its trace to 2^85 here, 2^-44 to 2^-75.)"""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    cfg = si.RelayConfig("scale", 41, 1, 4, 2, 128, 300, 8, budget, rank, "f32", "structured", outlier_frac=0.01)
+    K, V, Q = (gpu.to_dev(x, "f32") for x in si.make_cache(cfg, 0))
+    variant = Bd.make_variant(subspace_iters=iters) if iters else None
+    run = lambda v: Bd.compress_relay(K, v, Q, budget=budget, rank=rank, want_delta=True, variant=variant)["delta"]
+    ref = run(V)
+    assert bool((ref != 0).any(dim=-1).all())
+    for e in (-44, -36, 26, 36):
+        assert torch.equal(run(V * 2.0 ** e) * 2.0 ** -e, ref), f"2^{e}"
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
 @pytest.mark.parametrize("N,g,W", [(1, 1, 1), (15, 1, 17), (16, 1, 16), (17, 3, 5), (33, 1, 33), (64, 2, 16), (65, 1, 1), (257, 1, 3),
                                    (4200, 4, 40)])        # tiles of 16 tokens and rows, one and several chunks, normalisers folded apart

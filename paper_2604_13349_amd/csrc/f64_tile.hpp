@@ -15,9 +15,9 @@ struct RowPart {
   static constexpr int NV = D / 4 * (int)sizeof(T) / 16;     // 16-byte pieces
   uint4 v[NV];
   __device__ __forceinline__ void load(const T* __restrict__ row, int lane) {
-    const uint4* p = (const uint4*)(row + (lane >> 4) * (D / 4));
+    const T* p = row + (lane >> 4) * (D / 4);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = p[i];
+    for (int i = 0; i < NV; ++i) __builtin_memcpy(&v[i], p + i * (16 / (int)sizeof(T)), 16);     // one load; rows need only be aligned to their elements
   }
   __device__ __forceinline__ double at(int s) const {         // entry s; s is a compile-time constant after unrolling
     if constexpr (sizeof(T) == 2) {

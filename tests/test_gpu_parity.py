@@ -197,6 +197,28 @@ def test_scores_of_fp32_and_half_width_heads(gpu, dtype, d, N, g, W):
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_scores_of_caches_off_their_alignment(gpu, dtype, d):
+    """Keys and queries that start one element behind a 16-byte boundary: the same masses, normalisers and re-decided list."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    cfg = si.RelayConfig("offset", 43, 1, 2, 2, d, 333, 9, 40, 0, dtype, "structured", outlier_frac=0.01)
+    K, _, Q = (gpu.to_dev(x, dtype) for x in si.make_cache(cfg, 0))
+
+    def moved(x):
+        held = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+        held[1:] = x.reshape(-1)
+        return held[1:].view(x.shape)
+
+    sh, res = Bd.shape_of(K, Q), []
+    for k, q in ((K, Q), (moved(K), moved(Q))):
+        sc, lse = Bd.score(k, q)
+        idx, n_keep = Bd.select_topk(sh, sc, budget=40, max_budget=40)
+        Bd.refine_boundary(k, q, sc, lse, idx, n_keep)
+        res.append((sc, lse, idx))
+    assert all(torch.equal(a, b) for a, b in zip(*res))
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
 @pytest.mark.parametrize("N", [14, 17, 65, 129, 1023, 1024, 1025, 2050])     # pairs of tokens per wave, load batches, chunks of 1024
 def test_deleted_row_statistics_of_fp32_and_half_width_heads(gpu, dtype, d, N):
     cfg = si.RelayConfig("delstats", 13, 1, 2, 1, d, N, 4, min(12, N - 1), 2, dtype, "structured", outlier_frac=0.01)

@@ -61,83 +61,52 @@ template <> struct RowLoad<float, 2> {
   }
 };
 
+constexpr int KS_LT = 17;                // row stride of an LDS tile in doubles: operand reads (16 rows, one column) without bank conflicts
+constexpr int KS_TILE = 16 * KS_LT;
+
+__host__ __device__ inline int ks_tile(int i, int j) { return i * (i + 1) / 2 + j; }
+
 struct KsShared {
   double red[KS_WAVES];
   float xv[128], yp[4][128];         // power iteration: iterate, partial products
   double qrow[128];                  // row j of A at a step (unscaled)
   double crow[128];                  // row j of C at a step (before the loop: the diagonal of C)
   uint32_t wkey[2][2];
+  int stop;                          // the blocked factorisation leaves the head to the pivoted loop
 };
-
-// Stages 16-byte pieces of the retained rows into LDS as float, row stride d + 1.
-template <typename T, int D>
-__device__ __forceinline__ void ks_stage_rows(const T* __restrict__ Vh, const int32_t* __restrict__ id, int n, float* stg) {
-  constexpr int EPP = 16 / (int)sizeof(T);                     // elements per piece
-  constexpr int PPR = D / EPP;                                 // pieces per row
-  for (int e = threadIdx.x; e < n * PPR; e += KS_THREADS) {
-    const int i = e / PPR, pc = e - i * PPR;
-    const uint4 q = *(const uint4*)(Vh + (size_t)id[i] * D + pc * EPP);
-    float* o = stg + i * (D + 1) + pc * EPP;
-    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-    if constexpr (sizeof(T) == 2) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) { o[2 * k] = __uint_as_float(w[k] << 16); o[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u); }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = __uint_as_float(w[k]);
-    }
-  }
-}
 
 // One head.  TI = ceil(n / 16) rounded up to even, CW = d / 32.  Returns r.
 // C is stored padded to NP = 16 TI rows and columns (zero beyond n), so that every index below is an immediate.
+// Lt: the Gram matrix as ks_chol_head leaves it, 16 x 16 tiles on and below the diagonal (LDS, behind C).
 template <typename T, int TI, int CW>
 __device__ __forceinline__ int ks_head(const T* __restrict__ Vh, const int32_t* __restrict__ id, int n, float* __restrict__ bh,
-                       double* C, KsShared& sh) {
+                       double* C, const double* Lt, KsShared& sh) {
   constexpr int d = 32 * CW;
   constexpr int TJ = TI / 2;                                   // column blocks of 32 of a thread's C elements
   constexpr int NP = 16 * TI;
   const int tid = threadIdx.x, lane = tid & 63;
   const int ty = tid >> 5, tx = tid & 31;
-  float* stg = (float*)C;                                      // Gram staging [n][d + 1], before the copy of C is stored
-  float* Cf = (float*)C;                                       // [NP][NP]
+  float* Cf = (float*)C;                                       // [NP][NP], single-precision copy for the power iteration
 
-  // ---- Gram matrix: thread (ty, tx) accumulates C[ty + 16a][tx + 32b]
+  // ---- Gram matrix: thread (ty, tx) takes C[ty + 16a][tx + 32b]
   double creg[TI][TJ];
   {
+    const int tc = tx & 15;
 #pragma unroll
     for (int a = 0; a < TI; ++a)
 #pragma unroll
-      for (int b = 0; b < TJ; ++b) creg[a][b] = 0.0;
-    __syncthreads();
-    ks_stage_rows<T, d>(Vh, id, n, stg);
-    __syncthreads();
-    const float* ap[TI];
-    const float* bp[TJ];
-#pragma unroll
-    for (int a = 0; a < TI; ++a) ap[a] = stg + min(ty + 16 * a, n - 1) * (d + 1);
-#pragma unroll
-    for (int b = 0; b < TJ; ++b) bp[b] = stg + min(tx + 32 * b, n - 1) * (d + 1);
-#pragma unroll 4
-    for (int c = 0; c < d; ++c) {
-      double av[TI], bv[TJ];
-#pragma unroll
-      for (int a = 0; a < TI; ++a) av[a] = (double)ap[a][c];
-#pragma unroll
-      for (int b = 0; b < TJ; ++b) bv[b] = (double)bp[b][c];
-#pragma unroll
-      for (int a = 0; a < TI; ++a)
-#pragma unroll
-        for (int b = 0; b < TJ; ++b) creg[a][b] = fma(av[a], bv[b], creg[a][b]);
-    }
-    __syncthreads();                                           // the staging area aliases C
+      for (int b = 0; b < TJ; ++b) {
+        const int bt = 2 * b + (tx >> 4);                      // tile column
+        const int o = (a >= bt) ? ks_tile(a, bt) * KS_TILE + ty * KS_LT + tc : ks_tile(bt, a) * KS_TILE + tc * KS_LT + ty;
+        creg[a][b] = (ty + 16 * a < n && tx + 32 * b < n) ? Lt[o] : 0.0;
+      }
+    __syncthreads();                                           // the tiles are read (the copy may lie over them)
 #pragma unroll
     for (int a = 0; a < TI; ++a)
 #pragma unroll
       for (int b = 0; b < TJ; ++b) {
         const int i = ty + 16 * a, jj = tx + 32 * b;
-        if (!(i < n && jj < n)) creg[a][b] = 0.0;                // rows past n were clamped reads
-        Cf[i * NP + jj] = (float)creg[a][b];                     // single-precision copy for the power iteration
+        Cf[i * NP + jj] = (float)creg[a][b];
         if (i == jj) sh.crow[i] = creg[a][b];
       }
     __syncthreads();
@@ -281,14 +250,14 @@ __device__ __forceinline__ int ks_head(const T* __restrict__ Vh, const int32_t* 
 // most (the computed factor is that of C + E, |E| <= n 2^-52 trace), and L^-1 A is orthonormal to better than its single-precision
 // storage.  An estimate from sign vectors instead of the identity takes as long (those waves have nothing else to do) and misses
 // dependences whose coefficients are orthogonal to all of them.  Any other head takes the pivoted loop above, one row at a time.
-// Bound by the chain of pivots inside the panels.  288 heads, d = 128, the kernel alone: 65 us at n = 96 and 17 at n = 32; the pivoted loop
-// takes 224 and 56.
+// A head that will not pass is given up as early as that shows: after the first panel where two rows alone are too close (repeated
+// values), one panel after a pivot that is too small, else at the end; the pivoted loop then starts from the Gram matrix formed here.
+// Bound by the chain of pivots inside the panels.  288 heads, d = 128, 32 rows of 256 tokens and 96 of 2048: 22 and 96 us where all heads
+// pass, 44 and 178 with the heads of one layer in 36 repeating value rows, 58 and 225 with all of them.  The pivoted loop for all
+// heads, with its Gram matrix from scalar multiply-adds, took 59 and 239 (56 and 232 with repeated rows); both routes one after the other, each
+// from its own Gram matrix, 67 and 289.
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double ks_f64x4;
-constexpr int KS_LT = 17;                // row stride of an LDS tile in doubles: operand reads (16 rows, one column) without bank conflicts
-constexpr int KS_TILE = 16 * KS_LT;
 constexpr double kCholLimit = 1.0e7;     // largest trace(C) trace(C^-1) of a head that is settled here
-
-__host__ __device__ inline int ks_tile(int i, int j) { return i * (i + 1) / 2 + j; }
 
 __device__ __forceinline__ double ks_lane_f64(const double x, const int l) {
   const uint64_t u = (uint64_t)__double_as_longlong(x);
@@ -303,7 +272,7 @@ __device__ __forceinline__ void ks_untri(const int t, int& i, int& j) {
   j = t - i * (i + 1) / 2;
 }
 
-// 16 x 16 product a b^T (or with the sign of `neg`) added to acc; both operands 16 x 16 tiles in LDS
+// 16 x 16 product a b^T subtracted from acc; both operands 16 x 16 tiles in LDS
 __device__ __forceinline__ ks_f64x4 ks_mul_bt(const double* a, const double* b, const int lane, ks_f64x4 acc) {
   const int o = (lane & 15) * KS_LT + (lane >> 4);
 #pragma unroll
@@ -311,7 +280,7 @@ __device__ __forceinline__ ks_f64x4 ks_mul_bt(const double* a, const double* b, 
   return acc;
 }
 
-// LDS of a head of n rows: the rows as they are stored (row stride KS_SLD elements: 16 rows, 4 consecutive entries each, on different
+// LDS of a head of n rows: the rows as they are stored (row stride ks_row_elems: 16 rows, 4 consecutive entries each, on different
 // banks), then the tiles.
 template <typename T> __host__ __device__ constexpr int ks_row_elems(int d) { return d + 16 / (int)sizeof(T); }
 template <typename T> __host__ __device__ constexpr size_t ks_tiles_off(int nb, int d) { return (size_t)16 * nb * ks_row_elems<T>(d) * sizeof(T); }
@@ -326,7 +295,8 @@ __device__ __forceinline__ void ks_load4(const float* p, double (&o)[4]) {
   o[0] = (double)q.x; o[1] = (double)q.y; o[2] = (double)q.z; o[3] = (double)q.w;
 }
 
-// NBM: most 16-row blocks (n <= 16 NBM).  True when the head was settled: its n basis rows are in bh.  All threads call.
+// NBM: most 16-row blocks (n <= 16 NBM).  True when the head was settled: its n basis rows are in bh.  False: C is in the tiles, for ks_head.
+// All threads call.
 template <typename T, int D, int NBM>
 __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int32_t* __restrict__ id, const int n, float* __restrict__ bh,
                                              double* lds, KsShared& sh) {
@@ -337,6 +307,7 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
   const int NB = (n + 15) >> 4;
   T* stg = (T*)lds;
   double* Lt = (double*)((char*)lds + ks_tiles_off<T>(NB, D));
+  if (tid == 0) sh.stop = 0;
   {
     constexpr int EPP = 16 / (int)sizeof(T), PPR = D / EPP;
 #pragma unroll 4
@@ -348,36 +319,61 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
     }
   }
   __syncthreads();
-  double tr = 0.0;
+  // C, and the diagonal to sh.crow (past n: infinite); this thread's share of the trace
+  auto gram = [&]() -> double {
+    double tr = 0.0;
 #pragma unroll 1
-  for (int q = 0; q < GT; ++q) {
-    const int t = wave + KS_WAVES * q;
-    if (t >= NB * (NB + 1) / 2) break;
-    int i, j;
-    ks_untri(t, i, j);
-    ks_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    const T* pa = stg + (16 * i + r16) * SLD + 4 * g;
-    const T* pb = stg + (16 * j + r16) * SLD + 4 * g;
+    for (int q = 0; q < GT; ++q) {
+      const int t = wave + KS_WAVES * q;
+      if (t >= NB * (NB + 1) / 2) break;
+      int i, j;
+      ks_untri(t, i, j);
+      ks_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      const T* pa = stg + (16 * i + r16) * SLD + 4 * g;
+      const T* pb = stg + (16 * j + r16) * SLD + 4 * g;
 #pragma unroll 4
-    for (int c = 0; c < D; c += 16) {
-      double a[4], b[4];
-      ks_load4(pa + c, a);
-      ks_load4(pb + c, b);
+      for (int c = 0; c < D; c += 16) {
+        double a[4], b[4];
+        ks_load4(pa + c, a);
+        ks_load4(pb + c, b);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], acc, 0, 0, 0);
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], acc, 0, 0, 0);
+      }
+      double* o = Lt + ks_tile(i, j) * KS_TILE;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = g + 4 * r;
+        double v = acc[r];
+        if (i == j && row == r16) {
+          const bool real = 16 * i + row < n;
+          if (real) tr += v; else v = 1.0;                     // rows past n: an identity
+          sh.crow[16 * i + row] = real ? v : INFINITY;
+        }
+        o[row * KS_LT + r16] = v;
+      }
     }
-    double* o = Lt + ks_tile(i, j) * KS_TILE;
+    return tr;
+  };
+  const double trace = ks_block_sum(gram(), sh.red);           // (its barriers also publish the tiles)
+
+  // Two rows alone bound the trace of the inverse from below, by (C_ii + C_jj) / (C_ii C_jj - C_ij^2), which is at the limit over trace(C)
+  // where (C_ii - floor) (C_jj - floor) - floor^2 = C_ij^2: rows that repeat, or vanish, are seen beside the first panel.  c: C(i, j)
+  const double floor = trace * (1.0 / kCholLimit);
+  auto look_at_pairs = [&](const int i, const int j, const double (&c)[4]) {
+    const double b = sh.crow[16 * j + r16] - floor;
+    bool ok = true;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int row = g + 4 * r;
-      double v = acc[r];
-      if (i == j && row == r16) {
-        if (16 * i + row < n) tr += v; else v = 1.0;           // rows past n: an identity
-      }
-      o[row * KS_LT + r16] = v;
+      const double a = sh.crow[16 * i + g + 4 * r] - floor;
+      ok &= (i == j && g + 4 * r == r16) ? a > 0.0 : fma(a, b, -floor * floor) > c[r] * c[r];
     }
-  }
-  const double trace = ks_block_sum(tr, sh.red);               // (its barriers also publish the tiles)
+    if (!ok) sh.stop = 1;
+  };
+  auto tile_entries = [&](const int t, double (&c)[4]) {
+    const double* o = Lt + t * KS_TILE + g * KS_LT + r16;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c[r] = o[4 * r * KS_LT];
+  };
 
   // trailing tiles after panel k, a tile per wave
   auto trail = [&](const int k) {
@@ -407,7 +403,7 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
         else at[i][r] = (i == k0 && row == 16 * i + r16) ? 1.0 : 0.0;
       }
     for (int k = k0; k < NB; ++k) {
-      before_step(k);
+      if (!before_step(k)) break;
       const int o = r16 * KS_LT + g;
       const double* iv = Lt + ks_tile(k, k) * KS_TILE + o;
       ks_f64x4 b = {0.0, 0.0, 0.0, 0.0}, q = {0.0, 0.0, 0.0, 0.0};
@@ -435,7 +431,10 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
     }
   };
   const int cblk = (D == 128) ? wave : wave - 4;               // this wave's columns of A
-  // Three barriers per panel for every wave, whatever it does between them: rows read - panel written - trailing tiles written.
+  // Three barriers per panel for every wave, whatever it does between them: rows read - panel written - trailing tiles written.  At the
+  // second every wave learns whether a pair of rows, or a pivot of an earlier panel, fell below what the limit allows (1 / pivot is a
+  // lower bound of the inverse's trace; the waves beside the panels look) and leaves if one did.
+  bool stop = false;
   if (wave < 3) {
 #pragma unroll 1
     for (int k = 0; k < NB; ++k) {
@@ -482,25 +481,52 @@ __device__ __forceinline__ bool ks_chol_head(const T* __restrict__ Vh, const int
         }
       }
       lds_barrier();
+      stop = sh.stop != 0;                                     // uniform
+      if (stop) break;
       trail(k);
       lds_barrier();
     }
-    if (cblk >= 0) solve(cblk, 0, [](int) {});
+    if (cblk >= 0 && !stop) solve(cblk, 0, [](int) { return true; });
   } else {
     // step k of the solve runs beside panel k + 1
     solve(cblk >= 0 ? cblk : 0, 0, [&](const int k) {
-      if (k == 0) lds_barrier();                               // (the rows of panel 0 are read)
+      if (k == 0) {
+        double c[2][4];                                        // column block 0 changes in the panel: its tiles are fetched before
+#pragma unroll
+        for (int u = 0; u < 2; ++u) { const int i = wave - 3 + 5 * u; tile_entries(i < NB ? ks_tile(i, 0) : 0, c[u]); }
+        lds_barrier();                                         // (the rows of panel 0 are read)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) { const int i = wave - 3 + 5 * u; if (i < NB) look_at_pairs(i, 0, c[u]); }
+#pragma unroll 1
+        for (int t = wave - 3; t < NB * (NB - 1) / 2; t += 5) {
+          int i, j;
+          ks_untri(t, i, j);
+          tile_entries(ks_tile(i + 1, j + 1), c[0]);
+          look_at_pairs(i + 1, j + 1, c[0]);
+        }
+      }
       lds_barrier();
+      stop = sh.stop != 0;
+      if (stop) return false;
       trail(k);
       lds_barrier();
       if (k + 1 < NB) lds_barrier();
+      const double d = Lt[ks_tile(k, k) * KS_TILE + r16 * (KS_LT + 1)];        // 1 / square root of a pivot
+      if (16 * k + r16 < n && !(floor * d * d < 1.0)) sh.stop = 1;
+      return true;
     });
     // block columns of the identity: wave w takes w - 3, and of the last three, which are the shortest, number 12 - w: eight steps at most
 #pragma unroll 1
-    for (int b = wave - 3; b < NB; b = (b < 5 && 12 - wave > b) ? 12 - wave : NB) solve(-1, b, [](int) {});
+    for (int b = stop ? NB : wave - 3; b < NB; b = (b < 5 && 12 - wave > b) ? 12 - wave : NB) solve(-1, b, [](int) { return true; });
   }
-  const double inv_trace = ks_block_sum(ss, sh.red);
-  return trace * inv_trace < kCholLimit;                       // false also when a pivot was not positive
+  if (!stop) {
+    const double inv_trace = ks_block_sum(ss, sh.red);
+    if (trace * inv_trace < kCholLimit) return true;           // false also when a pivot was not positive
+  }
+  __syncthreads();
+  (void)gram();                                                // for the pivoted loop: the factor lies where C was
+  __syncthreads();
+  return false;
 }
 
 template <typename T, bool BIG>
@@ -513,7 +539,7 @@ __global__ __launch_bounds__(KS_THREADS, BIG ? 2 : 4) void k_bf_keep_basis_small
   const int n = n_keep[head];
   if (n > d) return;                         // heads of the general kernel
   if ((n > 96) != BIG) return;               // n > 96: larger LDS buffer and register budget, a launch of its own
-  extern __shared__ double Cs[];             // staging area of the Gram accumulation, then the single-precision copy of C
+  extern __shared__ double Cs[];             // the rows and C's tiles, or the single-precision copy of C
   __shared__ KsShared sh;
   const int n_del = N - n;
   const float* sc = scores + (size_t)head * scs;
@@ -546,15 +572,16 @@ __global__ __launch_bounds__(KS_THREADS, BIG ? 2 : 4) void k_bf_keep_basis_small
     }
     r_keep = n;
     if (!done) {
+      const double* Lt = (const double*)((const char*)Cs + ks_tiles_off<T>((n + 15) >> 4, d));
       if constexpr (BIG) {
-        r_keep = ks_head<T, 8, 4>(Vh, id, n, bh, Cs, sh);
+        r_keep = ks_head<T, 8, 4>(Vh, id, n, bh, Cs, Lt, sh);
       } else if (d == 128) {
-        if (n <= 32) r_keep = ks_head<T, 2, 4>(Vh, id, n, bh, Cs, sh);
-        else if (n <= 64) r_keep = ks_head<T, 4, 4>(Vh, id, n, bh, Cs, sh);
-        else r_keep = ks_head<T, 6, 4>(Vh, id, n, bh, Cs, sh);
+        if (n <= 32) r_keep = ks_head<T, 2, 4>(Vh, id, n, bh, Cs, Lt, sh);
+        else if (n <= 64) r_keep = ks_head<T, 4, 4>(Vh, id, n, bh, Cs, Lt, sh);
+        else r_keep = ks_head<T, 6, 4>(Vh, id, n, bh, Cs, Lt, sh);
       } else {
-        if (n <= 32) r_keep = ks_head<T, 2, 2>(Vh, id, n, bh, Cs, sh);
-        else r_keep = ks_head<T, 4, 2>(Vh, id, n, bh, Cs, sh);
+        if (n <= 32) r_keep = ks_head<T, 2, 2>(Vh, id, n, bh, Cs, Lt, sh);
+        else r_keep = ks_head<T, 4, 2>(Vh, id, n, bh, Cs, Lt, sh);
       }
     }
     active = (r_keep < d) ? 1 : 0;
@@ -571,12 +598,12 @@ __global__ __launch_bounds__(KS_THREADS, BIG ? 2 : 4) void k_bf_keep_basis_small
   }
 }
 
-// dynamic LDS of a launch whose heads keep at most nmax rows: the padded Gram matrix or the row staging of the pivoted loop, the rows and
-// the tiles of the blocked factorisation
+// dynamic LDS of a launch whose heads keep at most nmax rows: the rows and the tiles of the blocked factorisation, or the padded
+// single-precision Gram matrix of the pivoted loop
 template <typename T>
 static size_t ks_smem(size_t nmax, int d) {
   const size_t np = (nmax + 31) / 32 * 32, nb = (nmax + 15) / 16;
-  return max(max(np * np * sizeof(float), nmax * (size_t)(d + 1) * sizeof(float)),
+  return max(np * np * sizeof(float),
              ks_tiles_off<T>((int)nb, d) + nb * (nb + 1) / 2 * KS_TILE * sizeof(double));
 }
 

@@ -250,25 +250,38 @@ def test_nearly_dependent_retained_rows(gpu, noise):
     assert any(r.skipped == 0 for r in reps)
 
 
-@pytest.mark.parametrize("slots", [(1, 18, 22, 32), (15, 16, 31, 47)])
-def test_four_retained_rows_that_sum_to_zero(gpu, slots):
-    """One exact dependence among the retained rows, small whole numbers otherwise: the last of the four pivots is a rounding error of
-    either sign, and it is only that dependence that makes the inverse of the Gram matrix large.  (The slots of the first set have signs
-    that cancel in each of sixteen vectors of a hash once used to estimate the trace of that inverse.)"""
-    heads, B = 16, 48
-    cfg = si.RelayConfig("zerosum", 37, 1, heads, 1, 128, 300, 8, B, 2, "bf16", "structured", outlier_frac=0.0)
+def _zero_sum_rows(gpu, d, dtype, B, slots, heads):
+    """Small whole numbers as values, four retained rows of every head (the slots) that sum to zero."""
+    cfg = si.RelayConfig("zerosum", 37, 1, heads, 1, d, 300, 8, B, 2, dtype, "structured", outlier_frac=0.0)
 
     def edit(K, V, Q):
         r = np.random.default_rng(sum(slots))
         for h in range(heads):
-            A = O.attention_mass(O.decode(K[0, h], "bf16"), O.decode(Q[0, h], "bf16").reshape(-1, 128))
-            idx = O.select_topk(A, B)
-            rows = r.integers(-8, 9, (300, 128)).astype(np.float32)
+            idx = O.select_topk(O.attention_mass(O.decode(K[0, h], dtype), O.decode(Q[0, h], dtype).reshape(-1, d)), B)
+            rows = r.integers(-8, 9, (300, d)).astype(np.float32)
             rows[idx[slots[3]]] = -(rows[idx[slots[0]]] + rows[idx[slots[1]]] + rows[idx[slots[2]]])
-            V[0, h] = O.round_to_io(rows, "bf16")
+            V[0, h] = O.round_to_io(rows, dtype)
 
     reps = _check_cfg(gpu, cfg, edit=edit, expect_active=True)
     assert sum(r.r_keep == B - 1 for r in reps) == heads
+
+
+@pytest.mark.parametrize("slots", [(1, 18, 22, 32), (15, 16, 31, 47)])
+def test_four_retained_rows_that_sum_to_zero(gpu, slots):
+    """One exact dependence among the retained rows: the last of the four pivots is a rounding error of either sign, and it is only that
+    dependence that makes the inverse of the Gram matrix large.  (The slots of the first set have signs that cancel in each of sixteen
+    vectors of a hash once used to estimate the trace of that inverse.)"""
+    _zero_sum_rows(gpu, 128, "bf16", 48, slots, 16)
+
+
+@pytest.mark.parametrize("d,dtype,B,slots", [
+    (128, "bf16", 30, (0, 3, 7, 9)), (128, "f32", 32, (2, 5, 11, 31)),                    # met in the first and the last of two panels
+    (128, "bf16", 96, (4, 17, 50, 95)), (128, "f32", 127, (5, 40, 80, 126)), (128, "bf16", 113, (1, 2, 3, 64)),
+    (64, "f32", 63, (0, 20, 40, 62)), (64, "bf16", 17, (3, 4, 5, 16)),
+])
+def test_dependence_met_in_each_panel(gpu, d, dtype, B, slots):
+    """The blocked factorisation is left once a panel has met the dependence, with the Gram matrix formed anew for the pivoted loop."""
+    _zero_sum_rows(gpu, d, dtype, B, slots, 2)
 
 
 @pytest.mark.parametrize("budget", [48, 300])

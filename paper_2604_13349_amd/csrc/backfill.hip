@@ -708,7 +708,12 @@ __device__ __forceinline__ void fn_complement(const int r, const int d, const in
   __syncthreads();
 }
 
-template <typename T>
+// LEAD: only a few leading eigenpairs are wanted (the method itself: k = pca_rank <= TE_MAXK, no Max-P / EVR rule) and every head that needs
+// them goes to the leading-eigenpair kernel (tridiagonalisation + bisection + inverse iteration, with a register budget of its own).  At
+// every width: 288 heads of 256 tokens take 501 against 558 us at 18, 514 against 519 at 4.  Otherwise all of T is diagonalised here.
+// Two kernels, not one with both: the registers of the one route spilled in the loops of the other (Max-P or rank 20 on 288 heads of 256 tokens,
+// budgets 32 and 8: 1180 -> 1118 us and 2490 -> 2382; the method itself 302 -> 301 and 384 -> 383, 8192 tokens with 96 kept 654 -> 646).
+template <typename T, bool LEAD>
 __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int nstat, int rank,
                                                             HeadState* __restrict__ state,
                                                             const float* __restrict__ basis,
@@ -719,7 +724,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
                                                             const float* __restrict__ scores,
                                                             const int32_t* __restrict__ idx, int vflags, float evr_tau,
                                                             int scs, float* __restrict__ rot /*nullable*/,
-                                                            LeadJob* __restrict__ lead /*nullable: no leading-eigenpair kernel follows*/) {
+                                                            LeadJob* __restrict__ lead /*LEAD*/) {
   extern __shared__ float sm[];
   const int head = blockIdx.x;
   const int ld = d + 1;
@@ -740,12 +745,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
   int k_used = 0;
   const int tid = threadIdx.x;
   const bool naive = (vflags & VF_NAIVE) != 0;
-  // Only a few leading eigenpairs wanted (the method itself: k = pca_rank, no Max-P / EVR rule): the head goes to the leading-eigenpair
-  // kernel (tridiagonalisation + bisection + inverse iteration, with a register budget of its own) instead of having all of T
-  // diagonalised here.  At every width: 288 heads of 256 tokens take 501 against 558 us at 18, 514 against 519 at 4.
   const int m_span = d - st.r_keep;
-  const bool direct_ok = lead != nullptr && !(vflags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) && min(rank, m_span) >= 1 &&
-                         min(rank, m_span) <= TE_MAXK;
   const int n_few = (vflags & VF_NO_PROJECTION) ? 0 : st.n_keep;       // (without the projection r = 0 whatever n is)
   {
     // Two launches share the heads: the first has fn_small_floats(d) floats of LDS (two workgroups per CU) and takes every head that
@@ -755,12 +755,12 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     if (st.active && !naive) {
       const int mm0 = m_span + (m_span & 1);
       need = fn_few(st.r_keep, n_few, d) ? fn_few_floats(st.r_keep, d) : m_span * ld;
-      if (!direct_ok) need = max(need, 2 * mm0 * (mm0 + 1));
+      if (!LEAD) need = max(need, 2 * mm0 * (mm0 + 1));
     }
     const int big = need > fn_small_floats(d);
     if (cls >= 0 && big != cls) return;
   }
-  if (lead && tid == 0) lead[head].pending = 0;
+  if (LEAD && tid == 0) lead[head].pending = 0;
 
   if (st.active && naive) {
     // Naive Aggregation (App. D): the plain mean of the deleted value rows, none of Eq. 3-6
@@ -1069,8 +1069,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     pcr = fmaxf(vd2 - res2, 0.f) / (vd2 + 1e-12f);
     const bool negligible = !(res2 > kRcrSkip * vd2) || m <= 0;
 
-    const bool direct = direct_ok && !negligible;
-    if (direct) {
+    if (LEAD && !negligible) {
       float* Tg = Gg;                                            // G itself is no longer needed
       // scaled by the power of two that brings the trace to [1, 2): squares and reciprocals of its entries then stay in the range of
       // single precision whatever the values' own scale is (unscaled they left it for values below 1e-10 or above 1e7)
@@ -1091,7 +1090,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
       }
       return;
     }
-    if (!negligible) {
+    if constexpr (!LEAD) if (!negligible) {
       U = (2 * mm * lt <= fn_small_floats(d)) ? sm + mm * lt : sm + d * ld;   // W next to T, or in the second buffer of the large launch
       if (ttile) {
 #pragma unroll
@@ -1773,7 +1772,8 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
   once_per_device(attr_mu, attr_seen, [] {
     (void)hipFuncSetAttribute((const void*)k_bf_keep_basis<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 128 * 8);
     (void)hipFuncSetAttribute((const void*)k_bf_keep_gram_part<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 128 * 8);
-    (void)hipFuncSetAttribute((const void*)k_bf_finalize<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 129 * 4);
+    (void)hipFuncSetAttribute((const void*)k_bf_finalize<T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 129 * 4);
+    (void)hipFuncSetAttribute((const void*)k_bf_finalize<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 129 * 4);
     (void)hipFuncSetAttribute((const void*)k_bf_lead<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)(sizeof(float) * lead_lds_floats(128, TE_MAXK, 128)));
   });
@@ -1856,11 +1856,14 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     const bool small_only = !single && lead_ok && !var.skips_basis() && (min_budget > FN_FEW || fn_few_floats(max(min_budget, 0), m.d) <= fn_small_floats(m.d));
     for (int cls = single ? -1 : 0; cls < (single ? 0 : small_only ? 1 : 2); ++cls) {
       const size_t lds = (cls == 0) ? sizeof(float) * (size_t)fn_small_floats(m.d) : 2 * one;
-      hipLaunchKernelGGL(k_bf_finalize<T>, dim3(m.heads), dim3(FN_THREADS), lds, st, m.N, m.d,
-                         w.nstat, rank, state, basis, gram_part, mats, delta, delta_out, diag,
-                         (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, cls, scores, idx,
-                         var.flags, var.evr_tau, m.scs, (max_budget < m.d && rank > 0) ? (float*)(ws + w.rot) : (float*)nullptr,
-                         lead);
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(m.heads), dim3(FN_THREADS), lds, st, m.N, m.d,
+                           w.nstat, rank, state, basis, gram_part, mats, delta, delta_out, diag,
+                           (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, cls, scores, idx,
+                           var.flags, var.evr_tau, m.scs, (max_budget < m.d && rank > 0) ? (float*)(ws + w.rot) : (float*)nullptr,
+                           lead);
+      };
+      if (lead) go(k_bf_finalize<T, true>); else go(k_bf_finalize<T, false>);
     }
     if (check_launch("backfill finalize") != OBF_OK) return OBF_ERR_HIP;
     if (lead) {

@@ -246,10 +246,13 @@ __device__ __forceinline__ int ks_head(const T* __restrict__ Vh, const int32_t* 
 //           waves 0 - 2 at the end (head_dim 64: waves 4 - 7 have all of it).
 // Whether the rows really are independent by the rank rule is settled there too: waves 3 - 7 solve for the columns of the identity at the
 // end, a block of sixteen at a time, and |L^-1|_F^2 = trace(C^-1) >= 1 / lambda_min(C).  A head passes when that times trace(C) is below
-// 1e7: then every pivot in any order is at least 1e-7 of the trace, the rank threshold is (max(n, d) 2^-23)^2 lambda_max, 4e-10 of it at
-// most (the computed factor is that of C + E, |E| <= n 2^-52 trace), and L^-1 A is orthonormal to better than its single-precision
-// storage.  An estimate from sign vectors instead of the identity takes as long (those waves have nothing else to do) and misses
-// dependences whose coefficients are orthogonal to all of them.  Any other head takes the pivoted loop above, one row at a time.
+// 1e9: then every pivot in any order is at least 1e-9 of the trace, the rank threshold is (max(n, d) 2^-23)^2 lambda_max, 2.4e-10 of it at
+// most (the computed factor is that of C + E, |E| <= n 2^-52 trace), and L^-1 A is as far from orthonormal as the pivoted loop's rows are
+// (4e-9 at the limit, their rounding to single precision 2.5e-8).  An estimate from sign vectors instead of the identity takes as long
+// (those waves have nothing else to do) and misses dependences whose coefficients are orthogonal to all of them.  Any other head takes
+// the pivoted loop above, one row at a time.  Heads of n close to d are the ones that come near the limit: at 1e7 half of those of 127 rows
+// and nine tenths of those of 128 were given up at the end (288 heads of 700 tokens, basis: 291 us at 127 and 448 at 128; 131 and 284 with
+// 1e9; the pivoted loop alone 368 and 365).
 // A head that will not pass is given up as early as that shows: after the first panel where two rows alone are too close (repeated
 // values), one panel after a pivot that is too small, else at the end; the pivoted loop then starts from the Gram matrix formed here.
 // Bound by the chain of pivots inside the panels.  288 heads, d = 128, 32 rows of 256 tokens and 96 of 2048: 22 and 96 us where all heads
@@ -257,7 +260,7 @@ __device__ __forceinline__ int ks_head(const T* __restrict__ Vh, const int32_t* 
 // heads, with its Gram matrix from scalar multiply-adds, took 59 and 239 (56 and 232 with repeated rows); both routes one after the other, each
 // from its own Gram matrix, 67 and 289.
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double ks_f64x4;
-constexpr double kCholLimit = 1.0e7;     // largest trace(C) trace(C^-1) of a head that is settled here
+constexpr double kCholLimit = 1.0e9;     // largest trace(C) trace(C^-1) of a head that is settled here
 
 __device__ __forceinline__ double ks_lane_f64(const double x, const int l) {
   const uint64_t u = (uint64_t)__double_as_longlong(x);

@@ -237,9 +237,9 @@ def test_small_budget_basis_block_edges(gpu, d, dtype, budgets):
 
 @pytest.mark.parametrize("noise", [1e-1, 1e-2])
 def test_nearly_dependent_retained_rows(gpu, noise):
-    """Retained rows that repeat 20 distinct ones up to a small difference: trace(C) trace(C^-1) is about 2e3 / noise^2, so the blocked
-    factorisation settles the first case (limit 1e7) and hands the second to the pivoted loop.  (Differences of 1e-3 bring singular values
-    within a decade of the rank rule's threshold, where the checks compare nothing.)"""
+    """Retained rows that repeat 20 distinct ones up to a small difference: trace(C) trace(C^-1) is about 2e3 / noise^2, under the blocked
+    factorisation's limit of 1e9.  (Differences of 1e-3 bring singular values within a decade of the rank rule's threshold, where the
+    checks compare nothing.)"""
     cfg = si.RelayConfig("nearlydep", 31, 1, 3, 1, 128, 600, 8, 40, 2, "f32", "structured", outlier_frac=0.0)
     def edit(K, V, Q):
         r = np.random.default_rng(5)
@@ -248,6 +248,28 @@ def test_nearly_dependent_retained_rows(gpu, noise):
             V[0, h] = base[np.arange(600) % 20] + noise * r.standard_normal((600, 128)).astype(np.float32)
     reps = _check_cfg(gpu, cfg, edit=edit)
     assert any(r.skipped == 0 for r in reps)
+
+
+def test_retained_rows_past_the_conditioning_limit(gpu):
+    """The same at 1.2e-3: 1.4e9, with no pair of rows and no pivot that shows it, so the head is handed over at the very end.  The smallest
+    singular value is 1e-4 of the largest, seven times the rank rule's threshold; the offset is bound as everywhere."""
+    cfg = si.RelayConfig("pastlimit", 31, 1, 3, 1, 128, 600, 8, 40, 2, "f32", "structured", outlier_frac=0.0)
+    K, V, Q = si.make_cache(cfg, 0, threads=8)
+    r = np.random.default_rng(5)
+    for h in range(3):
+        V[0, h] = V[0, h, :20][np.arange(600) % 20] + 1.2e-3 * r.standard_normal((600, 128)).astype(np.float32)
+    out = gpu.run_fused(cfg, K, V, Q, budgets=[40] * 3)
+    for h in range(3):
+        ref = O.compress_head(K[0, h], V[0, h], Q[0, h:h + 1], 40, 2, "f32")
+        if not np.array_equal(out["idx"][0, h], ref.idx):
+            continue
+        v = O.decode(V[0, h], "f32")[ref.idx]
+        w = np.linalg.eigvalsh(v @ v.T)
+        assert w.sum() * (1 / w).sum() > 1.1e9 and np.sqrt(w[0] / w[-1]) > 5 * 128 * 2.0 ** -23
+        assert out["diag"][0, h]["r_keep"] == ref.diag.r_keep == 40
+        if not ref.diag.skipped:
+            err = np.linalg.norm(out["delta"][0, h].astype(np.float64) - ref.diag.delta)
+            assert err <= 2e-3 * parity.gap_factor(ref.diag) * np.linalg.norm(ref.diag.delta)
 
 
 def _zero_sum_rows(gpu, d, dtype, B, slots, heads):

@@ -9,6 +9,8 @@ sample of the same workload.
 from __future__ import annotations
 
 import argparse
+import glob
+import hashlib
 import json
 import os
 import sys
@@ -20,6 +22,16 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "compressed KV-head-tokens/s + achieved HBM GB/s, Qwen3-8B-shape 8K cache"
+
+
+def sources_id() -> str:
+    """Names the kernel sources that counted bytes belong to."""
+    h = hashlib.sha256()
+    csrc = os.path.join(ROOT, "paper_2604_13349_amd", "csrc")
+    for path in sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "*.hpp"))):
+        with open(path, "rb") as f:
+            h.update(os.path.basename(path).encode() + b"\0" + f.read())
+    return h.hexdigest()[:16]
 
 
 def stage_bytes(stage: str, cfg, budgets, active_heads: int) -> float:
@@ -205,17 +217,19 @@ def main() -> int:
         ach = kbytes / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else 0.0
         pb = sum(path_bytes(cfg_, b, active) for b in buds)
         step_s = r["elapsed"] / steps
-        traffic = None
+        traffic = None                    # counted bytes of these very kernels, or none
         tfile = os.path.join(ROOT, "profiles", f"traffic_config{tname}.json")
         if os.path.exists(tfile):
             with open(tfile) as f:
-                traffic = json.load(f).get(r["dominant"])
+                counted = json.load(f)
+            if counted.get("_sources") == sources_id():
+                traffic = counted.get(r["dominant"])
         roof = {"bound": "hbm", "scope": "dominant kernel only (the whole path is the 'path' object)", "kernel": r["dominant"],
                 "achieved": round(ach, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "kernel_ms": round(avg_ms, 4), "kernel_bytes": kbytes,
                 "stage_ms": {k: round(v, 4) for k, v in r["stage_ms"].items()}}
         if r["dominant"] in ("keep_basis", "finalize", "select", "keep_cert"):
-            roof["note"] = ("a per-head sequential factorisation / bisection: bound by the latency of its dependent steps, "
+            roof["note"] = ("a per-head sequential factorisation or selection: bound by the latency of its dependent steps, "
                             "the HBM fraction only says how far from streaming it is")
         path = {"bytes": pb, "GBps": round(pb / step_s / 1e9, 2), "frac": round(pb / step_s / 1e9 / HBM_PEAK_GBS, 4),
                 "target_frac": 0.60, "unit": "GB/s of algorithmic bytes (K, Q once; retained rows read and written; V where the back-fill is active)"}

@@ -1837,7 +1837,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
   {
     ProfScope prof_(ST_FINALIZE, st);
     const size_t one = sizeof(float) * m.d * (m.d + 1);
-    // Heads that only need a few leading eigenpairs of a wide enough complement go to k_bf_lead after the finalisation
+    // Heads that only need a few leading eigenpairs go to k_bf_lead after the finalisation
     // (not under the Max-P / EVR rules, which need the whole spectrum).  Its LDS holds the reflectors packed, 52 KB for up to four
     // directions at head_dim 128, so that complements of every width take that route with two workgroups per CU.
     // The fast path of App. H lives in that kernel too and then takes every head that reaches Eq. 4.
@@ -1852,7 +1852,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     const bool single = min_budget > m.d && m.N > m.d && !var.skips_basis();
     // every head leaves its eigenpairs to the leading-eigenpair kernel and none has few enough rows to need the large LDS: the second
     // launch, 5 us with every workgroup leaving at once, is not made
-    // (256 tokens, budget 32: 302 -> 297 us; eight agents in lanes: 2215 -> 2074)
+    // (256 tokens, budget 32: 302 -> 297 us; a batch of twelve samples: 2215 -> 2074)
     const bool small_only = !single && lead_ok && !var.skips_basis() && (min_budget > FN_FEW || fn_few_floats(max(min_budget, 0), m.d) <= fn_small_floats(m.d));
     for (int cls = single ? -1 : 0; cls < (single ? 0 : small_only ? 1 : 2); ++cls) {
       const size_t lds = (cls == 0) ? sizeof(float) * (size_t)fn_small_floats(m.d) : 2 * one;

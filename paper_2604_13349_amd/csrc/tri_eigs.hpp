@@ -454,7 +454,9 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
       {
         // unit length (scaled by the largest magnitude first, so that the squares cannot overflow); this also clears what
         // is left of the start vector in blocks that S decouples from this eigenvalue (an exactly zero sub-diagonal
-        // entry): some twenty orders of magnitude down, exact zeros in exact arithmetic
+        // entry), exact zeros in exact arithmetic: after two solves the square of 1e-7 over the relative gap to that block's
+        // eigenvalues, 1e-14 where the gap is of the order of the spectrum's extent (a smaller gap leaves more than the bound
+        // below, but less than the rounding of T itself does to such a vector)
         const float big = scal[8 + wave];
         const float sc = (big > 0.f && big < INFINITY) ? 1.f / big : 1.f;
         w0 *= sc; w1 *= sc;

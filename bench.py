@@ -208,6 +208,8 @@ def main() -> int:
     head_tokens = cfg.n_heads * cfg.n_tokens * len(calls)
     value = head_tokens / (elapsed / args.steps)
 
+    plain = variant is None and sink is None and not layerwise and gen_rows is None and cfg.agents == 1
+
     def roofline_of(r, cfg_, buds, active, steps, tname):
         """The dominant kernel against the HBM roofline (its algorithmic bytes over its own average launch time) and, as a
         separate object, the whole path (all algorithmic bytes of a step over the step time)."""
@@ -217,12 +219,12 @@ def main() -> int:
         ach = kbytes / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else 0.0
         pb = sum(path_bytes(cfg_, b, active) for b in buds)
         step_s = r["elapsed"] / steps
-        traffic = None                    # counted bytes of these very kernels, or none
+        traffic = None                    # counted bytes of these very kernels on the plain call, or none
         tfile = os.path.join(ROOT, "profiles", f"traffic_config{tname}.json")
         if os.path.exists(tfile):
             with open(tfile) as f:
                 counted = json.load(f)
-            if counted.get("_sources") == sources_id():
+            if plain and not args.layers and counted.get("_sources") == sources_id():
                 traffic = counted.get(r["dominant"])
         roof = {"bound": "hbm", "scope": "dominant kernel only (the whole path is the 'path' object)", "kernel": r["dominant"],
                 "achieved": round(ach, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
@@ -242,7 +244,6 @@ def main() -> int:
     # The full Orthogonal BackFill path (budget below head_dim, every head injects), measured in the same run: the
     # same resident cache with budget 96 (shadow of this config) and the paper's own shape (N = 256, budget 32, rank 2).
     full_path = []
-    plain = variant is None and sink is None and not layerwise and gen_rows is None and cfg.agents == 1
     if args.full_path and plain and cfg.name in ("3", "2", "4"):
         shadows = [(si.CONFIGS[cfg.name + "s"], calls[0])]
         pc = si.CONFIGS["paper"]

@@ -18,7 +18,7 @@
 // The basis kernels may run on a second stream beside the gather and the statistics pass (small budgets).
 #include "common.hpp"
 #include "wave_ops.hpp"
-#include "tri_eigs.hpp"
+#include "backfill_emit.hpp"
 
 namespace obf {
 
@@ -26,9 +26,6 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int KB_THREADS = 256;
 constexpr int KB_WAVES = KB_THREADS / 64;
-constexpr double kRankEps = 1.1920928955078125e-07;   // 2^-23, the rank rule's epsilon
-constexpr float kRcrSkip = 1.0e-6f;                   // "||R||_F negligible": ||R||^2 <= 1e-6 ||V_del||^2
-constexpr float kEigFloor = 1.0e-6f;                  // resolution of the fp32 residual Gram (relative)
 
 // ------------------------------------------------------------------------------------------------
 // small block helpers (KB_THREADS threads)
@@ -537,61 +534,6 @@ __device__ __forceinline__ bool jacobi_lead_rows_done(const float* T, int lt, in
   return *ok != 0;
 }
 
-// Outputs of one head, shared by the two kernels that can finish it: delta, the head state, the diagnostics, and Eq. 7 on
-// the retained rows.  uvec (LDS) holds delta when the head is not skipped.  NT threads, all must call.
-template <typename T, int NT>
-__device__ __forceinline__ void fn_emit(const int head, const int d, const int rank, HeadState st, const int skipped,
-                                        const int k_used, const float rcr, const float ivn, const float pcr, const float pc,
-                                        const float revr, const float fast_err, const float* uvec,
-                                        HeadState* __restrict__ state,
-                                        float* __restrict__ delta, float* __restrict__ delta_out, obf_diag_t* __restrict__ diag,
-                                        T* __restrict__ V_out, const int max_budget, const float* __restrict__ scores,
-                                        const int32_t* __restrict__ idx, const int vflags, const int scs) {
-  const int tid = threadIdx.x;
-  if (tid < d) {
-    const float v = skipped ? 0.f : uvec[tid];
-    delta[(size_t)head * d + tid] = v;
-    if (delta_out) delta_out[(size_t)head * d + tid] = v;
-  }
-  if (tid == 0) {
-    st.active = skipped ? 0 : 1;
-    st.k_used = k_used; st.rcr = rcr; st.ivn = ivn;
-    state[head] = st;
-    if (diag) {
-      obf_diag_t dg;
-      dg.n_keep = st.n_keep; dg.r_keep = st.r_keep; dg.k_used = k_used; dg.skipped = skipped;
-      dg.a_keep = (float)st.a_keep; dg.a_del = (float)st.a_del; dg.rcr = rcr; dg.ivn = ivn;
-      // a head whose retained span is all of R^d has its deleted values entirely inside it
-      dg.pcr = (rank > 0 && st.n_keep > 0 && st.n_del > 0 && st.r_keep >= d) ? 1.f : pcr;
-      dg.pc = pc; dg.revr = revr;
-      dg.dr = (float)(st.a_del / (st.a_keep + kEps));
-      dg.fast_err = fast_err;
-      dg.select_flags = 0;                                     // the fused call fills it in afterwards
-      diag[head] = dg;
-    }
-  }
-  // Eq. 7: the one offset is added to every retained value row (rounded once to the storage type); under Attn-inject
-  // (App. D) row t receives n_keep A_t / (a_keep + eps) times the offset instead
-  if (!skipped && V_out) {
-    const int total = st.n_keep * d;
-    T* base = V_out + (size_t)head * max_budget * d;
-    if (vflags & VF_ATTN_INJECT) {
-      const float per_mass = (float)((double)st.n_keep / (st.a_keep + kEps));
-      const float* sc = scores + (size_t)head * scs;
-      const int32_t* id = idx + (size_t)head * max_budget;
-      for (int e = tid; e < total; e += NT) {
-        T* p = base + e;
-        Elem<T>::store(p, fmaf(per_mass * sc[id[e / d]], uvec[e % d], Elem<T>::load(p)));
-      }
-    } else {
-      for (int e = tid; e < total; e += NT) {
-        T* p = base + e;
-        Elem<T>::store(p, Elem<T>::load(p) + uvec[e % d]);
-      }
-    }
-  }
-}
-
 // ---- An orthonormal basis Z of the complement of at most FN_FEW orthonormal rows Q [r][d], m = d - r.
 // Householder reconstruction (Ballard, Demmel, Grigori, Jacquelin, Nguyen, Solomonik: "Reconstructing Householder vectors from
 // tall-skinny QR"): with Q1 = Q[:, :r], Q2 = Q[:, r:] and signs S = diag(+-1), M = Q1^T - S factors without pivoting when
@@ -708,12 +650,7 @@ __device__ __forceinline__ void fn_complement(const int r, const int d, const in
   __syncthreads();
 }
 
-// LEAD: only a few leading eigenpairs are wanted (the method itself: k = pca_rank <= TE_MAXK, no Max-P / EVR rule) and every head that needs
-// them goes to the leading-eigenpair kernel (tridiagonalisation + bisection + inverse iteration, with a register budget of its own).  At
-// every width: 288 heads of 256 tokens take 501 against 558 us at 18, 514 against 519 at 4.  Otherwise all of T is diagonalised here.
-// Two kernels, not one with both: the registers of the one route spilled in the loops of the other (Max-P or rank 20 on 288 heads of 256 tokens,
-// budgets 32 and 8: 1180 -> 1118 us and 2490 -> 2382; the method itself 302 -> 301 and 384 -> 383, 8192 tokens with 96 kept 654 -> 646).
-template <typename T, bool LEAD>
+template <typename T>
 __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int nstat, int rank,
                                                             HeadState* __restrict__ state,
                                                             const float* __restrict__ basis,
@@ -723,8 +660,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
                                                             T* __restrict__ V_out, int max_budget, int cls,
                                                             const float* __restrict__ scores,
                                                             const int32_t* __restrict__ idx, int vflags, float evr_tau,
-                                                            int scs, float* __restrict__ rot /*nullable*/,
-                                                            LeadJob* __restrict__ lead /*LEAD*/) {
+                                                            int scs, float* __restrict__ rot /*nullable*/) {
   extern __shared__ float sm[];
   const int head = blockIdx.x;
   const int ld = d + 1;
@@ -755,12 +691,11 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     if (st.active && !naive) {
       const int mm0 = m_span + (m_span & 1);
       need = fn_few(st.r_keep, n_few, d) ? fn_few_floats(st.r_keep, d) : m_span * ld;
-      if (!LEAD) need = max(need, 2 * mm0 * (mm0 + 1));
+      need = max(need, 2 * mm0 * (mm0 + 1));
     }
     const int big = need > fn_small_floats(d);
     if (cls >= 0 && big != cls) return;
   }
-  if (LEAD && tid == 0) lead[head].pending = 0;
 
   if (st.active && naive) {
     // Naive Aggregation (App. D): the plain mean of the deleted value rows, none of Eq. 3-6
@@ -1069,28 +1004,7 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
     pcr = fmaxf(vd2 - res2, 0.f) / (vd2 + 1e-12f);
     const bool negligible = !(res2 > kRcrSkip * vd2) || m <= 0;
 
-    if (LEAD && !negligible) {
-      float* Tg = Gg;                                            // G itself is no longer needed
-      // scaled by the power of two that brings the trace to [1, 2): squares and reciprocals of its entries then stay in the range of
-      // single precision whatever the values' own scale is (unscaled they left it for values below 1e-10 or above 1e7)
-      const int ex = min(max((int)(__float_as_uint(res2) >> 23) - 127, -126), 126);
-      const float down = __uint_as_float((uint32_t)(127 - ex) << 23);
-      if (ttile) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int srow = sblk * 32 + (i >> 2) * 8 + lh * 4 + (i & 3), t = tblk2 * 32 + l31;
-          if (srow < m && t <= srow) { Tg[srow * m + t] = ta[i] * down; Tg[t * m + srow] = ta[i] * down; }    // the upper triangle mirrors the lower one
-        }
-      }
-      if (tid < d) delta[(size_t)head * d + tid] = uvec[tid];    // u = sum_j A_j v_j; the other kernel replaces it by delta
-      if (tid == 0) {
-        LeadJob jb;
-        jb.pending = 1; jb.m = m; jb.res2 = res2; jb.vd2 = vd2; jb.pc = pc; jb.pcr = pcr; jb.rcr = rcr; jb.unit = __uint_as_float((uint32_t)(127 + ex) << 23);
-        lead[head] = jb;
-      }
-      return;
-    }
-    if constexpr (!LEAD) if (!negligible) {
+    if (!negligible) {
       U = (2 * mm * lt <= fn_small_floats(d)) ? sm + mm * lt : sm + d * ld;   // W next to T, or in the second buffer of the large launch
       if (ttile) {
 #pragma unroll
@@ -1415,321 +1329,6 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
 }
 
 // ------------------------------------------------------------------------------------------------
-// orth of App. H's iteration for one wave: Gram-Schmidt over the kk <= KQ rows of Yb (128 floats apart, m entries) in order, two passes
-// each; a row left with at most 1e-5 of the first row's norm depends on the rows before it and is dropped.  The kept rows go to Ya;
-// returns their number.  All rows are in registers, a pass takes the coefficients on all earlier rows at once (a dropped row is zero).
-template <int KQ>
-__device__ __forceinline__ int lead_orth(float* __restrict__ Ya, const float* __restrict__ Yb, const int m, const int kk) {
-  const int lane = threadIdx.x & 63;
-  float x0[KQ], x1[KQ];
-#pragma unroll
-  for (int i = 0; i < KQ; ++i) {
-    x0[i] = (i < kk && lane < m) ? Yb[i * 128 + lane] : 0.f;
-    x1[i] = (i < kk && lane + 64 < m) ? Yb[i * 128 + lane + 64] : 0.f;
-  }
-  int nk = 0;
-  float first = -1.f;
-#pragma unroll
-  for (int i = 0; i < KQ; ++i) {
-    if (i < kk) {
-#pragma unroll
-      for (int pass = 0; pass < 2; ++pass) {
-        float g[KQ + 2];
-#pragma unroll
-        for (int j = 0; j < i; j += 3) {
-          const int j1 = (j + 1 < i) ? j + 1 : j, j2 = (j + 2 < i) ? j + 2 : j;
-          te_wave_sum3(fmaf(x0[i], x0[j], x1[i] * x1[j]), fmaf(x0[i], x0[j1], x1[i] * x1[j1]), fmaf(x0[i], x0[j2], x1[i] * x1[j2]),
-                       g[j], g[j + 1], g[j + 2]);
-        }
-#pragma unroll
-        for (int j = 0; j < i; ++j) { x0[i] = fmaf(-g[j], x0[j], x0[i]); x1[i] = fmaf(-g[j], x1[j], x1[i]); }
-      }
-      const float nn = sqrtf(te_wave_sum(fmaf(x0[i], x0[i], x1[i] * x1[i])));
-      if (first < 0.f) first = nn;
-      const bool kept = first > 0.f && nn > 1e-5f * first;
-      const float rn = kept ? 1.f / nn : 0.f;
-      x0[i] = kept ? x0[i] * rn : 0.f; x1[i] = kept ? x1[i] * rn : 0.f;
-      if (kept) {
-        if (lane < m) Ya[nk * 128 + lane] = x0[i];
-        if (lane + 64 < m) Ya[nk * 128 + lane + 64] = x1[i];
-        ++nk;
-      }
-    }
-  }
-  return nk;
-}
-
-// ------------------------------------------------------------------------------------------------
-// The heads the finalisation handed over: leading eigenpairs of T by the direct route, then Eq. 4-7 as there.
-// iters > 0 selects the fast path of App. H instead: `iters` steps of C <- orth(C G) from a fixed orthonormal start,
-// carried out in complement coordinates (G = Z^T T Z, so a row c of C is followed as its coordinates c Z^T and
-// C G becomes Y T); the direct route then runs only when diagnostics are wanted, to report how far the fast path's
-// Delta is from it.
-// Floats of dynamic LDS of that kernel for complements up to mmax wide and kq directions; d != 0: the fast path at that head_dim
-// (start rows behind the scratch of the direct route; the rows, their images and the partial sums take 128 floats a row).
-inline size_t lead_lds_floats(int mmax, int kq, int d) {
-  const size_t mat = (size_t)tri_refl_floats(mmax) + 4, direct = tri_work_floats(mmax, kq) + (size_t)kq * d;
-  const size_t fast = d ? (size_t)128 * (2 * kq + 4 * (kq < 4 ? kq : 4)) : 0;
-  return mat + (direct > fast ? direct : fast);
-}
-
-template <typename T>
-__global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int d, int rank, HeadState* __restrict__ state, float* __restrict__ mats,
-                                                          float* __restrict__ delta, float* __restrict__ delta_out,
-                                                          obf_diag_t* __restrict__ diag, T* __restrict__ V_out, int max_budget,
-                                                          const float* __restrict__ scores, const int32_t* __restrict__ idx,
-                                                          int vflags, int scs, const LeadJob* __restrict__ lead, int iters) {
-  extern __shared__ float sm[];
-  __shared__ float uvec[128], rbar[128], dvec[16], dcomp[128], dex[128];
-  __shared__ int s_k;
-  __shared__ float s_off;
-  const int head = blockIdx.x;
-  const LeadJob jb = lead[head];
-  if (!jb.pending) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const HeadState st = state[head];
-  const int m = jb.m, r = st.r_keep;
-  const float* Zg = mats + (size_t)head * 3 * d * d;           // [m][d] basis of the complement
-  const float* Tg = Zg + 2 * (size_t)d * d;                    // [m][m], over jb.unit
-  float* Rf = sm;
-  float* work = sm + ((tri_refl_floats(m) + 3) & ~3);          // 16-byte aligned
-  const int kq = min(rank, m);
-  // y = Z u (Eq. 4 in complement coordinates), a wave per row, four rows' loads in flight (the first four beside u's)
-  float z0[4], z1[4];
-  auto fetch_rows = [&](const int t0) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int t = min(t0 + q * TE_WAVES, m - 1);
-      z0[q] = (lane < d) ? Zg[(size_t)t * d + lane] : 0.f;
-      z1[q] = (lane + 64 < d) ? Zg[(size_t)t * d + lane + 64] : 0.f;
-    }
-  };
-  fetch_rows(wave);
-  if (tid < d) uvec[tid] = delta[(size_t)head * d + tid];      // u
-  __syncthreads();
-  {
-    const float u0 = (lane < d) ? uvec[lane] : 0.f, u1 = (lane + 64 < d) ? uvec[lane + 64] : 0.f;
-    for (int t0 = wave; t0 < m; t0 += 4 * TE_WAVES) {
-      float sy[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sy[q] = fmaf(z1[q], u1, z0[q] * u0);
-      fetch_rows(t0 + 4 * TE_WAVES);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float y = te_wave_sum(sy[q]);
-        if (lane == 0 && t0 + q * TE_WAVES < m) rbar[t0 + q * TE_WAVES] = y;
-      }
-    }
-  }
-  // Delta in complement coordinates (times a_del + eps) from kk orthonormal rows, `cs` floats apart in Cb: Eq. 5
-  auto project = [&](const float* Cb, const int cs, const int kk) {
-    for (int v = wave; v < kk; v += TE_WAVES) {
-      float sc = (lane < m) ? rbar[lane] * Cb[v * cs + lane] : 0.f;
-      if (lane + 64 < m) sc = fmaf(rbar[lane + 64], Cb[v * cs + lane + 64], sc);
-      sc = te_wave_sum(sc);
-      if (lane == 0) dvec[v] = sc;
-    }
-    __syncthreads();
-    if (tid < m) {
-      float sd = 0.f;
-      for (int i = 0; i < kk; ++i) sd = fmaf(dvec[i], Cb[i * cs + tid], sd);
-      dcomp[tid] = sd;
-    }
-    __syncthreads();
-  };
-  // Per-token alternative (App. D): the subspace goes to the head's second scratch matrix in head_dim coordinates
-  // (row i: sum_t Cb[i][t] Z[t][:]) for the kernel that forms the per-slot directions.
-  auto export_basis = [&](const float* Cb, const int cs, const int kk) {
-    if (!(vflags & VF_PER_TOKEN)) return;
-    float* Cg = mats + ((size_t)head * 3 + 1) * d * d;
-    for (int e = tid; e < kk * d; e += TE_THREADS) {
-      const int i = e / d, c = e - i * d;
-      float s = 0.f;
-      for (int t = 0; t < m; ++t) s = fmaf(Cb[i * cs + t], Zg[(size_t)t * d + c], s);
-      Cg[e] = s;
-    }
-  };
-  int k_used = 0;
-  float revr = 0.f, fast_err = -1.f;
-  if (iters <= 0 || diag != nullptr) {
-    const float* th;
-    const float* Wk;
-    if (kq <= 4) tri_top_eigs<4>(Tg, m, Rf, m, kq, work, &th, &Wk);
-    else tri_top_eigs<8>(Tg, m, Rf, m, kq, work, &th, &Wk);
-    if (tid == 0) {
-      const float lmax = th[0];
-      const float srel = (float)max(st.n_del, d) * (float)kRankEps;
-      const float floor_rel = fmaxf(srel * srel, kEigFloor);
-      int rankR = 0;
-      for (int j = 0; j < kq; ++j) if (th[j] > lmax * floor_rel) ++rankR;      // descending: the count is a prefix
-      rankR = min(rankR, min(min(st.n_del, d - r), d));
-      s_k = min(rank, rankR);
-      double top = 0.0;
-      for (int j = 0; j < s_k; ++j) top += (double)th[j];
-      s_off = (float)(top * (double)jb.unit / ((double)jb.res2 + 1e-12));
-    }
-    __syncthreads();
-    k_used = s_k;
-    revr = (k_used > 0) ? s_off : 0.f;
-    __syncthreads();
-    project(Wk, m, k_used);
-    if (iters <= 0) export_basis(Wk, m, k_used);
-  }
-  if (iters > 0) {
-    if (diag != nullptr && tid < m) dex[tid] = dcomp[tid];     // the direct route's Delta, for the error report
-    __syncthreads();                                           // the direct route's LDS is free
-    // T lives in registers: thread (t, g) = (tid % 128, tid / 128) holds T[s][t] for the rp rows s = rp g + u
-    const int t = tid & 127, grp = tid >> 7, rp = ((m + 15) >> 4) << 2;
-    float tr[32];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) tr[u] = (u < rp && grp * rp + u < m && t < m) ? Tg[(size_t)(grp * rp + u) * m + t] : 0.f;
-    float* Ya = work;                                          // [kq][128] the current rows, zero past m
-    float* Yb = Ya + kq * 128;                                 // [kq][128] their images under T
-    float* psum = Yb + kq * 128;                               // [4 groups][4 rows][128], once the start rows are done with
-    float* c0 = work + tri_work_floats(m, kq);                 // [k][d] start rows (the host sized the LDS for them)
-    const int k0 = min(min(rank, m), st.n_del);
-    for (int e = tid; e < kq * 128; e += TE_THREADS) Ya[e] = 0.f;
-    // C_0: the first rows of the orthonormal cosine basis, C_0[i][c] = sqrt(2/d) cos(pi (i + 1/2)(c + 1/2) / d)
-    for (int e = tid; e < k0 * d; e += TE_THREADS) {
-      const int i = e / d, c = e - i * d;
-      c0[e] = sqrtf(2.f / (float)d) * cospif((float)((2 * i + 1) * (2 * c + 1)) / (float)(4 * d));
-    }
-    __syncthreads();
-    // Y_0 = C_0 Z^T, a wave per complement row as for y above, three start rows' sums at a time
-    fetch_rows(wave);
-    for (int t0 = wave; t0 < m; t0 += 4 * TE_WAVES) {
-      float c0v[4], c1v[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { c0v[q] = z0[q]; c1v[q] = z1[q]; }
-      fetch_rows(t0 + 4 * TE_WAVES);
-      for (int v = 0; v < k0; v += 3) {
-        float x0[3], x1[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          const float* cr = c0 + min(v + i, k0 - 1) * d;
-          x0[i] = (lane < d) ? cr[lane] : 0.f; x1[i] = (lane + 64 < d) ? cr[lane + 64] : 0.f;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float g[3];
-          te_wave_sum3(fmaf(c1v[q], x1[0], c0v[q] * x0[0]), fmaf(c1v[q], x1[1], c0v[q] * x0[1]), fmaf(c1v[q], x1[2], c0v[q] * x0[2]),
-                       g[0], g[1], g[2]);
-          const int t = t0 + q * TE_WAVES;
-          if (lane < 3 && v + lane < k0 && t < m) Ya[(v + lane) * 128 + t] = (lane == 0) ? g[0] : (lane == 1) ? g[1] : g[2];
-        }
-      }
-    }
-    if (tid == 0) s_k = k0;
-    __syncthreads();
-    auto times_T = [&](const int kk) {                         // Yb = Ya T (T is symmetric), four rows at a time
-      for (int v0 = 0; v0 < kk; v0 += 4) {
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int u = 0; u < 32; u += 4) {
-          if (u < rp) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float4 y = *(const float4*)&Ya[min(v0 + i, kk - 1) * 128 + grp * rp + u];
-              acc[i] = fmaf(y.w, tr[u + 3], fmaf(y.z, tr[u + 2], fmaf(y.y, tr[u + 1], fmaf(y.x, tr[u], acc[i]))));
-            }
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (v0 + i < kk) psum[(grp * min(kk, 4) + i) * 128 + t] = acc[i];
-        __syncthreads();
-        if (v0 + grp < kk) {                                   // group g adds row v0 + g
-          const int n = min(kk, 4);
-          Yb[(v0 + grp) * 128 + t] = (psum[grp * 128 + t] + psum[(n + grp) * 128 + t]) + (psum[(2 * n + grp) * 128 + t] + psum[(3 * n + grp) * 128 + t]);
-        }
-        __syncthreads();
-      }
-    };
-    for (int it = 0; it < iters; ++it) {
-      const int kk = s_k;
-      __syncthreads();
-      if (kk == 0) break;                                      // uniform
-      times_T(kk);
-      if (wave == 0) {
-        const int nk = (kk <= 4) ? lead_orth<4>(Ya, Yb, m, kk) : lead_orth<TE_MAXK>(Ya, Yb, m, kk);
-        if (lane == 0) s_k = nk;
-      }
-      __syncthreads();
-    }
-    k_used = s_k;
-    __syncthreads();
-    revr = 0.f;
-    if (k_used > 0) {
-      times_T(k_used);                                         // explained share: sum_i c_i T c_i^T over the trace
-      for (int v = wave; v < k_used; v += TE_WAVES) {
-        float sc = (lane < m) ? Ya[v * 128 + lane] * Yb[v * 128 + lane] : 0.f;
-        if (lane + 64 < m) sc = fmaf(Ya[v * 128 + lane + 64], Yb[v * 128 + lane + 64], sc);
-        sc = te_wave_sum(sc);
-        if (lane == 0) dvec[v] = sc;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        double top = 0.0;
-        for (int i = 0; i < k_used; ++i) top += (double)dvec[i];
-        s_off = (float)(top * (double)jb.unit / ((double)jb.res2 + 1e-12));
-      }
-      __syncthreads();
-      revr = s_off;
-      __syncthreads();
-      project(Ya, 128, k_used);
-      export_basis(Ya, 128, k_used);
-    } else {
-      if (tid < m) dcomp[tid] = 0.f;
-      __syncthreads();
-    }
-    if (diag != nullptr) {
-      if (tid == 0) {
-        double num = 0.0, den = 0.0;
-        for (int t = 0; t < m; ++t) { const double e = (double)dcomp[t] - dex[t]; num += e * e; den += (double)dex[t] * dex[t]; }
-        s_off = (den > 0.0) ? (float)sqrt(num / den) : 0.f;
-      }
-      __syncthreads();
-      fast_err = s_off;
-      __syncthreads();
-    }
-  }
-  int skipped = 1;
-  float ivn = 0.f;
-  if (k_used > 0) {
-    // Delta back in head_dim coordinates: four groups of 128 threads share the complement's rows, their sums meet in LDS (the
-    // reflectors are done with)
-    __syncthreads();                                           // (a narrow complement's subspace may lie in that range: its last readers)
-    {
-      const int g = tid >> 7, c = tid & 127;
-      float s = 0.f;
-      if (c < d) {
-#pragma unroll 8
-        for (int t = g; t < m; t += TE_THREADS / 128) s = fmaf(Zg[(size_t)t * d + c], dcomp[t], s);
-      }
-      sm[tid] = s;
-    }
-    __syncthreads();                                           // (and every thread has read u)
-    if (tid < d) {
-      const float s = (sm[tid] + sm[128 + tid]) + (sm[256 + tid] + sm[384 + tid]);
-      const double alpha = (vflags & VF_NO_SCALING) ? 1.0 : st.a_del / (st.a_keep + kEps);          // Eq. 6
-      uvec[tid] = (float)(alpha * ((double)s / (st.a_del + kEps)));
-    }
-    __syncthreads();
-    if (wave == 0) {
-      double s = (lane < d) ? (double)uvec[lane] * uvec[lane] : 0.0;
-      if (lane + 64 < d) s += (double)uvec[lane + 64] * uvec[lane + 64];
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-      if (lane == 0) s_off = (float)sqrt(s);
-    }
-    __syncthreads();
-    ivn = s_off;
-    skipped = 0;
-  }
-  fn_emit<T, TE_THREADS>(head, d, rank, st, skipped, k_used, jb.rcr, ivn, jb.pcr, jb.pc, revr, fast_err, uvec, state, delta, delta_out,
-                         diag, V_out, max_budget, scores, idx, vflags, scs);
-}
-
-// ------------------------------------------------------------------------------------------------
 // host side
 // True when the basis of the retained span may be computed beside the gather and the statistics pass: with every
 // budget below the head dimension each head with deleted rows is active whatever its basis turns out to be.
@@ -1772,18 +1371,15 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
   once_per_device(attr_mu, attr_seen, [] {
     (void)hipFuncSetAttribute((const void*)k_bf_keep_basis<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 128 * 8);
     (void)hipFuncSetAttribute((const void*)k_bf_keep_gram_part<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 128 * 8);
-    (void)hipFuncSetAttribute((const void*)k_bf_finalize<T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 129 * 4);
-    (void)hipFuncSetAttribute((const void*)k_bf_finalize<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 129 * 4);
-    (void)hipFuncSetAttribute((const void*)k_bf_lead<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)(sizeof(float) * lead_lds_floats(128, TE_MAXK, 128)));
+    (void)hipFuncSetAttribute((const void*)k_bf_finalize<T>, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 128 * 129 * 4);
   });
   if (var.subspace_iters > 0 && !(var.flags & VF_NAIVE) &&
-      (rank > TE_MAXK || (var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) || m.d > 128)) {
+      (rank > kLeadMaxRank || (var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) || m.d > 128)) {
     set_error("backfill: the subspace iteration takes the rank rule with pca_rank <= 16 and head_dim <= 128");
     return OBF_ERR_UNSUPPORTED;
   }
   if ((var.flags & VF_PER_TOKEN) &&
-      (rank > TE_MAXK || (var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE | VF_ATTN_INJECT)) || m.d > 128)) {
+      (rank > kLeadMaxRank || (var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE | VF_ATTN_INJECT)) || m.d > 128)) {
     set_error("backfill: the per-token variant takes the rank rule with pca_rank <= 16 and head_dim <= 128, without Naive Aggregation or Attn-inject");
     return OBF_ERR_UNSUPPORTED;
   }
@@ -1836,44 +1432,24 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
   if (join.now() != OBF_OK) return OBF_ERR_HIP;
   {
     ProfScope prof_(ST_FINALIZE, st);
-    const size_t one = sizeof(float) * m.d * (m.d + 1);
-    // Heads that only need a few leading eigenpairs go to k_bf_lead after the finalisation
-    // (not under the Max-P / EVR rules, which need the whole spectrum).  Its LDS holds the reflectors packed, 52 KB for up to four
-    // directions at head_dim 128, so that complements of every width take that route with two workgroups per CU.
-    // The fast path of App. H lives in that kernel too and then takes every head that reaches Eq. 4.
-    // So does the Per-token alternative (it needs the subspace itself, which only that kernel exports).
+    // The rank rule with few directions (the method's own setting, App. H's fast path, the Per-token alternative): one kernel for every
+    // head.  Max-P, EVR and larger ranks need more of the spectrum and diagonalise.
     const int iters = (var.flags & VF_NAIVE) ? 0 : var.subspace_iters;
-    const bool all_lead = iters > 0 || (var.flags & VF_PER_TOKEN);
-    const bool lead_ok = rank > 0 && rank <= TE_MAXK && !(var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE)) &&
-                         (all_lead || !(min_budget > m.d && m.N > m.d && !var.skips_basis()));
-    LeadJob* lead = lead_ok ? (LeadJob*)(ws + w.lead_job) : (LeadJob*)nullptr;
+    if (rank > 0 && rank <= kLeadMaxRank && !(var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE)))
+      return launch_backfill_lead(m, w, ws, scores, idx, max_budget, rank, max_budget > 0 ? V_inject : nullptr, delta_out, diag, st,
+                                  var.flags, iters);
+    const size_t one = sizeof(float) * m.d * (m.d + 1);
     // every budget above head_dim: heads that need the finalisation are rare (the certificate settles the others), so one
     // launch with the large LDS size serves both classes instead of two launches that mostly exit at once
     const bool single = min_budget > m.d && m.N > m.d && !var.skips_basis();
-    // every head leaves its eigenpairs to the leading-eigenpair kernel and none has few enough rows to need the large LDS: the second
-    // launch, 5 us with every workgroup leaving at once, is not made
-    // (256 tokens, budget 32: 302 -> 297 us; a batch of twelve samples: 2215 -> 2074)
-    const bool small_only = !single && lead_ok && !var.skips_basis() && (min_budget > FN_FEW || fn_few_floats(max(min_budget, 0), m.d) <= fn_small_floats(m.d));
-    for (int cls = single ? -1 : 0; cls < (single ? 0 : small_only ? 1 : 2); ++cls) {
+    for (int cls = single ? -1 : 0; cls < (single ? 0 : 2); ++cls) {
       const size_t lds = (cls == 0) ? sizeof(float) * (size_t)fn_small_floats(m.d) : 2 * one;
-      auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(m.heads), dim3(FN_THREADS), lds, st, m.N, m.d,
-                           w.nstat, rank, state, basis, gram_part, mats, delta, delta_out, diag,
-                           (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, cls, scores, idx,
-                           var.flags, var.evr_tau, m.scs, (max_budget < m.d && rank > 0) ? (float*)(ws + w.rot) : (float*)nullptr,
-                           lead);
-      };
-      if (lead) go(k_bf_finalize<T, true>); else go(k_bf_finalize<T, false>);
+      hipLaunchKernelGGL(k_bf_finalize<T>, dim3(m.heads), dim3(FN_THREADS), lds, st, m.N, m.d,
+                         w.nstat, rank, state, basis, gram_part, mats, delta, delta_out, diag,
+                         (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, cls, scores, idx,
+                         var.flags, var.evr_tau, m.scs, (max_budget < m.d && rank > 0) ? (float*)(ws + w.rot) : (float*)nullptr);
     }
     if (check_launch("backfill finalize") != OBF_OK) return OBF_ERR_HIP;
-    if (lead) {
-      const int kq = rank < TE_MAXK ? rank : TE_MAXK;
-      const size_t lds = sizeof(float) * lead_lds_floats(m.d, kq, iters > 0 ? m.d : 0);
-      hipLaunchKernelGGL(k_bf_lead<T>, dim3(m.heads), dim3(TE_THREADS), lds, st, m.d, rank, state, mats, delta, delta_out, diag,
-                         (rank > 0 && max_budget > 0) ? (T*)V_inject : (T*)nullptr, max_budget, scores, idx, var.flags, m.scs,
-                         (const LeadJob*)lead, iters);
-      if (check_launch("backfill leading eigenpairs") != OBF_OK) return OBF_ERR_HIP;
-    }
   }
   return OBF_OK;
 }

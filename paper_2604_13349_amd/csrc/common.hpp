@@ -68,7 +68,6 @@ struct Workspace {
   size_t fro_part;     // double  [heads][ceil(max_budget/16)]   per-gather-block sums of squares of the retained V rows
   size_t rot;          // float   [heads][kJacobiSweeps][d-1][d/2]  rotation tangents of the Jacobi iteration (max_budget < d only)
   size_t keep_gram;    // double  [kKeepGramSlots][kKeepGramChunks][d*d]  partial Gram matrices (max_budget >= kKeepGramMinBudget)
-  size_t lead_job;     // LeadJob [heads]                 hand-over from the finalisation to the leading-eigenpair kernel
   size_t inv_norm;     // float   [heads][max_budget]     reciprocal norms of the retained keys (cache merging)
   size_t route;        // int32   [heads][N]              retained slot of every deleted token (cache merging, when not an output)
   size_t total;
@@ -85,14 +84,6 @@ struct HeadState {
   int32_t k_used;
   int32_t pad;
   float rcr, ivn;
-};
-
-// What the finalisation hands to the leading-eigenpair kernel for a head it does not diagonalise itself.
-struct LeadJob {
-  int32_t pending;      // 1: the residual Gram matrix T (m x m, complement coordinates) over `unit` waits in the head's scratch
-  int32_t m;
-  float res2, vd2, pc, pcr, rcr;
-  float unit;           // power of two
 };
 
 // One chunk's statistics of the deleted values: G [d][d] (tiles on and below the diagonal), u = sum_j A_j v_j [d],
@@ -141,7 +132,6 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.fro_part = take(sizeof(double) * (size_t)m.heads * ((max_budget > 0 ? max_budget : 0) / kGatherRows + 1));
   w.rot = take((max_budget < m.d && rank > 0) ? sizeof(float) * (size_t)m.heads * kJacobiSweeps * (m.d - 1) * (m.d / 2) : 0);
   w.keep_gram = take(max_budget >= kKeepGramMinBudget ? sizeof(double) * kKeepGramSlots * kKeepGramChunks * (size_t)m.d * m.d : 0);
-  w.lead_job = take(sizeof(LeadJob) * (size_t)m.heads);
   w.inv_norm = take(sizeof(float) * (size_t)m.heads * (max_budget > 0 ? max_budget : 0));
   w.route = take(sizeof(int32_t) * (size_t)m.heads * m.N);
   w.total = off;
@@ -295,5 +285,11 @@ obf_status_t launch_backfill(const Dims& m, const Workspace& w, char* ws, const 
                              const double* fro_part = nullptr,
                              bool basis_started = false, int32_t min_budget = -1 /*smallest per-head budget if known*/,
                              Variant var = Variant());
+
+// Rank rule with at most kLeadMaxRank directions: everything after the statistics pass (backfill_lead.hip), App. H's fast path included.
+constexpr int kLeadMaxRank = 16;
+obf_status_t launch_backfill_lead(const Dims& m, const Workspace& w, char* ws, const float* scores, const int32_t* idx, int32_t max_budget,
+                                  int32_t rank, void* V_out /*nullable*/, float* delta_out, obf_diag_t* diag, hipStream_t st, int vflags,
+                                  int iters);
 
 }  // namespace obf

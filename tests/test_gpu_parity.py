@@ -158,6 +158,36 @@ def test_leading_eigenpairs_at_tile_edges(gpu, dtype, d, rank, iters, budgets):
     _check_cfg(gpu, cfg, budgets=budgets, max_budget=max(budgets), expect_active=True, variant=variant)
 
 
+@pytest.mark.parametrize("d,budget,spectrum,rank", [
+    (128, 32, "ladder", 4), (128, 32, "ladder", 5), (64, 16, "ladder", 12), (128, 32, "ladder", 13), (128, 32, "ladder", 16),    # blocks of 8 and 16, two groups
+    (128, 32, "steep", 12), (64, 16, "steep", 13),     # eigenvalues down to 3e-4 of the first: several groups
+    (128, 32, "flat", 4), (64, 16, "flat", 8),         # neighbours 1e-4 apart, more of them than a block holds: the direct route
+    (128, 32, "two", 5), (64, 16, "two", 14),          # fewer directions than asked for
+    (128, 111, "ladder", 3), (128, 112, "ladder", 3), (128, 119, "ladder", 9), (128, 120, "two", 8), (64, 48, "steep", 12), (64, 55, "ladder", 16),  # as narrow as a block
+])
+def test_leading_directions_of_planted_spectra(gpu, d, budget, spectrum, rank):
+    """Retained rows that span the first `budget` coordinates exactly and deleted rows with one entry behind them: the residual Gram
+    matrix is diagonal, its eigenvalues are the planted ones.  Tolerances as everywhere (2e-3 of the offset before rounding, widened by
+    what a gap under 0.05 amplifies)."""
+    cfg = si.RelayConfig("planted", 43, 1, 3, 2, d, 700, 8, budget, rank, "f32", "structured")
+    m = d - budget
+    lam = {"ladder": 0.8 ** np.arange(m), "steep": 10.0 ** (-0.3 * np.arange(m)), "flat": 1.0 - 1e-4 * np.arange(m),
+           "two": np.where(np.arange(m) < 2, 1.0 - 0.3 * np.arange(m), 0.0)}[spectrum]
+
+    def edit(K, V, Q):
+        r = np.random.default_rng(3)
+        for h in range(V.shape[1]):
+            keep = O.compress_head(K[0, h], V[0, h], Q[0, 2 * h:2 * h + 2], budget, 0, "f32").idx
+            rows = np.setdiff1d(np.arange(cfg.n_tokens), keep)
+            at = np.arange(rows.size) % m
+            V[0, h, :, budget:] = 0
+            V[0, h, keep, :budget] = np.linalg.qr(r.standard_normal((budget, budget)))[0]
+            V[0, h, rows, budget + at] = (r.choice([-1.0, 1.0], m) * np.sqrt(lam / np.bincount(at, minlength=m)))[at]
+
+    reps = _check_cfg(gpu, cfg, edit=edit, expect_active=True)
+    assert all(r.v_checked and not r.ambiguous for r in reps)
+
+
 @pytest.mark.parametrize("budget,rank,iters", [(16, 2, 0), (32, 4, 0), (115, 2, 0), (24, 10, 0), (32, 2, 3)])
 def test_offset_follows_the_scale_of_the_values(gpu, budget, rank, iters):
     """Values times a power of two give the offset times that power, bit for bit: no step rounds differently unless a square or a

@@ -49,6 +49,16 @@ inline int score_rows_per_group(int R) {
   return (g5 * 160 - R < g4 * 128 - R) ? 160 : 128;
 }
 
+// 32-token tiles per persistent workgroup of those kernels, TT in all: as many ranges as make a multiple of 8 (one share per XCD) such that an
+// XCD's ranges x row groups fit its 32 compute units.
+inline int score_tiles_per_range(long TT, int rgroups) {
+  const int per_xcd = (kNumCU / 8) / rgroups > 0 ? (kNumCU / 8) / rgroups : 1;
+  const int G = 8 * per_xcd;
+  long T = (TT + G - 1) / G;
+  T = ((T + 3) / 4) * 4;
+  return (int)(T < 4 ? 4 : T);
+}
+
 // Workspace carving.  Every region is 256-byte aligned; offsets are from the workspace base.
 struct Workspace {
   size_t stats_part;   // double2 [heads][nchunk][R]      partial (max, sum-exp) per score chunk
@@ -103,13 +113,8 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.tiles_per_head = (m.N + 31) / 32;
   {
     const long TT = (long)m.heads * w.tiles_per_head;
-    // ranges: a multiple of 8 (one share per XCD) such that an XCD's ranges x row groups fit its 32 compute units
-    const int per_xcd = (kNumCU / 8) / w.rgroups > 0 ? (kNumCU / 8) / w.rgroups : 1;
-    const int G = 8 * per_xcd;
-    long T = (TT + G - 1) / G;
-    T = ((T + 3) / 4) * 4;
-    if (T < 4) T = 4;
-    w.tiles_per_range = (int)T;
+    const int T = score_tiles_per_range(TT, w.rgroups);
+    w.tiles_per_range = T;
     w.nranges = (int)((TT + T - 1) / T);
     w.nslot = (int)((w.tiles_per_head + T - 1) / T) + 1;
   }

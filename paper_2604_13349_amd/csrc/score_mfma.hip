@@ -22,9 +22,9 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int SM_THREADS = 256;
 constexpr int SM_WAVES = 4;
-// The kernels are instantiated for (RB, KBUF) = (4, 3) and (5, 2): RB 32-row blocks of query rows per workgroup (RB * 32 = 128
-// or 160 rows, their Q operand in RB * 32 registers per lane) and KBUF rotating K fragment buffers.  RB * KBUF is even, so the
-// two accumulators keep alternating across the iterations of the tile loop.
+// The kernels are instantiated for (RB, KBUF) = (4, 3) and (5, 2), the second pass also for (8, 2): RB 32-row blocks of query
+// rows per workgroup (RB * 32 = 128, 160 or 256 rows, their Q operand in RB * 32 registers per lane) and KBUF rotating K
+// fragment buffers.  RB * KBUF is even, so the two accumulators keep alternating across the iterations of the tile loop.
 constexpr int SM_D = 128;
 constexpr int SM_KK = SM_D / 16;         // MFMA k-steps
 constexpr int SM_TILE = 32;              // tokens per MFMA tile
@@ -139,27 +139,35 @@ __device__ __forceinline__ void stats_block_ragged(const f32x16& acc, float& m, 
 // Pass B epilogue: acc[i] is the raw dot product of query row row0 + rb*32 + (i/4)*8 + (lane/32)*4 + (i%4) with
 // token tok + lane%32; b2 holds lse[row] * log2(e) for the same (rb, i).  The column sum of a tile is
 // complete after its last row block.
+// Up to five row blocks their b2 stay in registers; more (NRB > 5) leave no room and are read from LDS.  Their two halves
+// are summed apart and added last, as k_score_sum_groups adds two row groups: the same mass to the last bit.
 template <int NRB>
 struct MassEp {
-  const float (&b2)[NRB][16];
+  const float* b2;       // registers [NRB][16], or LDS [NRB * 32]
   float a2;
   float* __restrict__ dst;
   int t_end, lane;
-  float c0, c1, c2, c3;
+  float c0, c1, c2, c3, half = 0.f;
   template <int RB>
   __device__ __forceinline__ void block(const f32x16& acc, int tok) {
     if (RB == 0) { c0 = 0.f; c1 = 0.f; c2 = 0.f; c3 = 0.f; }
 #pragma unroll
     for (int i = 0; i < 16; i += 4) {
-      c0 += fast_exp2(fmaf(acc[i], a2, -b2[RB][i]));
-      c1 += fast_exp2(fmaf(acc[i + 1], a2, -b2[RB][i + 1]));
-      c2 += fast_exp2(fmaf(acc[i + 2], a2, -b2[RB][i + 2]));
-      c3 += fast_exp2(fmaf(acc[i + 3], a2, -b2[RB][i + 3]));
+      const float4 b = (NRB > 5) ? *(const float4*)(b2 + RB * 32 + 2 * i + (lane >> 5) * 4)
+                                 : make_float4(b2[RB * 16 + i], b2[RB * 16 + i + 1], b2[RB * 16 + i + 2], b2[RB * 16 + i + 3]);
+      c0 += fast_exp2(fmaf(acc[i], a2, -b.x));
+      c1 += fast_exp2(fmaf(acc[i + 1], a2, -b.y));
+      c2 += fast_exp2(fmaf(acc[i + 2], a2, -b.z));
+      c3 += fast_exp2(fmaf(acc[i + 3], a2, -b.w));
+    }
+    if (NRB > 5 && RB == NRB / 2 - 1) {
+      half = (c0 + c1) + (c2 + c3);
+      c0 = 0.f; c1 = 0.f; c2 = 0.f; c3 = 0.f;
     }
     if (RB == NRB - 1) {
       float col = (c0 + c1) + (c2 + c3);
-      const float other = __shfl_xor(col, 32);
-      col = (lane < 32) ? (col + other) : (other + col);
+      col += __shfl_xor(col, 32);
+      if (NRB > 5) col = (half + __shfl_xor(half, 32)) + col;
       const int t = tok + (lane & 31);
       if (lane < 32 && t < t_end) dst[t] = col;
     }
@@ -317,8 +325,9 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_
                                                                    const double* __restrict__ stats_part,
                                                                    double* __restrict__ row_lse,
                                                                    float* __restrict__ out, int N, int R, int RG,
-                                                                   size_t rg_stride, Part pt, int nslot) {
+                                                                   size_t rg_stride, Part pt, int t_stats, int nslot) {
   __shared__ double s_lse[(RB * 32)];
+  __shared__ __attribute__((aligned(16))) float s_b2[RB > 5 ? RB * 32 : 4];
   // Workgroups are dealt to the 8 XCDs round-robin.  The RG workgroups that stream the same K range (one per row
   // group) get block indices 8 apart, so they run on one XCD side by side and share its L2.
   const int blk_group = blockIdx.x / (8 * RG), blk_in = blockIdx.x - blk_group * (8 * RG);
@@ -343,11 +352,11 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_
     float* dst = out + (size_t)rg * rg_stride + (size_t)head * N;
 
     __syncthreads();
-    if (threadIdx.x < (RB * 32)) {
-      const int row = row0 + threadIdx.x;
+    for (int rl = threadIdx.x; rl < RB * 32; rl += SM_THREADS) {
+      const int row = row0 + rl;
       double lse = INFINITY;                                   // padded rows: exp2(-inf) = 0
       if (row < R) {
-        const int s_first = (int)(hs / pt.T), s_last = (int)((hs + pt.TH - 1) / pt.T);
+        const int s_first = (int)(hs / t_stats), s_last = (int)((hs + pt.TH - 1) / t_stats);
         const double* p = stats_part + ((size_t)head * nslot * R + row) * 2;
         double M = -INFINITY;
         for (int sl = 0; sl <= s_last - s_first; ++sl) M = fmax(M, p[(size_t)sl * R * 2]);
@@ -359,22 +368,22 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_
         lse = M + log(L);
         if (cur == hs) row_lse[(size_t)head * R + row] = lse;
       }
-      s_lse[threadIdx.x] = lse;
+      if (RB > 5) s_b2[rl] = (float)(lse * 1.4426950408889634); else s_lse[rl] = lse;
     }
     __syncthreads();
 
     Frag qf[RB][SM_KK];
     load_q(qf, Qh, row0, R, lane);
-    float b2[RB][16];
+    float b2[RB > 5 ? 1 : RB * 16];
+    if constexpr (RB <= 5) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        b2[rb][i] = (float)(s_lse[rb * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] * 1.4426950408889634);
+      for (int i = 0; i < RB * 16; ++i)
+        b2[i] = (float)(s_lse[(i >> 4) * 32 + ((i & 15) >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] * 1.4426950408889634);
+    }
 
     const int first = ta + wave * SM_TILE;
     const int nt = (first < tb) ? ((tb - first - 1) / STEP + 1) : 0;      // tiles of this wave, the last may be ragged
-    MassEp<RB> ep{b2, a2, dst, tb, lane, 0.f, 0.f, 0.f, 0.f};
+    MassEp<RB> ep{RB > 5 ? s_b2 : b2, a2, dst, tb, lane, 0.f, 0.f, 0.f, 0.f};
     run_tiles<false, RB, KBUF>(Kh, first + (nt - 1) * STEP, -STEP, nt, tb, lane, qf, ep);
     se = cur;
   }
@@ -451,12 +460,10 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_head_mfma(const uint16_
     s_lse[row] = lse;
   }
   __syncthreads();
-  float b2[RB][16];
+  float b2[RB * 16];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      b2[rb][i] = (float)(s_lse[rb * 32 + (i >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] * 1.4426950408889634);
+  for (int i = 0; i < RB * 16; ++i)
+    b2[i] = (float)(s_lse[(i >> 4) * 32 + ((i & 15) >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] * 1.4426950408889634);
   const int nt = (first < N) ? ((N - first - 1) / STEP + 1) : 0;          // tiles of this wave, the last may be ragged
   MassEp<RB> ep{b2, a2, dst, N, lane, 0.f, 0.f, 0.f, 0.f};
   run_tiles<false, RB, KBUF>(Kh, first + (nt - 1) * STEP, -STEP, nt, N, lane, qf, ep);
@@ -501,17 +508,28 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
       hipLaunchKernelGGL((k_score_stats_mfma<4, 3>), grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
                          stats_part, m.N, m.R, RG, pt, w.nslot); }
   if (check_launch("score stats (mfma)") != OBF_OK) return OBF_ERR_HIP;
+  // The second pass carries 256 rows where the first has pairs of 128, so that the two groups do not each stream K and leave partial sums
+  // to be added (the first pass keeps its groups: its normalisers depend on where a row's tokens are split).
+  // 288 heads of 32768 tokens, 256 rows: 796 + 35 us -> 785, one launch less.  320 rows at once instead of two groups of 160 were slower
+  // (504 + 20 -> 559: the compiler moves Q operands between the register files), so those stay.
+  const bool tall = !five && RG % 2 == 0;
+  const int RGB = tall ? RG / 2 : RG;
+  if (RGB == 1) part = scores;
+  Part pb = pt;
+  if (tall) pb.T = score_tiles_per_range(pt.TT, RGB);
+  const dim3 grid_b((unsigned)(((pb.TT + pb.T - 1) / pb.T + 7) / 8 * 8 * RGB));
   { ProfScope prof_(ST_SCORE_MASS, st);
-    if (five)
-      hipLaunchKernelGGL((k_score_mass_mfma<5, 2>), grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
-                         (const double*)stats_part, row_lse, part, m.N, m.R, RG, rg_stride, pt, w.nslot);
-    else
-      hipLaunchKernelGGL((k_score_mass_mfma<4, 3>), grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
-                         (const double*)stats_part, row_lse, part, m.N, m.R, RG, rg_stride, pt, w.nslot); }
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid_b, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
+                         (const double*)stats_part, row_lse, part, m.N, m.R, RGB, rg_stride, pb, pt.T, w.nslot);
+    };
+    if (tall) go(k_score_mass_mfma<8, 2>);
+    else if (five) go(k_score_mass_mfma<5, 2>);
+    else go(k_score_mass_mfma<4, 3>); }
   if (check_launch("score mass (mfma)") != OBF_OK) return OBF_ERR_HIP;
-  if (RG > 1) {
+  if (RGB > 1) {
     const size_t n = (size_t)m.heads * m.N;
-    hipLaunchKernelGGL(k_score_sum_groups, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, scores, n, RG,
+    hipLaunchKernelGGL(k_score_sum_groups, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, scores, n, RGB,
                        rg_stride);
     if (check_launch("score sum groups") != OBF_OK) return OBF_ERR_HIP;
   }

@@ -8,8 +8,10 @@
 //           query row and keeps its running maximum and sum);
 //   pass B: a wave keeps the operand of 16 tokens and walks all query rows (rows x tokens: a lane owns one token).
 // Bound by the double-precision matrix rate (64 multiply-adds per clock and compute unit: 43 us a pass at the first shape below) and
-// the exponentials, which the same units compute.  96 heads x 2048 tokens x 128 rows at head_dim 64: 102 and 88 us; 2 heads x 512
-// tokens x 32 rows: 12 and 8 us.  With the products as scalar multiply-adds fed from LDS: 975 and 853 us, 224 and 215 us.
+// the exponentials, which the same units compute: f64_exp.hpp's, of half the math library's instructions.  96 heads x 2048 tokens x
+// 128 rows at head_dim 64: 88 and 85 us (102 and 88 with the library's exponential).  With the products as scalar multiply-adds fed from
+// LDS: 975 and 853 us; 2 heads x 512 tokens x 32 rows 224 and 215, now 12 and 6.
+#include "f64_exp.hpp"
 #include "f64_tile.hpp"
 
 namespace obf {
@@ -44,7 +46,10 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_stats_f64(const T* __re
   const int head = blockIdx.y, lane = threadIdx.x & 63;
   const int w = blockIdx.x * GS_WAVES + (threadIdx.x >> 6);
   const int chunk = w / nrb, row = (w - chunk * nrb) * GS_T + (lane & 15);
-  if (chunk >= nchunk) return;                                // whole wave; there is no barrier
+  __shared__ double etab[kExpTab];
+  exp_table(etab, threadIdx.x);
+  __syncthreads();
+  if (chunk >= nchunk) return;                                // whole wave; no barrier follows
   const int t0 = chunk * chunk_tokens, t1 = min(N, t0 + chunk_tokens);
   const T* Kh = K + (size_t)head * kvs * D;
   const double scale = 1.0 / sqrt((double)D);
@@ -62,20 +67,30 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_stats_f64(const T* __re
     nxt.load(Kh + (size_t)min(tt + GS_T + (lane & 15), N - 1) * D, lane);      // clamped: masked below
     const f64x4 acc = tile_product<T, D>(q, cur);
     double x[4];
-    bool ok[4];
+    const bool full = tt + GS_T <= t1;                        // uniform; only a chunk's last tile may not be
+    if (full) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      ok[i] = tt + (lane >> 4) + 4 * i < t1;
-      x[i] = ok[i] ? acc[i] * scale : -INFINITY;
+      for (int i = 0; i < 4; ++i) x[i] = acc[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = (tt + (lane >> 4) + 4 * i < t1) ? acc[i] : -INFINITY;
     }
-    const double mx = fmax(fmax(x[0], x[1]), fmax(x[2], x[3]));
+    const double mx = fmax(fmax(x[0], x[1]), fmax(x[2], x[3])) * scale;
     if (__ballot(mx > m)) {                                   // rare after the first tiles: the sum is rescaled only when a maximum moved
       const double mn = fmax(m, mx);
       if (mn > m) l *= exp(m - mn);
       m = mn;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) l += ok[i] ? exp(x[i] - m) : 0.0;
+    for (int i = 0; i < 4; ++i) x[i] = fma(x[i], scale, -m);
+    exp_clamp(x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = exp_tab(x[i], etab);
+    if (!full) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = (tt + (lane >> 4) + 4 * i < t1) ? x[i] : 0.0;
+    }
+    l += (x[0] + x[1]) + (x[2] + x[3]);
     cur = nxt;
   }
   // the four lanes of a row
@@ -120,6 +135,7 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __res
                                                                   double* __restrict__ row_lse, float* __restrict__ scores, int N,
                                                                   int R, int kvs) {
   extern __shared__ double s_lse[];                           // [R rounded up to 16]
+  __shared__ double etab[kExpTab];
   const int head = blockIdx.y, lane = threadIdx.x & 63;
   const int tok = (blockIdx.x * GS_WAVES + (threadIdx.x >> 6)) * GS_T + (lane & 15);
   const T* Qh = Q + (size_t)head * R * D;
@@ -139,6 +155,7 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __res
     }
     s_lse[r] = lse;
   }
+  exp_table(etab, threadIdx.x);
   __syncthreads();
   double k[D / 4];
 #pragma unroll
@@ -147,8 +164,11 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __res
   for (int r0 = 0; r0 < R; r0 += GS_T) {
     nxt.load(Qh + (size_t)min(r0 + GS_T + (lane & 15), R - 1) * D, lane);
     const f64x4 acc = tile_product<T, D>(k, cur);
+    double x[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) col += exp(acc[i] * scale - s_lse[r0 + (lane >> 4) + 4 * i]);
+    for (int i = 0; i < 4; ++i) x[i] = fma(acc[i], scale, -s_lse[r0 + (lane >> 4) + 4 * i]);
+    exp_clamp(x);
+    col += (exp_tab(x[0], etab) + exp_tab(x[1], etab)) + (exp_tab(x[2], etab) + exp_tab(x[3], etab));
     cur = nxt;
   }
   col += __shfl_xor(col, 16);

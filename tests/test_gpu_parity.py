@@ -226,6 +226,35 @@ def test_scores_of_fp32_and_half_width_heads(gpu, dtype, d, N, g, W):
         np.testing.assert_allclose(lse[0, h], ref, rtol=1e-13, atol=1e-13)
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("spread", [1.0, 60.0, 4000.0])     # logits of a row lie about as far apart: within, around and far past what the exponent holds
+def test_scores_of_logits_far_apart(gpu, dtype, d, spread):
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    r = np.random.default_rng(int(spread) + d)
+    N, R = 77, 21
+    K = O.round_to_io((r.standard_normal((1, 1, N, d)) * spread).astype(np.float32), dtype)
+    Q = O.round_to_io(r.standard_normal((1, 1, R, d)).astype(np.float32), dtype)
+    Kd, Qd = gpu.to_dev(K, dtype), gpu.to_dev(Q, dtype)
+    scores, lse = Bd.score(Kd, Qd)
+    torch.cuda.synchronize()
+    x = O.decode(Q[0, 0], dtype) @ O.decode(K[0, 0], dtype).T / np.sqrt(d)
+    m = x.max(axis=1, keepdims=True)
+    want_lse = (m + np.log(np.exp(x - m).sum(axis=1, keepdims=True)))
+    want = np.exp(x - want_lse).sum(axis=0)
+    # a logit of size X carries d rounding errors of X 2^-53, and so do the normaliser and every exponential's argument; the stored sum 2^-24
+    err = 4 * d * np.abs(x).max() * 2.0 ** -53
+    assert np.abs(lse.cpu().numpy().reshape(-1) - want_lse.reshape(-1)).max() <= err
+    got = scores.cpu().numpy().reshape(-1).astype(np.float64)
+    assert np.all(np.abs(got - want) <= want * (2.0 ** -24 + 2 * err) + 1.2e-38)     # the smallest normal float
+    # not a number in one key reaches every token's mass
+    Kn = Kd.clone()
+    Kn[0, 0, 5, 3] = float("nan")
+    scores, lse = Bd.score(Kn, Qd)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(scores).all()) and bool(torch.isnan(lse).all())
+
+
 @pytest.mark.parametrize("R", [161, 255, 256, 481, 512])     # row groups in pairs: the last one ragged, or full
 @pytest.mark.parametrize("L,N", [(1, 33), (1, 333), (6, 4109)])      # less than a wave's tiles each; several tiles, heads split over ranges
 def test_scores_of_paired_row_groups(gpu, R, L, N):

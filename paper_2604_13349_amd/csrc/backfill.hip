@@ -1398,7 +1398,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
   if (!basis_started && !var.skips_basis()) {
     const size_t smem_kb = sizeof(double) * (size_t)m.d * m.d;
     int32_t* decided = nullptr;
-    if (keep_cert_supported(m)) {
+    if (keep_cert_supported(m, max_budget)) {
       decided = (int32_t*)(ws + w.decided);
       if (launch_keep_cert(m, V_out, 0, scores, idx, n_keep, max_budget, rank, state, decided, st, fro_part, diag != nullptr) != OBF_OK)
         return OBF_ERR_HIP;

@@ -1,10 +1,10 @@
 // Fast decision "the retained values span all of R^d" (then Eq. 3's residual is identically zero and
-// the head stays plain eviction) for bf16 caches with head_dim 128 and more retained rows than
-// head_dim.  It is a sufficient test only: heads it cannot certify go to the reference-precision
+// the head stays plain eviction) for heads with more retained rows than head_dim.  It is a sufficient test only: heads it cannot certify go to the reference-precision
 // basis kernel.
 //
 //   G   = V_s^T V_s over a strided subset V_s of the retained rows (all rows up to 512), on the matrix
-//         cores: products of bf16 values are exact in fp32, accumulation is fp32;
+//         cores: products of bf16 values are exact in fp32, accumulation is fp32 (fp32 caches and head_dim
+//         64: products and sums in fp32);
 //   mu  = (max(n, d) 2^-23)^2 ||V_keep||_F^2;
 //   S   = D^-1/2 G D^-1/2 with D = diag(G): G - mu I is positive definite iff S - mu D^-1 is;
 //   if the LDL^T factorisation of S - mu D^-1 - eps I (eps: allowance for the fp32 error of G and of the
@@ -38,6 +38,172 @@ __device__ __forceinline__ void wave_tiles(int wave, int (&rb)[3], int (&cb)[3],
   else { rb[0] = 3; cb[0] = 0; rb[1] = 2; cb[1] = 2; rb[2] = 0; cb[2] = 0; nt = 2; }
 }
 
+// What a workgroup shares during the factorisation.  bad is zeroed by the kernel ahead of a barrier.
+template <int D>
+struct CertShared {
+  __attribute__((aligned(16))) float panel[2][D][4];
+  float4 ypan[D], lpan[D];
+  __attribute__((aligned(16))) float isd[D];
+  int bad;
+};
+
+// Factors G - mu I (scaled, less the allowance) for the Gram matrix G that the workgroup's waves hold in the tiles (trb, tcb) of g; sh.bad
+// is set where a pivot is not positive.
+template <int D>
+__device__ __forceinline__ void cert_factor(f32x16 (&g)[3], const int (&trb)[3], const int (&tcb)[3], const int nt, const float mu,
+                                            CertShared<D>& sh) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int lr = lane & 31, lh = lane >> 5;
+  const bool has_diag = ((lr & 7) >> 2) == lh;
+  const int di = (lr >> 3) * 4 + (lr & 3);
+  // Symmetric diagonal scaling S = D^-1/2 G D^-1/2 (unit diagonal): G - mu I is positive definite iff S - mu D^-1 is,
+  // and the scaled matrix no longer carries the spread of the channel magnitudes (a few outlier channels otherwise
+  // own the trace, and with it the rounding allowance, while lambda_min sits in the small ones).
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    if (t < nt && trb[t] == tcb[t] && has_diag) {
+      float v = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) if (i == di) v = g[t][i];
+      sh.isd[tcb[t] * 32 + lr] = __builtin_amdgcn_rsqf(v);            // a zero column gives inf, then NaN pivots: not certified
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    if (t < nt) {
+      const float sc_col = sh.isd[tcb[t] * 32 + lr];
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const float4 sr = *(const float4*)&sh.isd[trb[t] * 32 + i4 * 8 + lh * 4];
+        g[t][4 * i4 + 0] *= sr.x * sc_col; g[t][4 * i4 + 1] *= sr.y * sc_col;
+        g[t][4 * i4 + 2] *= sr.z * sc_col; g[t][4 * i4 + 3] *= sr.w * sc_col;
+      }
+      if (trb[t] == tcb[t] && has_diag) {
+        const float shift = fmaf(mu, sc_col * sc_col, kCertErr * (float)D);   // mu / G_jj + allowance relative to trace(S) = d
+#pragma unroll
+        for (int i = 0; i < 16; ++i) if (i == di) g[t][i] -= shift;
+      }
+    }
+  }
+
+  // ---- LDL^T of G - mu I in registers, four columns per step.  panel[s & 1][row] holds columns 4s .. 4s+3 of
+  // the current matrix when step s starts.  Thread r < D factors the 4x4 diagonal block (the same arithmetic in
+  // every thread, so no broadcast) and turns panel row r into y = L d (a 4-term forward substitution) and L; after a
+  // second barrier every wave applies the rank-4 update to its tiles: first to the one tile (per wave) that holds
+  // the next four columns, which are then published, then to the rest, so the chain block -> next block only
+  // contains one tile update.  A non-positive pivot sets a flag (no early exit: the steps stay free of
+  // divergent control flow); entries above the diagonal are carried along and never read.
+  auto publish = [&](int k) {                         // columns k .. k+3 (k % 4 == 0) -> panel[(k / 4) & 1]
+    const int kb = k >> 5, kc = k & 31;
+    float* pw = &sh.panel[(k >> 2) & 1][0][0];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      if (t < nt && tcb[t] == kb && (lr & ~3) == kc) {
+        const int c = lr & 3;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pw[(trb[t] * 32 + (i >> 2) * 8 + lh * 4 + (i & 3)) * 4 + c] = g[t][i];
+      }
+    }
+  };
+  publish(0);
+  for (int k = 0; k < D; k += 4) {
+    __syncthreads();                                   // this panel visible; ypan / lpan free again
+    if (tid < D) {
+      const float4* pr = (const float4*)&sh.panel[(k >> 2) & 1][0][0];
+      // 4x4 diagonal block: rows k .. k+3, lower triangle
+      const float4 r0 = pr[k], r1 = pr[k + 1], r2 = pr[k + 2], r3 = pr[k + 3];
+      const float4 x = pr[tid];
+      const float d0 = r0.x;
+      const float i0 = __builtin_amdgcn_rcpf(d0);
+      const float l10 = r1.x * i0, l20 = r2.x * i0, l30 = r3.x * i0;
+      const float d1 = fmaf(-l10, r1.x, r1.y);
+      const float i1 = __builtin_amdgcn_rcpf(d1);
+      const float l21 = fmaf(-l20, r1.x, r2.y) * i1, l31 = fmaf(-l30, r1.x, r3.y) * i1;
+      const float y21 = l21 * d1, y31 = l31 * d1;
+      const float d2 = fmaf(-l21, y21, fmaf(-l20, r2.x, r2.z));
+      const float i2 = __builtin_amdgcn_rcpf(d2);
+      const float l32 = fmaf(-l31, y21, fmaf(-l30, r2.x, r3.z)) * i2;
+      const float y32 = l32 * d2;
+      const float d3 = fmaf(-l32, y32, fmaf(-l31, y31, fmaf(-l30, r3.x, r3.w)));
+      const float i3 = __builtin_amdgcn_rcpf(d3);
+      if (!((d0 > 0.f) && (d1 > 0.f) && (d2 > 0.f) && (d3 > 0.f))) sh.bad = 1;
+      // y = L d of panel row x: y0 = x0, y1 = x1 - y0 l10, y2 = x2 - y0 l20 - y1 l21, y3 = x3 - y0 l30 - y1 l31 - y2 l32
+      const float y0 = x.x;
+      const float y1 = fmaf(-y0, l10, x.y);
+      const float y2 = fmaf(-y1, l21, fmaf(-y0, l20, x.z));
+      const float y3 = fmaf(-y2, l32, fmaf(-y1, l31, fmaf(-y0, l30, x.w)));
+      sh.ypan[tid] = make_float4(y0, y1, y2, y3);
+      sh.lpan[tid] = make_float4(y0 * i0, y1 * i1, y2 * i2, y3 * i3);
+    }
+    __syncthreads();
+    const int kb = k >> 5;
+    const int kbn = (k + 4) >> 5;                      // column block of the next four columns
+    // rank-4 update of a tile on the matrix cores in fp32: G_tile -= Y_rows (32 x 4) * L_cols^T (4 x 32), two
+    // v_mfma_f32_32x32x2_f32 (A: lane l holds row l%32, k = l/32; B: k = l/32, column l%32)
+    auto update = [&](int t) {
+      const float* yp = (const float*)sh.ypan + (trb[t] * 32 + lr) * 4 + lh;
+      const float* lp = (const float*)sh.lpan + (tcb[t] * 32 + lr) * 4 + lh;
+      const float y0 = -yp[0], y1 = -yp[2], l0 = lp[0], l1 = lp[2];
+      g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0, l0, g[t], 0, 0, 0);
+      g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1, l1, g[t], 0, 0, 0);
+    };
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (t < nt && tcb[t] == kbn && tcb[t] >= kb) update(t);
+    if (k + 4 < D) publish(k + 4);
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (t < nt && tcb[t] != kbn && tcb[t] >= kb) update(t);
+  }
+}
+
+// Certified: r = d, OBF is the identity on this head; fills in the demand sums (Eq. 6) for the diagnostics.  pk: what the caller has
+// already added of the retained tokens' scores, which go on from `first`.
+__device__ __forceinline__ void cert_settle(double pk, const int first, const float* __restrict__ sc, const int32_t* __restrict__ id, const int n,
+                                            const int N, const int want_sums, const int d, const int head, HeadState* __restrict__ state,
+                                            int32_t* __restrict__ decided, double* red, double* red2) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool vec_scores = (N & 3) == 0 && ((uintptr_t)sc & 15) == 0;
+  const int ns = want_sums ? n : 0, Ns = want_sums ? N : 0;          // extents of the two sums
+  double ptot = 0.0;
+  for (int i0 = first; i0 < ns; i0 += 8 * KC_THREADS) {      // further batches of index -> score loads
+    int j[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { const int i = i0 + u * KC_THREADS; j[u] = (i < ns) ? id[i] : -1; }
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = (j[u] >= 0) ? sc[j[u]] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) pk += (double)v[u];
+  }
+  if (vec_scores) {
+    const float4* sc4 = (const float4*)sc;
+    const int n4 = Ns >> 2;
+    for (int i0 = tid; i0 < n4; i0 += 8 * KC_THREADS) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) { const int i = i0 + u * KC_THREADS; v[u] = (i < n4) ? sc4[i] : make_float4(0.f, 0.f, 0.f, 0.f); }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ptot += ((double)v[u].x + (double)v[u].y) + ((double)v[u].z + (double)v[u].w);
+    }
+  } else {
+    for (int i = tid; i < Ns; i += KC_THREADS) ptot += (double)sc[i];
+  }
+  for (int off = 32; off > 0; off >>= 1) { pk += __shfl_xor(pk, off); ptot += __shfl_xor(ptot, off); }
+  if (lane == 0) { red[wave] = pk; red2[wave] = ptot; }
+  __syncthreads();
+  if (tid == 0) {
+    const double a_keep = ((red[0] + red[1]) + red[2]) + red[3];
+    const double a_tot = ((red2[0] + red2[1]) + red2[2]) + red2[3];
+    HeadState s;
+    s.a_keep = a_keep; s.a_del = fmax(a_tot - a_keep, 0.0); s.n_keep = n; s.n_del = N - n; s.r_keep = d; s.active = 0;
+    s.k_used = 0; s.pad = 0; s.rcr = 0.f; s.ivn = 0.f;
+    state[head] = s;
+    decided[head] = 1;
+  }
+}
+
 template <bool via_idx>
 __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* __restrict__ Vsrc /*via_idx ? V [heads][N][d] : gathered rows [heads][max_budget][d]*/,
                                                              const float* __restrict__ scores,
@@ -49,10 +215,7 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
                                                              int fro_blocks, int scs, int kvs,
                                                              int want_sums /*0: the demand sums of a certified head (diagnostics only) are left at zero*/) {
   __shared__ __attribute__((aligned(16))) uint32_t stage[2][GS_STAGE_WORDS];
-  __shared__ __attribute__((aligned(16))) float panel[2][KC_D][4];
-  __shared__ float4 ypan[KC_D], lpan[KC_D];
-  __shared__ __attribute__((aligned(16))) float isd[KC_D];
-  __shared__ int s_bad;
+  __shared__ CertShared<KC_D> sh;
   __shared__ double red[KC_THREADS / 64], red2[KC_THREADS / 64];
   const int head = blockIdx.x;
   const int n = n_keep[head];
@@ -60,7 +223,7 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept in a scalar register
   const int lr = lane & 31, lh = lane >> 5;
-  if (tid == 0) decided[head] = 0;
+  if (tid == 0) { decided[head] = 0; sh.bad = 0; }
   if (!(rank > 0 && n > KC_D && n_del > 0)) return;
   const float* sc = scores + (size_t)head * scs;
   const int32_t* id = idx + (size_t)head * max_budget;
@@ -115,8 +278,7 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
   // The demand sums of Eq. 6 (diagnostics of a certified head) need sum(scores[idx]) and sum(scores): their first
   // batch of loads is issued here and consumed after the factorisation, so that its latency is hidden.
   int ej[8];
-  const bool vec_scores = (N & 3) == 0 && ((uintptr_t)sc & 15) == 0;
-  const int ns = want_sums ? n : 0, Ns = want_sums ? N : 0;          // extents of the two sums
+  const int ns = want_sums ? n : 0;
 #pragma unroll
   for (int u = 0; u < 8; ++u) { const int i = tid + u * KC_THREADS; ej[u] = (i < ns) ? id[i] : -1; }
   // tile j is staged in stage[j % 2]; the loads run two tiles ahead in registers
@@ -196,163 +358,128 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
     f2 = (red[0] + red[1]) + (red[2] + red[3]);
     __syncthreads();
   }
-  // Symmetric diagonal scaling S = D^-1/2 G D^-1/2 (unit diagonal): G - mu I is positive definite iff S - mu D^-1 is,
-  // and the scaled matrix no longer carries the spread of the channel magnitudes (a few outlier channels otherwise
-  // own the trace, and with it the rounding allowance, while lambda_min sits in the small ones).
   const double thr_rel = (double)max(n, KC_D) * 1.1920928955078125e-07;
-  const float mu = (float)(thr_rel * thr_rel * f2);
+  cert_factor<KC_D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), sh);
+  __syncthreads();
+  const bool ok = (sh.bad == 0);
+  if (!ok) return;
+
+  double pk = 0.0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) pk += (double)ev[u];
+  cert_settle(pk, tid + 8 * KC_THREADS, sc, id, n, N, want_sums, KC_D, head, state, decided, red, red2);
+}
+
+// The same for the other shapes (fp32 caches, head_dim 64): the Gram matrix by v_mfma_f32_32x32x2_f32 straight from the gathered rows - the
+// operand's lane l holds row l / 32 of a pair and column l % 32, which is how rows lie in memory - a wave per tile or three, the next
+// KF_PAIRS row pairs in flight.  A column whose sum of squares leaves single precision's comfortable range is not certified.
+// Bound by the latency of the factorisation's D / 4 steps.  96 heads, 205 rows of 64 fp32 values: 20 us, and 5 for the exact basis
+// kernel, which then finds nothing to do (80 with every head in it).
+constexpr int KF_PAIRS = 8;
+constexpr float kCertMinSquare = 1e-30f, kCertMaxSquare = 1e30f;
+
+template <typename T, int D>
+__global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert_rows(const T* __restrict__ Vsrc /*gathered rows [heads][max_budget][d]*/,
+                                                                  const float* __restrict__ scores, const int32_t* __restrict__ idx,
+                                                                  const int32_t* __restrict__ n_keep, int N, int max_budget, int rank,
+                                                                  HeadState* __restrict__ state, int32_t* __restrict__ decided, int scs,
+                                                                  int want_sums) {
+  __shared__ CertShared<D> sh;
+  __shared__ double red[KC_WAVES], red2[KC_WAVES];
+  const int head = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = n_keep[head];
+  if (tid == 0) { decided[head] = 0; sh.bad = 0; }
+  if (!(rank > 0 && n > D && N - n > 0)) return;
+  const int lr = lane & 31, lh = lane >> 5;
+  const T* Vh = Vsrc + (size_t)head * max_budget * D;
+  const int cap = max(KC_MINROWS, n >> 2);
+  const int stride = (n + cap - 1) / cap;
+  const int rows = (n + stride - 1) / stride;
+  int trb[3] = {0, 0, 0}, tcb[3] = {0, 0, 0}, nt;
+  if constexpr (D == 128) wave_tiles(wave, trb, tcb, nt);
+  else { nt = wave < 3 ? 1 : 0; trb[0] = wave > 0 ? 1 : 0; tcb[0] = wave > 1 ? 1 : 0; }      // (0,0), (1,0), (1,1)
+  constexpr int NT = D == 128 ? 3 : 1;
+  f32x16 acc[3];
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+  if (nt > 0) {                                                // wave-uniform; no barrier inside
+    float a[2][NT][KF_PAIRS], b[2][NT][KF_PAIRS];
+    auto fetch = [&](const int buf, const int r0) {
+#pragma unroll
+      for (int p = 0; p < KF_PAIRS; ++p) {
+        const int r = r0 + 2 * p + lh;
+        const T* row = Vh + (size_t)min(r * stride, n - 1) * D + lr;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const float x = Elem<T>::load(row + trb[t] * 32), y = Elem<T>::load(row + tcb[t] * 32);
+          a[buf][t][p] = r < rows ? x : 0.f;                   // rows past the subset add nothing, whatever they hold
+          b[buf][t][p] = r < rows ? y : 0.f;
+        }
+      }
+    };
+    auto sum = [&](const int buf) {
+#pragma unroll
+      for (int p = 0; p < KF_PAIRS; ++p)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[buf][t][p], b[buf][t][p], acc[t], 0, 0, 0);
+    };
+    fetch(0, 0);
+    for (int r0 = 0; r0 < rows; r0 += 4 * KF_PAIRS) {
+      fetch(1, r0 + 2 * KF_PAIRS);
+      sum(0);
+      fetch(0, r0 + 4 * KF_PAIRS);
+      sum(1);
+    }
+  }
+  // ||V_keep||_F^2: the trace where every row is in G, else a sum over all rows
+  const bool has_diag = ((lr & 7) >> 2) == lh;
+  const int di = (lr >> 3) * 4 + (lr & 3);
+  double part = 0.0;
+  bool out = false;
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     if (t < nt && trb[t] == tcb[t] && has_diag) {
       float v = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) if (i == di) v = acc[t][i];
-      isd[tcb[t] * 32 + lr] = __builtin_amdgcn_rsqf(v);            // a zero column gives inf, then NaN pivots: not certified
+      part += (double)v;
+      out |= !(v > kCertMinSquare && v < kCertMaxSquare);
     }
   }
+  if (stride > 1) {
+    part = 0.0;
+#pragma unroll 8
+    for (int e = tid; e < n * D; e += KC_THREADS) { const float v = Elem<T>::load(Vh + e); part += (double)v * v; }
+  }
+  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+  if (lane == 0) red[wave] = part;
+  __syncthreads();                                             // (sh.bad is zero from here)
+  if (out) sh.bad = 1;
+  const double f2 = (red[0] + red[1]) + (red[2] + red[3]);
+  const double thr_rel = (double)n * 1.1920928955078125e-07;   // n > D
+  cert_factor<D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), sh);
   __syncthreads();
-#pragma unroll
-  for (int t = 0; t < 3; ++t) {
-    if (t < nt) {
-      const float sc_col = isd[tcb[t] * 32 + lr];
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const float4 sr = *(const float4*)&isd[trb[t] * 32 + i4 * 8 + lh * 4];
-        acc[t][4 * i4 + 0] *= sr.x * sc_col; acc[t][4 * i4 + 1] *= sr.y * sc_col;
-        acc[t][4 * i4 + 2] *= sr.z * sc_col; acc[t][4 * i4 + 3] *= sr.w * sc_col;
-      }
-      if (trb[t] == tcb[t] && has_diag) {
-        const float shift = fmaf(mu, sc_col * sc_col, kCertErr * (float)KC_D);   // mu / G_jj + allowance relative to trace(S) = d
-#pragma unroll
-        for (int i = 0; i < 16; ++i) if (i == di) acc[t][i] -= shift;
-      }
-    }
-  }
-
-  // ---- LDL^T of G - mu I in registers, four columns per step.  panel[s & 1][row] holds columns 4s .. 4s+3 of
-  // the current matrix when step s starts.  Thread r < 128 factors the 4x4 diagonal block (the same arithmetic in
-  // every thread, so no broadcast) and turns panel row r into y = L d (a 4-term forward substitution) and L; after a
-  // second barrier every wave applies the rank-4 update to its tiles: first to the one tile (per wave) that holds
-  // the next four columns, which are then published, then to the rest, so the chain block -> next block only
-  // contains one tile update.  A non-positive pivot sets a flag (no early exit: the steps stay free of
-  // divergent control flow); entries above the diagonal are carried along and never read.
-  f32x16 (&g)[3] = acc;
-  auto publish = [&](int k) {                         // columns k .. k+3 (k % 4 == 0) -> panel[(k / 4) & 1]
-    const int kb = k >> 5, kc = k & 31;
-    float* pw = &panel[(k >> 2) & 1][0][0];
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      if (t < nt && tcb[t] == kb && (lr & ~3) == kc) {
-        const int c = lr & 3;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) pw[(trb[t] * 32 + (i >> 2) * 8 + lh * 4 + (i & 3)) * 4 + c] = g[t][i];
-      }
-    }
-  };
-  if (tid == 0) s_bad = 0;
-  publish(0);
-  for (int k = 0; k < KC_D; k += 4) {
-    __syncthreads();                                   // this panel visible; ypan / lpan free again
-    if (tid < KC_D) {
-      const float4* pr = (const float4*)&panel[(k >> 2) & 1][0][0];
-      // 4x4 diagonal block: rows k .. k+3, lower triangle
-      const float4 r0 = pr[k], r1 = pr[k + 1], r2 = pr[k + 2], r3 = pr[k + 3];
-      const float4 x = pr[tid];
-      const float d0 = r0.x;
-      const float i0 = __builtin_amdgcn_rcpf(d0);
-      const float l10 = r1.x * i0, l20 = r2.x * i0, l30 = r3.x * i0;
-      const float d1 = fmaf(-l10, r1.x, r1.y);
-      const float i1 = __builtin_amdgcn_rcpf(d1);
-      const float l21 = fmaf(-l20, r1.x, r2.y) * i1, l31 = fmaf(-l30, r1.x, r3.y) * i1;
-      const float y21 = l21 * d1, y31 = l31 * d1;
-      const float d2 = fmaf(-l21, y21, fmaf(-l20, r2.x, r2.z));
-      const float i2 = __builtin_amdgcn_rcpf(d2);
-      const float l32 = fmaf(-l31, y21, fmaf(-l30, r2.x, r3.z)) * i2;
-      const float y32 = l32 * d2;
-      const float d3 = fmaf(-l32, y32, fmaf(-l31, y31, fmaf(-l30, r3.x, r3.w)));
-      const float i3 = __builtin_amdgcn_rcpf(d3);
-      if (!((d0 > 0.f) && (d1 > 0.f) && (d2 > 0.f) && (d3 > 0.f))) s_bad = 1;
-      // y = L d of panel row x: y0 = x0, y1 = x1 - y0 l10, y2 = x2 - y0 l20 - y1 l21, y3 = x3 - y0 l30 - y1 l31 - y2 l32
-      const float y0 = x.x;
-      const float y1 = fmaf(-y0, l10, x.y);
-      const float y2 = fmaf(-y1, l21, fmaf(-y0, l20, x.z));
-      const float y3 = fmaf(-y2, l32, fmaf(-y1, l31, fmaf(-y0, l30, x.w)));
-      ypan[tid] = make_float4(y0, y1, y2, y3);
-      lpan[tid] = make_float4(y0 * i0, y1 * i1, y2 * i2, y3 * i3);
-    }
-    __syncthreads();
-    const int kb = k >> 5;
-    const int kbn = (k + 4) >> 5;                      // column block of the next four columns
-    // rank-4 update of a tile on the matrix cores in fp32: G_tile -= Y_rows (32 x 4) * L_cols^T (4 x 32), two
-    // v_mfma_f32_32x32x2_f32 (A: lane l holds row l%32, k = l/32; B: k = l/32, column l%32)
-    auto update = [&](int t) {
-      const float* yp = (const float*)ypan + (trb[t] * 32 + lr) * 4 + lh;
-      const float* lp = (const float*)lpan + (tcb[t] * 32 + lr) * 4 + lh;
-      const float y0 = -yp[0], y1 = -yp[2], l0 = lp[0], l1 = lp[2];
-      g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0, l0, g[t], 0, 0, 0);
-      g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1, l1, g[t], 0, 0, 0);
-    };
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-      if (t < nt && tcb[t] == kbn && tcb[t] >= kb) update(t);
-    if (k + 4 < KC_D) publish(k + 4);
-#pragma unroll
-    for (int t = 0; t < 3; ++t)
-      if (t < nt && tcb[t] != kbn && tcb[t] >= kb) update(t);
-  }
-  __syncthreads();
-  const bool ok = (s_bad == 0);
-  if (!ok) return;
-
-  // certified: r = d, OBF is the identity on this head; fill in the demand sums (Eq. 6) for the diagnostics
-  double pk = 0.0, ptot = 0.0;
-#pragma unroll
-  for (int u = 0; u < 8; ++u) pk += (double)ev[u];
-  for (int i0 = tid + 8 * KC_THREADS; i0 < ns; i0 += 8 * KC_THREADS) {      // further batches of index -> score loads
-    int j[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) { const int i = i0 + u * KC_THREADS; j[u] = (i < ns) ? id[i] : -1; }
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = (j[u] >= 0) ? sc[j[u]] : 0.f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) pk += (double)v[u];
-  }
-  if (vec_scores) {
-    const float4* sc4 = (const float4*)sc;
-    const int n4 = Ns >> 2;
-    for (int i0 = tid; i0 < n4; i0 += 8 * KC_THREADS) {
-      float4 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) { const int i = i0 + u * KC_THREADS; v[u] = (i < n4) ? sc4[i] : make_float4(0.f, 0.f, 0.f, 0.f); }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) ptot += ((double)v[u].x + (double)v[u].y) + ((double)v[u].z + (double)v[u].w);
-    }
-  } else {
-    for (int i = tid; i < Ns; i += KC_THREADS) ptot += (double)sc[i];
-  }
-  for (int off = 32; off > 0; off >>= 1) { pk += __shfl_xor(pk, off); ptot += __shfl_xor(ptot, off); }
-  if (lane == 0) { red[wave] = pk; red2[wave] = ptot; }
-  __syncthreads();
-  if (tid == 0) {
-    const double a_keep = ((red[0] + red[1]) + red[2]) + red[3];
-    const double a_tot = ((red2[0] + red2[1]) + red2[2]) + red2[3];
-    HeadState s;
-    s.a_keep = a_keep; s.a_del = fmax(a_tot - a_keep, 0.0); s.n_keep = n; s.n_del = n_del; s.r_keep = KC_D; s.active = 0;
-    s.k_used = 0; s.pad = 0; s.rcr = 0.f; s.ivn = 0.f;
-    state[head] = s;
-    decided[head] = 1;
-  }
+  if (sh.bad) return;
+  cert_settle(0.0, tid, scores + (size_t)head * scs, idx + (size_t)head * max_budget, n, N, want_sums, D, head, state, decided, red, red2);
 }
 
-bool keep_cert_supported(const Dims& m) { return m.dtype == OBF_BF16 && m.d == KC_D; }
+// (no head retains more than head_dim rows under a smaller max_budget: nothing to certify)
+bool keep_cert_supported(const Dims& m, int max_budget) { return max_budget > m.d; }
 
 obf_status_t launch_keep_cert(const Dims& m, const void* Vsrc, int via_idx, const float* scores, const int32_t* idx,
                               const int32_t* n_keep, int32_t max_budget, int32_t rank, HeadState* state,
                               int32_t* decided, hipStream_t st, const double* fro_part, bool want_sums) {
   const int fro_blocks = (max_budget + kGatherRows - 1) / kGatherRows;
   { ProfScope prof_(ST_KEEP_CERT, st);
-    if (via_idx)
+#define OBF_KC_ROWS(T, D) hipLaunchKernelGGL((k_bf_keep_cert_rows<T, D>), dim3(m.heads), dim3(KC_THREADS), 0, st, (const T*)Vsrc, scores, idx, \
+                                             n_keep, m.N, max_budget, rank, state, decided, m.scs, want_sums ? 1 : 0)
+    if (m.dtype == OBF_F32) { if (m.d == 128) OBF_KC_ROWS(float, 128); else OBF_KC_ROWS(float, 64); }
+    else if (m.d == 64) OBF_KC_ROWS(uint16_t, 64);
+#undef OBF_KC_ROWS
+    else if (via_idx)
       hipLaunchKernelGGL(k_bf_keep_cert<true>, dim3(m.heads), dim3(KC_THREADS), 0, st, (const uint16_t*)Vsrc, scores, idx,
                          n_keep, m.N, max_budget, rank, state, decided, fro_part, fro_blocks, m.scs, m.kvs, want_sums ? 1 : 0);
     else

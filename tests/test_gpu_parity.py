@@ -442,6 +442,27 @@ def test_rank_deficient_large_budget_uses_partial_gram_sums(gpu):
     assert sum(r.r_keep < 128 for r in reps) == 8 and sum(r.r_keep == 128 for r in reps) == 2
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_full_rank_decision_of_fp32_and_half_width_heads(gpu, dtype, d):
+    """Just above head_dim, around a batch of row pairs, every row in the decision's Gram matrix (512) and every second one (513, 700);
+    the second half of the heads repeats 20 + h distinct rows, one of them with a single free direction missing."""
+    half = [d + 1, d + 31, 255 + d // 64, 512, 513, 700]
+    budgets = half + half
+    cfg = si.RelayConfig("fullrank", 23, 1, len(budgets), 1, d, 1100, 8, 0, 3, dtype, "structured", outlier_frac=0.01)
+
+    def edit(K, V, Q):
+        N = V.shape[2]
+        for h in range(len(half), 2 * len(half)):
+            if h == 2 * len(half) - 1:
+                V[0, h, :, 3] = V[0, h, :, 2]                  # rank d - 1, exactly
+                continue
+            V[0, h] = np.where((np.arange(N) % 97 == 5)[:, None], V[0, h], V[0, h, :20 + h].copy()[np.arange(N) % (20 + h)])
+
+    reps = _check_cfg(gpu, cfg, budgets=budgets, max_budget=max(budgets), edit=edit)
+    assert all(r.r_keep == d for r in reps[2: len(half)]) and all(r.r_keep < d for r in reps[len(half):] if r.r_keep is not None)
+    assert reps[-1].r_keep == d - 1
+
+
 def test_few_active_heads_among_many_certified_ones(gpu):
     """256 heads of 16K tokens with budgets above head_dim, twelve of them rank-deficient: the certificate settles the
     other 244, and the statistics launch (whose full grid would be 4096 workgroups) finds the twelve on the device, in

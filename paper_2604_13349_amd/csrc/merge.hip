@@ -220,11 +220,20 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_unroute_kept(const int32_t* _
   if (t < n_keep[head] && t < max_budget) route[(size_t)head * N + idx[(size_t)head * max_budget + t]] = -1;
 }
 
-// Deleted tokens sorted by slot, one workgroup per head: offs[slot] .. offs[slot + 1] of `order` lists the tokens of a slot, in no
-// particular order within it (the merge sorts its own, short, list).
+// Deleted tokens sorted by slot, one workgroup per head: entries offs[slot] .. offs[slot + 1] of `order` list the tokens of a slot with
+// their weights, in no particular order within it (the merge sorts its own, short, list).  The weight is worked out here, a thread per
+// token: in the merge it would cost every slot's wave a double-precision division and two more reads in its chain.
+struct MgEntry { int32_t tok; float w; };
+
+// A_j / (A_t + eps), rounded once; the Per-token alternative weighs by A_j itself
+__device__ __forceinline__ float mg_weight(float aj, float at, bool per_token) { return per_token ? aj : (float)((double)aj / ((double)at + kEps)); }
+
+constexpr int MB_AHEAD = 4;              // tokens of a thread whose reads travel together
 constexpr int MB_THREADS = 1024;
-__global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restrict__ route, const int32_t* __restrict__ n_keep, int N,
-                                                          int max_budget, int32_t* __restrict__ order /*[heads][hstride]*/,
+__global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restrict__ route, const int32_t* __restrict__ n_keep,
+                                                          const int32_t* __restrict__ idx, const float* __restrict__ scores, int N, int scs,
+                                                          int max_budget, int per_token,
+                                                          int32_t* __restrict__ order /*[heads][hstride]: N entries, then the offsets*/,
                                                           size_t hstride) {
   extern __shared__ int cnt[];                                 // [n_keep] counts, then running positions
   __shared__ int wsum[MB_THREADS / 64];
@@ -232,8 +241,10 @@ __global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restr
   const int nk = min(n_keep[head], max_budget);
   if (nk <= 0) return;
   const int32_t* rt = route + (size_t)head * N;
-  int32_t* ord = order + (size_t)head * hstride;
-  int32_t* offs = ord + N;                                     // [n_keep + 1]
+  const int32_t* id = idx + (size_t)head * max_budget;
+  const float* sc = scores + (size_t)head * scs;
+  MgEntry* ord = (MgEntry*)(order + (size_t)head * hstride);   // hstride is even
+  int32_t* offs = (int32_t*)(ord + N);                         // [n_keep + 1]
   for (int i = tid; i < nk; i += MB_THREADS) cnt[i] = 0;
   __syncthreads();
   for (int j = tid; j < N; j += MB_THREADS) { const int r = rt[j]; if (r >= 0) atomicAdd(&cnt[r], 1); }
@@ -252,7 +263,21 @@ __global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restr
     __syncthreads();
   }
   if (tid == 0) offs[nk] = carry;
-  for (int j = tid; j < N; j += MB_THREADS) { const int r = rt[j]; if (r >= 0) ord[atomicAdd(&cnt[r], 1)] = j; }
+  for (int j0 = tid; j0 < N; j0 += MB_AHEAD * MB_THREADS) {
+    int r[MB_AHEAD];
+    float aj[MB_AHEAD], at[MB_AHEAD];
+#pragma unroll
+    for (int u = 0; u < MB_AHEAD; ++u) {
+      const int j = min(j0 + u * MB_THREADS, N - 1);
+      r[u] = j == j0 + u * MB_THREADS ? rt[j] : -1;
+      aj[u] = sc[j];
+    }
+#pragma unroll
+    for (int u = 0; u < MB_AHEAD; ++u) at[u] = sc[id[max(r[u], 0)]];
+#pragma unroll
+    for (int u = 0; u < MB_AHEAD; ++u)
+      if (r[u] >= 0) ord[atomicAdd(&cnt[r[u]], 1)] = MgEntry{j0 + u * MB_THREADS, mg_weight(aj[u], at[u], per_token != 0)};
+  }
 }
 
 // The same per-slot sums serve the Per-token alternative of App. D (PER_TOKEN; the reading: the deleted tokens are shared
@@ -266,9 +291,10 @@ __global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restr
 // sum in registers (a lane owns D / 64 columns): the order of the additions is fixed, so the result is the same on every run.  A list of
 // up to MG_LIST tokens is put in order first (every entry counts the smaller ones); a longer one is not: the head's routes are scanned
 // instead, which finds the slot's tokens in order.  Sixteen rows are in flight at a time.  Slots that received nothing are left as the
-// bit copies the gather wrote.  Bound by a wave's instructions per token and its chain offsets - list - masses - rows (nine tokens a
-// slot here), then by the pass over V: 77 us on 288 heads x 2048 tokens x 205 slots, and 7 for the lists; 99 with eight rows ahead and
-// every lane read waited for by itself, 157 with four slots per wave, 247 with each wave scanning all routes.
+// bit copies the gather wrote.  Bound by a wave's instructions per token and its chain offsets - list - rows (nine tokens a
+// slot here; the offsets' read does not wait for n_keep, nor the store for the slot's own value), then by the pass over V: 60 us on 288
+// heads x 2048 tokens x 205 slots, and 9 for the lists; 78 and 7 with the weights worked out here, 99 with eight rows ahead and every lane
+// read waited for by itself, 157 with four slots per wave, 247 with each wave scanning all routes.
 constexpr int MG_LIST = 256;
 constexpr int MG_AHEAD = 16;
 
@@ -289,11 +315,16 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V
                                                          int no_scaling) {
   constexpr int CPL = D / 64;
   typedef LaneCols<T, CPL> LC;
-  __shared__ int list[MG_THREADS / 64][MG_LIST];
+  __shared__ MgEntry list[MG_THREADS / 64][MG_LIST];
   __shared__ float cb[PER_TOKEN ? 16 : 1][MG_D];               // the rows of C
   const int head = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int slot = blockIdx.x * (MG_THREADS / 64) + wave;
+  const MgEntry* ord = (const MgEntry*)(order + (size_t)head * hstride);
+  const int32_t* offs = (const int32_t*)(ord + N);
   const int nk = min(n_keep[head], max_budget);
+  const int at0 = min(slot, N);                                // the reads do not wait for n_keep; the workspace holds N + 1 offsets and more
+  const int off = offs[at0], end = offs[at0 + 1];
   int kc = 0;
   float pt_scale = 0.f;
   if (PER_TOKEN) {
@@ -305,21 +336,19 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V
     pt_scale = (float)((double)hs.n_keep * (no_scaling ? 1.0 : hs.a_del / (hs.a_keep + kEps)) / (hs.a_del + kEps));
     __syncthreads();
   }
-  const int slot = blockIdx.x * (MG_THREADS / 64) + wave;
   if (slot >= nk) return;                                      // whole wave (no barrier below)
-  const int32_t* ord = order + (size_t)head * hstride;
-  const int off = ord[N + slot], len = ord[N + slot + 1] - off;
+  const int len = end - off;
   if (len <= 0) return;
-  const float* sc = scores + (size_t)head * scs;
   const T* Vh = V + (size_t)head * kvs * D + lane * CPL;
-  const double a_slot = PER_TOKEN ? 0.0 : (double)sc[idx[(size_t)head * max_budget + slot]] + kEps;
+  T* o = V_out + ((size_t)head * max_budget + slot) * D + lane * CPL;
+  float old[CPL];                                              // the slot's own value, read beside the list
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) old[c] = Elem<T>::load(o + c);
   float acc[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
   // the rows of the tokens that the first `n` lanes hold, added in lane order
-  auto add_rows = [&](const int n, const int tok) {
-    float w = 0.f;
-    if (lane < n) w = PER_TOKEN ? sc[tok] : (float)((double)sc[tok] / a_slot);
+  auto add_rows = [&](const int n, const int tok, const float w) {
     for (int i0 = 0; i0 < n; i0 += MG_AHEAD) {
       typename LC::type v[MG_AHEAD];
 #pragma unroll
@@ -340,38 +369,39 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V
     }
   };
   if (len <= MG_LIST) {
-    const int32_t* src = ord + off;
-    int* dst = list[wave];
+    const MgEntry* src = ord + off;
+    MgEntry* dst = list[wave];
     for (int i0 = 0; i0 < len; i0 += 64) {
-      const int mine = (i0 + lane < len) ? src[i0 + lane] : 0x7fffffff;
+      const MgEntry mine = (i0 + lane < len) ? src[i0 + lane] : MgEntry{0x7fffffff, 0.f};
       int rank = 0;
       for (int q0 = 0; q0 < len; q0 += 64) {
-        const int other = (q0 + lane < len) ? src[q0 + lane] : 0x7fffffff;
+        const int other = (q0 == i0) ? mine.tok : (q0 + lane < len) ? src[q0 + lane].tok : 0x7fffffff;
         const int n = min(64, len - q0);
         for (int q = 0; q < n; q += 8) {                       // lane reads ahead of their uses; past the end the entries are never smaller
           int k[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u) k[u] = __builtin_amdgcn_readlane(other, q + u);
 #pragma unroll
-          for (int u = 0; u < 8; ++u) rank += (k[u] < mine) ? 1 : 0;
+          for (int u = 0; u < 8; ++u) rank += (k[u] < mine.tok) ? 1 : 0;
         }
       }
       if (i0 + lane < len) dst[rank] = mine;
     }
     __builtin_amdgcn_wave_barrier();
-    for (int i0 = 0; i0 < len; i0 += 64) add_rows(min(64, len - i0), dst[min(i0 + lane, len - 1)]);
+    for (int i0 = 0; i0 < len; i0 += 64) { const MgEntry e = dst[min(i0 + lane, len - 1)]; add_rows(min(64, len - i0), e.tok, e.w); }
   } else {
     const int32_t* rt = route + (size_t)head * N;
+    const float* sc = scores + (size_t)head * scs;
+    const float at = PER_TOKEN ? 0.f : sc[idx[(size_t)head * max_budget + slot]];
     for (int base = 0; base < N; base += 64) {
       const int j = base + lane;
       uint64_t mask = __ballot(j < N && rt[min(j, N - 1)] == slot);
       const int n = __popcll(mask);
       int tok = 0;
       for (int i = 0; i < n; ++i) { const int b = __builtin_ctzll(mask); mask &= mask - 1; if (lane == i) tok = base + b; }
-      if (n) add_rows(n, tok);
+      if (n) add_rows(n, tok, lane < n ? mg_weight(sc[tok], at, PER_TOKEN) : 0.f);
     }
   }
-  T* o = V_out + ((size_t)head * max_budget + slot) * D + lane * CPL;
   if (PER_TOKEN) {
     float dsum[CPL];
 #pragma unroll
@@ -385,10 +415,10 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V
       for (int c = 0; c < CPL; ++c) dsum[c] = fmaf(g, cb[i][lane * CPL + c], dsum[c]);
     }
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) Elem<T>::store(o + c, fmaf(pt_scale, dsum[c], Elem<T>::load(o + c)));
+    for (int c = 0; c < CPL; ++c) Elem<T>::store(o + c, fmaf(pt_scale, dsum[c], old[c]));
   } else {
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) Elem<T>::store(o + c, Elem<T>::load(o + c) + acc[c]);
+    for (int c = 0; c < CPL; ++c) Elem<T>::store(o + c, old[c] + acc[c]);
   }
 }
 
@@ -408,8 +438,8 @@ static obf_status_t run_merge(const Dims& m, const Workspace& w, char* ws, const
   }
   float* inv_norm = (float*)(ws + w.inv_norm);
   int32_t* route = route_out ? route_out : (int32_t*)(ws + w.route);
-  // the tokens by slot and the slots' offsets, N + n_keep + 1 <= 2 N + 1 numbers a head, lie where the statistics of the deleted values
-  // are during a back-fill (over 4 N a head): done with by now
+  // the tokens by slot with their weights and the slots' offsets, 2 N + n_keep + 1 <= 3 N + 1 numbers a head (the merge's early read of the
+  // offsets goes to 3 N + 2), lie where the statistics of the deleted values are during a back-fill (over 4 N a head): done with by now
   int32_t* order = (int32_t*)(ws + w.gram_part);
   const size_t hstride = (size_t)w.nstat * gram_stride(m.d);
   const bool bf = m.dtype == OBF_BF16;
@@ -439,7 +469,7 @@ static obf_status_t run_merge(const Dims& m, const Workspace& w, char* ws, const
     (void)hipFuncSetAttribute((const void*)k_mg_bucket, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(int) * kMaxTokens);
   });
   hipLaunchKernelGGL(k_mg_bucket, dim3(m.heads), dim3(MB_THREADS), sizeof(int) * (size_t)(max_budget < m.N ? max_budget : m.N), st, route,
-                     n_keep, m.N, max_budget, order, hstride);
+                     n_keep, idx, scores, m.N, m.scs, max_budget, per_token ? 1 : 0, order, hstride);
   if (check_launch("merge bucket") != OBF_OK) return OBF_ERR_HIP;
   dim3 gm((max_budget + MG_THREADS / 64 - 1) / (MG_THREADS / 64), m.heads);
 #define OBF_MG_LAUNCH(T, D, PT) hipLaunchKernelGGL((k_mg_merge<T, D, PT>), gm, dim3(MG_THREADS), 0, st, (const T*)V, scores, idx, n_keep, \

@@ -22,14 +22,18 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int SM_THREADS = 256;
 constexpr int SM_WAVES = 4;
-// The kernels are instantiated for (RB, KBUF) = (4, 3) and (5, 2), the second pass also for (8, 2): RB 32-row blocks of query
-// rows per workgroup (RB * 32 = 128, 160 or 256 rows, their Q operand in RB * 32 registers per lane) and KBUF rotating K
+// The kernels are instantiated for (RB, KBUF) = (4, 3) and (5, 2), the second pass also for (8, 2), the one of short prompts for (1, 4),
+// (2, 3) and (4, 2): RB 32-row blocks of query
+// rows per workgroup (RB * 32 = 32 to 256 rows, their Q operand in RB * 32 registers per lane) and KBUF rotating K
 // fragment buffers.  RB * KBUF is even, so the two accumulators keep alternating across the iterations of the tile loop.
 constexpr int SM_D = 128;
 constexpr int SM_KK = SM_D / 16;         // MFMA k-steps
 constexpr int SM_TILE = 32;              // tokens per MFMA tile
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kScoreOneLaunchTokens = 768;   // prompts up to this length take both score passes in one launch (a tie with two launches near 1024)
+// Prompts that take both score passes in one launch, a workgroup per head (128 rows, us, one launch against two): 288 heads 36 - 40 at 768
+// tokens, 44 - 49 at 1024, 52 - 55 at 1280, 60 - 60 at 1536; 96 heads 20 - 33 at 768, 27 - 38 at 1280; 32 heads, which leave most of the
+// chip idle, 20 - 19 at 768 and 23 - 20 at 1024.
+constexpr int kScoreOneLaunchTokens = 768, kScoreOneLaunchTokensMany = 1280, kScoreOneLaunchMany = 96;
 
 union Frag { uint4 u; bf16x8 v; };
 
@@ -141,7 +145,7 @@ __device__ __forceinline__ void stats_block_ragged(const f32x16& acc, float& m, 
 // complete after its last row block.
 // Up to five row blocks their b2 stay in registers; more (NRB > 5) leave no room and are read from LDS.  Their two halves
 // are summed apart and added last, as k_score_sum_groups adds two row groups: the same mass to the last bit.
-template <int NRB>
+template <int NRB, bool LDS = (NRB > 5)>
 struct MassEp {
   const float* b2;       // registers [NRB][16], or LDS [NRB * 32]
   float a2;
@@ -153,7 +157,7 @@ struct MassEp {
     if (RB == 0) { c0 = 0.f; c1 = 0.f; c2 = 0.f; c3 = 0.f; }
 #pragma unroll
     for (int i = 0; i < 16; i += 4) {
-      const float4 b = (NRB > 5) ? *(const float4*)(b2 + RB * 32 + 2 * i + (lane >> 5) * 4)
+      const float4 b = LDS ? *(const float4*)(b2 + RB * 32 + 2 * i + (lane >> 5) * 4)
                                  : make_float4(b2[RB * 16 + i], b2[RB * 16 + i + 1], b2[RB * 16 + i + 2], b2[RB * 16 + i + 3]);
       c0 += fast_exp2(fmaf(acc[i], a2, -b.x));
       c1 += fast_exp2(fmaf(acc[i + 1], a2, -b.y));
@@ -394,13 +398,17 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_
 // workgroup per head keeps Q in registers, takes the row maxima and sums over the head's tokens, forms the row
 // log-sum-exp in LDS and walks the same tokens again, backwards, for the masses.  Same arithmetic, in the same order, as
 // the two launches make of a head that lies inside one range.
+// Bound by latency (Q, the first tiles, the fold between the passes).  Two workgroups share a compute unit: two K buffers instead of three
+// and the normalisers in LDS bring a wave to 256 registers.  288 heads, 128 rows, of 256, 340, 512 and 768 tokens: 21, 24, 28 and 36 us; with one
+// workgroup per compute unit, 256 heads and then 32, 25, 31, 36 and 44.  As many row blocks as there are rows
+// for: 32 rows of 256 and 700 tokens 11 and 25 us where four blocks took 22 and 40.
 template <int RB, int KBUF>
-__global__ __launch_bounds__(SM_THREADS, 1) void k_score_head_mfma(const uint16_t* __restrict__ K,
+__global__ __launch_bounds__(SM_THREADS, 2) void k_score_head_mfma(const uint16_t* __restrict__ K,
                                                                    const uint16_t* __restrict__ Q,
                                                                    double* __restrict__ row_lse, float* __restrict__ out,
                                                                    int N, int R, long kstride) {
   __shared__ double s_m[SM_WAVES][(RB * 32)], s_l[SM_WAVES][(RB * 32)];
-  __shared__ double s_lse[(RB * 32)];
+  __shared__ __attribute__((aligned(16))) float s_b2[(RB * 32)];
   const int head = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float a2 = kLog2e / sqrtf((float)SM_D);
@@ -457,15 +465,11 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_head_mfma(const uint16_
       lse = M * 0.6931471805599453 + log(L);                   // log2 units -> natural log
       row_lse[(size_t)head * R + row] = lse;
     }
-    s_lse[row] = lse;
+    s_b2[row] = (float)(lse * 1.4426950408889634);
   }
   __syncthreads();
-  float b2[RB * 16];
-#pragma unroll
-  for (int i = 0; i < RB * 16; ++i)
-    b2[i] = (float)(s_lse[(i >> 4) * 32 + ((i & 15) >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] * 1.4426950408889634);
   const int nt = (first < N) ? ((N - first - 1) / STEP + 1) : 0;          // tiles of this wave, the last may be ragged
-  MassEp<RB> ep{b2, a2, dst, N, lane, 0.f, 0.f, 0.f, 0.f};
+  MassEp<RB, true> ep{s_b2, a2, dst, N, lane, 0.f, 0.f, 0.f, 0.f};
   run_tiles<false, RB, KBUF>(Kh, first + (nt - 1) * STEP, -STEP, nt, N, lane, qf, ep);
 }
 
@@ -494,10 +498,15 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
   pt.kstride = (long)m.kvs * SM_D;
   dim3 grid(((w.nranges + 7) / 8) * 8 * RG);
   const bool five = score_rows_per_group(m.R) == 160;     // five row blocks per workgroup, two K buffers (e.g. 320 rows = 2 x 160)
-  if (RG == 1 && !five && m.N <= kScoreOneLaunchTokens) {  // short prompts: both passes in one launch, a workgroup per head
+  if (RG == 1 && !five && m.N <= (m.heads >= kScoreOneLaunchMany ? kScoreOneLaunchTokensMany : kScoreOneLaunchTokens)) {
     ProfScope prof_(ST_SCORE_STATS, st);
-    hipLaunchKernelGGL((k_score_head_mfma<4, 3>), dim3(m.heads), dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
-                       row_lse, scores, m.N, m.R, pt.kstride);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(m.heads), dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, row_lse, scores, m.N, m.R,
+                         pt.kstride);
+    };
+    if (m.R <= 32) go(k_score_head_mfma<1, 4>);
+    else if (m.R <= 64) go(k_score_head_mfma<2, 3>);
+    else go(k_score_head_mfma<4, 2>);
     return check_launch("score, one launch per call (mfma)");
   }
   { ProfScope prof_(ST_SCORE_STATS, st);

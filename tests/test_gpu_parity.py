@@ -255,19 +255,17 @@ def test_scores_of_logits_far_apart(gpu, dtype, d, spread):
     assert bool(torch.isnan(scores).all()) and bool(torch.isnan(lse).all())
 
 
-@pytest.mark.parametrize("R", [161, 255, 256, 481, 512])     # row groups in pairs: the last one ragged, or full
-@pytest.mark.parametrize("L,N", [(1, 33), (1, 333), (6, 4109)])      # less than a wave's tiles each; several tiles, heads split over ranges
-def test_scores_of_paired_row_groups(gpu, R, L, N):
-    """bf16 heads of width 128 whose rows fill an even number of 128-row groups.  A logit is a sum of 128 exact products in float, so
+def _check_masses(gpu, R, L, N, layers):
+    """bf16 heads of width 128 against the oracle.  A logit is a sum of 128 exact products in float, so
     it is off by at most 128 * 2^-24 * |q|.|k| / sqrt(d) in either pass; a term's exponential adds 2^-21, the float sums 2^-19."""
     import torch
     from paper_2604_13349_amd import binding as B
-    cfg = si.RelayConfig("paired", 29, L, 2, 1, 128, N, R, 1, 0, "bf16", "structured", outlier_frac=0.01)
+    cfg = si.RelayConfig("masses", 29, L, 2, 1, 128, N, R, 1, 0, "bf16", "structured", outlier_frac=0.01)
     K, _, Q = si.make_cache(cfg, 0)
     sc, lse = B.score(gpu.to_dev(K, "bf16"), gpu.to_dev(Q, "bf16"))
     torch.cuda.synchronize()
     sc, lse = sc.cpu().numpy(), lse.cpu().numpy()
-    for l in range(L):
+    for l in layers:
         for h in range(2):
             k, q = O.decode(K[l, h], "bf16"), O.decode(Q[l, h], "bf16").reshape(-1, 128)
             off = 128 * 2.0 ** -24 * (np.abs(q) @ np.abs(k).T).max() / np.sqrt(128)
@@ -275,6 +273,20 @@ def test_scores_of_paired_row_groups(gpu, R, L, N):
             S = q @ k.T / np.sqrt(128)
             ref = S.max(1) + np.log(np.exp(S - S.max(1, keepdims=True)).sum(1))
             np.testing.assert_allclose(lse[l, h], ref, rtol=0, atol=off + 2.0 ** -19)
+
+
+@pytest.mark.parametrize("R", [161, 255, 256, 481, 512])     # row groups in pairs: the last one ragged, or full
+@pytest.mark.parametrize("L,N", [(1, 33), (1, 333), (6, 4109)])      # less than a wave's tiles each; several tiles, heads split over ranges
+def test_scores_of_paired_row_groups(gpu, R, L, N):
+    """Rows that fill an even number of 128-row groups."""
+    _check_masses(gpu, R, L, N, range(L))
+
+
+@pytest.mark.parametrize("R", [1, 32, 33, 64, 65, 128])      # one, two and four row blocks
+@pytest.mark.parametrize("L,N", [(1, 1), (1, 31), (1, 129), (1, 161), (2, 767), (2, 769), (8, 2053), (48, 769), (48, 1280), (48, 1281)])
+def test_scores_of_one_row_group(gpu, R, L, N):
+    """Short prompts, a workgroup per head, and those just past them (96 heads: 1280 tokens, fewer: 768)."""
+    _check_masses(gpu, R, L, N, sorted({0, L // 2, L - 1}))
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])

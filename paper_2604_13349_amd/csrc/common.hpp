@@ -112,11 +112,20 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.rgroups = (m.R + score_rows_per_group(m.R) - 1) / score_rows_per_group(m.R);
   w.tiles_per_head = (m.N + 31) / 32;
   {
+    int T = score_tiles_per_range((long)m.heads * w.tiles_per_head, w.rgroups);
+    w.nslot = (int)((w.tiles_per_head + T - 1) / T) + 1;          // (no less for the longer ranges below)
+    // Ranges that end with their head, where that makes them at most a round of tiles longer: a range that goes on into the next head loads
+    // its queries and fills its pipeline again, 5 us a pass.  128 rows, both passes, before and after: 16 heads of 1300, 2500 and 4100 tokens 35, 38
+    // and 42 us, 21, 25 and 29; 120 heads of 1300 and 4100: 43 and 65, 30 and 53; 160 heads would need half as many tiles again and stay.
+    // The head is padded with tiles past its tokens, which take no time.
+    const int per_head = kNumCU / m.heads;
+    if (w.rgroups == 1 && per_head >= 1 && m.dtype == OBF_BF16 && m.d == 128) {
+      const int own = ((w.tiles_per_head + per_head - 1) / per_head + 3) / 4 * 4;
+      if (own <= T + 4) { T = own; w.tiles_per_head = (w.tiles_per_head + T - 1) / T * T; }
+    }
     const long TT = (long)m.heads * w.tiles_per_head;
-    const int T = score_tiles_per_range(TT, w.rgroups);
     w.tiles_per_range = T;
     w.nranges = (int)((TT + T - 1) / T);
-    w.nslot = (int)((w.tiles_per_head + T - 1) / T) + 1;
   }
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };

@@ -42,12 +42,12 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_inv_norm(const T* __restrict_
 // products has, in entry i of lane l, slot s0 + (i/4)*8 + (l/32)*4 + i%4 against token l%32, so the running maximum is kept per lane
 // over slots in ascending order and the two lanes of a token are combined at the end.  Retained tokens are written as -1 here.
 // Bound by the vector work on the tiles (multiply, compare, two selects per entry) beside one pass over K.
-// 58 us on 288 heads x 2048 tokens x 205 slots; 423 us with the slots' rows and norms read from memory by every wave, and two more
+// 56 us on 288 heads x 2048 tokens x 205 slots (59 with three waves per SIMD); 423 us with the slots' rows and norms read from memory by every wave, and two more
 // launches (19 us) for the norms and the retained tokens.
 constexpr int MG_TOK = 256;              // tokens per workgroup
 constexpr int MG_LDB = MG_D * 2 + 16;    // LDS bytes per staged slot row: 16-byte reads of eight consecutive rows use different banks
 
-__global__ __launch_bounds__(MG_THREADS, 3) void k_mg_route_mfma(const uint16_t* __restrict__ K, const uint16_t* __restrict__ K_out,
+__global__ __launch_bounds__(MG_THREADS, 4) void k_mg_route_mfma(const uint16_t* __restrict__ K, const uint16_t* __restrict__ K_out,
                                                                  const int32_t* __restrict__ idx, const int32_t* __restrict__ n_keep,
                                                                  int N, int kvs, int max_budget, int32_t* __restrict__ route) {
   __shared__ __attribute__((aligned(16))) uint8_t stage[2][32 * MG_LDB];

@@ -6,10 +6,10 @@
 // query rows; operand layout in f64_tile.hpp).
 //   pass A: a wave keeps the operand of 16 query rows and walks the tiles of its chunk of tokens (tokens x rows: a lane owns one
 //           query row and keeps its running maximum and sum);
-//   pass B: a wave keeps the operand of 16 tokens and walks all query rows (rows x tokens: a lane owns one token).
+//   pass B: a wave keeps the operand of 16 or 32 tokens and walks all query rows (rows x tokens: a lane owns one token).
 // Bound by the double-precision matrix rate (64 multiply-adds per clock and compute unit: 43 us a pass at the first shape below) and
 // the exponentials, which the same units compute: f64_exp.hpp's, of half the math library's instructions.  96 heads x 2048 tokens x
-// 128 rows at head_dim 64: 88 and 85 us (102 and 88 with the library's exponential).  With the products as scalar multiply-adds fed from
+// 128 rows at head_dim 64: 88 and 79 us (102 and 88 with the library's exponential and a tile of tokens per wave).  With the products as scalar multiply-adds fed from
 // LDS: 975 and 853 us; 2 heads x 512 tokens x 32 rows 224 and 215, now 12 and 6.
 #include "f64_exp.hpp"
 #include "f64_tile.hpp"
@@ -21,20 +21,32 @@ constexpr int GS_WAVES = GS_THREADS / 64;
 constexpr int GS_T = 16;                 // tokens and query rows per tile
 constexpr int GS_MIN_TILES = 2;          // shortest chunk of pass A, in tiles
 constexpr int GS_TARGET_WAVES = 4096;    // waves of pass A that fill the chip (four per SIMD); fewer, longer chunks beyond
+// A wave of pass B takes two tiles of tokens, which share the query operand's reads and conversions, from this many tokens of all heads and query
+// rows on: 96 heads x 2048 x 128 rows 85 -> 79 us, both passes of 40 x 4000 x 64 rows 97 -> 93, of 288 x 2048 x 128 447 -> 433; 96 x 1500 x 128, which
+// then no longer fills the chip evenly, 118 -> 120, and 32 rows gain nothing.
+constexpr long GS_WIDE_TOKENS = 160000;
+constexpr int GS_WIDE_ROWS = 64;
 constexpr int GS_FOLD = 1024;            // partials per head up to which pass B folds them itself (each of its workgroups reads them all;
                                          // a launch of its own costs 5 us)
 
-// 16 x 16 tile of dot products: `moving`, the operand a wave streams, gives the rows of the result, `fixed`, the one it keeps, the
+// NT 16 x 16 tiles of dot products: `moving`, the operand a wave streams, gives the rows of the result, `fixed`, the one it keeps, the
 // columns.  Two chains, so that an instruction does not wait for the one before it.
-template <typename T, int D>
-__device__ __forceinline__ f64x4 tile_product(const double (&fixed)[D / 4], const RowPart<T, D>& moving) {
-  f64x4 a = {0.0, 0.0, 0.0, 0.0}, b = {0.0, 0.0, 0.0, 0.0};
+template <typename T, int D, int NT>
+__device__ __forceinline__ void tile_products(f64x4 (&out)[NT], const double (&fixed)[NT][D / 4], const RowPart<T, D>& moving) {
+  f64x4 a[NT], b[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) { a[t] = f64x4{0.0, 0.0, 0.0, 0.0}; b[t] = a[t]; }
 #pragma unroll
   for (int s = 0; s < D / 4; s += 2) {
-    a = __builtin_amdgcn_mfma_f64_16x16x4f64(moving.at(s), fixed[s], a, 0, 0, 0);
-    b = __builtin_amdgcn_mfma_f64_16x16x4f64(moving.at(s + 1), fixed[s + 1], b, 0, 0, 0);
+    const double x = moving.at(s), y = moving.at(s + 1);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      a[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, fixed[t][s], a[t], 0, 0, 0);
+      b[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(y, fixed[t][s + 1], b[t], 0, 0, 0);
+    }
   }
-  return a + b;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) out[t] = a[t] + b[t];
 }
 
 // Pass A: partial (max, sum exp(logit - max)) per query row over one chunk of tokens.  Wave w of the grid's first dimension takes row
@@ -53,19 +65,21 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_stats_f64(const T* __re
   const int t0 = chunk * chunk_tokens, t1 = min(N, t0 + chunk_tokens);
   const T* Kh = K + (size_t)head * kvs * D;
   const double scale = 1.0 / sqrt((double)D);
-  double q[D / 4];
+  double q[1][D / 4];
   {
     RowPart<T, D> p;
     p.load(Q + ((size_t)head * R + min(row, R - 1)) * D, lane);     // rows past R: the last one again, not written
 #pragma unroll
-    for (int s = 0; s < D / 4; ++s) q[s] = p.at(s);
+    for (int s = 0; s < D / 4; ++s) q[0][s] = p.at(s);
   }
   double m = -INFINITY, l = 0.0;
   RowPart<T, D> cur, nxt;
   cur.load(Kh + (size_t)min(t0 + (lane & 15), N - 1) * D, lane);
   for (int tt = t0; tt < t1; tt += GS_T) {
     nxt.load(Kh + (size_t)min(tt + GS_T + (lane & 15), N - 1) * D, lane);      // clamped: masked below
-    const f64x4 acc = tile_product<T, D>(q, cur);
+    f64x4 dots[1];
+    tile_products<T, D, 1>(dots, q, cur);
+    const f64x4 acc = dots[0];
     double x[4];
     const bool full = tt + GS_T <= t1;                        // uniform; only a chunk's last tile may not be
     if (full) {
@@ -127,9 +141,9 @@ __global__ void k_score_lse(const double* __restrict__ stats_part, double* __res
   row_lse[i] = fold_lse(stats_part + ((size_t)head * nchunk * R + row) * 2, nchunk, (size_t)R * 2);
 }
 
-// Pass B: scores[j] = sum_rows exp(logit - lse[row]).  A workgroup takes 64 tokens of a head, a wave sixteen.  With stats_part the
+// Pass B: scores[j] = sum_rows exp(logit - lse[row]).  A workgroup takes 64 NT tokens of a head, a wave 16 NT.  With stats_part the
 // head's row normalisers are folded here first, by every workgroup alike; the first one writes them out.
-template <typename T, int D>
+template <typename T, int D, int NT>
 __global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __restrict__ K, const T* __restrict__ Q,
                                                                   const double* __restrict__ stats_part /*nullable*/, int nchunk,
                                                                   double* __restrict__ row_lse, float* __restrict__ scores, int N,
@@ -137,11 +151,12 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __res
   extern __shared__ double s_lse[];                           // [R rounded up to 16]
   __shared__ double etab[kExpTab];
   const int head = blockIdx.y, lane = threadIdx.x & 63;
-  const int tok = (blockIdx.x * GS_WAVES + (threadIdx.x >> 6)) * GS_T + (lane & 15);
+  const int tok = (blockIdx.x * GS_WAVES + (threadIdx.x >> 6)) * NT * GS_T + (lane & 15);     // and the 16 behind
   const T* Qh = Q + (size_t)head * R * D;
   const double scale = 1.0 / sqrt((double)D);
-  RowPart<T, D> kp, cur, nxt;
-  kp.load(K + ((size_t)head * kvs + min(tok, N - 1)) * D, lane);        // tokens past the end: the last one again, not written
+  RowPart<T, D> kp[NT], cur, nxt;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) kp[t].load(K + ((size_t)head * kvs + min(tok + t * GS_T, N - 1)) * D, lane);   // tokens past the end: the last one again, not written
   cur.load(Qh + (size_t)min(lane & 15, R - 1) * D, lane);
   for (int r = threadIdx.x; r < (R + GS_T - 1) / GS_T * GS_T; r += GS_THREADS) {
     double lse = INFINITY;                                    // rows past R add exp(-inf) = 0
@@ -157,23 +172,33 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __res
   }
   exp_table(etab, threadIdx.x);
   __syncthreads();
-  double k[D / 4];
+  double k[NT][D / 4], col[NT];
 #pragma unroll
-  for (int s = 0; s < D / 4; ++s) k[s] = kp.at(s);
-  double col = 0.0;
+  for (int t = 0; t < NT; ++t) {
+    col[t] = 0.0;
+#pragma unroll
+    for (int s = 0; s < D / 4; ++s) k[t][s] = kp[t].at(s);
+  }
   for (int r0 = 0; r0 < R; r0 += GS_T) {
     nxt.load(Qh + (size_t)min(r0 + GS_T + (lane & 15), R - 1) * D, lane);
-    const f64x4 acc = tile_product<T, D>(k, cur);
-    double x[4];
+    f64x4 acc[NT];
+    tile_products<T, D, NT>(acc, k, cur);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = fma(acc[i], scale, -s_lse[r0 + (lane >> 4) + 4 * i]);
-    exp_clamp(x);
-    col += (exp_tab(x[0], etab) + exp_tab(x[1], etab)) + (exp_tab(x[2], etab) + exp_tab(x[3], etab));
+    for (int t = 0; t < NT; ++t) {
+      double x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] = fma(acc[t][i], scale, -s_lse[r0 + (lane >> 4) + 4 * i]);
+      exp_clamp(x);
+      col[t] += (exp_tab(x[0], etab) + exp_tab(x[1], etab)) + (exp_tab(x[2], etab) + exp_tab(x[3], etab));
+    }
     cur = nxt;
   }
-  col += __shfl_xor(col, 16);
-  col += __shfl_xor(col, 32);
-  if (lane < 16 && tok < N) scores[(size_t)head * N + tok] = (float)col;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    col[t] += __shfl_xor(col[t], 16);
+    col[t] += __shfl_xor(col[t], 32);
+    if (lane < 16 && tok + t * GS_T < N) scores[(size_t)head * N + tok + t * GS_T] = (float)col[t];
+  }
 }
 
 template <typename T, int D>
@@ -199,9 +224,14 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     if (check_launch("score lse") != OBF_OK) return OBF_ERR_HIP;
   }
   { ProfScope prof_(ST_SCORE_MASS, st);
-    hipLaunchKernelGGL((k_score_mass_f64<T, D>), dim3((m.N + GS_WAVES * GS_T - 1) / (GS_WAVES * GS_T), m.heads), dim3(GS_THREADS),
-                       sizeof(double) * nrb * GS_T, st, (const T*)K, (const T*)Q, fold ? (const double*)stats_part : (const double*)nullptr,
-                       nchunk, row_lse, scores, m.N, m.R, m.kvs); }
+    constexpr int WIDE = D == 64 ? 2 : 1;                     // (two operands of head_dim 128 fill the registers)
+    auto go = [&](auto kernel, const int nt) {
+      const int per_wg = GS_WAVES * GS_T * nt;
+      hipLaunchKernelGGL(kernel, dim3((m.N + per_wg - 1) / per_wg, m.heads), dim3(GS_THREADS), sizeof(double) * nrb * GS_T, st, (const T*)K,
+                         (const T*)Q, fold ? (const double*)stats_part : (const double*)nullptr, nchunk, row_lse, scores, m.N, m.R, m.kvs);
+    };
+    if ((long)m.heads * m.N >= GS_WIDE_TOKENS && m.R >= GS_WIDE_ROWS) go(k_score_mass_f64<T, D, WIDE>, WIDE);
+    else go(k_score_mass_f64<T, D, 1>, 1); }
   return check_launch("score mass (f64)");
 }
 

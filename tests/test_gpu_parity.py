@@ -226,6 +226,21 @@ def test_scores_of_fp32_and_half_width_heads(gpu, dtype, d, N, g, W):
         np.testing.assert_allclose(lse[0, h], ref, rtol=1e-13, atol=1e-13)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,R", [(2001, 64), (2049, 67), (2064, 128), (2079, 80)])     # tokens left to a wave's second tile: none, one to sixteen
+def test_scores_of_many_half_width_heads(gpu, dtype, N, R):
+    """Two tiles of tokens per wave; what is left is half a unit in the stored mass's last place, as with one."""
+    import torch
+    from paper_2604_13349_amd import binding as B
+    cfg = si.RelayConfig("wide64", 31, 40, 2, 1, 64, N, R, 1, 0, dtype, "structured", outlier_frac=0.01)
+    K, _, Q = si.make_cache(cfg, 0)
+    sc, lse = B.score(gpu.to_dev(K, dtype), gpu.to_dev(Q, dtype))
+    torch.cuda.synchronize()
+    for l in (0, 17, 39):
+        k, q = O.decode(K[l, 1], dtype), O.decode(Q[l, 1], dtype).reshape(-1, 64)
+        np.testing.assert_allclose(sc[l, 1].cpu().numpy(), O.attention_mass(k, q), rtol=6.1e-8, atol=1e-38)
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
 @pytest.mark.parametrize("spread", [1.0, 60.0, 4000.0])     # logits of a row lie about as far apart: within, around and far past what the exponent holds
 def test_scores_of_logits_far_apart(gpu, dtype, d, spread):

@@ -33,10 +33,14 @@ constexpr int LE_LDR = 132;              // floats between rows of a subspace ba
 constexpr int kBlockMaxRank = 12;        // most directions the block iteration is asked for at a time
 constexpr int kThinWidth = 16;           // complements no wider than this are spanned by a block
 constexpr int kGroups = 4;               // most times that it goes on with the rest of the matrix
-constexpr float kGroupSpan = 1e-3f;      // eigenvalues below this share of a group's first are left to the next
-constexpr int kBlockRounds = 9;          // most Rayleigh-Ritz steps of it
+// A wanted eigenvalue below this share of the first sends the head to the direct route: the residual, which is relative to the first, no longer
+// tells whether its direction has settled, and the block's columns grow so differently that single precision loses some of them.  (Offsets of planted
+// ladders against double precision, worst of 150 heads: 0.546^i, 12 directions 1e-3 by the block iteration, 9e-7 this way, 425 and 346 us;
+// 0.38^i, 8 directions 3.5e-4 and 2e-6, 360 and 310 us.  The benchmark's caches have 0.1 at twelve directions and 0.03 at sixteen.)
+constexpr float kSteep = 1.f / 128;
+constexpr int kBlockRounds = 12;         // most Rayleigh-Ritz steps of it
 constexpr int kBlockSteps = 24;          // highest polynomial degree between two of them
-constexpr int kBlockReach = 60;          // products still to come beyond which a head takes the direct route
+constexpr int kBlockReach = 80;          // products still to come beyond which a head takes the direct route (which takes as long as 100 to 180)
 
 // Floats of dynamic LDS: the whole matrix or operands from Q, then (in the same place) the block's two copies, the partial Gram matrices and the
 // subspace's rows, or the scratch of the direct route.  (All of it in 16-byte pieces: on a base off that alignment the iteration took twice as long.)
@@ -696,9 +700,10 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
               lds_barrier();
               const float th1 = uniform(s_th[0]);
               if (group == 0) first = th1;
-              const float least = fmaxf(first * floor_rel, th1 * kGroupSpan);
+              const float least = first * floor_rel;
               kc = 0;
               for (int i = 0; i < want; ++i) if (s_th[i] > least) ++kc;
+              if (kc > 0 && s_th[kc - 1] < kSteep * first) { direct = true; break; }       // uniform, as kc is
               if (own) {
                 const float4 s4 = s_rot[lane];
                 const f32x4 S = {s4.x, s4.y, s4.z, s4.w};
@@ -722,8 +727,9 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
 #pragma unroll
               for (int w = 0; w < NT; ++w) rn += red[w];
               rn = uniform(sqrtf(rn) / th1);                     // residual of the wanted directions, relative to the spectrum
-              // done: at the rounding of the matrix, or there by the polynomial's own estimate, or as near as it gets
-              if (rn <= 3e-7f || (last && (rn <= 1e-6f || (rn <= 1e-5f && rn > 0.25f * rn_before)))) break;
+              // done: at the rounding of the products; there by the polynomial's own estimate; or no longer falling, and then near enough for the
+              // last wanted direction, or at the rounding that P G P brought along (of G, 1 / rcr times its own trace)
+              if (rn <= 3e-7f || (last && rn <= 1e-6f) || (rn > 0.5f * rn_before && (rn * th1 <= 1e-5f * s_th[kc - 1] || rn * th1 * rcr <= 3e-8f))) break;
               rn_before = rn;
               // columns that depended on the others make room for new ones (a steep spectrum hides all but its leading directions from
               // the first products), unless the matrix has no more directions

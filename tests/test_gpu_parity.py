@@ -188,6 +188,38 @@ def test_leading_directions_of_planted_spectra(gpu, d, budget, spectrum, rank):
     assert all(r.v_checked and not r.ambiguous for r in reps)
 
 
+@pytest.mark.parametrize("d,m,rank,spectrum", [
+    (128, 96, 12, "0.546"), (128, 40, 12, "0.546"), (64, 48, 12, "0.546"), (128, 96, 8, "0.38"), (64, 48, 8, "0.38"), (128, 96, 6, "0.26"),
+    (128, 96, 12, "0.7"), (128, 32, 12, "0.9"), (128, 96, 4, "0.6"),      # not as steep
+])
+def test_offset_of_many_residual_spectra(gpu, d, m, rank, spectrum):
+    """Ladders lambda_i = q^i in random orthonormal complements of random retained spans, 48 heads each.  What single precision leaves: the
+    rounding of the residual Gram matrix, taken as 16 2^-24 of its Frobenius norm, turns the last wanted direction by that over the
+    gap to the next eigenvalue, and that direction carries sqrt(lambda_k / lambda_1) of the offset."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    heads, n_del, r = 48, 4 * d, d - m
+    g = np.random.default_rng(17)
+    lam = float(spectrum) ** np.arange(m)
+    V = np.empty((heads, r + n_del, d), dtype=np.float32)
+    for h in range(heads):
+        basis = np.linalg.qr(g.standard_normal((d, d)))[0]
+        V[h, :r] = np.linalg.qr(g.standard_normal((r, r)))[0] @ basis[:, :r].T
+        V[h, r:] = (np.linalg.qr(g.standard_normal((n_del, m)))[0] * np.sqrt(lam)) @ basis[:, r:].T
+    A = (g.random((heads, r + n_del)) + 0.1).astype(np.float32)
+    idx = np.arange(r, dtype=np.int32)
+    Vd = torch.from_numpy(V).cuda()
+    delta = torch.empty((heads, d), dtype=torch.float32, device="cuda")
+    Bd.backfill(Bd.make_shape(1, heads, 1, d, r + n_del, 1, "f32"), Vd, torch.from_numpy(A).cuda(), torch.from_numpy(np.tile(idx, (1, heads, 1))).cuda(),
+                torch.full((1, heads), r, dtype=torch.int32, device="cuda"), rank, Vd[:, :r].contiguous(), delta_out=delta)
+    torch.cuda.synchronize()
+    got = delta.cpu().numpy().astype(np.float64)
+    tol = 16 * 2.0 ** -24 * np.linalg.norm(lam) / (lam[rank - 1] - lam[rank]) * np.sqrt(lam[rank - 1])
+    for h in range(heads):
+        want = O.backfill(V[h].astype(np.float64), A[h].astype(np.float64), idx, rank)[1].delta
+        assert np.linalg.norm(got[h] - want) <= tol * np.linalg.norm(want), f"head {h}"
+
+
 @pytest.mark.parametrize("budget,rank,iters", [(16, 2, 0), (32, 4, 0), (115, 2, 0), (24, 10, 0), (32, 2, 3)])
 def test_offset_follows_the_scale_of_the_values(gpu, budget, rank, iters):
     """Values times a power of two give the offset times that power, bit for bit: no step rounds differently unless a square or a

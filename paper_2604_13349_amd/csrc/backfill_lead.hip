@@ -839,7 +839,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
           __syncthreads();
           k_used = s_k;
           revr = (k_used > 0) ? s_val : 0.f;
-          offset(Wk, D, k_used, false);
+          offset(Wk, D, k_used, true);
           if (!FAST) export_basis(Wk, D, k_used);
         }
         if (FAST && kept_matrix) {

@@ -5,7 +5,7 @@
 //   2. the k largest eigenvalues of the tridiagonal S by multisection on Sturm counts (every thread evaluates one
 //      shift per round; three or four rounds shrink an eigenvalue's bracket below single-precision resolution);
 //   3. their eigenvectors by inverse iteration on S - theta I (tridiagonal elimination with row exchanges, one lane
-//      per eigenvector, two solves from a fixed pseudo-random start), eight at a time;
+//      per eigenvector, two solves from a fixed pseudo-random start, three under one shift for eigenvalues that agree), eight at a time;
 //   4. back-transformation through the reflectors (one wave per eigenvector) and a final Gram-Schmidt pass over the
 //      k vectors (eigenvalues that agree to rounding give vectors that only span the right subspace together).
 // All arithmetic is single precision; nothing here depends on convergence of an iteration.
@@ -60,6 +60,30 @@ __device__ __forceinline__ void te_wave_sum3(const float p, const float q, const
   sp = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 0));
   sr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 16));
   sq = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 32));
+}
+
+// One wave: each of the kb vectors (entry t of vector i at z[t * KS + i], n entries) whose bit is set in `which` is made orthogonal to those before
+// it whose eigenvalues follow one another by at most `close`.  Not inlined: its registers would count against the whole caller.
+template <int KS>
+__device__ __attribute__((noinline)) void te_separate(float* z, const float* th, const int n, const int kb, const float close, const uint64_t which) {
+  const int lane = threadIdx.x & 63;
+  const bool a = lane < n, b = lane + 64 < n;
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+  for (int i = 1; i < kb; ++i) {
+    if (!((which >> i) & 1)) continue;
+    float x0 = a ? z[lane * KS + i] : 0.f, x1 = b ? z[(lane + 64) * KS + i] : 0.f;
+    for (int j = i - 1; j >= 0 && th[j] - th[j + 1] <= close; --j) {
+      const float y0 = a ? z[lane * KS + j] : 0.f, y1 = b ? z[(lane + 64) * KS + j] : 0.f;
+      const float xy = te_wave_sum(fmaf(x0, y0, x1 * y1)), yy = te_wave_sum(fmaf(y0, y0, y1 * y1));
+      const float f = (yy > 0.f && yy < INFINITY) ? xy / yy : 0.f;
+      x0 = fmaf(-f, y0, x0); x1 = fmaf(-f, y1, x1);
+    }
+    if (a) z[lane * KS + i] = x0;
+    if (b) z[(lane + 64) * KS + i] = x1;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // Inverse iteration on the tridiagonal S - theta I for one eigenvector per lane.  Arrays of the factorisation live at
@@ -427,24 +451,47 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
   float* Wv = (k > TE_BATCH) ? zz + m * KS : lu;               // [k][m]; a single pass leaves it where the factors were
   for (int b0 = 0; b0 < k; b0 += TE_BATCH) {
     const int kb = min(TE_BATCH, k - b0);
-    // start: a fixed pseudo-random right-hand side of the first back substitution
+    // start: a fixed right-hand side of the first back substitution, pseudo-random from vector to vector too (vectors of a multiple
+    // eigenvalue are told apart by nothing else)
     for (int e = tid; e < m * KS; e += TE_THREADS) {
-      const uint32_t h = ((uint32_t)(e / KS) * 2654435761u + (uint32_t)(b0 + e % KS) * 40503u + 12345u) >> 8;
-      lu[5 * m * KS + e] = (float)(h & 0xffffu) * (1.f / 65536.f) - 0.5f;
+      uint32_t h = (uint32_t)(e / KS) * 2654435761u + (uint32_t)(b0 + e % KS + 1) * 2246822519u;
+      h ^= h >> 15; h *= 2246822519u; h ^= h >> 13; h *= 3266489917u; h ^= h >> 16;
+      lu[5 * m * KS + e] = (float)(int)h * (1.f / 4294967296.f);
     }
     __syncthreads();
-    if (wave == 0 && lane < kb) {
+    if (wave == 0) {
       float* za = zz + lane;
       float* zb = lu + 5 * m * KS + lane;                      // second vector buffer (behind the factors)
-      te_factor<KS>(dv, ev, m, th[b0 + lane], scal[3], lu + lane);
-      // Two solves, the first one without its row operations (a random right-hand side is one as well as the other): theta is within
-      // 1e-7 of the spectrum's extent of the eigenvalue, so a solve shrinks the rest of the vector by the gap over that, and two
-      // leave nothing that single precision could tell.  Between them the iterate is only rescaled by its largest magnitude (the
-      // squares of the last normalisation cannot overflow, and nothing else depends on the length).
-      float big = te_backward<KS>(lu + lane, m, zb, za);
-      te_forward<KS>(lu + lane, m, za, zb, (big > 0.f && big < INFINITY) ? 1.f / big : 1.f);
-      big = te_backward<KS>(lu + lane, m, zb, za);
-      scal[8 + lane] = big;                                    // the waves of the back-transformation bring it to unit length
+      // Eigenvalues that agree to 3e-6 of the largest share a shift just above them: with their own, each accurate to 1e-7, the vectors
+      // of an exact multiple lean towards whichever of its shifts is nearest, and what tells them apart is lost.
+      const float close = 25.f * scal[3];
+      bool shared = false;
+      float big = 0.f;
+      if (lane < kb) {
+        int top = b0 + lane;
+        while (top > 0 && th[top - 1] - th[top] <= close) --top;
+        shared = top < b0 + lane || (top + 1 < k && th[top] - th[top + 1] <= close);
+        te_factor<KS>(dv, ev, m, shared ? th[top] + 0.5f * close : th[top], scal[3], lu + lane);
+        // Two solves, the first one without its row operations (a random right-hand side is one as well as the other): theta is within
+        // 1e-7 of the spectrum's extent of the eigenvalue, so a solve shrinks the rest of the vector by the gap over that, and two
+        // leave nothing that single precision could tell.  Between them the iterate is only rescaled by its largest magnitude (the
+        // squares of the last normalisation cannot overflow, and nothing else depends on the length).
+        big = te_backward<KS>(lu + lane, m, zb, za);
+      }
+      // Those under one shift are made orthogonal between the solves, three here; rounding that this enlarges lies outside their subspace, where the
+      // next solve shrinks it.  (With two solves and start vectors that differed little from each other, offsets of planted multiples among
+      // small eigenvalues were off by up to 7e-2.)
+      const uint64_t together = __ballot(shared);
+      for (int left = together ? 2 : 1; left > 0; --left) {
+        if (together) te_separate<KS>(zz, th + b0, m, kb, close, together);
+        if (lane < kb) {
+          te_forward<KS>(lu + lane, m, za, zb, (big > 0.f && big < INFINITY) ? 1.f / big : 1.f);
+          big = te_backward<KS>(lu + lane, m, zb, za);
+        }
+      }
+      if (lane < kb) {
+        scal[8 + lane] = big;                                  // the waves of the back-transformation bring it to unit length
+      }
     }
     __syncthreads();
     float w0 = 0.f, w1 = 0.f;

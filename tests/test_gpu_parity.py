@@ -191,16 +191,23 @@ def test_leading_directions_of_planted_spectra(gpu, d, budget, spectrum, rank):
 @pytest.mark.parametrize("d,m,rank,spectrum", [
     (128, 96, 12, "0.546"), (128, 40, 12, "0.546"), (64, 48, 12, "0.546"), (128, 96, 8, "0.38"), (64, 48, 8, "0.38"), (128, 96, 6, "0.26"),
     (128, 96, 12, "0.7"), (128, 32, 12, "0.9"), (128, 96, 4, "0.6"),      # not as steep
+    (128, 96, 8, "pairs"), (64, 48, 8, "pairs"), (128, 64, 8, "plateau"), (64, 24, 8, "plateau"),      # equal eigenvalues, exactly
 ])
 def test_offset_of_many_residual_spectra(gpu, d, m, rank, spectrum):
-    """Ladders lambda_i = q^i in random orthonormal complements of random retained spans, 48 heads each.  What single precision leaves: the
+    """Eigenvalues q^i and others in random orthonormal complements of random retained spans, 48 heads each.  What single precision leaves: the
     rounding of the residual Gram matrix, taken as 16 2^-24 of its Frobenius norm, turns the last wanted direction by that over the
     gap to the next eigenvalue, and that direction carries sqrt(lambda_k / lambda_1) of the offset."""
     import torch
     from paper_2604_13349_amd import binding as Bd
     heads, n_del, r = 48, 4 * d, d - m
     g = np.random.default_rng(17)
-    lam = float(spectrum) ** np.arange(m)
+    i = np.arange(m)
+    if spectrum == "pairs":
+        lam = 0.1 ** (i // 2)
+    elif spectrum == "plateau":
+        lam = np.where(i < 3, 0.5 ** i, np.where(i < 8, 2e-3, 0.0))
+    else:
+        lam = float(spectrum) ** i
     V = np.empty((heads, r + n_del, d), dtype=np.float32)
     for h in range(heads):
         basis = np.linalg.qr(g.standard_normal((d, d)))[0]
@@ -215,9 +222,10 @@ def test_offset_of_many_residual_spectra(gpu, d, m, rank, spectrum):
     torch.cuda.synchronize()
     got = delta.cpu().numpy().astype(np.float64)
     tol = 16 * 2.0 ** -24 * np.linalg.norm(lam) / (lam[rank - 1] - lam[rank]) * np.sqrt(lam[rank - 1])
-    for h in range(heads):
-        want = O.backfill(V[h].astype(np.float64), A[h].astype(np.float64), idx, rank)[1].delta
-        assert np.linalg.norm(got[h] - want) <= tol * np.linalg.norm(want), f"head {h}"
+    want = np.stack([O.backfill(V[h].astype(np.float64), A[h].astype(np.float64), idx, rank)[1].delta for h in range(heads)])
+    length = np.linalg.norm(want, axis=1)
+    err = np.linalg.norm(got - want, axis=1) / np.maximum(length, np.median(length))      # (weights may nearly cancel along the leading directions)
+    assert err.max() <= tol, f"head {err.argmax()}: {err.max():.1e} > {tol:.1e}"
 
 
 @pytest.mark.parametrize("budget,rank,iters", [(16, 2, 0), (32, 4, 0), (115, 2, 0), (24, 10, 0), (32, 2, 3)])

@@ -35,9 +35,10 @@ constexpr int kThinWidth = 16;           // complements no wider than this are s
 constexpr int kGroups = 4;               // most times that it goes on with the rest of the matrix
 // A wanted eigenvalue below this share of the first sends the head to the direct route: the residual, which is relative to the first, no longer
 // tells whether its direction has settled, and the block's columns grow so differently that single precision loses some of them.  (Offsets of planted
-// ladders against double precision, worst of 150 heads: 0.546^i, 12 directions 1e-3 by the block iteration, 9e-7 this way, 425 and 346 us;
-// 0.38^i, 8 directions 3.5e-4 and 2e-6, 360 and 310 us.  The benchmark's caches have 0.1 at twelve directions and 0.03 at sixteen.)
+// ladders against double precision, worst of 150 heads: 0.546^i, 12 directions 1e-3 by the block iteration, 9e-7 this way, 425 and 200 us;
+// 0.38^i, 8 directions 3.5e-4 and 2e-6, 360 and 187 us.  The benchmark's caches have 0.1 at twelve directions and about 0.03 at sixteen.)
 constexpr float kSteep = 1.f / 128;
+constexpr float kLeftShare = 1.5e-6f;    // what the direct route may drop, relative to ||P G P||_F (whose rounding is about a tenth of that)
 constexpr int kBlockRounds = 12;         // most Rayleigh-Ritz steps of it
 constexpr int kBlockSteps = 24;          // highest polynomial degree between two of them
 constexpr int kBlockReach = 80;          // products still to come beyond which a head takes the direct route (which takes as long as 100 to 180)
@@ -249,13 +250,27 @@ struct DirectResult { int theta, W; };
 template <int D>
 __device__ __attribute__((noinline)) DirectResult lead_direct(const float* Tg, int kq) {
   extern __shared__ __attribute__((aligned(16))) float sm[];
+  float f = 0.f;                                               // ||P G P||_F
+  for (int e = threadIdx.x; e < D * D / 4; e += TE_THREADS) {
+    const f32x4 t = *(const f32x4*)(Tg + 4 * e);
+    f += fmaf(t[0], t[0], t[1] * t[1]) + fmaf(t[2], t[2], t[3] * t[3]);
+  }
+  f = te_wave_sum(f);
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = f;
+  __syncthreads();
+  f = 0.f;
+#pragma unroll
+  for (int w = 0; w < TE_WAVES; ++w) f += sm[w];
+  __syncthreads();
+  const float left_tol = kLeftShare * sqrtf(f);
   float* work = sm + ((tri_refl_floats(D) + 3) & ~3);          // 16-byte aligned
   const float* th;
   const float* Wk;
   int md = D;
   asm volatile("" : "+s"(md));                                 // (loops unrolled for a width known to the compiler spill)
-  if (kq <= 4) tri_top_eigs<4>(Tg, D, sm, md, kq, work, &th, &Wk);
-  else tri_top_eigs<8>(Tg, D, sm, md, kq, work, &th, &Wk);
+  const int n = tri_start<D / 32>(Tg, D, sm, md, left_tol, work);
+  if (kq <= 4) tri_top_eigs<4>(sm, md, n, kq, work, &th, &Wk);
+  else tri_top_eigs<8>(sm, md, n, kq, work, &th, &Wk);
   return DirectResult{(int)(th - sm), (int)(Wk - sm)};
 }
 

@@ -1,7 +1,7 @@
 // Leading eigenpairs of a small symmetric matrix, for a workgroup of 512 threads: the direct route for
 // the case "a few leading right singular vectors of the residual" (Sec. 4.4: k = pca_rank is small against the
 // width of the complement), in place of a full Jacobi diagonalisation:
-//   1. Householder tridiagonalisation T = H S H^T (m - 2 reflectors, one barrier each);
+//   1. Householder tridiagonalisation T = H S H^T (m - 2 reflectors, one barrier each; fewer where T has low rank);
 //   2. the k largest eigenvalues of the tridiagonal S by multisection on Sturm counts (every thread evaluates one
 //      shift per round; three or four rounds shrink an eigenvalue's bracket below single-precision resolution);
 //   3. their eigenvectors by inverse iteration on S - theta I (tridiagonal elimination with row exchanges, one lane
@@ -187,11 +187,18 @@ __device__ __forceinline__ float te_backward(const float* __restrict__ f, const 
 // Repeating the vector work in every wave leaves one barrier and one LDS round trip per reflector (none of the waves' barriers once
 // the trailing matrix fits one block); it is why only MB waves take part: two waves on a SIMD share its instruction issue, and two
 // tiles on each of eight waves took as long (2900 cycles a step at m = 96) as the same work on the vector ALU with four barriers.
-// Bound by the dependent chain of a step: 0.85 us at m = 96 and 0.55 at m = 32 (1.3 us before); 2 directions of 288 complements 96
-// wide in a 256-token call: 514 -> 445 us for the whole call.
+// Bound by the dependent chain of a step and, with two workgroups on a compute unit, by instruction issue: 2600 cycles at m = 128.
+//
+// A matrix of rank r is done early: after r + 1 steps the reflectors' columns span its range and what is left is rounding (a step more
+// for each time that the columns run into an invariant subspace and start again, as clusters of eigenvalues make them; fewer where the
+// eigenvalues fall below the rounding).  A column no longer than left_tol makes the waves look at all that is left, which is dropped
+// when its Frobenius norm is no more than that either.  Returns the width of S: m, or one more than the reflectors so far.
+// The residual Gram matrix P G P has the rank of the complement at most.  Back-fill of 288 heads with eigenvalues 1 - 1e-4 i, 2 directions, us, all columns and
+// this way: complements 64, 32 and 20 wide 360 and 335, 407 and 317, 446 and 323; 96 wide, where the starts use up the rest of the
+// columns, 334 and 355 (the last row block's loop is no longer unrolled for the columns before it).  0.546^i, 96 wide, 12 directions: 346 and 200.
 template <int MB>
-__device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const int ls, float* Rf, const int m, float* dv, float* ev,
-                                           float* bet, float* cbuf, float* ybuf) {
+__device__ __forceinline__ int tri_reduce(const float* __restrict__ Tsrc, const int ls, float* Rf, const int m, const float left_tol,
+                                          float* dv, float* ev, float* bet, float* cbuf, float* ybuf /*[256 + 7]*/) {
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr bool TWO = MB > 2;                                 // a lane holds two entries of a vector
@@ -217,10 +224,11 @@ __device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const
   // the row this lane is left with: entry 8 b4 + 4 b3 + 2 b2 + b1 of the tile's sixteen (b: the bits of the lane number)
   const bool l3 = (lane & 8) != 0, l2 = (lane & 4) != 0, l1 = (lane & 2) != 0;
   const int my_row = wave * 32 + ((lane >> 4) & 1) * 16 + ((lane >> 3) & 1) * 8 + lh * 4 + ((lane >> 2) & 1) * 2 + ((lane >> 1) & 1);
-  auto step = [&](const int j, const bool alone) {
-    const int b0 = (j + 1) >> 5, par = j & 1;                  // the block in which the trailing matrix starts
+  float* lsum = ybuf + 256;                                    // [4] the waves' sums of squares, the width of S, [2] |x| by step parity
+  auto step = [&](const int j, const int b0 /*block in which the trailing matrix starts*/, const bool alone) -> bool {      // was |x| at most left_tol (uniform)
+    const int par = j & 1;
     const bool live = wave < MB && wave >= b0;                 // uniform over the wave
-    float alpha = 0.f, beta = 0.f, head = 0.f;
+    float alpha = 0.f, beta = 0.f, head = 0.f, norm = 0.f;
     if (live) {
       const auto X0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(xa), __float_as_uint(xa), false, false);   // blocks 0 and 1 of x,
       const auto X1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(xb), __float_as_uint(xb), false, false);   // 2 and 3, in both half-waves
@@ -264,8 +272,10 @@ __device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const
         alpha = (head >= 0.f) ? -sigma : sigma;
         beta = __builtin_amdgcn_rcpf(sigma * (sigma + fabsf(head)));
       }
+      norm = sigma;
+      if (!alone && wave == MB - 1 && lane == 0) lsum[5 + par] = sigma;
     }
-    if (alone) __builtin_amdgcn_wave_barrier(); else lds_barrier();
+    if (alone) __builtin_amdgcn_wave_barrier(); else { lds_barrier(); norm = lsum[5 + par]; }
     if (live) {
       const float* yr = ybuf + par * 128;
       const float* cr = cbuf + par * 128;
@@ -303,7 +313,7 @@ __device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const
       const int cn = j + 2;                                    // the next raw column
 #pragma unroll
       for (int cb = 0; cb < MB; ++cb)
-        if (cb == (cn >> 5)) {
+        if (cb >= b0 && cb == (cn >> 5)) {
           if (lr == (cn & 31)) {
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4)
@@ -312,38 +322,92 @@ __device__ __forceinline__ void tri_reduce(const float* __restrict__ Tsrc, const
           }
         }
     }
+    return __builtin_amdgcn_readfirstlane(norm <= left_tol ? 1 : 0) != 0;
   };
+  // sum of squares of this wave's entries past row and column j, the last wave's with x
+  auto left = [&](const int j, const int b0) -> float {
+    float f = (wave == MB - 1) ? fmaf(xa, xa, xb * xb) : 0.f;
+    int over = wave * 32 + lh * 4 - j;
+    asm volatile("" : "+v"(over));                             // (the comparisons below, kept ahead of the loop, push the tiles to scratch)
+#pragma unroll
+    for (int cb = 0; cb < MB; ++cb)
+      if (cb >= b0) {
+        float g = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) g = (over > -((i >> 2) * 8 + (i & 3))) ? fmaf(tile[cb][i], tile[cb][i], g) : g;
+        f += (cb * 32 + lr > j) ? g : 0.f;
+      }
+    return te_wave_sum(f);
+  };
+  const float left2 = left_tol * left_tol;
+  bool done = false, look = false;
   int j = 0;
-  for (; j + 2 < m && ((j + 1) >> 5) < MB - 1; ++j) step(j, false);
+  for (; j + 2 < m && ((j + 1) >> 5) < MB - 1; ++j) {
+    const int b0 = (j + 1) >> 5;
+    if (look) {                                                // uniform
+      if (wave >= b0 && wave < MB) { const float f = left(j, b0); if (lane == 0) lsum[wave] = f; }
+      lds_barrier();
+      float f = 0.f;
+      for (int w = b0; w < MB; ++w) f += lsum[w];
+      if (__builtin_amdgcn_readfirstlane(f <= left2 ? 1 : 0)) { done = true; break; }
+    }
+    look = step(j, b0, false);
+  }
   lds_barrier();                                               // the other row blocks' last column is published
   if (wave == MB - 1) {
-    for (; j + 2 < m; ++j) step(j, true);
-    // the last 2 x 2 block: x is column m - 2, the published column is m - 1
-    const float last = lane_val((TWO && m - 1 >= 64) ? xb : xa, (m - 1) & 63);
-    __builtin_amdgcn_wave_barrier();
-    if (m >= 2 && lane == 0) { ev[m - 2] = last; dv[m - 1] = cbuf[(m & 1) * 128 + m - 1]; }
+    if (!done) {
+      for (; j + 2 < m; ++j) {
+        if (look && __builtin_amdgcn_readfirstlane(left(j, MB - 1) <= left2 ? 1 : 0)) { done = true; break; }
+        look = step(j, MB - 1, true);
+      }
+    }
+    if (!done) {
+      // the last 2 x 2 block: x is column m - 2, the published column is m - 1
+      const float last = lane_val((TWO && m - 1 >= 64) ? xb : xa, (m - 1) & 63);
+      __builtin_amdgcn_wave_barrier();
+      if (m >= 2 && lane == 0) { ev[m - 2] = last; dv[m - 1] = cbuf[(m & 1) * 128 + m - 1]; }
+    }
+    if (lane == 0) *(int*)&lsum[4] = done ? j + 1 : m;
   }
   __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*(const int*)&lsum[4]);
 }
 
-// Tsrc: the m x m symmetric matrix (row stride ls; global or LDS, read once).  Rf: LDS, tri_refl_floats(m) floats, with `work` behind
-// it (masked lanes read past it).  m <= 128.
-// work: LDS scratch of tri_work_floats(m, k) floats, 16-byte aligned.  1 <= k <= min(m, TE_MAXK); KS = tri_lane_stride(k).
+// The scratch of the direct route starts with these arrays; tri_work_floats(m, k) floats in all, in LDS and 16-byte aligned.
+struct TriWork {
+  float *cbuf, *dv, *ev, *e2, *bet;
+  int* cnt;
+  __device__ __forceinline__ TriWork(float* work, const int m) {
+    cbuf = work;                      // [2][128] tridiagonalisation: the raw next column, by step parity
+    dv = cbuf + 256;                  // diagonal of S
+    ev = dv + m;                      // sub-diagonal of S: ev[j] = S[j+1][j]
+    e2 = ev + m;
+    bet = e2 + m;                     // reflector j is I - bet[j] v v^T, v in column j of Rf
+    cnt = (int*)(bet + m);            // [TE_THREADS]
+  }
+};
+
+// Step 1.  Tsrc: the m x m symmetric matrix (row stride ls; global or LDS, read once), m = 32 MB.  Rf: LDS, tri_refl_floats(m) floats, with
+// `work` behind it (masked lanes read past it).  left_tol, the result: see tri_reduce.  Every thread of the workgroup must call.
+template <int MB>
+__device__ __forceinline__ int tri_start(const float* __restrict__ Tsrc, const int ls, float* Rf, const int m, const float left_tol, float* work) {
+  const TriWork w(work, m);
+  return tri_reduce<MB>(Tsrc, ls, Rf, m, left_tol, w.dv, w.ev, w.bet, w.cbuf, (float*)w.cnt);       // (the counts come later)
+}
+
+// Steps 2 to 4 on the n x n tridiagonal matrix of tri_start.  1 <= k0 <= TE_MAXK; KS = tri_lane_stride(k0).
 // More than TE_BATCH eigenpairs are found in passes of TE_BATCH (the eigenvalues' multisection, the inverse iteration and
 // the back-transformation each run once per pass on the same scratch).
-// On return (after its own final barrier) *theta points at the k eigenvalues, largest first, and *W at the k unit
-// eigenvectors, W[i * m + t].  Every thread of the workgroup must call.
+// On return (after its own final barrier) *theta points at the k0 eigenvalues, largest first, and *W at the unit eigenvectors, W[i * m + t].
+// Where S is narrower than k0 the eigenvalues past its width are zero and have no vectors.  Every thread of the workgroup must call.
 template <int KS>
-__device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, const int ls, float* Rf, const int m,
-                                             const int k, float* work, const float** theta, const float** W) {
+__device__ __forceinline__ void tri_top_eigs(const float* Rf, const int m, const int n, const int k0, float* work, const float** theta,
+                                             const float** W) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  float* cbuf = work;                 // [2][128] tridiagonalisation: the raw next column, by step parity (work is 16-byte aligned)
-  float* dv = cbuf + 256;             // diagonal of S
-  float* ev = dv + m;                 // sub-diagonal of S: ev[j] = S[j+1][j]
-  float* e2 = ev + m;
-  float* bet = e2 + m;                // reflector j is I - bet[j] v v^T, v in column j of Rf
-  int* cnt = (int*)(bet + m);         // [TE_THREADS]
+  const TriWork tw(work, m);
+  float *dv = tw.dv, *ev = tw.ev, *e2 = tw.e2, *bet = tw.bet;
+  int* cnt = tw.cnt;
   float* br_a = (float*)(cnt + TE_THREADS); // [16] brackets, then eigenvalues
   float* br_b = br_a + 16;
   float* th = br_b + 16;
@@ -352,19 +416,15 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
   float* lu = scal + 32;              // [5][m][KS] factors of S - theta I per eigenvector + [m][KS] second iteration vector; later W [k][m]
   float* zz = lu + 6 * m * KS;        // [m][KS] iteration vectors
 
-  // ---- 1. tridiagonalisation (the counts come later)
-  if (m <= 32) tri_reduce<1>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
-  else if (m <= 64) tri_reduce<2>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
-  else if (m <= 96) tri_reduce<3>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
-  else tri_reduce<4>(Tsrc, ls, Rf, m, dv, ev, bet, cbuf, (float*)cnt);
+  const int k = min(k0, n);
   if (wave == 0) {
     // Gershgorin interval of S and its squared sub-diagonal entries: lane l looks at rows l and l + 64
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int i = lane + 64 * h;
-      if (i < m) {
-        const float below = (i + 1 < m) ? ev[i] : 0.f, above = (i > 0) ? ev[i - 1] : 0.f;
+      if (i < n) {
+        const float below = (i + 1 < n) ? ev[i] : 0.f, above = (i > 0) ? ev[i - 1] : 0.f;
         const float r = fabsf(above) + fabsf(below);
         lo = fminf(lo, dv[i] - r); hi = fmaxf(hi, dv[i] + r);
         e2[i] = fmaxf(below * below, 1e-36f);                    // never 0: see the Sturm recurrence
@@ -389,14 +449,14 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
     float q = dv[0] - x;
     int c = q < 0.f;
     int i = 1;
-    for (; i + TE_AHEAD <= m; i += TE_AHEAD) {
+    for (; i + TE_AHEAD <= n; i += TE_AHEAD) {
       float d[TE_AHEAD], e[TE_AHEAD];
 #pragma unroll
       for (int u = 0; u < TE_AHEAD; ++u) { d[u] = dv[i + u] - x; e[u] = e2[i + u - 1]; }
 #pragma unroll
       for (int u = 0; u < TE_AHEAD; ++u) { q = fmaf(-e[u], __builtin_amdgcn_rcpf(q), d[u]); c += q < 0.f; }
     }
-    for (; i < m; ++i) { q = fmaf(-e2[i - 1], __builtin_amdgcn_rcpf(q), dv[i] - x); c += q < 0.f; }
+    for (; i < n; ++i) { q = fmaf(-e2[i - 1], __builtin_amdgcn_rcpf(q), dv[i] - x); c += q < 0.f; }
     return c;
   };
   {
@@ -404,8 +464,8 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
     constexpr float step = 1.f / (float)(TE_THREADS + 1);
     cnt[tid] = sturm(lo + (hi - lo) * ((float)(tid + 1) * step));
     __syncthreads();
-    if (tid < k) {                                             // eigenvalue tid from the top is number m - 1 - tid from below
-      const int tgt = m - 1 - tid;
+    if (tid < k) {                                             // eigenvalue tid from the top is number n - 1 - tid from below
+      const int tgt = n - 1 - tid;
       int a = 0, b = TE_THREADS;                               // first shift whose count exceeds tgt
       while (a < b) { const int mid = (a + b) >> 1; if (cnt[mid] <= tgt) a = mid + 1; else b = mid; }
       br_a[tid] = (a > 0) ? lo + (hi - lo) * ((float)a * step) : lo;
@@ -427,7 +487,7 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
       float a = 0.f, b = 0.f;
       if (g < kb) {
         a = br_a[g0 + g]; b = br_b[g0 + g];
-        below = sturm(a + (b - a) * ((float)(s + 1) / (float)(S + 1))) <= m - 1 - (g0 + g);
+        below = sturm(a + (b - a) * ((float)(s + 1) / (float)(S + 1))) <= n - 1 - (g0 + g);
       }
       const int c = __popcll(__ballot(below));
       if (lane == 0) wc[wave] = c;
@@ -445,15 +505,16 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
     if (tid < kb) th[g0 + tid] = 0.5f * (br_a[g0 + tid] + br_b[g0 + tid]);
     __syncthreads();
   }
+  if (tid >= k && tid < k0) th[tid] = 0.f;
 
   // ---- 3. eigenvectors of S: inverse iteration, lane i of wave 0 owns eigenvector b0 + i; 4. back-transformation
-  // w = H_0 H_1 ... H_{m-3} z, one wave per eigenvector, lane l holds entries l and l + 64
-  float* Wv = (k > TE_BATCH) ? zz + m * KS : lu;               // [k][m]; a single pass leaves it where the factors were
+  // w = H_0 H_1 ... z, one wave per eigenvector, lane l holds entries l and l + 64
+  float* Wv = (k0 > TE_BATCH) ? zz + m * KS : lu;               // [k][m]; a single pass leaves it where the factors were
   for (int b0 = 0; b0 < k; b0 += TE_BATCH) {
     const int kb = min(TE_BATCH, k - b0);
     // start: a fixed right-hand side of the first back substitution, pseudo-random from vector to vector too (vectors of a multiple
     // eigenvalue are told apart by nothing else)
-    for (int e = tid; e < m * KS; e += TE_THREADS) {
+    for (int e = tid; e < n * KS; e += TE_THREADS) {
       uint32_t h = (uint32_t)(e / KS) * 2654435761u + (uint32_t)(b0 + e % KS + 1) * 2246822519u;
       h ^= h >> 15; h *= 2246822519u; h ^= h >> 13; h *= 3266489917u; h ^= h >> 16;
       lu[5 * m * KS + e] = (float)(int)h * (1.f / 4294967296.f);
@@ -471,22 +532,22 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
         int top = b0 + lane;
         while (top > 0 && th[top - 1] - th[top] <= close) --top;
         shared = top < b0 + lane || (top + 1 < k && th[top] - th[top + 1] <= close);
-        te_factor<KS>(dv, ev, m, shared ? th[top] + 0.5f * close : th[top], scal[3], lu + lane);
+        te_factor<KS>(dv, ev, n, shared ? th[top] + 0.5f * close : th[top], scal[3], lu + lane);
         // Two solves, the first one without its row operations (a random right-hand side is one as well as the other): theta is within
         // 1e-7 of the spectrum's extent of the eigenvalue, so a solve shrinks the rest of the vector by the gap over that, and two
         // leave nothing that single precision could tell.  Between them the iterate is only rescaled by its largest magnitude (the
         // squares of the last normalisation cannot overflow, and nothing else depends on the length).
-        big = te_backward<KS>(lu + lane, m, zb, za);
+        big = te_backward<KS>(lu + lane, n, zb, za);
       }
       // Those under one shift are made orthogonal between the solves, three here; rounding that this enlarges lies outside their subspace, where the
       // next solve shrinks it.  (With two solves and start vectors that differed little from each other, offsets of planted multiples among
       // small eigenvalues were off by up to 7e-2.)
       const uint64_t together = __ballot(shared);
       for (int left = together ? 2 : 1; left > 0; --left) {
-        if (together) te_separate<KS>(zz, th + b0, m, kb, close, together);
+        if (together) te_separate<KS>(zz, th + b0, n, kb, close, together);
         if (lane < kb) {
-          te_forward<KS>(lu + lane, m, za, zb, (big > 0.f && big < INFINITY) ? 1.f / big : 1.f);
-          big = te_backward<KS>(lu + lane, m, zb, za);
+          te_forward<KS>(lu + lane, n, za, zb, (big > 0.f && big < INFINITY) ? 1.f / big : 1.f);
+          big = te_backward<KS>(lu + lane, n, zb, za);
         }
       }
       if (lane < kb) {
@@ -496,8 +557,8 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
     __syncthreads();
     float w0 = 0.f, w1 = 0.f;
     if (wave < kb) {
-      w0 = (lane < m) ? zz[lane * KS + wave] : 0.f;
-      w1 = (lane + 64 < m) ? zz[(lane + 64) * KS + wave] : 0.f;
+      w0 = (lane < n) ? zz[lane * KS + wave] : 0.f;
+      w1 = (lane + 64 < n) ? zz[(lane + 64) * KS + wave] : 0.f;
       {
         // unit length (scaled by the largest magnitude first, so that the squares cannot overflow); this also clears what
         // is left of the start vector in blocks that S decouples from this eigenvalue (an exactly zero sub-diagonal
@@ -516,7 +577,7 @@ __device__ __forceinline__ void tri_top_eigs(const float* __restrict__ Tsrc, con
       // Two reflectors at a time: (I - b2 v2 v2^T)(I - b1 v1 v1^T) w needs v1.w, v2.w and v1.v2, three sums that go through the wave
       // together; the next pair is fetched meanwhile.
       const int ia = lane < m ? lane : -1, ib = lane + 64 < m ? lane + 64 : -1;      // entries of this lane; -1: none
-      int j = m - 3;
+      int j = min(n - 2, m - 3);                               // the last reflector
       float p0 = 0.f, p1 = 0.f, q0 = 0.f, q1 = 0.f, bp = 0.f, bq = 0.f;
       auto fetch = [&](const int jj) {                         // reflectors jj and jj - 1
         const int a = max(jj, 0), b = max(jj - 1, 0), oa = tri_refl_off(m, a) + lane, ob = tri_refl_off(m, b) + lane;

@@ -191,7 +191,10 @@ def test_leading_directions_of_planted_spectra(gpu, d, budget, spectrum, rank):
 @pytest.mark.parametrize("d,m,rank,spectrum", [
     (128, 96, 12, "0.546"), (128, 40, 12, "0.546"), (64, 48, 12, "0.546"), (128, 96, 8, "0.38"), (64, 48, 8, "0.38"), (128, 96, 6, "0.26"),
     (128, 96, 12, "0.7"), (128, 32, 12, "0.9"), (128, 96, 4, "0.6"),      # not as steep
-    (128, 96, 8, "pairs"), (64, 48, 8, "pairs"), (128, 64, 8, "plateau"), (64, 24, 8, "plateau"),      # equal eigenvalues, exactly
+    # the direct route's reduction done after about 14, 37, 79 and 97 columns: in each row block of 32 and in the last one
+    (128, 96, 4, "step 0.5"), (128, 96, 4, "step 0.8"), (128, 96, 4, "step 0.9"), (128, 96, 12, "step 0.97"), (128, 20, 6, "step 0.9"),
+    (64, 48, 4, "step 0.5"), (64, 48, 4, "step 0.8"), (64, 30, 12, "step 0.9"),
+    (128, 96, 8, "pairs"), (64, 48, 8, "pairs"), (128, 64, 8, "plateau"), (64, 24, 8, "plateau"),      # equal eigenvalues: several starts; nothing left
 ])
 def test_offset_of_many_residual_spectra(gpu, d, m, rank, spectrum):
     """Eigenvalues q^i and others in random orthonormal complements of random retained spans, 48 heads each.  What single precision leaves: the
@@ -206,6 +209,8 @@ def test_offset_of_many_residual_spectra(gpu, d, m, rank, spectrum):
         lam = 0.1 ** (i // 2)
     elif spectrum == "plateau":
         lam = np.where(i < 3, 0.5 ** i, np.where(i < 8, 2e-3, 0.0))
+    elif spectrum.startswith("step"):
+        lam = np.where(i == 0, 1.0, 5e-3 * float(spectrum[5:]) ** i)
     else:
         lam = float(spectrum) ** i
     V = np.empty((heads, r + n_del, d), dtype=np.float32)

@@ -244,6 +244,53 @@ __device__ __forceinline__ void project_vector(const float* __restrict__ Qb, con
   __syncthreads();
 }
 
+// Where the block iteration's arrays lie in the dynamic LDS.
+template <int D>
+struct BlockLds {
+  static constexpr int NT = D / 16;
+  bf16x4* sbuf;                          // [2][3][NT / 2][64][2] the block in its three parts, two copies
+  float4* xbuf;                          // [2][NT][LE_XTILE] the blocks X and Y for their transposition
+  f32x4* gbuf;                           // [2][NT][64] partial X^T X and X^T Y
+  float* rows;                           // [16][LE_LDR]
+  float* lam;                            // [16]
+  __device__ __forceinline__ BlockLds(float* sm) {
+    sbuf = (bf16x4*)sm;
+    xbuf = (float4*)(sbuf + 2 * 3 * NT * 64);
+    gbuf = (f32x4*)(xbuf + 2 * NT * LE_XTILE);
+    rows = (float*)(gbuf + 2 * NT * 64);
+    lam = rows + 16 * LE_LDR;
+  }
+};
+
+// a block in its three parts to LDS, each wave's sixteen rows
+template <int D>
+__device__ __forceinline__ void publish(bf16x4* b, const f32x4 x) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const Split s = split3(x);
+  bf16x4* o = b + ((wave >> 1) * 64 + lane) * 2 + (wave & 1);
+  o[0] = s.hi; o[D / 16 * 64] = s.mid; o[2 * (D / 16) * 64] = s.lo;
+}
+
+// y0 + y1 + y2 += a times rows 32 p .. of the block b
+template <int D>
+__device__ __forceinline__ void multiply(const Split8& a, const bf16x4* b, const int p, f32x4& y0, f32x4& y1, f32x4& y2) {
+  const bf16x8* v = (const bf16x8*)b + (threadIdx.x & 63);
+  const bf16x8 hi = v[p * 64], mid = v[(D / 32 + p) * 64], lo = v[(D / 16 + p) * 64];
+  y0 = mfma32(a.hi, hi, y0);
+  y1 = mfma32(a.hi, mid, y1);
+  y2 = mfma32(a.hi, lo, y2);
+  y1 = mfma32(a.mid, hi, y1);
+  y2 = mfma32(a.mid, mid, y2);
+  y2 = mfma32(a.lo, hi, y2);
+}
+
+// entry (row, j) of a start block, in [-1, 1), fixed
+__device__ __forceinline__ float block_random(const int row, const int j, const int seed) {
+  uint32_t h = (uint32_t)(row * 16 + j) * 2654435761u + (uint32_t)seed * 40503u + 12345u;
+  h ^= h >> 15; h *= 2246822519u; h ^= h >> 13; h *= 3266489917u; h ^= h >> 16;
+  return (float)(int)h * (1.f / 2147483648.f);
+}
+
 // The direct route on the D x D matrix Tg, in the workgroup's dynamic LDS: where in it the eigenvalues and the eigenvectors (D floats apart)
 // lie.  A function of its own, not inlined: its register tiles otherwise push values of the block iteration's loops to scratch.
 struct DirectResult { int theta, W; };
@@ -307,18 +354,144 @@ __device__ __attribute__((noinline)) void lead_deflate(const float* from, float*
   }
 }
 
+// The exact directions of a head whose complement is only m <= kThinWidth wide, from G itself (D x D, of which a lane reads what it wrote): an orthonormal
+// basis of the complement from m random vectors, projected and orthonormalised until nothing depended on the rest twice in a row
+// (twice in all, as a rule), then one Rayleigh-Ritz step, which is the whole eigenproblem.  Leaves the m vectors in the block's rows and
+// the Ritz values, descending and then zeros, in lam; ends with a barrier.  Not inlined: see lead_direct (the operands of the projection
+// beside the matrix of the block iteration fill the registers).
+template <int D>
+__device__ __attribute__((noinline)) void lead_thin(const float* Q_, const float* G_, const int r_, const int m_) {
+  constexpr int NT = D / 16;
+  // (a function of its own sees neither that its arguments are the same in all lanes nor that the pointers are to global memory)
+  typedef const __attribute__((address_space(1))) float* Global;
+  typedef const __attribute__((address_space(1))) f32x4* Global4;
+  auto same = [](const float* p) -> Global {
+    const uint64_t u = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)u), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32));
+    return (Global)(((uint64_t)hi << 32) | lo);
+  };
+  const Global Qb = same(Q_), G = same(G_);
+  const int r = __builtin_amdgcn_readfirstlane(r_), m = __builtin_amdgcn_readfirstlane(m_);
+  extern __shared__ __attribute__((aligned(16))) float sm[];
+  const BlockLds<D> lds(sm);
+  float4* s_rot = lds.xbuf + NT * LE_XTILE;                    // [64], where the block iteration has Y
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, j = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool own = wave < NT;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 x = zero, y = zero;
+  // X <- X - Q^T (Q X): wave w takes rows 16 w .. of Q X (in place of the partial Gram matrices), then its rows of the update
+  auto project = [&]() {
+    bf16x4 *b = lds.sbuf, *bs = (bf16x4*)lds.gbuf;
+    if (own) publish<D>(b, x);
+    f32x4 qa[NT / 2][2], qc[NT / 2][2];
+    const bool in = 16 * wave + j < r;
+    int last = r - 1;
+    asm volatile("" : "+s"(last));                           // (the rows' places, kept from one projection to the next, fill the registers)
+    if (own) {
+      const uint32_t at = (uint32_t)(min(16 * wave + j, last) * D + 4 * q);
+#pragma unroll
+      for (int p = 0; p < NT / 2; ++p) {
+        qa[p][0] = *(Global4)(Qb + at + 32 * p); qa[p][1] = *(Global4)(Qb + at + 32 * p + 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = 32 * p + 4 * q + e;                    // rows past the last: Q X is zero there
+          qc[p][0][e] = Qb[(uint32_t)(min(k, last) * D + 16 * wave + j)]; qc[p][1][e] = Qb[(uint32_t)(min(k + 16, last) * D + 16 * wave + j)];
+        }
+      }
+    }
+    lds_barrier();
+    if (own) {
+      f32x4 y0 = zero, y1 = zero, y2 = zero;
+#pragma unroll
+      for (int p = 0; p < NT / 2; ++p) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { if (!in) { qa[p][0][e] = 0.f; qa[p][1][e] = 0.f; } }
+        multiply<D>(split8(qa[p][0], qa[p][1]), b, p, y0, y1, y2);
+      }
+      publish<D>(bs, y0 + (y1 + y2));
+    }
+    lds_barrier();
+    if (own) {
+      f32x4 y0 = zero, y1 = zero, y2 = zero;
+#pragma unroll
+      for (int p = 0; p < NT / 2; ++p) multiply<D>(split8(qc[p][0], qc[p][1]), bs, p, y0, y1, y2);
+      x -= y0 + (y1 + y2);
+    }
+    lds_barrier();
+  };
+  // X <- X S; the Ritz values (basis_only: one, or zero where dropped) in lam
+  auto small_problem = [&](const bool basis_only) {
+    float4* xb = lds.xbuf + wave * LE_XTILE;
+    if (own) {
+      lds.gbuf[wave * 64 + lane] = mul_t(x, x, zero);
+      lds.gbuf[(NT + wave) * 64 + lane] = basis_only ? mul_t(x, x, zero) : mul_t(y, x, mul_t(x, y, zero)) * 0.5f;
+      xb[q * 17 + j] = make_float4(x[0], x[1], x[2], x[3]);
+    }
+    lds_barrier();
+    if (wave == 0) {
+      f32x4 M = lds.gbuf[lane], H = lds.gbuf[NT * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < NT; ++w) { M += lds.gbuf[w * 64 + lane]; H += lds.gbuf[(NT + w) * 64 + lane]; }
+      f32x4 S;
+      float theta;
+      int place;
+      const int sweeps = basis_only ? 0 : 12;
+      if (m <= 8) small_ritz<8>(M, H, 1e-6f, 3e-4f, sweeps, S, theta, place);
+      else small_ritz<16>(M, H, 1e-6f, 3e-4f, sweeps, S, theta, place);
+      s_rot[q * 16 + place] = make_float4(S[0], S[1], S[2], S[3]);
+      if (q == 0) lds.lam[place] = theta;
+    }
+    lds_barrier();
+    if (own) {
+      const float4 s4 = s_rot[lane];
+      const float* xs = (const float*)(xb + (j >> 2) * 17 + 4 * q) + (j & 3);
+      f32x4 xt;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xt[e] = xs[4 * e];
+      x = mul_t(xt, f32x4{s4.x, s4.y, s4.z, s4.w}, zero);
+    }
+  };
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = (j < m) ? block_random(16 * wave + 4 * q + e, j, -1) : 0.f;
+  project();
+  int whole_before = 0;
+  for (int pass = 0; pass < 6 && whole_before < 2; ++pass) {
+    small_problem(true);
+    const bool all = lds.lam[m - 1] > 0.f;                     // uniform
+    whole_before = all ? whole_before + 1 : 0;
+    if (!all) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) if (j < m && !(lds.lam[j] > 0.f)) x[e] = block_random(16 * wave + 4 * q + e, j, pass);
+    }
+    project();
+  }
+  if (own) publish<D>(lds.sbuf, x);
+  lds_barrier();
+  if (own) {                                                   // Y = G X
+    f32x4 y0 = zero, y1 = zero, y2 = zero;
+    const Global g = G + (uint32_t)((16 * wave + j) * D + 4 * q);
+#pragma unroll
+    for (int p = 0; p < NT / 2; ++p) multiply<D>(split8(*(Global4)(g + 32 * p), *(Global4)(g + 32 * p + 16)), lds.sbuf, p, y0, y1, y2);
+    y = y0 + (y1 + y2);
+  }
+  small_problem(false);
+  if (own && j < m) *(f32x4*)&lds.rows[j * LE_LDR + 16 * wave + 4 * q] = x;
+  __syncthreads();
+}
+
 // a value that every lane holds, moved to a scalar register
 __device__ __forceinline__ float uniform(const float v) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(v)));
 }
 
 // FAST selects the fast path of App. H: `iters` steps of C <- orth(C P G P) from a fixed orthonormal start; the exact directions are
-// then only found when diagnostics are wanted, to report how far the fast path's Delta is from theirs.  (Two kernels: the registers of
-// its orthogonalisation would push parts of the matrix to scratch in the other's loops.)
+// then only found when diagnostics are wanted, to report how far the fast path's Delta is from theirs.  (A kernel of its own: the calls
+// to the orthogonalisation push six values of each of its products to scratch, none of the others'.)
 // THIN: some heads may retain so many directions that their complement is no wider than a block (kThinWidth).  P G P is not formed for
 // those (Q has more rows than there would be products): products with G are followed by a projection of the block, and the block's Ritz
-// values give the trace.  (288 heads of 900 tokens, 120
-// kept, rank 8: 350 us formed, 332 this way; 500 tokens of head_dim 64, 56 kept: 294 and 251.)
+// values give the trace; see lead_thin.  (288 heads of 1024 tokens, 112, 120 and 126 kept, whole call, 8 directions: 302, 316 and 313 us
+// with that in here, where its operands pushed the matrix to scratch; 293, 305 and 303 as a function.)
 template <typename T, int D, bool FAST, bool THIN>
 __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, HeadState* __restrict__ state,
                                                           const float* __restrict__ basis, const float* __restrict__ gram_part,
@@ -465,86 +638,34 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
       const int ex = min(max((int)(__float_as_uint(res2) >> 23) - 127, -126), 126);
       const float down = __uint_as_float((uint32_t)(127 - ex) << 23);
       const double unit = (double)__uint_as_float((uint32_t)(127 + ex) << 23);
-      Split8 mat[NT / 2];                                      // rows 16 w .. of P G P (thin: of G)
+      Split8 mat[NT / 2];                                      // rows 16 w .. of P G P
 #pragma unroll
       for (int p = 0; p < NT / 2; ++p) mat[p] = split8(acc[2 * p] * down, acc[2 * p + 1] * down);
+      if (thin && own) {                                       // G, for lead_thin: each lane what it reads itself
+        float* g = mats + (size_t)head * 3 * D * D + (16 * wave + j) * D + 4 * q;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *(f32x4*)(g + 16 * t) = acc[t] * down;
+      }
       const float srel = (float)max(st.n_del, D) * (float)kRankEps;
       const float floor_rel = fmaxf(srel * srel, kEigFloor);
       const int kq = min(rank, m), kmax = min(kq, st.n_del);
 
-      bf16x4* sbuf = (bf16x4*)sm;                              // [2][3][NT / 2][64][2] the block in its three parts, two copies
-      float4* xbuf = (float4*)(sbuf + 2 * 3 * NT * 64);        // [2][NT][LE_XTILE] the blocks X and Y for their transposition
-      f32x4* gbuf = (f32x4*)(xbuf + 2 * NT * LE_XTILE);        // [2][NT][64] partial X^T X and X^T Y
-      float* rows = (float*)(gbuf + 2 * NT * 64);              // [16][LE_LDR]
-      float* lam = rows + 16 * LE_LDR;                         // [16]
+      const BlockLds<D> lds(sm);
+      bf16x4* sbuf = lds.sbuf;
+      float4* xbuf = lds.xbuf;
+      f32x4* gbuf = lds.gbuf;
+      float *rows = lds.rows, *lam = lds.lam;
       int copy = 0;                                            // of the block, that the next product uses
-      // a block in its three parts to LDS, each wave's sixteen rows
-      auto publish = [&](bf16x4* b, const f32x4 x) {
-        const Split s = split3(x);
-        bf16x4* o = b + ((wave >> 1) * 64 + lane) * 2 + (wave & 1);
-        o[0] = s.hi; o[NT * 64] = s.mid; o[2 * NT * 64] = s.lo;
-      };
-      auto multiply = [&](const Split8& a, const bf16x4* b, const int p, f32x4& y0, f32x4& y1, f32x4& y2) {       // rows 32 p .. of the block b
-        const bf16x8* v = (const bf16x8*)b + lane;
-        const bf16x8 hi = v[p * 64], mid = v[(NT / 2 + p) * 64], lo = v[(NT + p) * 64];
-        y0 = mfma32(a.hi, hi, y0);
-        y1 = mfma32(a.hi, mid, y1);
-        y2 = mfma32(a.hi, lo, y2);
-        y1 = mfma32(a.mid, hi, y1);
-        y2 = mfma32(a.mid, mid, y2);
-        y2 = mfma32(a.lo, hi, y2);
-      };
-      // X - Q^T (Q X): wave w takes rows 16 w .. of Q X (in place of the partial Gram matrices), then its rows of the update
-      auto project_block = [&](f32x4 x) -> f32x4 {
-        bf16x4* b = sbuf + copy * (3 * NT * 64);
-        bf16x4* bs = (bf16x4*)gbuf;
-        copy ^= 1;
-        if (own) publish(b, x);
-        f32x4 qa[NT / 2][2], qc[NT / 2][2];
-        const bool in = 16 * wave + j < r;
-        if (own) {
-          const float* qr = Qb + (size_t)min(16 * wave + j, r - 1) * D + 4 * q;
-#pragma unroll
-          for (int p = 0; p < NT / 2; ++p) {
-            qa[p][0] = *(const f32x4*)(qr + 32 * p); qa[p][1] = *(const f32x4*)(qr + 32 * p + 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int k = 32 * p + 4 * q + e;                // rows past the last: Q X is zero there
-              qc[p][0][e] = Qb[(size_t)min(k, r - 1) * D + 16 * wave + j]; qc[p][1][e] = Qb[(size_t)min(k + 16, r - 1) * D + 16 * wave + j];
-            }
-          }
-        }
-        lds_barrier();
-        if (own) {
-          f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f}, y2 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int p = 0; p < NT / 2; ++p) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { if (!in) { qa[p][0][e] = 0.f; qa[p][1][e] = 0.f; } }
-            multiply(split8(qa[p][0], qa[p][1]), b, p, y0, y1, y2);
-          }
-          publish(bs, y0 + (y1 + y2));
-        }
-        lds_barrier();
-        if (own) {
-          f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f}, y2 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int p = 0; p < NT / 2; ++p) multiply(split8(qc[p][0], qc[p][1]), bs, p, y0, y1, y2);
-          x -= y0 + (y1 + y2);
-        }
-        lds_barrier();
-        return x;
-      };
-      // (P G P) X for the block whose sixteen rows each wave holds; one barrier (thin: G X)
+      // (P G P) X for the block whose sixteen rows each wave holds; one barrier
       auto product = [&](const f32x4 x) -> f32x4 {
         bf16x4* b = sbuf + copy * (3 * NT * 64);
         copy ^= 1;
-        if (own) publish(b, x);
+        if (own) publish<D>(b, x);
         lds_barrier();
         f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f}, y2 = {0.f, 0.f, 0.f, 0.f};
         if (own) {
 #pragma unroll
-          for (int p = 0; p < NT / 2; ++p) multiply(mat[p], b, p, y0, y1, y2);
+          for (int p = 0; p < NT / 2; ++p) multiply<D>(mat[p], b, p, y0, y1, y2);
           __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);   // two groups of reads ahead of the products
           __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
           if (NT > 4) {
@@ -603,74 +724,19 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
           kept_matrix = true;
         };
         const int P = (kmax <= 4) ? 8 : 16;
-        auto random_entry = [&](const int e, const int seed) -> float {          // in [-1, 1), fixed
-          uint32_t h = (uint32_t)((16 * wave + 4 * q + e) * 16 + j) * 2654435761u + (uint32_t)seed * 40503u + 12345u;
-          h ^= h >> 15; h *= 2246822519u; h ^= h >> 13; h *= 3266489917u; h ^= h >> 16;
-          return (float)(int)h * (1.f / 2147483648.f);
-        };
+        auto random_entry = [&](const int e, const int seed) -> float { return block_random(16 * wave + 4 * q + e, j, seed); };
         f32x4 x, y;
         int found = 0, group = 0;
         if (thin) {
-          // An orthonormal basis of the complement from m random vectors, projected and orthonormalised until nothing depended on the
-          // rest twice in a row (twice in all, as a rule), then one Rayleigh-Ritz step, which is the whole eigenproblem.
-          float4* xb = xbuf + wave * LE_XTILE;
-          const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-          auto small_problem = [&](const bool basis_only) {    // X <- X S; the Ritz values (basis_only: one, or zero where dropped) in s_th
-            if (own) {
-              gbuf[wave * 64 + lane] = mul_t(x, x, zero);
-              gbuf[(NT + wave) * 64 + lane] = basis_only ? mul_t(x, x, zero) : mul_t(y, x, mul_t(x, y, zero)) * 0.5f;
-              xb[q * 17 + j] = make_float4(x[0], x[1], x[2], x[3]);
-            }
-            lds_barrier();
-            if (wave == 0) {
-              f32x4 M = gbuf[lane], H = gbuf[NT * 64 + lane];
-#pragma unroll
-              for (int w = 1; w < NT; ++w) { M += gbuf[w * 64 + lane]; H += gbuf[(NT + w) * 64 + lane]; }
-              f32x4 S;
-              float theta;
-              int place;
-              const int sweeps = basis_only ? 0 : 12;
-              if (m <= 8) small_ritz<8>(M, H, 1e-6f, 3e-4f, sweeps, S, theta, place);
-              else small_ritz<16>(M, H, 1e-6f, 3e-4f, sweeps, S, theta, place);
-              s_rot[q * 16 + place] = make_float4(S[0], S[1], S[2], S[3]);
-              if (q == 0) s_th[place] = theta;
-            }
-            lds_barrier();
-            if (own) {
-              const float4 s4 = s_rot[lane];
-              const float* xs = (const float*)(xb + (j >> 2) * 17 + 4 * q) + (j & 3);
-              f32x4 xt;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) xt[e] = xs[4 * e];
-              x = mul_t(xt, f32x4{s4.x, s4.y, s4.z, s4.w}, zero);
-            }
-          };
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = (j < m) ? random_entry(e, -1) : 0.f;
-          x = project_block(x);
-          int whole_before = 0;
-          for (int pass = 0; pass < 6 && whole_before < 2; ++pass) {
-            small_problem(true);
-            const bool all = s_th[m - 1] > 0.f;                // uniform
-            whole_before = all ? whole_before + 1 : 0;
-            if (!all) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) if (j < m && !(s_th[j] > 0.f)) x[e] = random_entry(e, pass);
-            }
-            x = project_block(x);
-          }
-          y = product(x);
-          small_problem(false);
+          lead_thin<D>(Qb, Tg, r, m);
           float total = 0.f;
-          for (int i = 0; i < m; ++i) total += s_th[i];
+          for (int i = 0; i < m; ++i) total += lam[i];
           res2 = uniform(total) * (float)unit;
           rcr = uniform(res2 / (vd2 + 1e-12f));
           pcr = uniform(fmaxf(vd2 - res2, 0.f) / (vd2 + 1e-12f));
           if (res2 > kRcrSkip * vd2) {                         // (not negligible)
-            for (int i = 0; i < kmax; ++i) if (s_th[i] > s_th[0] * floor_rel) ++found;
+            for (int i = 0; i < kmax; ++i) if (lam[i] > lam[0] * floor_rel) ++found;
           }
-          if (own && j < found) *(f32x4*)&rows[j * LE_LDR + 16 * wave + 4 * q] = x;
-          if (tid < 16) lam[tid] = s_th[tid];
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[e] = (j < P) ? random_entry(e, -1) : 0.f;

@@ -1,6 +1,6 @@
 // Fast decision "the retained values span all of R^d" (then Eq. 3's residual is identically zero and
-// the head stays plain eviction) for heads with more retained rows than head_dim.  It is a sufficient test only: heads it cannot certify go to the reference-precision
-// basis kernel.
+// the head stays plain eviction) for heads with more retained rows than head_dim.  Heads it cannot certify go to the reference-precision
+// basis kernel; the allowance for rounding below keeps it from certifying others.
 //
 //   G   = V_s^T V_s over a strided subset V_s of the retained rows (all rows up to 512), on the matrix
 //         cores: products of bf16 values are exact in fp32, accumulation is fp32 (fp32 caches and head_dim
@@ -24,7 +24,16 @@ constexpr int KC_WAVES = KC_THREADS / 64;
 constexpr int KC_D = GS_D;
 constexpr int KC_TILE = GS_TILE;         // rows staged per iteration
 constexpr int KC_MINROWS = 512;          // rows entering G: all up to 512, else about max(512, n/4) at a constant stride
-constexpr float kCertErr = 1.6e-5f;      // allowance for fp32 Gram + factorisation error, relative to the trace of the scaled Gram matrix (= d)
+// Allowance for the rounding of G and of the factorisation, relative to the trace of the scaled Gram matrix (= d).  An entry of S errs by at most as
+// many 2^-24 as its sum and the factorisation's chain have roundings, and d times that bounds the matrix's error.  For bf16 values, whose products are
+// exact, 1.6e-5 is ten times and more what the sums of up to 512 rows and n/4 from there err by with rounding errors of independent signs
+// (the bound itself would be rows 2^-24, above it from 140 rows on).  In single precision (cert_allowance) it is the bound: sums in
+// parts of KF_PART rows, d steps of the factorisation, and 32 for products, scaling and reciprocals.
+constexpr float kCertErr = 1.6e-5f;
+constexpr int KF_PART = 128;
+__device__ __forceinline__ float cert_allowance(const int rows, const int d) {
+  return fmaxf(kCertErr, (float)(KF_PART + (rows + KF_PART - 1) / KF_PART + d + 32) * 5.9604645e-8f);
+}
 
 
 // The lower triangle of G is ten 32x32 tiles (row block rb >= column block cb).  Each tile lives in one wave's
@@ -51,7 +60,7 @@ struct CertShared {
 // is set where a pivot is not positive.
 template <int D>
 __device__ __forceinline__ void cert_factor(f32x16 (&g)[3], const int (&trb)[3], const int (&tcb)[3], const int nt, const float mu,
-                                            CertShared<D>& sh) {
+                                            CertShared<D>& sh, const float allowance = kCertErr) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int lr = lane & 31, lh = lane >> 5;
   const bool has_diag = ((lr & 7) >> 2) == lh;
@@ -80,7 +89,7 @@ __device__ __forceinline__ void cert_factor(f32x16 (&g)[3], const int (&trb)[3],
         g[t][4 * i4 + 2] *= sr.z * sc_col; g[t][4 * i4 + 3] *= sr.w * sc_col;
       }
       if (trb[t] == tcb[t] && has_diag) {
-        const float shift = fmaf(mu, sc_col * sc_col, kCertErr * (float)D);   // mu / G_jj + allowance relative to trace(S) = d
+        const float shift = fmaf(mu, sc_col * sc_col, allowance * (float)D);   // mu / G_jj + allowance relative to trace(S) = d
 #pragma unroll
         for (int i = 0; i < 16; ++i) if (i == di) g[t][i] -= shift;
       }
@@ -372,7 +381,7 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
 
 // The same for the other shapes (fp32 caches, head_dim 64): the Gram matrix by v_mfma_f32_32x32x2_f32 straight from the gathered rows - the
 // operand's lane l holds row l / 32 of a pair and column l % 32, which is how rows lie in memory - a wave per tile or three, the next
-// KF_PAIRS row pairs in flight.  A column whose sum of squares leaves single precision's comfortable range is not certified.
+// KF_PAIRS row pairs in flight, summed in parts of KF_PART rows so that the rounding does not grow with their number.  A column whose sum of squares leaves single precision's comfortable range is not certified.
 // Bound by the latency of the factorisation's D / 4 steps.  96 heads, 205 rows of 64 fp32 values: 20 us, and 5 for the exact basis
 // kernel, which then finds nothing to do (80 with every head in it).
 constexpr int KF_PAIRS = 8;
@@ -400,11 +409,13 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert_rows(const T* __
   if constexpr (D == 128) wave_tiles(wave, trb, tcb, nt);
   else { nt = wave < 3 ? 1 : 0; trb[0] = wave > 0 ? 1 : 0; tcb[0] = wave > 1 ? 1 : 0; }      // (0,0), (1,0), (1,1)
   constexpr int NT = D == 128 ? 3 : 1;
-  f32x16 acc[3];
+  f32x16 acc[3], sums[NT];                                     // of all parts, and of the present one
 #pragma unroll
   for (int t = 0; t < 3; ++t)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) sums[t] = acc[t];
   if (nt > 0) {                                                // wave-uniform; no barrier inside
     float a[2][NT][KF_PAIRS], b[2][NT][KF_PAIRS];
     auto fetch = [&](const int buf, const int r0) {
@@ -424,7 +435,7 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert_rows(const T* __
 #pragma unroll
       for (int p = 0; p < KF_PAIRS; ++p)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[buf][t][p], b[buf][t][p], acc[t], 0, 0, 0);
+        for (int t = 0; t < NT; ++t) sums[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[buf][t][p], b[buf][t][p], sums[t], 0, 0, 0);
     };
     fetch(0, 0);
     for (int r0 = 0; r0 < rows; r0 += 4 * KF_PAIRS) {
@@ -432,6 +443,13 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert_rows(const T* __
       sum(0);
       fetch(0, r0 + 4 * KF_PAIRS);
       sum(1);
+      static_assert(KF_PART % (4 * KF_PAIRS) == 0, "a part is whole rounds");
+      if ((r0 + 4 * KF_PAIRS) % KF_PART == 0 || r0 + 4 * KF_PAIRS >= rows) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) { acc[t][i] += sums[t][i]; sums[t][i] = 0.f; }
+      }
     }
   }
   // ||V_keep||_F^2: the trace where every row is in G, else a sum over all rows
@@ -460,7 +478,7 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert_rows(const T* __
   if (out) sh.bad = 1;
   const double f2 = (red[0] + red[1]) + (red[2] + red[3]);
   const double thr_rel = (double)n * 1.1920928955078125e-07;   // n > D
-  cert_factor<D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), sh);
+  cert_factor<D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), sh, cert_allowance(rows, D));
   __syncthreads();
   if (sh.bad) return;
   cert_settle(0.0, tid, scores + (size_t)head * scs, idx + (size_t)head * max_budget, n, N, want_sums, D, head, state, decided, red, red2);

@@ -536,6 +536,24 @@ def test_full_rank_decision_of_fp32_and_half_width_heads(gpu, dtype, d):
     assert reps[-1].r_keep == d - 1
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_full_rank_decision_over_thousands_of_rows(gpu, dtype, d):
+    """Up to 8190 retained rows, of which every fourth enters the decision's Gram matrix (sixteen parts of its sums and a rest): ordinary
+    heads, heads with one direction missing, and heads of 20 and 50 distinct rows."""
+    budgets = [4097, 8190, 4100, 8190, 6001, 8190]
+    cfg = si.RelayConfig("manyrows", 24, 1, len(budgets), 1, d, 9000, 4, 0, 3, dtype, "structured", outlier_frac=0.01)
+
+    def edit(K, V, Q):
+        N = V.shape[2]
+        V[0, 2, :, 3] = V[0, 2, :, 2]
+        V[0, 3, :, 5] = V[0, 3, :, 6] - V[0, 3, :, 7] if dtype == "f32" else V[0, 3, :, 6]      # a rounding off, far below the rank rule's threshold
+        for h, rows in ((4, 20), (5, 50)):
+            V[0, h] = V[0, h, :rows].copy()[np.arange(N) % rows]
+
+    reps = _check_cfg(gpu, cfg, budgets=budgets, max_budget=max(budgets), edit=edit)
+    assert [r.r_keep for r in reps] == [d, d, d - 1, d - 1, 20, 50]
+
+
 def test_few_active_heads_among_many_certified_ones(gpu):
     """256 heads of 16K tokens with budgets above head_dim, twelve of them rank-deficient: the certificate settles the
     other 244, and the statistics launch (whose full grid would be 4096 workgroups) finds the twelve on the device, in

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_stats_f64(const T* __re
   const int head = blockIdx.y, lane = threadIdx.x & 63;
   const int w = blockIdx.x * GS_WAVES + (threadIdx.x >> 6);
   const int chunk = w / nrb, row = (w - chunk * nrb) * GS_T + (lane & 15);
-  __shared__ double etab[kExpTab];
+  __shared__ ExpTable etab;
   exp_table(etab, threadIdx.x);
   __syncthreads();
   if (chunk >= nchunk) return;                                // whole wave; no barrier follows
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(GS_THREADS, 2) void k_score_mass_f64(const T* __res
                                                                   double* __restrict__ row_lse, float* __restrict__ scores, int N,
                                                                   int R, int kvs) {
   extern __shared__ double s_lse[];                           // [R rounded up to 16]
-  __shared__ double etab[kExpTab];
+  __shared__ ExpTable etab;
   const int head = blockIdx.y, lane = threadIdx.x & 63;
   const int tok = (blockIdx.x * GS_WAVES + (threadIdx.x >> 6)) * NT * GS_T + (lane & 15);     // and the 16 behind
   const T* Qh = Q + (size_t)head * R * D;

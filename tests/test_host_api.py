@@ -3,7 +3,11 @@ declares, sizes its workspace, and rejects bad arguments before anything is enqu
 import ctypes as C
 import os
 import re
+import struct
+from decimal import Decimal, localcontext
+from fractions import Fraction
 
+import numpy as np
 import pytest
 
 from paper_2604_13349_amd import binding as B
@@ -168,3 +172,38 @@ def test_batch_entry_point_checks_every_sample_on_the_host(lib):
     assert lib.obf_workspace_bytes_batch(C.byref(sh), 9, 128, 40, 2) == 3 * one
     assert call(lens, 128, 0, buds, 0, 40, one // 2) == 3                       # OBF_ERR_WORKSPACE_TOO_SMALL
     assert lib.obf_workspace_bytes_batch(C.byref(sh), 3, 40000, 40, 2) == 0
+
+
+def test_table_exponential_is_as_close_as_the_library_one():
+    """The steps of exp_tab in f64_exp.hpp with the constants of that file, every fma rounded once: at most 1.2e-16 of the result off
+    (half a unit in the last place is 1.11e-16; the series adds 0.05e-16, the rounding of r at most 0.02e-16) however large the argument is."""
+    text = open(os.path.join(ROOT, "paper_2604_13349_amd", "csrc", "f64_exp.hpp")).read()
+    frac = [float.fromhex(x) for x in re.findall(r"0x1\.[0-9a-f]{13}p\+0", text)]
+    rest = [struct.unpack("<d", struct.pack("<Q", int(x, 16) << 32))[0] for x in re.findall(r"(0x[0-9a-f]{8}),", text)] or [0.0] * len(frac)
+    per = float.fromhex(re.search(r"fma\(x, (0x1[^,]*p\+\d)", text).group(1))
+    parts = [-float.fromhex(x) for x in re.findall(r"-(0x1\.[0-9a-f]+p-\d+)", text)]       # ln2 over the table's length: the large one, the small one
+    series = re.search(r"double p = (.*);", text).group(1)
+    coeff = [float(Fraction(1, int(n))) if n else float.fromhex(c) for n, c in re.findall(r"(?:1\.0 / (\d+)|(0x1\.[0-9a-f]+p-\d))", series)] + [0.5, 1.0]
+    size = len(frac)
+    assert size == len(rest) and size in (64, 256) and len(coeff) >= 4
+    fma = lambda a, b, c: float(Fraction(a) * Fraction(b) + Fraction(c))
+    magic = 1.5 * 2.0 ** 52
+    rng = np.random.default_rng(3)
+    worst = 0.0
+    with localcontext() as ctx:
+        ctx.prec = 40
+        for lo in (-1e-3, -1.0, -10.0, -40.0, -690.0):
+            for x in rng.uniform(lo, 0.0, 400):
+                x = float(x)
+                n = fma(x, per, magic) - magic
+                r = x
+                for c in sorted(parts):
+                    r = fma(n, c, r)
+                k = int(n)
+                f = frac[k % size] * 2.0 ** (k // size)
+                p = coeff[0]
+                for c in coeff[1:]:
+                    p = fma(r, p, c)
+                e = Decimal(x).exp()
+                worst = max(worst, abs(float((Decimal(fma(f, fma(p, r, rest[k % size]), f)) - e) / e)))
+    assert worst <= 1.2e-16

@@ -9,7 +9,7 @@
 //   pass B: a wave keeps the operand of 16 or 32 tokens and walks all query rows (rows x tokens: a lane owns one token).
 // Bound by the double-precision matrix rate (64 multiply-adds per clock and compute unit: 43 us a pass at the first shape below) and
 // the exponentials, which the same units compute: f64_exp.hpp's, of half the math library's instructions.  96 heads x 2048 tokens x
-// 128 rows at head_dim 64: 88 and 79 us (102 and 88 with the library's exponential and a tile of tokens per wave).  With the products as scalar multiply-adds fed from
+// 128 rows at head_dim 64, both: 153 us (170 with the library's exponential and a tile of tokens per wave).  With the products as scalar multiply-adds fed from
 // LDS: 975 and 853 us; 2 heads x 512 tokens x 32 rows 224 and 215, now 12 and 6.
 #include "f64_exp.hpp"
 #include "f64_tile.hpp"
@@ -21,10 +21,12 @@ constexpr int GS_WAVES = GS_THREADS / 64;
 constexpr int GS_T = 16;                 // tokens and query rows per tile
 constexpr int GS_MIN_TILES = 2;          // shortest chunk of pass A, in tiles
 constexpr int GS_TARGET_WAVES = 4096;    // waves of pass A that fill the chip (four per SIMD); fewer, longer chunks beyond
-// A wave of pass B takes two tiles of tokens, which share the query operand's reads and conversions, from this many tokens of all heads and query
-// rows on: 96 heads x 2048 x 128 rows 85 -> 79 us, both passes of 40 x 4000 x 64 rows 97 -> 93, of 288 x 2048 x 128 447 -> 433; 96 x 1500 x 128, which
-// then no longer fills the chip evenly, 118 -> 120, and 32 rows gain nothing.
-constexpr long GS_WIDE_TOKENS = 160000;
+// A wave of pass B takes two tiles of tokens, which share the query operand's reads and conversions, where the compute unit with most
+// workgroups then has at most a tenth more tokens to do (from this many query rows on: with fewer there is little to share).  Both passes, us,
+// one tile - two a wave:
+//   as many       96 heads x 1024 x 128 rows 88 - 84, x 2048 161 - 155; 64 x 2048 x 128 123 - 119; 40 x 4000 x 64 102 - 97; 8 x 16384 x 64 81 - 79
+//   a tenth more  96 x 1500 x 128 124 - 125; 288 x 512 x 128 129 - 129
+//   more          96 x 768 x 128 80 - 82; 288 x 256 x 128 73 - 76; 96 x 1300 x 128 110 - 117; 1280 x 130 x 128 167 - 180
 constexpr int GS_WIDE_ROWS = 64;
 constexpr int GS_FOLD = 1024;            // partials per head up to which pass B folds them itself (each of its workgroups reads them all;
                                          // a launch of its own costs 5 us)
@@ -230,7 +232,11 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
       hipLaunchKernelGGL(kernel, dim3((m.N + per_wg - 1) / per_wg, m.heads), dim3(GS_THREADS), sizeof(double) * nrb * GS_T, st, (const T*)K,
                          (const T*)Q, fold ? (const double*)stats_part : (const double*)nullptr, nchunk, row_lse, scores, m.N, m.R, m.kvs);
     };
-    if ((long)m.heads * m.N >= GS_WIDE_TOKENS && m.R >= GS_WIDE_ROWS) go(k_score_mass_f64<T, D, WIDE>, WIDE);
+    auto busiest = [&](const int nt) {                        // tiles of tokens of a wave of the compute unit with most of them
+      const int per_wg = GS_WAVES * GS_T * nt;
+      return (((long)m.heads * ((m.N + per_wg - 1) / per_wg) + kNumCU - 1) / kNumCU) * nt;
+    };
+    if (10 * busiest(2) <= 11 * busiest(1) && m.R >= GS_WIDE_ROWS) go(k_score_mass_f64<T, D, WIDE>, WIDE);
     else go(k_score_mass_f64<T, D, 1>, 1); }
   return check_launch("score mass (f64)");
 }

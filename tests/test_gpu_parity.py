@@ -286,6 +286,18 @@ def test_scores_of_many_half_width_heads(gpu, dtype, N, R):
         np.testing.assert_allclose(sc[l, 1].cpu().numpy(), O.attention_mass(k, q), rtol=6.1e-8, atol=1e-38)
 
 
+@pytest.mark.parametrize("N", [8192, 8193, 16384, 16385])     # two tiles of tokens per wave in the middle ones, where that leaves no compute unit behind
+def test_scores_of_few_long_half_width_heads(gpu, N):
+    import torch
+    from paper_2604_13349_amd import binding as B
+    cfg = si.RelayConfig("long64", 37, 1, 2, 1, 64, N, 65, 1, 0, "f32", "structured", outlier_frac=0.01)
+    K, _, Q = si.make_cache(cfg, 0)
+    sc, _ = B.score(gpu.to_dev(K, "f32"), gpu.to_dev(Q, "f32"))
+    torch.cuda.synchronize()
+    for h in range(2):                                        # half a unit in the stored mass's last place
+        np.testing.assert_allclose(sc[0, h].cpu().numpy(), O.attention_mass(K[0, h].astype(np.float64), Q[0, h].astype(np.float64)), rtol=6.1e-8, atol=1e-38)
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
 @pytest.mark.parametrize("spread", [1.0, 60.0, 4000.0])     # logits of a row lie about as far apart: within, around and far past what the exponent holds
 def test_scores_of_logits_far_apart(gpu, dtype, d, spread):

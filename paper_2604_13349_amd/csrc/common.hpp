@@ -64,7 +64,7 @@ struct Workspace {
   size_t stats_part;   // double2 [heads][nchunk][R]      partial (max, sum-exp) per score chunk
   size_t row_lse;      // double  [heads][R]
   size_t scores;       // float   [heads][N]              (fused call without scores_out)
-  size_t score_part;   // float   [RG][heads][N]          per-row-group column sums when group*window > 128
+  size_t score_part;   // float   [mass_groups][heads][N] per-row-group column sums where the second score pass has several
   size_t head_state;   // HeadState [heads]
   size_t decided;      // int32   [heads]                 1: the fast full-rank test settled the head
   size_t basis;        // float   [heads][d][d]           orthonormal basis of the retained span (columns)
@@ -82,7 +82,7 @@ struct Workspace {
   size_t route;        // int32   [heads][N]              retained slot of every deleted token (cache merging, when not an output)
   size_t total;
   int nchunk;          // most chunks per head of the double-precision score path
-  int rgroups, tiles_per_head, tiles_per_range, nranges, nslot;   // matrix-core score partition
+  int rgroups, mass_groups, tiles_per_head, tiles_per_range, nranges, nslot;   // matrix-core score partition
   int nstat;           // statistics chunks per head
 };
 
@@ -132,7 +132,10 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.stats_part = take(sizeof(double) * 2 * (size_t)m.heads * (w.nchunk > w.nslot ? w.nchunk : w.nslot) * m.R);
   w.row_lse = take(sizeof(double) * (size_t)m.heads * m.R);
   w.scores = take(sizeof(float) * (size_t)m.heads * m.N);
-  w.score_part = take(w.rgroups > 1 ? sizeof(float) * (size_t)w.rgroups * m.heads * m.N : 0);
+  // the second pass takes pairs of 128-row groups as one (and the double-precision path all rows); a single group writes its sums to the scores
+  w.mass_groups = (w.rgroups % 2 == 0 && score_rows_per_group(m.R) == 128) ? w.rgroups / 2 : w.rgroups;
+  if (m.dtype != OBF_BF16 || m.d != 128) w.mass_groups = 1;
+  w.score_part = take(w.mass_groups > 1 ? sizeof(float) * (size_t)w.mass_groups * m.heads * m.N : 0);
   w.head_state = take(sizeof(HeadState) * (size_t)m.heads);
   w.decided = take(sizeof(int32_t) * (size_t)m.heads);
   w.basis = take(sizeof(float) * (size_t)m.heads * m.d * m.d);

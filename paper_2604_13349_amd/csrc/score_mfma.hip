@@ -492,7 +492,6 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
   double* stats_part = (double*)(ws + w.stats_part);
   const int RG = w.rgroups;
   const size_t rg_stride = (size_t)m.heads * m.N;
-  float* part = (RG > 1) ? (float*)(ws + w.score_part) : scores;
   Part pt;
   pt.TH = w.tiles_per_head; pt.T = w.tiles_per_range; pt.TT = (long)m.heads * w.tiles_per_head;
   pt.kstride = (long)m.kvs * SM_D;
@@ -521,9 +520,9 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
   // to be added (the first pass keeps its groups: its normalisers depend on where a row's tokens are split).
   // 288 heads of 32768 tokens, 256 rows: 796 + 35 us -> 785, one launch less.  320 rows at once instead of two groups of 160 were slower
   // (504 + 20 -> 559: the compiler moves Q operands between the register files), so those stay.
-  const bool tall = !five && RG % 2 == 0;
-  const int RGB = tall ? RG / 2 : RG;
-  if (RGB == 1) part = scores;
+  const int RGB = w.mass_groups;
+  const bool tall = RGB != RG;
+  float* part = (RGB > 1) ? (float*)(ws + w.score_part) : scores;
   Part pb = pt;
   if (tall) pb.T = score_tiles_per_range(pt.TT, RGB);
   const dim3 grid_b((unsigned)(((pb.TT + pb.T - 1) / pb.T + 7) / 8 * 8 * RGB));

@@ -207,3 +207,18 @@ def test_table_exponential_is_as_close_as_the_library_one():
                 e = Decimal(x).exp()
                 worst = max(worst, abs(float((Decimal(fma(f, fma(p, r, rest[k % size]), f)) - e) / e)))
     assert worst <= 1.2e-16
+
+
+@pytest.mark.parametrize("window,dtype,d,sums", [(128, "bf16", 128, 0), (256, "bf16", 128, 0), (320, "bf16", 128, 2), (384, "bf16", 128, 3),
+                                                 (512, "bf16", 128, 2), (384, "f32", 128, 0), (384, "bf16", 64, 0)])
+def test_workspace_holds_column_sums_of_the_second_pass_groups_only(lib, window, dtype, d, sums):
+    """One set of column sums per row group of the second score pass where it has several: pairs of 128-row groups are one there,
+    and the double-precision path takes all rows at once.  What else grows with the rows is 16 bytes per row and chunk of tokens."""
+    heads, N = 288, 32768
+    size = lambda w: B.workspace_bytes(B.make_shape(36, 8, 1, d, N, w, dtype), 64, 2)
+    rest = heads * window * (16 * (N // 512 + 2) + 8)
+    extra = size(window) - size(1)
+    if sums == 0:
+        assert extra <= rest
+    else:
+        assert 4 * heads * N * sums <= extra <= 4 * heads * N * sums + rest

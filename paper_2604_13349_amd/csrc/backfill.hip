@@ -501,39 +501,6 @@ __host__ __device__ inline int fn_small_floats(int d) {
   return a > b ? a : b;
 }
 
-// Check after a Jacobi sweep, for a workgroup of FN_THREADS threads (all must call): have the rows of the `rank` largest
-// diagonal entries of the symmetric mm x mm matrix T (upper triangle current, row stride lt) separated from the rest?
-// True when each of those rows has off-diagonal energy of at most tol / 100 and every other row's Gershgorin bound is
-// under 0.99 times the smallest of those diagonal entries.  *total receives the off-diagonal energy of the whole of T.
-// The arrays are LDS scratch of mm floats.
-__device__ __forceinline__ bool jacobi_lead_rows_done(const float* T, int lt, int mm, int rank, float tol, float* dg,
-                                                   float* rowe, float* gers, float* lead_min, int* ok, float* total) {
-  const int tid = threadIdx.x;
-  if (tid < mm) {
-    float ro = 0.f, ga = 0.f;
-    for (int b = 0; b < mm; ++b) {
-      if (b != tid) { const float v = T[min(tid, b) * lt + max(tid, b)]; ro = fmaf(v, v, ro); ga += fabsf(v); }
-    }
-    const float dgv = T[tid * lt + tid];
-    dg[tid] = dgv; rowe[tid] = ro; gers[tid] = dgv + ga;
-  }
-  if (tid == 0) *ok = 1;
-  __syncthreads();
-  int rk = mm;
-  if (tid < mm) {
-    const float mine = dg[tid];
-    rk = 0;
-    for (int j = 0; j < mm; ++j) { const float o = dg[j]; rk += (o > mine) || (o == mine && j < tid); }
-    if (rk < rank && !(rowe[tid] <= 0.01f * tol)) *ok = 0;
-    if (rk == rank - 1) *lead_min = mine;
-  }
-  if (tid == 0) { float t = 0.f; for (int a = 0; a < mm; ++a) t += rowe[a]; *total = t; }
-  __syncthreads();
-  if (tid < mm && rk >= rank && !(gers[tid] < 0.99f * *lead_min)) *ok = 0;
-  __syncthreads();
-  return *ok != 0;
-}
-
 // ---- An orthonormal basis Z of the complement of at most FN_FEW orthonormal rows Q [r][d], m = d - r.
 // Householder reconstruction (Ballard, Demmel, Grigori, Jacquelin, Nguyen, Solomonik: "Reconstructing Householder vectors from
 // tall-skinny QR"): with Q1 = Q[:, :r], Q2 = Q[:, r:] and signs S = diag(+-1), M = Q1^T - S factors without pivoting when
@@ -1159,33 +1126,22 @@ __global__ __launch_bounds__(FN_THREADS, 8) void k_bf_finalize(int N, int d, int
           }
           lds_barrier();
         }
-        // The sweeps stop when the off-diagonal energy is below single-precision noise of the trace.  Where only a few
-        // leading eigenpairs are used (no Max-P / EVR rule, rank <= mm/8) they also stop as soon as the rows of the
-        // `rank` largest diagonal entries are each a hundred times further below that level and every other row's
-        // Gershgorin bound stays under the smallest of them by 1 %: those diagonal entries are then the leading
-        // eigenvalues and their rotations' columns the eigenvectors, to the same residual as at full convergence,
-        // whatever the rest of T still looks like.
+        // The sweeps stop when the off-diagonal energy is below single-precision noise of the trace.
         const float tol = 1e-13f * res2 * res2;
-        const bool lead_only = !(vflags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR)) && 8 * rank <= mm;
-        bool lead_done = false;
-        if (lead_only) {
-          lead_done = jacobi_lead_rows_done(M, lt, mm, rank, tol, lamv, svec, dvec, &fred[1], &s_k, &s_off);
-        } else {
-          float off = 0.f;
-          for (int e = tid; e < mm * mm; e += FN_THREADS) {
-            const int a = e / mm, b = e - a * mm;
-            if (a < b) { const float v = M[a * lt + b]; off = fmaf(2.f * v, v, off); }
-          }
-          for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o);
-          if ((tid & 63) == 0) fred[tid >> 6] = off;
-          __syncthreads();
-          if (tid == 0) { float t = 0.f; for (int i = 0; i < FN_WAVES; ++i) t += fred[i]; s_off = t; }
-          __syncthreads();
+        float off = 0.f;
+        for (int e = tid; e < mm * mm; e += FN_THREADS) {
+          const int a = e / mm, b = e - a * mm;
+          if (a < b) { const float v = M[a * lt + b]; off = fmaf(2.f * v, v, off); }
         }
+        for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o);
+        if ((tid & 63) == 0) fred[tid >> 6] = off;
+        __syncthreads();
+        if (tid == 0) { float t = 0.f; for (int i = 0; i < FN_WAVES; ++i) t += fred[i]; s_off = t; }
+        __syncthreads();
         const float offn = s_off;
         __syncthreads();
         nsweeps = sweep + 1;
-        if (offn <= tol || lead_done) break;
+        if (offn <= tol) break;
       }
       if (replay && tid < half) {                              // whole sweeps end in the layout of set 0
         rbar[tid == 0 ? mm - 1 : tid] = za;

@@ -30,9 +30,11 @@ constexpr int SM_D = 128;
 constexpr int SM_KK = SM_D / 16;         // MFMA k-steps
 constexpr int SM_TILE = 32;              // tokens per MFMA tile
 constexpr float kLog2e = 1.4426950408889634f;
-// Prompts that take both score passes in one launch, a workgroup per head (128 rows, us, one launch against two): 288 heads 36 - 40 at 768
-// tokens, 44 - 49 at 1024, 52 - 55 at 1280, 60 - 60 at 1536; 96 heads 20 - 33 at 768, 27 - 38 at 1280; 32 heads, which leave most of the
-// chip idle, 20 - 19 at 768 and 23 - 20 at 1024.
+// Prompts that take both score passes in one launch, a workgroup per head (us, one launch - two):
+//   288 heads x 128 rows  1280 tokens 53 - 57, 1536 60 - 62    x 64 rows  45 - 50, 53 - 54    x 32 rows  43 - 47, 51 - 51
+//    96 heads x 128 rows  1280 tokens 27 - 28, 1536 30 - 29    x 64 rows  24 - 25, 27 - 27    x 32 rows  23 - 24, 26 - 26
+//    64 heads x 128 rows   768 tokens 21 - 22, 1024 24 - 22    x 64 rows  17 - 19, 21 - 20    x 32 rows  16 - 18, 19 - 19
+//    32 heads x 128 rows   768 tokens 21 - 20, 1024 24 - 21    x 64 rows  17 - 17, 21 - 18    x 32 rows  16 - 16, 19 - 18
 constexpr int kScoreOneLaunchTokens = 768, kScoreOneLaunchTokensMany = 1280, kScoreOneLaunchMany = 96;
 
 union Frag { uint4 u; bf16x8 v; };

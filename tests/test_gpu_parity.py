@@ -356,7 +356,7 @@ def test_scores_of_paired_row_groups(gpu, R, L, N):
 
 @pytest.mark.parametrize("R", [1, 32, 33, 64, 65, 128])      # one, two and four row blocks
 @pytest.mark.parametrize("L,N", [(1, 1), (1, 31), (1, 129), (1, 161), (2, 767), (2, 769), (8, 2053), (48, 769), (48, 1280), (48, 1281),
-                                 (1, 4100), (60, 1300)])     # ranges that end with their head, the last of them empty
+                                 (1, 4100), (60, 1300)])     # ranges that end with their head, padded with tiles past its tokens
 def test_scores_of_one_row_group(gpu, R, L, N):
     """Short prompts, a workgroup per head, those just past them (96 heads: 1280 tokens, fewer: 768), and longer ones."""
     _check_masses(gpu, R, L, N, sorted({0, L // 2, L - 1}))

@@ -84,7 +84,8 @@ typedef struct {
   int32_t n_keep;   /* retained tokens */
   int32_t r_keep;   /* dimension of the retained value span (Eq. 2); 0 if not computed */
   int32_t k_used;   /* residual principal directions used (Sec. 4.4, k = min(pca_rank, rank R)) */
-  int32_t skipped;  /* 1: no injection (empty P_del, rank 0, span = R^d, negligible residual) */
+  int32_t skipped;  /* 1: no injection (empty P_del, rank 0, span = R^d, negligible residual, or deleted values whose squares
+                       add up past single precision's 3.4e38: plain eviction) */
   float a_keep;     /* sum of attention mass over retained tokens (Eq. 6) */
   float a_del;      /* sum over deleted tokens */
   float rcr;        /* residual content ratio ||R||_F^2 / (||V_del||_F^2 + eps) */

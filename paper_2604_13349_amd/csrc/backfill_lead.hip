@@ -15,8 +15,17 @@
 // small problems on one wave (8000 cycles a step for eight columns, 14000 for sixteen).  At m = 96, k = 2 a workgroup takes 120000 cycles:
 // G 10, the projection 17, sixteen products 30, four small problems 30 with 10 around them, the rest loads and the tail.  It took the place
 // of a basis of the complement, the tridiagonalisation of its m x m matrix and inverse iteration (68 + 148 us for 288 heads of 256 tokens with 32
-// kept, 2 directions; 66 now, the whole call 296 -> 156; twelve samples 2060 -> 1050), and the offset's error against double
+// kept, 2 directions; 79 now, the whole call 299 -> 155; twelve samples 2060 -> 1020), and the offset's error against double
 // precision fell from 8.6e-7 to 3.3e-7 (2000 tokens with 96 kept, 8 directions: 4.0e-6 to 5.0e-7).
+//
+// What it depends on: this kernel against those before it (us, 288 heads), and the whole call
+//   256 tokens, 32 kept    2, 8, 12, 16 directions   210 223 272 282 -> 79 97 125 164    299 312 360 369 -> 155 173 201 241
+//   1024 tokens, 80 kept                             165 172 199 207 -> 107 127 152 200  331 338 365 373 -> 244 263 286 330
+//   2000 tokens, 96 kept                             130 136 156 163 -> 117 133 156 198  366 371 390 395 -> 311 327 353 391
+//   1024 tokens, 112 kept                             99 103 118 123 -> 101 100 100 101  316 320 336 340 -> 299 301 301 300
+// A narrow complement costs as much as a wide one here, the kernels before it worked in its own coordinates: at 32 columns they are ahead from
+// thirteen directions on, and where the direct route takes over after the first products (eigenvalues closer than the block can tell
+// apart, 2 directions: complements 96, 64, 32 and 20 wide 308 300 267 275 -> 355 338 315 327).
 #include "common.hpp"
 #include "wave_ops.hpp"
 #include "tri_eigs.hpp"
@@ -29,7 +38,7 @@ constexpr int LE_XTILE = 68;             // float4 of one wave's 16 x 16 tile of
 constexpr int LE_LDR = 132;              // floats between rows of a subspace basis in LDS
 // The widths and limits of the block iteration.  Eight columns for up to four directions (a sweep of the small problem costs 2000 cycles
 // against 5000, which the slower convergence does not make up), sixteen for more; up to twelve directions at a time (twelve together:
-// 206 us for 288 heads of 256 tokens with 32 kept and 339 with 96 of 2000; as eight and four: 226 and 363), the thirteenth on in groups of eight.
+// the whole call takes 206 us for 288 heads of 256 tokens with 32 kept and 339 with 96 of 2000; as eight and four: 226 and 363), the thirteenth on in groups of eight.
 constexpr int kBlockMaxRank = 12;        // most directions the block iteration is asked for at a time
 constexpr int kThinWidth = 16;           // complements no wider than this are spanned by a block
 constexpr int kGroups = 4;               // most times that it goes on with the rest of the matrix
@@ -487,7 +496,8 @@ __device__ __forceinline__ float uniform(const float v) {
 
 // FAST selects the fast path of App. H: `iters` steps of C <- orth(C P G P) from a fixed orthonormal start; the exact directions are
 // then only found when diagnostics are wanted, to report how far the fast path's Delta is from theirs.  (A kernel of its own: the calls
-// to the orthogonalisation push six values of each of its products to scratch, none of the others'.)
+// to the orthogonalisation push six values of each of its products to scratch.  The compiler reports 38 registers that go to scratch
+// somewhere in the plain kernel of head_dim 128, 116 in this one and 97 in the THIN one; at head_dim 64 none, 89 and 13.)
 // THIN: some heads may retain so many directions that their complement is no wider than a block (kThinWidth).  P G P is not formed for
 // those (Q has more rows than there would be products): products with G are followed by a projection of the block, and the block's Ritz
 // values give the trace; see lead_thin.  (288 heads of 1024 tokens, 112, 120 and 126 kept, whole call, 8 directions: 302, 316 and 313 us

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(SEL_THREADS, 4) void k_select(const float* __restri
 
   if (B == 0 || B == N) {
     for (int i = tid; i < max_budget; i += SEL_THREADS) out[i] = (i < B) ? i : -1;
-    if (tid == 0) n_keep[head] = B;
+    if (tid == 0) { n_keep[head] = B; if (REFINE && sel_flags) sel_flags[head] = 0; }
     return;
   }
   const int base = tid * SEG;

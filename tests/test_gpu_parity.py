@@ -1598,3 +1598,15 @@ def test_relay_row_codes_at_workgroup_edges(gpu, dtype, d, bits, rows, offset):
     back = Bd.dequantize_rows(chold[offset:].view(codes.shape), scale, zero, d, flat.dtype, bits)
     torch.cuda.synchronize()
     assert np.array_equal(gpu.to_host(back, dtype), O.round_to_io(O.dequantize_rows(q_ref, s_ref, z_ref), dtype))
+
+
+def test_select_flags_of_heads_that_keep_nothing_or_everything(gpu):
+    """Nothing is re-decided for them: their flags are zero, whatever the workspace held."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    cfg = si.RelayConfig("flags", 53, 1, 3, 2, 128, 70, 8, 0, 2, "bf16", "structured", outlier_frac=0.01)
+    K, V, Q = (gpu.to_dev(x, "bf16") for x in si.make_cache(cfg, 0))
+    ws = torch.full((Bd.workspace_bytes(Bd.shape_of(K, Q), 70, 2),), 0x55, dtype=torch.uint8, device="cuda")
+    o = Bd.compress_relay(K, V, Q, budgets=np.array([0, 70, 20], np.int32), rank=2, max_budget=70, want_diag=True, ws=ws)
+    torch.cuda.synchronize()
+    assert np.all(Bd.diag_to_numpy(o["diag"])["select_flags"] == 0)

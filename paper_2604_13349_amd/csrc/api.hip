@@ -297,9 +297,11 @@ static obf_status_t compress_heads(int layerwise, Variant var, const Dims& mf, i
   }
   // the gather also leaves the sums of squares of the retained V rows for the full-rank certificate
   double* fro_part = (m.dtype == OBF_BF16 && m.d == 128) ? (double*)(base + w.fro_part) : nullptr;
-  // small budgets: the bases of the retained spans start now on a second stream, beside the gather
+  // small budgets: the bases of the retained spans, the statistics and the gather are one launch, or (more than 96 rows) the bases start now on a
+  // second stream, beside the gather
   bool basis_started = false;
-  if (!var.skips_basis()) {
+  const bool together = !var.skips_basis() && basis_stats_supported(max_budget, rank, m.d);
+  if (!var.skips_basis() && !together) {
     const obf_status_t bs = launch_backfill_basis(m, w, base, V, scores, idx, n_keep, max_budget, rank, st, aux, &basis_started);
     if (bs != OBF_OK) {
       if (basis_started) (void)stream_after(st, aux, EV_BASIS_JOIN);      // never leave the second stream un-joined
@@ -310,7 +312,9 @@ static obf_status_t compress_heads(int layerwise, Variant var, const Dims& mf, i
   // V rows (which the certificate waits for) are through, beside the latency-bound per-head kernels.
   bool k_beside = false;
   obf_status_t rs = OBF_OK;
-  if (!basis_started && aux && aux != st && (size_t)max_budget * m.heads >= 65536) {
+  if (together) {
+    rs = launch_basis_stats(m, w, base, K, V, scores, idx, n_keep, max_budget, rank, K_out, V_out, st);
+  } else if (!basis_started && aux && aux != st && (size_t)max_budget * m.heads >= 65536) {
     rs = launch_gather(m, nullptr, V, idx, n_keep, max_budget, nullptr, V_out, st, fro_part);
     if (rs == OBF_OK) rs = stream_after(aux, st, EV_KROWS_FORK);
     if (rs == OBF_OK) { k_beside = true; rs = launch_gather(m, K, nullptr, idx, n_keep, max_budget, K_out, nullptr, aux, nullptr); }
@@ -323,7 +327,7 @@ static obf_status_t compress_heads(int layerwise, Variant var, const Dims& mf, i
   if (rs == OBF_OK || basis_started) {
     const obf_status_t fs = (rs == OBF_OK)
         ? launch_backfill(m, w, base, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part,
-                          basis_started, min_budget, var)
+                          together ? Begun::statistics : basis_started ? Begun::bases : Begun::nothing, min_budget, var)
         : stream_after(st, aux, EV_BASIS_JOIN);
     if (rs == OBF_OK) rs = fs;
   }
@@ -412,7 +416,7 @@ obf_status_t obf_backfill_variant(const obf_shape_t* shape, const void* V, const
   Workspace w = carve(m, max_budget, rank);
   OBF_TRY(check_ws(m, w, ws, ws_bytes));
   return launch_backfill(m, w, (char*)ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag,
-                         (hipStream_t)stream, aux_stream(0), nullptr, false, -1, var);
+                         (hipStream_t)stream, aux_stream(0), nullptr, Begun::nothing, -1, var);
 }
 
 obf_status_t obf_compress_relay_window(const obf_shape_t* shape, const obf_window_t* window,

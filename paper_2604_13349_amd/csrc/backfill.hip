@@ -1309,7 +1309,8 @@ template <typename T>
 static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void* V, const float* scores,
                         const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank, void* V_out,
                         float* delta_out, obf_diag_t* diag, hipStream_t st, hipStream_t aux, const double* fro_part,
-                        bool basis_started, int32_t min_budget, Variant var) {
+                        Begun begun, int32_t min_budget, Variant var) {
+  bool basis_started = begun == Begun::bases;
   // Once the bases run on `aux`, every way out of this function joins it back into `st` first, errors included: the
   // caller is promised that all work of the call is ordered on its stream.
   struct Join {
@@ -1340,18 +1341,23 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     return OBF_ERR_UNSUPPORTED;
   }
   void* V_inject = (var.flags & VF_PER_TOKEN) ? nullptr : V_out;   // Per-token: the per-slot directions are added by a later kernel
+  if (begun == Begun::nothing && !var.skips_basis() && basis_stats_supported(max_budget, rank, m.d)) {
+    if (launch_basis_stats(m, w, ws, nullptr, V, scores, idx, n_keep, max_budget, rank, nullptr, nullptr, st) != OBF_OK) return OBF_ERR_HIP;
+    begun = Begun::statistics;
+  }
+  const bool prepared = begun == Begun::statistics;
   if (var.skips_basis()) {
-    if (basis_started) { set_error("backfill: a basis was started for a variant without one"); return OBF_ERR_INVALID_ARG; }
+    if (begun != Begun::nothing) { set_error("backfill: a basis was started for a variant without one"); return OBF_ERR_INVALID_ARG; }
     ProfScope prof_(ST_KEEP_BASIS, st);
     hipLaunchKernelGGL(k_bf_plain_state, dim3(m.heads), dim3(KB_THREADS), 0, st, scores, idx, n_keep, m.N, max_budget, rank, state, m.scs);
     if (check_launch("backfill plain state") != OBF_OK) return OBF_ERR_HIP;
-  } else if (!basis_started) {
+  } else if (!basis_started && !prepared) {
     // the caller did not start the bases earlier: try here (beside the statistics pass only)
     const obf_status_t bs = launch_backfill_basis(m, w, ws, V, scores, idx, n_keep, max_budget, rank, st, aux, &basis_started);
     join.armed = basis_started;
     if (bs != OBF_OK) return OBF_ERR_HIP;
   }
-  if (!basis_started && !var.skips_basis()) {
+  if (!basis_started && !prepared && !var.skips_basis()) {
     const size_t smem_kb = sizeof(double) * (size_t)m.d * m.d;
     int32_t* decided = nullptr;
     if (keep_cert_supported(m, max_budget)) {
@@ -1378,7 +1384,8 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
   }
   // while the bases are still being written on the second stream the statistics pass must not read the head states
   const int32_t* nk_stats = basis_started ? n_keep : nullptr;
-  if (rank > 0 && del_stats_mfma_supported(m)) {
+  if (prepared) {                                                // done
+  } else if (rank > 0 && del_stats_mfma_supported(m)) {
     // every budget above head_dim: the certificate settles nearly every head, the few others are found on the device
     const bool few_active = min_budget > m.d && m.N > m.d && !var.skips_basis();
     if (launch_del_stats_mfma(m, w, V, scores, idx, max_budget, state, nk_stats, gram_part, st, few_active) != OBF_OK) return OBF_ERR_HIP;
@@ -1413,10 +1420,10 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
 obf_status_t launch_backfill(const Dims& m, const Workspace& w, char* ws, const void* V, const float* scores,
                              const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank,
                              void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, hipStream_t aux,
-                             const double* fro_part, bool basis_started, int32_t min_budget, Variant var) {
+                             const double* fro_part, Begun begun, int32_t min_budget, Variant var) {
   if (m.dtype == OBF_BF16)
-    return run<uint16_t>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, basis_started, min_budget, var);
-  return run<float>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, basis_started, min_budget, var);
+    return run<uint16_t>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, begun, min_budget, var);
+  return run<float>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, begun, min_budget, var);
 }
 
 }  // namespace obf

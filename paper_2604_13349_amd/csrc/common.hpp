@@ -293,15 +293,22 @@ void set_single_stream(bool on);
 enum EventSlot { EV_SCORED = 0, EV_BASIS_FORK, EV_BASIS_JOIN, EV_KROWS_FORK, EV_KROWS_JOIN, EV_BATCH_FORK, EV_BATCH_JOIN, EV_COUNT };
 obf_status_t stream_after(hipStream_t waiter, hipStream_t signaller, int slot);
 // Optional early start of the retained-span bases on `aux` (forked from st), for shapes where they do not depend on
-// the gather; *started is then passed on to launch_backfill as basis_started, which joins `aux` back.
+// the gather; *started is then passed on to launch_backfill as Begun::bases, which joins `aux` back.
 obf_status_t launch_backfill_basis(const Dims& m, const Workspace& w, char* ws, const void* V, const float* scores,
                                    const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank,
                                    hipStream_t st, hipStream_t aux, bool* started);
+// Bases, statistics and, with K_out and V_out given, the gathered rows of calls with small budgets in one launch (basis_stats.hip).
+bool basis_stats_supported(int32_t max_budget, int32_t rank, int d);
+obf_status_t launch_basis_stats(const Dims& m, const Workspace& w, char* ws, const void* K, const void* V, const float* scores,
+                                const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank, void* K_out /*nullable*/,
+                                void* V_out /*nullable*/, hipStream_t st);
+// What of the back-fill the caller has already enqueued: nothing; the bases, on `aux`; the bases and the statistics, on `st`.
+enum class Begun { nothing, bases, statistics };
 obf_status_t launch_backfill(const Dims& m, const Workspace& w, char* ws, const void* V, const float* scores,
                              const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank,
                              void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, hipStream_t aux /*nullable*/,
                              const double* fro_part = nullptr,
-                             bool basis_started = false, int32_t min_budget = -1 /*smallest per-head budget if known*/,
+                             Begun begun = Begun::nothing, int32_t min_budget = -1 /*smallest per-head budget if known*/,
                              Variant var = Variant());
 
 // Rank rule with at most kLeadMaxRank directions: everything after the statistics pass (backfill_lead.hip), App. H's fast path included.

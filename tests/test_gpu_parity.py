@@ -1610,3 +1610,24 @@ def test_select_flags_of_heads_that_keep_nothing_or_everything(gpu):
     o = Bd.compress_relay(K, V, Q, budgets=np.array([0, 70, 20], np.int32), rank=2, max_budget=70, want_diag=True, ws=ws)
     torch.cuda.synchronize()
     assert np.all(Bd.diag_to_numpy(o["diag"])["select_flags"] == 0)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("N,sink", [(97, 0), (1025, 0), (1026, 3)])     # one chunk of the statistics, and a second of one or two rows, behind a sink
+def test_bases_statistics_and_gather_in_one_launch(gpu, dtype, d, N, sink):
+    """Budgets that fit the common launch against the same budgets under a larger max_budget, which takes the kernels one by one: the same
+    bits, with heads that keep nothing, one row, a full block of rows and one more, all the launch takes, and every token."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    most = 96 if d == 128 else 63
+    bud = np.array([0, 1, 16, 17, 33, most, most - 1, 48], np.int32)
+    cfg = si.RelayConfig("onelaunch", 47, 2, 4, 2, d, N, 8, 0, 3, dtype, "structured", outlier_frac=0.01)
+    K, V, Q = (gpu.to_dev(x, dtype) for x in si.make_cache(cfg, 0))
+    kw = dict(budgets=bud, rank=3, want_delta=True, want_diag=True, n_tokens=N, sink=sink)
+    a = Bd.compress_relay(K, V, Q, max_budget=most, **kw)
+    b = Bd.compress_relay(K, V, Q, max_budget=most + 4, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(a["n_keep"], b["n_keep"]) and torch.equal(a["delta"], b["delta"]) and int((a["delta"] != 0).any(-1).sum()) >= 6
+    assert torch.equal(a["diag"].view(torch.uint8), b["diag"].view(torch.uint8))
+    for k in ("idx", "K_out", "V_out"):
+        assert torch.equal(a[k].view(torch.uint8), b[k][:, :, :most].contiguous().view(torch.uint8)), k

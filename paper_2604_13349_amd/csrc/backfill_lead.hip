@@ -11,14 +11,17 @@
 //   3. App. H's literal Gram subspace iteration, when asked for, on the same registers.
 //   4. rbar, Delta, delta and Eq. 7.
 //
-// What bounds it is latency: chains of small products with a barrier each (1600 cycles, of which the matrix cores work 800) and the
-// small problems on one wave (8000 cycles a step for eight columns, 14000 for sixteen).  At m = 96, k = 2 a workgroup takes 120000 cycles:
-// G 10, the projection 17, sixteen products 30, four small problems 30 with 10 around them, the rest loads and the tail.  It took the place
+// What bounds it is latency: chains of small products with a barrier each (1600 cycles, of which the matrix cores work 500 for eight columns, 800 for
+// sixteen) and the small problems on one wave (6500 cycles a step for eight columns, 10000 for sixteen, a sweep of rotations 2000 and 4500 of them).
+// At m = 96, k = 2 a workgroup alone on its compute unit takes 50 us: G 4, the projection 8, sixteen products 12, four small problems 12 with 5 around
+// them, the rest loads and the tail; two that share one take 73, most of the difference in the projection (14), which fills the vector ALU, the matrix
+// cores and LDS in turn, and so 288 heads on 256 compute units take 73 where 256 take 54.  With the middle parts in the block's free columns, a sweep
+// for the early small problems and the parts by conversion instructions 288 such heads went from 80 us to 73.  The kernel took the place
 // of a basis of the complement, the tridiagonalisation of its m x m matrix and inverse iteration (68 + 148 us for 288 heads of 256 tokens with 32
-// kept, 2 directions; 79 now, the whole call 299 -> 155; twelve samples 2060 -> 1020), and the offset's error against double
+// kept, 2 directions; 73 now, the whole call 299 -> 128; twelve samples 2060 -> 894), and the offset's error against double
 // precision fell from 8.6e-7 to 3.3e-7 (2000 tokens with 96 kept, 8 directions: 4.0e-6 to 5.0e-7).
 //
-// What it depends on: this kernel against those before it (us, 288 heads), and the whole call
+// What it depends on: this kernel, as it was before the blocks of eight columns had a kernel of their own, against those before it (us, 288 heads), and the whole call
 //   256 tokens, 32 kept    2, 8, 12, 16 directions   210 223 272 282 -> 79 97 125 164    299 312 360 369 -> 155 173 201 241
 //   1024 tokens, 80 kept                             165 172 199 207 -> 107 127 152 200  331 338 365 373 -> 244 263 286 330
 //   2000 tokens, 96 kept                             130 136 156 163 -> 117 133 156 198  366 371 390 395 -> 311 327 353 391
@@ -183,17 +186,28 @@ __device__ __forceinline__ void project_columns(f32x4 (&acc)[D / 16], const floa
         s[a][2] = mfma32(lo, v.hi, s[a][2]);
       }
     }
+    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);         // operands one step ahead of the products
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (p + 1 < NP) __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
+    }
     const Split8 c = split8(zero - (s[0][0] + (s[0][1] + s[0][2])), zero - (s[1][0] + (s[1][1] + s[1][2])));   // -(Q acc), rows 4 q + e and 16 + 4 q + e
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const bf16x8* o = cols + t * 64 + lane;
       const bf16x8 hi = o[0], mid = o[NT * 64], lo = o[2 * NT * 64];
-      f32x4 y = mfma32(hi, c.lo, zero);
-      y = mfma32(mid, c.mid, y);
-      y = mfma32(lo, c.hi, y);
-      y = mfma32(hi, c.mid, y);
-      y = mfma32(mid, c.hi, y);
-      acc[t] = mfma32(hi, c.hi, acc[t] + y);
+      f32x4 y0 = mfma32(hi, c.hi, acc[t]), y1 = mfma32(hi, c.mid, zero), y2 = mfma32(hi, c.lo, zero);
+      y1 = mfma32(mid, c.hi, y1);
+      y2 = mfma32(mid, c.mid, y2);
+      y2 = mfma32(lo, c.hi, y2);
+      acc[t] = y0 + (y1 + y2);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (t + 2 < NT) __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
     }
   }
 }
@@ -291,6 +305,27 @@ __device__ __forceinline__ void multiply(const Split8& a, const bf16x4* b, const
   y1 = mfma32(a.mid, hi, y1);
   y2 = mfma32(a.mid, mid, y2);
   y2 = mfma32(a.lo, hi, y2);
+}
+
+// The same for a block of eight columns: the middle parts take the place of columns 8 - 15, so that four products do where six are needed
+// for sixteen columns, and two reads of LDS, which each wave makes of the whole block, where three are.
+template <int D>
+__device__ __forceinline__ void publish_narrow(bf16x4* b, const f32x4 x) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const Split s = split3(x);
+  bf16x4* o = b + ((wave >> 1) * 64 + lane) * 2 + (wave & 1);
+  if ((lane & 15) < 8) { o[0] = s.hi; o[16] = s.mid; o[D / 16 * 64] = s.lo; }
+}
+
+// columns 0 - 7: y0 + y1 + y2 + y3, columns 8 - 15: y0 + y1 + y3, += their shares of a times rows 32 p .. (y2's columns 8 - 15 are not defined)
+template <int D>
+__device__ __forceinline__ void multiply_narrow(const Split8& a, const bf16x4* b, const int p, f32x4& y0, f32x4& y1, f32x4& y2, f32x4& y3) {
+  const bf16x8* v = (const bf16x8*)b + (threadIdx.x & 63);
+  const bf16x8 him = v[p * 64], lo = v[(D / 32 + p) * 64];
+  y0 = mfma32(a.hi, him, y0);
+  y1 = mfma32(a.mid, him, y1);
+  y2 = mfma32(a.hi, lo, y2);
+  y3 = mfma32(a.lo, him, y3);
 }
 
 // entry (row, j) of a start block, in [-1, 1), fixed
@@ -496,20 +531,21 @@ __device__ __forceinline__ float uniform(const float v) {
 
 // FAST selects the fast path of App. H: `iters` steps of C <- orth(C P G P) from a fixed orthonormal start; the exact directions are
 // then only found when diagnostics are wanted, to report how far the fast path's Delta is from theirs.  (A kernel of its own: the calls
-// to the orthogonalisation push six values of each of its products to scratch.  The compiler reports 38 registers that go to scratch
-// somewhere in the plain kernel of head_dim 128, 116 in this one and 97 in the THIN one; at head_dim 64 none, 89 and 13.)
+// to the orthogonalisation push six values of each of its products to scratch.  The compiler reports 37 to 41 registers that go to scratch
+// somewhere in the plain kernels of head_dim 128, 116 in this one and 93 in the THIN ones; at head_dim 64 none, 89 and 13.)
 // THIN: some heads may retain so many directions that their complement is no wider than a block (kThinWidth).  P G P is not formed for
 // those (Q has more rows than there would be products): products with G are followed by a projection of the block, and the block's Ritz
 // values give the trace; see lead_thin.  (288 heads of 1024 tokens, 112, 120 and 126 kept, whole call, 8 directions: 302, 316 and 313 us
 // with that in here, where its operands pushed the matrix to scratch; 293, 305 and 303 as a function.)
-template <typename T, int D, bool FAST, bool THIN>
+// NARROW: at most four directions, which take a block of eight columns; sixteen otherwise.
+template <typename T, int D, bool FAST, bool THIN, bool NARROW>
 __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, HeadState* __restrict__ state,
                                                           const float* __restrict__ basis, const float* __restrict__ gram_part,
                                                           float* __restrict__ mats, float* __restrict__ delta,
                                                           float* __restrict__ delta_out, obf_diag_t* __restrict__ diag,
                                                           T* __restrict__ V_out, int max_budget, const float* __restrict__ scores,
                                                           const int32_t* __restrict__ idx, int vflags, int scs, int iters) {
-  constexpr int NT = D / 16;
+  constexpr int NT = D / 16, P = NARROW ? 8 : 16;
   extern __shared__ __attribute__((aligned(16))) float sm[];
   __shared__ float uvec[128], svec[128], coef[128], part[TE_THREADS], dvec[2][16], dex[128];
   __shared__ double dred[TE_WAVES];
@@ -524,6 +560,9 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
   const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, j = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool own = wave < NT;                                  // uniform: the wave holds sixteen rows
+  // The wave that solves the small problems: another one in workgroups that share a compute unit (a launch deals its first 256 to one each),
+  // so that they do not wait for the same SIMD.
+  const int solver = (blockIdx.x / kNumCU) % TE_WAVES;
   if (st.active) {
     const int r = st.r_keep, m = D - r;
     const float* Qb = basis + (size_t)head * D * D;            // [r][D] orthonormal rows
@@ -670,9 +709,28 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
       auto product = [&](const f32x4 x) -> f32x4 {
         bf16x4* b = sbuf + copy * (3 * NT * 64);
         copy ^= 1;
-        if (own) publish<D>(b, x);
+        if (own) { if (NARROW) publish_narrow<D>(b, x); else publish<D>(b, x); }
         lds_barrier();
         f32x4 y0 = {0.f, 0.f, 0.f, 0.f}, y1 = {0.f, 0.f, 0.f, 0.f}, y2 = {0.f, 0.f, 0.f, 0.f};
+        if (NARROW) {
+          f32x4 y3 = {0.f, 0.f, 0.f, 0.f};
+          if (own) {
+#pragma unroll
+            for (int p = 0; p < NT / 2; ++p) multiply_narrow<D>(mat[p], b, p, y0, y1, y2, y3);
+            __builtin_amdgcn_sched_group_barrier(0x100, NT > 4 ? 6 : 4, 0);    // reads ahead of the products
+            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+            if (NT > 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, NT > 4 ? 12 : 4, 0);
+          }
+          f32x4 y;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            y1[e] += y3[e];
+            y[e] = y0[e] + ((row_xor<8>(y0[e]) + y1[e]) + (row_xor<8>(y1[e]) + y2[e]));
+            y[e] = (j < 8) ? y[e] : 0.f;
+          }
+          return y;
+        }
         if (own) {
 #pragma unroll
           for (int p = 0; p < NT / 2; ++p) multiply<D>(mat[p], b, p, y0, y1, y2);
@@ -733,7 +791,6 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
           }
           kept_matrix = true;
         };
-        const int P = (kmax <= 4) ? 8 : 16;
         auto random_entry = [&](const int e, const int seed) -> float { return block_random(16 * wave + 4 * q + e, j, seed); };
         f32x4 x, y;
         int found = 0, group = 0;
@@ -774,17 +831,15 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
                 yb[q * 17 + j] = make_float4(y[0], y[1], y[2], y[3]);
               }
               lds_barrier();
-              if (wave == 0) {
+              if (wave == solver) {
                 f32x4 M = gbuf[lane], H = gbuf[NT * 64 + lane];
 #pragma unroll
                 for (int w = 1; w < NT; ++w) { M += gbuf[w * 64 + lane]; H += gbuf[(NT + w) * 64 + lane]; }
                 f32x4 S;
                 float theta;
                 int place;
-                const float tol = last ? 3e-4f : 0.1f;
-                const int sweeps = round == 0 ? 2 : 8;
-                if (P == 8) small_ritz<8>(M, H, 1e-5f, tol, sweeps, S, theta, place);
-                else small_ritz<16>(M, H, 1e-5f, tol, sweeps, S, theta, place);
+                // Far from the end a sweep does, what it leaves goes with the next; where the residual decides, the vectors have to be exact.
+                small_ritz<P>(M, H, 1e-5f, 3e-4f, last || rn_before < 1e-2f ? 8 : 1, S, theta, place);
                 s_rot[q * 16 + place] = make_float4(S[0], S[1], S[2], S[3]);
                 if (q == 0) s_th[place] = theta;
               }
@@ -969,8 +1024,8 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
         };
         for (int it = 0; it < iters && kk > 0; ++it) {         // uniform
           images();
-          if (wave == 0) {
-            const int nk = (kk <= 4) ? lead_orth<4, D>((int)(Ya - sm), (int)(Yb - sm), kk) : lead_orth<TE_MAXK, D>((int)(Ya - sm), (int)(Yb - sm), kk);
+          if (wave == solver) {
+            const int nk = lead_orth<NARROW ? 4 : TE_MAXK, D>((int)(Ya - sm), (int)(Yb - sm), kk);
             if (lane == 0) s_k = nk;
           }
           __syncthreads();
@@ -1036,9 +1091,10 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const float
   static uint64_t attr_seen = 0;
   once_per_device(attr_mu, attr_seen, [] {
     const int most = (int)(sizeof(float) * lead_lds_floats(D, TE_MAXK));
-    (void)hipFuncSetAttribute((const void*)k_bf_lead<T, D, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    (void)hipFuncSetAttribute((const void*)k_bf_lead<T, D, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    (void)hipFuncSetAttribute((const void*)k_bf_lead<T, D, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    for (const void* k : {(const void*)k_bf_lead<T, D, false, false, false>, (const void*)k_bf_lead<T, D, false, true, false>,
+                          (const void*)k_bf_lead<T, D, true, false, false>, (const void*)k_bf_lead<T, D, false, false, true>,
+                          (const void*)k_bf_lead<T, D, false, true, true>, (const void*)k_bf_lead<T, D, true, false, true>})
+      (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
   });
   const size_t lds = sizeof(float) * lead_lds_floats(D, rank);
   auto go = [&](auto kernel) {
@@ -1047,9 +1103,9 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const float
                        delta_out, diag, (T*)V_out, max_budget, scores, idx, vflags, m.scs, iters);
   };
   const bool thin = max_budget >= D - kThinWidth && !(vflags & VF_NO_PROJECTION);       // no head can be otherwise
-  if (iters > 0) go(k_bf_lead<T, D, true, false>);
-  else if (thin) go(k_bf_lead<T, D, false, true>);
-  else go(k_bf_lead<T, D, false, false>);
+  if (iters > 0) { if (rank <= 4) go(k_bf_lead<T, D, true, false, true>); else go(k_bf_lead<T, D, true, false, false>); }
+  else if (thin) { if (rank <= 4) go(k_bf_lead<T, D, false, true, true>); else go(k_bf_lead<T, D, false, true, false>); }
+  else { if (rank <= 4) go(k_bf_lead<T, D, false, false, true>); else go(k_bf_lead<T, D, false, false, false>); }
   return check_launch("backfill leading directions");
 }
 

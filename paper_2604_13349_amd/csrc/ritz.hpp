@@ -20,19 +20,15 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 // instructions take 96 cycles where the eight in single precision take 256.
 struct Split { bf16x4 hi, mid, lo; };
 __device__ __forceinline__ Split split3(const f32x4 v) {
-  uint32_t h[4], m[4], b[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {                                // to the nearest, ties away from zero; the rest is exact
-    h[e] = __float_as_uint(v[e]) + 0x8000u;
-    const float r = v[e] - __uint_as_float(h[e] & 0xffff0000u);
-    m[e] = __float_as_uint(r) + 0x8000u;
-    b[e] = __float_as_uint(r - __uint_as_float(m[e] & 0xffff0000u)) + 0x8000u;
-  }
-  auto pack = [](const uint32_t (&x)[4]) -> bf16x4 {           // the upper halves
-    const uint2 p = make_uint2(__builtin_amdgcn_perm(x[1], x[0], 0x07060302u), __builtin_amdgcn_perm(x[3], x[2], 0x07060302u));
-    return __builtin_bit_cast(bf16x4, p);
+  auto rest = [](const f32x4 x, const bf16x4 h) -> f32x4 {      // x - h, exact
+    const uint2 u = __builtin_bit_cast(uint2, h);
+    return f32x4{x[0] - __uint_as_float(u.x << 16), x[1] - __uint_as_float(u.x & 0xffff0000u),
+                 x[2] - __uint_as_float(u.y << 16), x[3] - __uint_as_float(u.y & 0xffff0000u)};
   };
-  return Split{pack(h), pack(m), pack(b)};
+  const bf16x4 hi = __builtin_convertvector(v, bf16x4);        // to the nearest, one instruction for two
+  const f32x4 r = rest(v, hi);
+  const bf16x4 mid = __builtin_convertvector(r, bf16x4);
+  return Split{hi, mid, __builtin_convertvector(rest(r, mid), bf16x4)};
 }
 __device__ __forceinline__ bf16x8 join(const bf16x4 a, const bf16x4 b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
 

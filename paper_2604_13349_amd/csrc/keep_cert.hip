@@ -47,20 +47,46 @@ __device__ __forceinline__ void wave_tiles(int wave, int (&rb)[3], int (&cb)[3],
   else { rb[0] = 3; cb[0] = 0; rb[1] = 2; cb[1] = 2; rb[2] = 0; cb[2] = 0; nt = 2; }
 }
 
-// What a workgroup shares during the factorisation.  bad is zeroed by the kernel ahead of a barrier.
+// What a workgroup shares during the factorisation (its memory may have held something else before).
+constexpr int CF_LD = 20;                // floats between rows of 16 columns: rows are whole 16-byte pieces, 8 of them on different banks
 template <int D>
 struct CertShared {
-  __attribute__((aligned(16))) float panel[2][D][4];
-  float4 ypan[D], lpan[D];
+  __attribute__((aligned(16))) float panel[D][CF_LD];        // the columns that are factored next
+  __attribute__((aligned(16))) float y[2][D][CF_LD], l[2][D][CF_LD];     // -L d and L of a panel, for the updates
   __attribute__((aligned(16))) float isd[D];
-  int bad;
 };
 
-// Factors G - mu I (scaled, less the allowance) for the Gram matrix G that the workgroup's waves hold in the tiles (trb, tcb) of g; sh.bad
-// is set where a pivot is not positive.
+// value of lane K of each 16-lane row, in every lane of the row
+template <int K>
+__device__ __forceinline__ float cf_bcast(const float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x150 + K, 0xF, 0xF, true));
+}
+template <int C, int J>
+__device__ __forceinline__ void cf_eliminate(float (&a)[16], float (&b)[16], const float ma, const float mb) {
+  if constexpr (J < 16) {
+    const float e = cf_bcast<J>(b[C]);                         // entry (J, C) of the diagonal block
+    b[J] = fmaf(e, mb, b[J]);
+    a[J] = fmaf(e, ma, a[J]);
+    cf_eliminate<C, J + 1>(a, b, ma, mb);
+  }
+}
+// Columns C .. 15 of a panel: a is the lane's row, b row lane % 16 of the diagonal block.  Leaves L d in a, and 1 / d in rc.
+template <int C>
+__device__ __forceinline__ void cf_columns(float (&a)[16], float (&b)[16], float (&rc)[16], bool& positive) {
+  if constexpr (C < 16) {
+    const float d = cf_bcast<C>(b[C]);
+    positive = positive && d > 0.f;
+    rc[C] = __builtin_amdgcn_rcpf(d);
+    cf_eliminate<C, C + 1>(a, b, -(a[C] * rc[C]), -(b[C] * rc[C]));
+    cf_columns<C + 1>(a, b, rc, positive);
+  }
+}
+
+// Factors G - mu I (scaled, less the allowance) for the Gram matrix G that the workgroup's waves hold in the tiles (trb, tcb) of g; *bad, zeroed by
+// the kernel ahead of a barrier, is set where a pivot is not positive.
 template <int D>
 __device__ __forceinline__ void cert_factor(f32x16 (&g)[3], const int (&trb)[3], const int (&tcb)[3], const int nt, const float mu,
-                                            CertShared<D>& sh, const float allowance = kCertErr) {
+                                            CertShared<D>& sh, int* bad, const float allowance = kCertErr) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int lr = lane & 31, lh = lane >> 5;
   const bool has_diag = ((lr & 7) >> 2) == lh;
@@ -96,74 +122,79 @@ __device__ __forceinline__ void cert_factor(f32x16 (&g)[3], const int (&trb)[3],
     }
   }
 
-  // ---- LDL^T of G - mu I in registers, four columns per step.  panel[s & 1][row] holds columns 4s .. 4s+3 of
-  // the current matrix when step s starts.  Thread r < D factors the 4x4 diagonal block (the same arithmetic in
-  // every thread, so no broadcast) and turns panel row r into y = L d (a 4-term forward substitution) and L; after a
-  // second barrier every wave applies the rank-4 update to its tiles: first to the one tile (per wave) that holds
-  // the next four columns, which are then published, then to the rest, so the chain block -> next block only
-  // contains one tile update.  A non-positive pivot sets a flag (no early exit: the steps stay free of
-  // divergent control flow); entries above the diagonal are carried along and never read.
-  auto publish = [&](int k) {                         // columns k .. k+3 (k % 4 == 0) -> panel[(k / 4) & 1]
-    const int kb = k >> 5, kc = k & 31;
-    float* pw = &sh.panel[(k >> 2) & 1][0][0];
+  // ---- LDL^T in panels of sixteen columns.  A panel passes through LDS to the waves that factor it, a row below the diagonal block per lane, so
+  // two waves take the first three panels and one the rest.  Each of their 16-lane rows holds the diagonal block as well and eliminates it
+  // again: its entries, which every lane needs, then come from the same 16 lanes by DPP.  (As scalars read from one copy: 1.5 us a panel.)  The tiles stay with their waves, which update those with the next panel's columns
+  // first and publish these, the others beside the factorisation of the next panel: the chain from panel to panel is the factorisation
+  // (1 us), one tile update (eight matrix instructions) and two barriers.  The waves that factor have the fewest tiles left then.
+  // Entries above the diagonal and in finished columns are carried along and never read.
+  // 288 heads of 205 rows, the whole kernel: 28 us; 34.6 with steps of four columns, two barriers and the same 4 x 4 block factored by every thread (one
+  // barrier a step was slower).
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int part = D == 128 ? (wave == 2 ? 0 : wave == 3 ? 1 : 2) : (wave == 3 ? 0 : 2);      // which 64 rows below the diagonal block; 2: none
+  auto publish = [&](int k) {                         // columns 16 k .. 16 k + 15
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-      if (t < nt && tcb[t] == kb && (lr & ~3) == kc) {
-        const int c = lr & 3;
+      if (t < nt && tcb[t] == (k >> 1) && (lr >> 4) == (k & 1)) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) pw[(trb[t] * 32 + (i >> 2) * 8 + lh * 4 + (i & 3)) * 4 + c] = g[t][i];
+        for (int i = 0; i < 16; ++i) sh.panel[trb[t] * 32 + (i >> 2) * 8 + lh * 4 + (i & 3)][lr & 15] = g[t][i];
       }
     }
   };
+  // a tile less the product of panel k's columns: v_mfma_f32_32x32x2_f32, lane l with columns s + 8 (l / 32) of row l % 32 of either operand
+  auto update = [&](int t, int k) {
+    const float4* yp = (const float4*)&sh.y[k & 1][trb[t] * 32 + lr][8 * lh];
+    const float4* lp = (const float4*)&sh.l[k & 1][tcb[t] * 32 + lr][8 * lh];
+    const float4 y0 = yp[0], y1 = yp[1], l0 = lp[0], l1 = lp[1];
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0.x, l0.x, g[t], 0, 0, 0);
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0.y, l0.y, g[t], 0, 0, 0);
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0.z, l0.z, g[t], 0, 0, 0);
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0.w, l0.w, g[t], 0, 0, 0);
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1.x, l1.x, g[t], 0, 0, 0);
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1.y, l1.y, g[t], 0, 0, 0);
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1.z, l1.z, g[t], 0, 0, 0);
+    g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1.w, l1.w, g[t], 0, 0, 0);
+  };
   publish(0);
-  for (int k = 0; k < D; k += 4) {
-    __syncthreads();                                   // this panel visible; ypan / lpan free again
-    if (tid < D) {
-      const float4* pr = (const float4*)&sh.panel[(k >> 2) & 1][0][0];
-      // 4x4 diagonal block: rows k .. k+3, lower triangle
-      const float4 r0 = pr[k], r1 = pr[k + 1], r2 = pr[k + 2], r3 = pr[k + 3];
-      const float4 x = pr[tid];
-      const float d0 = r0.x;
-      const float i0 = __builtin_amdgcn_rcpf(d0);
-      const float l10 = r1.x * i0, l20 = r2.x * i0, l30 = r3.x * i0;
-      const float d1 = fmaf(-l10, r1.x, r1.y);
-      const float i1 = __builtin_amdgcn_rcpf(d1);
-      const float l21 = fmaf(-l20, r1.x, r2.y) * i1, l31 = fmaf(-l30, r1.x, r3.y) * i1;
-      const float y21 = l21 * d1, y31 = l31 * d1;
-      const float d2 = fmaf(-l21, y21, fmaf(-l20, r2.x, r2.z));
-      const float i2 = __builtin_amdgcn_rcpf(d2);
-      const float l32 = fmaf(-l31, y21, fmaf(-l30, r2.x, r3.z)) * i2;
-      const float y32 = l32 * d2;
-      const float d3 = fmaf(-l32, y32, fmaf(-l31, y31, fmaf(-l30, r3.x, r3.w)));
-      const float i3 = __builtin_amdgcn_rcpf(d3);
-      if (!((d0 > 0.f) && (d1 > 0.f) && (d2 > 0.f) && (d3 > 0.f))) sh.bad = 1;
-      // y = L d of panel row x: y0 = x0, y1 = x1 - y0 l10, y2 = x2 - y0 l20 - y1 l21, y3 = x3 - y0 l30 - y1 l31 - y2 l32
-      const float y0 = x.x;
-      const float y1 = fmaf(-y0, l10, x.y);
-      const float y2 = fmaf(-y1, l21, fmaf(-y0, l20, x.z));
-      const float y3 = fmaf(-y2, l32, fmaf(-y1, l31, fmaf(-y0, l30, x.w)));
-      sh.ypan[tid] = make_float4(y0, y1, y2, y3);
-      sh.lpan[tid] = make_float4(y0 * i0, y1 * i1, y2 * i2, y3 * i3);
+#pragma unroll 1
+  for (int k = 0; k < D / 16; ++k) {
+    lds_barrier();                                     // the panel is published
+    if (k > 0) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        if (t < nt && tcb[t] > (k >> 1)) update(t, k - 1);
     }
-    __syncthreads();
-    const int kb = k >> 5;
-    const int kbn = (k + 4) >> 5;                      // column block of the next four columns
-    // rank-4 update of a tile on the matrix cores in fp32: G_tile -= Y_rows (32 x 4) * L_cols^T (4 x 32), two
-    // v_mfma_f32_32x32x2_f32 (A: lane l holds row l%32, k = l/32; B: k = l/32, column l%32)
-    auto update = [&](int t) {
-      const float* yp = (const float*)sh.ypan + (trb[t] * 32 + lr) * 4 + lh;
-      const float* lp = (const float*)sh.lpan + (tcb[t] * 32 + lr) * 4 + lh;
-      const float y0 = -yp[0], y1 = -yp[2], l0 = lp[0], l1 = lp[2];
-      g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y0, l0, g[t], 0, 0, 0);
-      g[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(y1, l1, g[t], 0, 0, 0);
-    };
+    if (part == 0 || (part == 1 && 16 * (k + 1) + 64 < D)) {             // uniform
+      const int p = 16 * (k + 1) + 64 * part + lane;
+      const bool have = p < D;
+      float a[16], b[16], rc[16];
+      auto row_at = [&](const int r, float (&x)[16]) {
+        const float4* pr = (const float4*)sh.panel[r];
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
-      if (t < nt && tcb[t] == kbn && tcb[t] >= kb) update(t);
-    if (k + 4 < D) publish(k + 4);
+        for (int c = 0; c < 4; ++c) { const float4 v = pr[c]; x[4 * c] = v.x; x[4 * c + 1] = v.y; x[4 * c + 2] = v.z; x[4 * c + 3] = v.w; }
+      };
+      row_at(16 * k + (lane & 15), b);
+      row_at(have ? p : 16 * k, a);
+      bool positive = true;
+      cf_columns<0>(a, b, rc, positive);
+      if (!positive) *bad = 1;
+      if (have) {
+        float4* yo = (float4*)sh.y[k & 1][p];
+        float4* lo = (float4*)sh.l[k & 1][p];
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
-      if (t < nt && tcb[t] != kbn && tcb[t] >= kb) update(t);
+        for (int c = 0; c < 4; ++c) {
+          yo[c] = make_float4(-a[4 * c], -a[4 * c + 1], -a[4 * c + 2], -a[4 * c + 3]);
+          lo[c] = make_float4(a[4 * c] * rc[4 * c], a[4 * c + 1] * rc[4 * c + 1], a[4 * c + 2] * rc[4 * c + 2], a[4 * c + 3] * rc[4 * c + 3]);
+        }
+      }
+    }
+    lds_barrier();                                     // it is factored
+    if (k + 1 < D / 16) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        if (t < nt && tcb[t] == ((k + 1) >> 1)) update(t, k);
+      publish(k + 1);
+    }
   }
 }
 
@@ -223,8 +254,9 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
                                                              const double* __restrict__ fro_part /*optional: sums of squares of the retained rows, per gather block*/,
                                                              int fro_blocks, int scs, int kvs,
                                                              int want_sums /*0: the demand sums of a certified head (diagnostics only) are left at zero*/) {
-  __shared__ __attribute__((aligned(16))) uint32_t stage[2][GS_STAGE_WORDS];
-  __shared__ CertShared<KC_D> sh;
+  __shared__ __attribute__((aligned(16))) union { uint32_t stage[2][GS_STAGE_WORDS]; CertShared<KC_D> cert; } lds;
+  auto& stage = lds.stage;
+  __shared__ int bad;
   __shared__ double red[KC_THREADS / 64], red2[KC_THREADS / 64];
   const int head = blockIdx.x;
   const int n = n_keep[head];
@@ -232,7 +264,7 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept in a scalar register
   const int lr = lane & 31, lh = lane >> 5;
-  if (tid == 0) { decided[head] = 0; sh.bad = 0; }
+  if (tid == 0) { decided[head] = 0; bad = 0; }
   if (!(rank > 0 && n > KC_D && n_del > 0)) return;
   const float* sc = scores + (size_t)head * scs;
   const int32_t* id = idx + (size_t)head * max_budget;
@@ -368,9 +400,9 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
     __syncthreads();
   }
   const double thr_rel = (double)max(n, KC_D) * 1.1920928955078125e-07;
-  cert_factor<KC_D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), sh);
+  cert_factor<KC_D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), lds.cert, &bad);
   __syncthreads();
-  const bool ok = (sh.bad == 0);
+  const bool ok = (bad == 0);
   if (!ok) return;
 
   double pk = 0.0;
@@ -382,8 +414,8 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert(const uint16_t* 
 // The same for the other shapes (fp32 caches, head_dim 64): the Gram matrix by v_mfma_f32_32x32x2_f32 straight from the gathered rows - the
 // operand's lane l holds row l / 32 of a pair and column l % 32, which is how rows lie in memory - a wave per tile or three, the next
 // KF_PAIRS row pairs in flight, summed in parts of KF_PART rows so that the rounding does not grow with their number.  A column whose sum of squares leaves single precision's comfortable range is not certified.
-// Bound by the latency of the factorisation's D / 4 steps.  96 heads, 205 rows of 64 fp32 values: 20 us, and 5 for the exact basis
-// kernel, which then finds nothing to do (80 with every head in it).
+// Bound by the latency of the loads and of the factorisation.  96 heads, 205 rows of 64 fp32 values: 18.5 us (19.2 with steps of four
+// columns; sixteen pairs in flight change nothing), and 5 for the exact basis kernel, which then finds nothing to do (80 with every head in it).
 constexpr int KF_PAIRS = 8;
 constexpr float kCertMinSquare = 1e-30f, kCertMaxSquare = 1e30f;
 
@@ -394,11 +426,12 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert_rows(const T* __
                                                                   HeadState* __restrict__ state, int32_t* __restrict__ decided, int scs,
                                                                   int want_sums) {
   __shared__ CertShared<D> sh;
+  __shared__ int bad;
   __shared__ double red[KC_WAVES], red2[KC_WAVES];
   const int head = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = n_keep[head];
-  if (tid == 0) { decided[head] = 0; sh.bad = 0; }
+  if (tid == 0) { decided[head] = 0; bad = 0; }
   if (!(rank > 0 && n > D && N - n > 0)) return;
   const int lr = lane & 31, lh = lane >> 5;
   const T* Vh = Vsrc + (size_t)head * max_budget * D;
@@ -474,13 +507,13 @@ __global__ __launch_bounds__(KC_THREADS, 2) void k_bf_keep_cert_rows(const T* __
   }
   for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
   if (lane == 0) red[wave] = part;
-  __syncthreads();                                             // (sh.bad is zero from here)
-  if (out) sh.bad = 1;
+  __syncthreads();                                             // (bad is zero from here)
+  if (out) bad = 1;
   const double f2 = (red[0] + red[1]) + (red[2] + red[3]);
   const double thr_rel = (double)n * 1.1920928955078125e-07;   // n > D
-  cert_factor<D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), sh, cert_allowance(rows, D));
+  cert_factor<D>(acc, trb, tcb, nt, (float)(thr_rel * thr_rel * f2), sh, &bad, cert_allowance(rows, D));
   __syncthreads();
-  if (sh.bad) return;
+  if (bad) return;
   cert_settle(0.0, tid, scores + (size_t)head * scs, idx + (size_t)head * max_budget, n, N, want_sums, D, head, state, decided, red, red2);
 }
 

@@ -292,8 +292,8 @@ __global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restr
 // up to MG_LIST tokens is put in order first (every entry counts the smaller ones); a longer one is not: the head's routes are scanned
 // instead, which finds the slot's tokens in order.  Sixteen rows are in flight at a time.  Slots that received nothing are left as the
 // bit copies the gather wrote.  Bound by a wave's instructions per token and its chain offsets - list - rows (nine tokens a
-// slot here; the offsets' read does not wait for n_keep, nor the store for the slot's own value), then by the pass over V: 60 us on 288
-// heads x 2048 tokens x 205 slots, and 9 for the lists; 78 and 7 with the weights worked out here, 99 with eight rows ahead and every lane
+// slot here; the offsets' read does not wait for n_keep, nor the store for the slot's own value), then by the pass over V: 55 us on 288
+// heads x 2048 tokens x 205 slots, and 9 for the lists; 63 with sixteen loads for every list, 78 and 7 with the weights worked out here, 99 with eight rows ahead and every lane
 // read waited for by itself, 157 with four slots per wave, 247 with each wave scanning all routes.
 constexpr int MG_LIST = 256;
 constexpr int MG_AHEAD = 16;
@@ -351,10 +351,15 @@ __global__ __launch_bounds__(MG_THREADS) void k_mg_merge(const T* __restrict__ V
   auto add_rows = [&](const int n, const int tok, const float w) {
     for (int i0 = 0; i0 < n; i0 += MG_AHEAD) {
       typename LC::type v[MG_AHEAD];
-#pragma unroll
-      for (int u = 0; u < MG_AHEAD; ++u) {
+      auto load = [&](const int u) {
         const int j = __builtin_amdgcn_readlane(tok, min(i0 + u, n - 1));
         __builtin_memcpy(&v[u], Vh + (size_t)j * D, sizeof(v[u]));       // one load; V need only be aligned to its elements
+      };
+#pragma unroll
+      for (int u = 0; u < MG_AHEAD / 2; ++u) load(u);
+      if (i0 + MG_AHEAD / 2 < n) {                             // uniform; lists are short: the last row again costs as much as a new one
+#pragma unroll
+        for (int u = MG_AHEAD / 2; u < MG_AHEAD; ++u) load(u);
       }
 #pragma unroll
       for (int u = 0; u < MG_AHEAD; ++u) {

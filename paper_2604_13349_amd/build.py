@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libobf_relay.so")
-SOURCES = ["api.hip", "score_generic.hip", "score_mfma.hip", "select.hip", "refine.hip", "layerwise.hip", "gather.hip", "message.hip", "merge.hip", "quant.hip", "keep_cert.hip", "del_stats_mfma.hip", "del_stats_generic.hip", "keep_basis_small.hip", "basis_stats.hip", "backfill.hip", "backfill_lead.hip"]
+SOURCES = ["api.hip", "score_generic.hip", "score_mfma.hip", "score_tall.hip", "select.hip", "refine.hip", "layerwise.hip", "gather.hip", "message.hip", "merge.hip", "quant.hip", "keep_cert.hip", "del_stats_mfma.hip", "del_stats_generic.hip", "keep_basis_small.hip", "basis_stats.hip", "backfill.hip", "backfill_lead.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -18,7 +18,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-u
 
 
 # per-file extras: keep MFMA results in architectural VGPRs where the epilogue consumes them on the vector ALU
-FILE_FLAGS = {"score_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("score_mfma.hip", "score_tall.hip")}
 
 
 def _compile(src: str) -> str:

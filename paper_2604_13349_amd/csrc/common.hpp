@@ -59,12 +59,23 @@ inline int score_tiles_per_range(long TT, int rgroups) {
   return (int)(T < 4 ? 4 : T);
 }
 
+// Rows per group of the score kernels that carry 192 or 256 rows (score_tall.hip), 0 where those of 128 or 160 pad less (257 to 320 rows: two groups
+// of 160) or one such group holds all rows.
+inline int score_tall_rows(int R) {
+  if (R <= 160) return 0;
+  const int g = score_rows_per_group(R), narrow = (R + g - 1) / g * g;
+  const int p192 = (R + 191) / 192 * 192, p256 = (R + 255) / 256 * 256;
+  const int wide = p192 < p256 ? p192 : p256;
+  return wide > narrow ? 0 : p192 < p256 ? 192 : 256;
+}
+constexpr int kScoreTallStep = 64;       // tokens per step of them
+
 // Workspace carving.  Every region is 256-byte aligned; offsets are from the workspace base.
 struct Workspace {
   size_t stats_part;   // double2 [heads][nchunk][R]      partial (max, sum-exp) per score chunk
   size_t row_lse;      // double  [heads][R]
   size_t scores;       // float   [heads][N]              (fused call without scores_out)
-  size_t score_part;   // float   [mass_groups][heads][N] per-row-group column sums where the second score pass has several
+  size_t score_part;   // float   [rgroups][heads][N] per-row-group column sums where there are several
   size_t head_state;   // HeadState [heads]
   size_t decided;      // int32   [heads]                 1: the fast full-rank test settled the head
   size_t basis;        // float   [heads][d][d]           orthonormal basis of the retained span (columns)
@@ -82,7 +93,10 @@ struct Workspace {
   size_t route;        // int32   [heads][N]              retained slot of every deleted token (cache merging, when not an output)
   size_t total;
   int nchunk;          // most chunks per head of the double-precision score path
-  int rgroups, mass_groups, tiles_per_head, tiles_per_range, nranges, nslot;   // matrix-core score partition
+  int rgroups, tiles_per_head, tiles_per_range, nranges;       // matrix-core score partition (tiles of 32 tokens, or steps of 64 with tall row groups)
+  bool narrow_stats;   // tall row groups, but the first pass takes 128 rows at a time, on a partition of its own:
+  int stats_rgroups, stats_tiles_per_head, stats_tiles_per_range, stats_nranges;
+  int nslot;           // of the first pass: ranges that can meet in a head
   int nstat;           // statistics chunks per head
 };
 
@@ -109,11 +123,32 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.nstat = (m.N + kStatChunk - 1) / kStatChunk;
   // matrix-core score path: the flattened (head, 32-token tile) space is cut into one range per
   // persistent workgroup; a head is covered by at most nslot ranges
-  w.rgroups = (m.R + score_rows_per_group(m.R) - 1) / score_rows_per_group(m.R);
-  w.tiles_per_head = (m.N + 31) / 32;
-  {
+  const int tall = score_tall_rows(m.R);
+  const int group_rows = tall ? tall : score_rows_per_group(m.R);
+  w.rgroups = (m.R + group_rows - 1) / group_rows;
+  w.narrow_stats = false;
+  auto slots = [](int per_head, int per_range) { return (per_head + per_range - 1) / per_range + 1; };
+  if (tall) {                                                   // two workgroups per compute unit
+    w.tiles_per_head = (m.N + kScoreTallStep - 1) / kScoreTallStep;
+    const long TT = (long)m.heads * w.tiles_per_head;
+    const int per_xcd = (2 * kNumCU / 8) / w.rgroups > 0 ? (2 * kNumCU / 8) / w.rgroups : 1;
+    w.tiles_per_range = (int)((TT + 8 * per_xcd - 1) / (8 * per_xcd));
+    w.nranges = (int)((TT + w.tiles_per_range - 1) / w.tiles_per_range);
+    // First pass over 256 rows at once or 128 at a time (us): 288 heads of 2048, 4096, 8192, 32768 tokens 53 - 61, 97 - 105, 198 - 197, 763 - 729: where each
+    // workgroup has thousands of tokens both are bound by the card's power limit, and operands from LDS cost more than a second pass over K
+    // through the first-level cache.  The second pass is ahead throughout (50 - 61, 94 - 103, 183 - 192, 678 - 691), so is 192 rows at once.
+    w.narrow_stats = tall == 256 && (long)w.tiles_per_range * kScoreTallStep >= 4096;
+    if (w.narrow_stats) {
+      w.stats_rgroups = (m.R + 127) / 128;
+      w.stats_tiles_per_head = (m.N + 31) / 32;
+      const long ST = (long)m.heads * w.stats_tiles_per_head;
+      w.stats_tiles_per_range = score_tiles_per_range(ST, w.stats_rgroups);
+      w.stats_nranges = (int)((ST + w.stats_tiles_per_range - 1) / w.stats_tiles_per_range);
+    }
+  } else {
+    w.tiles_per_head = (m.N + 31) / 32;
     int T = score_tiles_per_range((long)m.heads * w.tiles_per_head, w.rgroups);
-    w.nslot = (int)((w.tiles_per_head + T - 1) / T) + 1;          // (no less for the longer ranges below)
+    w.nslot = slots(w.tiles_per_head, T);                         // (no less for the longer ranges below)
     // Ranges that end with their head, where that makes them at most a round of tiles longer: a range that goes on into the next head loads
     // its queries and fills its pipeline again, 5 us a pass.  128 rows, both passes, before and after: 16 heads of 1300, 2500 and 4100 tokens 35, 38
     // and 42 us, 21, 25 and 29; 120 heads of 1300 and 4100: 43 and 65, 30 and 53; 160 heads would need half as many tiles again and stay.
@@ -127,15 +162,17 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
     w.tiles_per_range = T;
     w.nranges = (int)((TT + T - 1) / T);
   }
+  if (!w.narrow_stats) {
+    w.stats_rgroups = w.rgroups; w.stats_tiles_per_head = w.tiles_per_head; w.stats_tiles_per_range = w.tiles_per_range; w.stats_nranges = w.nranges;
+  }
+  if (tall) w.nslot = slots(w.stats_tiles_per_head, w.stats_tiles_per_range);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
   w.stats_part = take(sizeof(double) * 2 * (size_t)m.heads * (w.nchunk > w.nslot ? w.nchunk : w.nslot) * m.R);
   w.row_lse = take(sizeof(double) * (size_t)m.heads * m.R);
   w.scores = take(sizeof(float) * (size_t)m.heads * m.N);
-  // the second pass takes pairs of 128-row groups as one (and the double-precision path all rows); a single group writes its sums to the scores
-  w.mass_groups = (w.rgroups % 2 == 0 && score_rows_per_group(m.R) == 128) ? w.rgroups / 2 : w.rgroups;
-  if (m.dtype != OBF_BF16 || m.d != 128) w.mass_groups = 1;
-  w.score_part = take(w.mass_groups > 1 ? sizeof(float) * (size_t)w.mass_groups * m.heads * m.N : 0);
+  // a single group, and the double-precision path, write their sums to the scores
+  w.score_part = take(w.rgroups > 1 && m.dtype == OBF_BF16 && m.d == 128 ? sizeof(float) * (size_t)w.rgroups * m.heads * m.N : 0);
   w.head_state = take(sizeof(HeadState) * (size_t)m.heads);
   w.decided = take(sizeof(int32_t) * (size_t)m.heads);
   w.basis = take(sizeof(float) * (size_t)m.heads * m.d * m.d);
@@ -196,6 +233,10 @@ template <> struct Elem<uint16_t> {
 obf_status_t launch_score_generic(const Dims& m, const Workspace& w, char* ws, const void* K, const void* Q,
                                   float* scores, double* row_lse, hipStream_t st);
 bool mfma_score_supported(const Dims& m);
+// Both passes with row groups of 192 or 256 rows (the first only where w.narrow_stats does not leave it to the other kernel); part: the scores, or a
+// group's sums each.
+obf_status_t launch_score_tall(const Dims& m, const Workspace& w, double* stats_part, const void* K, const void* Q, float* part, double* row_lse,
+                               hipStream_t st);
 obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, const void* K, const void* Q,
                                float* scores, double* row_lse, hipStream_t st);
 obf_status_t launch_select(const Dims& m, const float* scores, const int32_t* budgets_host, int32_t budget,

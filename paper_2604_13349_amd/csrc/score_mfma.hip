@@ -13,7 +13,7 @@
 //          in-lane sum plus one cross-lane add.
 // The whole Q operand of a 128-row group lives in registers for the lifetime of a workgroup;
 // K fragments are loaded straight from global memory in 16-byte pieces, one tile ahead.
-#include "common.hpp"
+#include "score_parts.hpp"
 
 namespace obf {
 
@@ -22,9 +22,8 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int SM_THREADS = 256;
 constexpr int SM_WAVES = 4;
-// The kernels are instantiated for (RB, KBUF) = (4, 3) and (5, 2), the second pass also for (8, 2), the one of short prompts for (1, 4),
-// (2, 3) and (4, 2): RB 32-row blocks of query
-// rows per workgroup (RB * 32 = 32 to 256 rows, their Q operand in RB * 32 registers per lane) and KBUF rotating K
+// The kernels are instantiated for (RB, KBUF) = (4, 3) and (5, 2), the one of short prompts for (1, 4), (2, 3) and (4, 2): RB 32-row blocks of query
+// rows per workgroup (RB * 32 = 32 to 160 rows; score_tall.hip has 192 and 256, their Q operand in RB * 32 registers per lane) and KBUF rotating K
 // fragment buffers.  RB * KBUF is even, so the two accumulators keep alternating across the iterations of the tile loop.
 constexpr int SM_D = 128;
 constexpr int SM_KK = SM_D / 16;         // MFMA k-steps
@@ -66,8 +65,6 @@ __device__ __forceinline__ void load_k(Frag (&kf)[SM_KK], const uint16_t* __rest
 // tile i+1 are issued in the same basic block as the vector-ALU epilogue of tile i (two accumulator
 // sets, two K fragment buffers), so that the matrix pipe and the vector ALU overlap within the one
 // wave a SIMD holds.
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }   // v_exp_f32, denormal results flush to 0
 
 // MFMA chain of one 32-row block against one 32-token tile (8 k-steps of 16).
 template <bool TOKENS_BY_ROWS>
@@ -145,15 +142,13 @@ __device__ __forceinline__ void stats_block_ragged(const f32x16& acc, float& m, 
 // Pass B epilogue: acc[i] is the raw dot product of query row row0 + rb*32 + (i/4)*8 + (lane/32)*4 + (i%4) with
 // token tok + lane%32; b2 holds lse[row] * log2(e) for the same (rb, i).  The column sum of a tile is
 // complete after its last row block.
-// Up to five row blocks their b2 stay in registers; more (NRB > 5) leave no room and are read from LDS.  Their two halves
-// are summed apart and added last, as k_score_sum_groups adds two row groups: the same mass to the last bit.
-template <int NRB, bool LDS = (NRB > 5)>
+template <int NRB, bool LDS = false>
 struct MassEp {
   const float* b2;       // registers [NRB][16], or LDS [NRB * 32]
   float a2;
   float* __restrict__ dst;
   int t_end, lane;
-  float c0, c1, c2, c3, half = 0.f;
+  float c0, c1, c2, c3;
   template <int RB>
   __device__ __forceinline__ void block(const f32x16& acc, int tok) {
     if (RB == 0) { c0 = 0.f; c1 = 0.f; c2 = 0.f; c3 = 0.f; }
@@ -166,14 +161,9 @@ struct MassEp {
       c2 += fast_exp2(fmaf(acc[i + 2], a2, -b.z));
       c3 += fast_exp2(fmaf(acc[i + 3], a2, -b.w));
     }
-    if (NRB > 5 && RB == NRB / 2 - 1) {
-      half = (c0 + c1) + (c2 + c3);
-      c0 = 0.f; c1 = 0.f; c2 = 0.f; c3 = 0.f;
-    }
     if (RB == NRB - 1) {
       float col = (c0 + c1) + (c2 + c3);
       col += __shfl_xor(col, 32);
-      if (NRB > 5) col = (half + __shfl_xor(half, 32)) + col;
       const int t = tok + (lane & 31);
       if (lane < 32 && t < t_end) dst[t] = col;
     }
@@ -331,9 +321,8 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_
                                                                    const double* __restrict__ stats_part,
                                                                    double* __restrict__ row_lse,
                                                                    float* __restrict__ out, int N, int R, int RG,
-                                                                   size_t rg_stride, Part pt, int t_stats, int nslot) {
+                                                                   size_t rg_stride, Part pt, int nslot) {
   __shared__ double s_lse[(RB * 32)];
-  __shared__ __attribute__((aligned(16))) float s_b2[RB > 5 ? RB * 32 : 4];
   // Workgroups are dealt to the 8 XCDs round-robin.  The RG workgroups that stream the same K range (one per row
   // group) get block indices 8 apart, so they run on one XCD side by side and share its L2.
   const int blk_group = blockIdx.x / (8 * RG), blk_in = blockIdx.x - blk_group * (8 * RG);
@@ -362,34 +351,24 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_
       const int row = row0 + rl;
       double lse = INFINITY;                                   // padded rows: exp2(-inf) = 0
       if (row < R) {
-        const int s_first = (int)(hs / t_stats), s_last = (int)((hs + pt.TH - 1) / t_stats);
-        const double* p = stats_part + ((size_t)head * nslot * R + row) * 2;
-        double M = -INFINITY;
-        for (int sl = 0; sl <= s_last - s_first; ++sl) M = fmax(M, p[(size_t)sl * R * 2]);
-        double L = 0.0;
-        for (int sl = 0; sl <= s_last - s_first; ++sl) {
-          const double pm = p[(size_t)sl * R * 2], pl = p[(size_t)sl * R * 2 + 1];
-          if (pm != -INFINITY) L += pl * exp(pm - M);
-        }
-        lse = M + log(L);
+        const int parts = (int)((hs + pt.TH - 1) / pt.T - hs / pt.T) + 1;
+        lse = fold_row_lse(stats_part + ((size_t)head * nslot * R + row) * 2, (size_t)R, parts);
         if (cur == hs) row_lse[(size_t)head * R + row] = lse;
       }
-      if (RB > 5) s_b2[rl] = (float)(lse * 1.4426950408889634); else s_lse[rl] = lse;
+      s_lse[rl] = lse;
     }
     __syncthreads();
 
     Frag qf[RB][SM_KK];
     load_q(qf, Qh, row0, R, lane);
-    float b2[RB > 5 ? 1 : RB * 16];
-    if constexpr (RB <= 5) {
+    float b2[RB * 16];
 #pragma unroll
-      for (int i = 0; i < RB * 16; ++i)
-        b2[i] = (float)(s_lse[(i >> 4) * 32 + ((i & 15) >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] * 1.4426950408889634);
-    }
+    for (int i = 0; i < RB * 16; ++i)
+      b2[i] = (float)(s_lse[(i >> 4) * 32 + ((i & 15) >> 2) * 8 + (lane >> 5) * 4 + (i & 3)] * 1.4426950408889634);
 
     const int first = ta + wave * SM_TILE;
     const int nt = (first < tb) ? ((tb - first - 1) / STEP + 1) : 0;      // tiles of this wave, the last may be ragged
-    MassEp<RB> ep{RB > 5 ? s_b2 : b2, a2, dst, tb, lane, 0.f, 0.f, 0.f, 0.f};
+    MassEp<RB> ep{b2, a2, dst, tb, lane, 0.f, 0.f, 0.f, 0.f};
     run_tiles<false, RB, KBUF>(Kh, first + (nt - 1) * STEP, -STEP, nt, tb, lane, qf, ep);
     se = cur;
   }
@@ -494,53 +473,51 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
   double* stats_part = (double*)(ws + w.stats_part);
   const int RG = w.rgroups;
   const size_t rg_stride = (size_t)m.heads * m.N;
-  Part pt;
-  pt.TH = w.tiles_per_head; pt.T = w.tiles_per_range; pt.TT = (long)m.heads * w.tiles_per_head;
-  pt.kstride = (long)m.kvs * SM_D;
-  dim3 grid(((w.nranges + 7) / 8) * 8 * RG);
-  const bool five = score_rows_per_group(m.R) == 160;     // five row blocks per workgroup, two K buffers (e.g. 320 rows = 2 x 160)
-  if (RG == 1 && !five && m.N <= (m.heads >= kScoreOneLaunchMany ? kScoreOneLaunchTokensMany : kScoreOneLaunchTokens)) {
-    ProfScope prof_(ST_SCORE_STATS, st);
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3(m.heads), dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, row_lse, scores, m.N, m.R,
-                         pt.kstride);
-    };
-    if (m.R <= 32) go(k_score_head_mfma<1, 4>);
-    else if (m.R <= 64) go(k_score_head_mfma<2, 3>);
-    else go(k_score_head_mfma<4, 2>);
-    return check_launch("score, one launch per call (mfma)");
+  float* part = (RG > 1) ? (float*)(ws + w.score_part) : scores;
+  if (score_tall_rows(m.R)) {
+    if (w.narrow_stats) {
+      ProfScope prof_(ST_SCORE_STATS, st);
+      Part pt;
+      pt.TH = w.stats_tiles_per_head; pt.T = w.stats_tiles_per_range; pt.TT = (long)m.heads * w.stats_tiles_per_head;
+      pt.kstride = (long)m.kvs * SM_D;
+      hipLaunchKernelGGL((k_score_stats_mfma<4, 3>), dim3(((w.stats_nranges + 7) / 8) * 8 * w.stats_rgroups), dim3(SM_THREADS), 0, st, (const uint16_t*)K,
+                         (const uint16_t*)Q, stats_part, m.N, m.R, w.stats_rgroups, pt, w.nslot);
+    }
+    if (launch_score_tall(m, w, stats_part, K, Q, part, row_lse, st) != OBF_OK) return OBF_ERR_HIP;
+  } else {
+    Part pt;
+    pt.TH = w.tiles_per_head; pt.T = w.tiles_per_range; pt.TT = (long)m.heads * w.tiles_per_head;
+    pt.kstride = (long)m.kvs * SM_D;
+    dim3 grid(((w.nranges + 7) / 8) * 8 * RG);
+    const bool five = score_rows_per_group(m.R) == 160;     // five row blocks per workgroup, two K buffers (e.g. 320 rows = 2 x 160)
+    if (RG == 1 && !five && m.N <= (m.heads >= kScoreOneLaunchMany ? kScoreOneLaunchTokensMany : kScoreOneLaunchTokens)) {
+      ProfScope prof_(ST_SCORE_STATS, st);
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(m.heads), dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, row_lse, scores, m.N, m.R,
+                           pt.kstride);
+      };
+      if (m.R <= 32) go(k_score_head_mfma<1, 4>);
+      else if (m.R <= 64) go(k_score_head_mfma<2, 3>);
+      else go(k_score_head_mfma<4, 2>);
+      return check_launch("score, one launch per call (mfma)");
+    }
+    { ProfScope prof_(ST_SCORE_STATS, st);
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, stats_part, m.N, m.R, RG, pt, w.nslot);
+      };
+      if (five) go(k_score_stats_mfma<5, 2>); else go(k_score_stats_mfma<4, 3>); }
+    if (check_launch("score stats (mfma)") != OBF_OK) return OBF_ERR_HIP;
+    { ProfScope prof_(ST_SCORE_MASS, st);
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, (const double*)stats_part, row_lse, part,
+                           m.N, m.R, RG, rg_stride, pt, w.nslot);
+      };
+      if (five) go(k_score_mass_mfma<5, 2>); else go(k_score_mass_mfma<4, 3>); }
+    if (check_launch("score mass (mfma)") != OBF_OK) return OBF_ERR_HIP;
   }
-  { ProfScope prof_(ST_SCORE_STATS, st);
-    if (five)
-      hipLaunchKernelGGL((k_score_stats_mfma<5, 2>), grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
-                         stats_part, m.N, m.R, RG, pt, w.nslot);
-    else
-      hipLaunchKernelGGL((k_score_stats_mfma<4, 3>), grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
-                         stats_part, m.N, m.R, RG, pt, w.nslot); }
-  if (check_launch("score stats (mfma)") != OBF_OK) return OBF_ERR_HIP;
-  // The second pass carries 256 rows where the first has pairs of 128, so that the two groups do not each stream K and leave partial sums
-  // to be added (the first pass keeps its groups: its normalisers depend on where a row's tokens are split).
-  // 288 heads of 32768 tokens, 256 rows: 796 + 35 us -> 785, one launch less.  320 rows at once instead of two groups of 160 were slower
-  // (504 + 20 -> 559: the compiler moves Q operands between the register files), so those stay.
-  const int RGB = w.mass_groups;
-  const bool tall = RGB != RG;
-  float* part = (RGB > 1) ? (float*)(ws + w.score_part) : scores;
-  Part pb = pt;
-  if (tall) pb.T = score_tiles_per_range(pt.TT, RGB);
-  const dim3 grid_b((unsigned)(((pb.TT + pb.T - 1) / pb.T + 7) / 8 * 8 * RGB));
-  { ProfScope prof_(ST_SCORE_MASS, st);
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, grid_b, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q,
-                         (const double*)stats_part, row_lse, part, m.N, m.R, RGB, rg_stride, pb, pt.T, w.nslot);
-    };
-    if (tall) go(k_score_mass_mfma<8, 2>);
-    else if (five) go(k_score_mass_mfma<5, 2>);
-    else go(k_score_mass_mfma<4, 3>); }
-  if (check_launch("score mass (mfma)") != OBF_OK) return OBF_ERR_HIP;
-  if (RGB > 1) {
+  if (RG > 1) {
     const size_t n = (size_t)m.heads * m.N;
-    hipLaunchKernelGGL(k_score_sum_groups, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, scores, n, RGB,
-                       rg_stride);
+    hipLaunchKernelGGL(k_score_sum_groups, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, scores, n, RG, rg_stride);
     if (check_launch("score sum groups") != OBF_OK) return OBF_ERR_HIP;
   }
   return OBF_OK;

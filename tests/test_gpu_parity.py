@@ -1631,3 +1631,33 @@ def test_bases_statistics_and_gather_in_one_launch(gpu, dtype, d, N, sink):
     assert torch.equal(a["diag"].view(torch.uint8), b["diag"].view(torch.uint8))
     for k in ("idx", "K_out", "V_out"):
         assert torch.equal(a[k].view(torch.uint8), b[k][:, :, :most].contiguous().view(torch.uint8)), k
+
+
+@pytest.mark.parametrize("R", [161, 192, 193, 384])          # 192 rows at once (the last block shared by two waves), 256 of which one is used, two groups
+@pytest.mark.parametrize("L,N", [(1, 1), (1, 63), (1, 64), (2, 65), (1, 96), (40, 1025)])     # steps of 64 tokens, their two tiles, heads over two ranges
+def test_scores_of_tall_row_groups(gpu, R, L, N):
+    """Row groups of 192 and 256 rows whose keys pass through LDS."""
+    _check_masses(gpu, R, L, N, sorted({0, L // 2, L - 1}))
+
+
+@pytest.mark.parametrize("R,off", [(256, 0), (192, 0), (192, 1)])
+def test_scores_of_tall_row_groups_over_many_ranges(gpu, R, off):
+    """Enough tokens that the first pass over 256 rows goes back to 128 at a time, on a partition of its own; keys off a 16-byte boundary."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    heads, N = 130, 16411
+    g = torch.Generator(device="cuda").manual_seed(7)
+    held = torch.randn(heads * N * 128 + 8, generator=g, device="cuda").bfloat16()
+    held[: 128 * 5] *= 8
+    K = held[off: off + heads * N * 128].view(heads, 1, N, 128)
+    Q = torch.randn((heads, 1, R, 128), generator=g, device="cuda").bfloat16()
+    sc, lse = Bd.score(K, Q)
+    torch.cuda.synchronize()
+    for h in (0, 63, 129):
+        k, q = K[h, 0].double(), Q[h, 0].double()
+        x = torch.matmul(q, k.t().contiguous()) / 128 ** 0.5
+        want = torch.logsumexp(x, 1)
+        mass = torch.exp(x - want[:, None]).sum(0)
+        bound = 128 * 2.0 ** -24 * float(torch.matmul(q.abs(), k.abs().t().contiguous()).max()) / 128 ** 0.5     # of a logit, see _check_masses
+        assert float((lse[h, 0] - want).abs().max()) <= bound + 2.0 ** -19
+        assert float(((sc[h, 0].double() - mass) / mass).abs().max()) <= 2 * bound + 2.0 ** -21 + 2.0 ** -19

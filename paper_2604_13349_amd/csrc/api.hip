@@ -321,13 +321,15 @@ static obf_status_t compress_heads(int layerwise, Variant var, const Dims& mf, i
   } else {
     rs = launch_gather(m, K, V, idx, n_keep, max_budget, K_out, V_out, st, fro_part);
   }
+  IdxShift shift{idx, sink, false};
   int32_t min_budget = budget;
   if (budgets_host) { min_budget = budgets_host[0]; for (int h = 1; h < mb.heads; ++h) min_budget = budgets_host[h] < min_budget ? budgets_host[h] : min_budget; }
   // (launch_backfill joins the bases' stream itself, on every path; after an earlier error it is only called for that)
   if (rs == OBF_OK || basis_started) {
     const obf_status_t fs = (rs == OBF_OK)
         ? launch_backfill(m, w, base, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part,
-                          together ? Begun::statistics : basis_started ? Begun::bases : Begun::nothing, min_budget, var)
+                          together ? Begun::statistics : basis_started ? Begun::bases : Begun::nothing, min_budget, var,
+                          k_beside ? nullptr : &shift /*the K rows on the second stream are still being copied by the lists*/)
         : stream_after(st, aux, EV_BASIS_JOIN);
     if (rs == OBF_OK) rs = fs;
   }
@@ -337,7 +339,8 @@ static obf_status_t compress_heads(int layerwise, Variant var, const Dims& mf, i
     OBF_TRY(launch_per_token_inject(m, w, base, K, V, scores, idx, n_keep, max_budget, K_out, V_out,
                                     (var.flags & VF_NO_SCALING) ? 1 : 0, st));
   if (diag && !layerwise) OBF_TRY(launch_diag_flags(diag, (const int32_t*)(base + w.sel_flags), m.heads, st));
-  return launch_idx_offset(idx, (size_t)m.heads * max_budget, sink, st);   // back to the head's own token numbers
+  // back to the head's own token numbers
+  return shift.done ? OBF_OK : launch_idx_offset(idx, (size_t)m.heads * max_budget, sink, st);
 }
 
 // Shared body of the fused calls; layerwise != 0 selects the per-layer retention rule.

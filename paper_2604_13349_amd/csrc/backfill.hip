@@ -1309,7 +1309,7 @@ template <typename T>
 static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void* V, const float* scores,
                         const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank, void* V_out,
                         float* delta_out, obf_diag_t* diag, hipStream_t st, hipStream_t aux, const double* fro_part,
-                        Begun begun, int32_t min_budget, Variant var) {
+                        Begun begun, int32_t min_budget, Variant var, IdxShift* shift) {
   bool basis_started = begun == Begun::bases;
   // Once the bases run on `aux`, every way out of this function joins it back into `st` first, errors included: the
   // caller is promised that all work of the call is ordered on its stream.
@@ -1398,9 +1398,11 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
     // The rank rule with few directions (the method's own setting, App. H's fast path, the Per-token alternative): one kernel for every
     // head.  Max-P, EVR and larger ranks need more of the spectrum and diagonalise.
     const int iters = (var.flags & VF_NAIVE) ? 0 : var.subspace_iters;
-    if (rank > 0 && rank <= kLeadMaxRank && !(var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE)))
+    if (rank > 0 && rank <= kLeadMaxRank && !(var.flags & (VF_SUBSPACE_ALL | VF_SUBSPACE_EVR | VF_NAIVE))) {
+      if (var.flags & VF_PER_TOKEN) shift = nullptr;             // the per-slot kernel still reads the lists
       return launch_backfill_lead(m, w, ws, scores, idx, max_budget, rank, max_budget > 0 ? V_inject : nullptr, delta_out, diag, st,
-                                  var.flags, iters);
+                                  var.flags, iters, shift);
+    }
     const size_t one = sizeof(float) * m.d * (m.d + 1);
     // every budget above head_dim: heads that need the finalisation are rare (the certificate settles the others), so one
     // launch with the large LDS size serves both classes instead of two launches that mostly exit at once
@@ -1420,10 +1422,10 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
 obf_status_t launch_backfill(const Dims& m, const Workspace& w, char* ws, const void* V, const float* scores,
                              const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank,
                              void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, hipStream_t aux,
-                             const double* fro_part, Begun begun, int32_t min_budget, Variant var) {
+                             const double* fro_part, Begun begun, int32_t min_budget, Variant var, IdxShift* shift) {
   if (m.dtype == OBF_BF16)
-    return run<uint16_t>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, begun, min_budget, var);
-  return run<float>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, begun, min_budget, var);
+    return run<uint16_t>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, begun, min_budget, var, shift);
+  return run<float>(m, w, ws, V, scores, idx, n_keep, max_budget, rank, V_out, delta_out, diag, st, aux, fro_part, begun, min_budget, var, shift);
 }
 
 }  // namespace obf

@@ -544,7 +544,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
                                                           float* __restrict__ mats, float* __restrict__ delta,
                                                           float* __restrict__ delta_out, obf_diag_t* __restrict__ diag,
                                                           T* __restrict__ V_out, int max_budget, const float* __restrict__ scores,
-                                                          const int32_t* __restrict__ idx, int vflags, int scs, int iters) {
+                                                          const int32_t* idx, int32_t* moved, int shift, int vflags, int scs, int iters) {
   constexpr int NT = D / 16, P = NARROW ? 8 : 16;
   extern __shared__ __attribute__((aligned(16))) float sm[];
   __shared__ float uvec[128], svec[128], coef[128], part[TE_THREADS], dvec[2][16], dex[128];
@@ -1082,11 +1082,17 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
   }
   fn_emit<T, TE_THREADS>(head, D, rank, st, skipped, k_used, rcr, ivn, pcr, pc, revr, fast_err, uvec, state, delta, delta_out, diag, V_out,
                          max_budget, scores, idx, vflags, scs);
+  if (shift > 0) {                                               // the lists of a token window: back to the head's own numbers, the -1 padding stays
+    __syncthreads();
+    int32_t* id = moved + (size_t)head * max_budget;
+    for (int i = tid; i < max_budget; i += TE_THREADS) { const int32_t v = id[i]; if (v >= 0) id[i] = v + shift; }
+  }
 }
 
 template <typename T, int D>
 static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const float* scores, const int32_t* idx, int32_t max_budget,
-                        int32_t rank, void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, int vflags, int iters) {
+                        int32_t rank, void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, int vflags, int iters,
+                        IdxShift* shift) {
   static std::mutex attr_mu;
   static uint64_t attr_seen = 0;
   once_per_device(attr_mu, attr_seen, [] {
@@ -1097,10 +1103,13 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const float
       (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
   });
   const size_t lds = sizeof(float) * lead_lds_floats(D, rank);
+  int32_t* moved = shift ? shift->idx : nullptr;
+  const int by = shift ? shift->by : 0;
+  if (shift) shift->done = true;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(m.heads), dim3(TE_THREADS), lds, st, w.nstat, rank, (HeadState*)(ws + w.head_state),
                        (const float*)(ws + w.basis), (const float*)(ws + w.gram_part), (float*)(ws + w.mats), (float*)(ws + w.delta),
-                       delta_out, diag, (T*)V_out, max_budget, scores, idx, vflags, m.scs, iters);
+                       delta_out, diag, (T*)V_out, max_budget, scores, idx, moved, by, vflags, m.scs, iters);
   };
   const bool thin = max_budget >= D - kThinWidth && !(vflags & VF_NO_PROJECTION);       // no head can be otherwise
   if (iters > 0) { if (rank <= 4) go(k_bf_lead<T, D, true, false, true>); else go(k_bf_lead<T, D, true, false, false>); }
@@ -1110,12 +1119,13 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const float
 }
 
 obf_status_t launch_backfill_lead(const Dims& m, const Workspace& w, char* ws, const float* scores, const int32_t* idx, int32_t max_budget,
-                                  int32_t rank, void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, int vflags, int iters) {
+                                  int32_t rank, void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, int vflags, int iters,
+                                  IdxShift* shift) {
   if (m.dtype == OBF_BF16)
-    return m.d == 128 ? run<uint16_t, 128>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters)
-                      : run<uint16_t, 64>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters);
-  return m.d == 128 ? run<float, 128>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters)
-                    : run<float, 64>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters);
+    return m.d == 128 ? run<uint16_t, 128>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters, shift)
+                      : run<uint16_t, 64>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters, shift);
+  return m.d == 128 ? run<float, 128>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters, shift)
+                    : run<float, 64>(m, w, ws, scores, idx, max_budget, rank, V_out, delta_out, diag, st, vflags, iters, shift);
 }
 
 }  // namespace obf

@@ -268,8 +268,8 @@ obf_status_t launch_keep_cert(const Dims& m, const void* Vsrc, int via_idx, cons
                               const int32_t* n_keep, int32_t max_budget, int32_t rank, HeadState* state,
                               int32_t* decided, hipStream_t st, const double* fro_part = nullptr, bool want_sums = true);
 obf_status_t launch_refine_layers(const Dims& m, const void* K, const void* Q, const float* layer_scores,
-                                  const double* row_lse, int32_t max_budget, int32_t* idx_layer,
-                                  const int32_t* n_keep_layer, double* part /*[heads][kBandCap]*/, hipStream_t st);
+                                  const double* row_lse, int32_t max_budget, const int32_t* idx_layer,
+                                  const int32_t* n_keep_layer, double* part /*[heads][kBandCap]*/, int32_t* idx, int32_t* n_keep, hipStream_t st);
 // Layerwise retention rule: TopK_B of the head-summed scores of each layer (with the exact re-decision at the
 // threshold), copied to every head of the layer.  budgets_host: per layer (nullable).
 obf_status_t launch_select_layerwise(const Dims& m, const Workspace& w, char* ws, const float* scores,
@@ -345,17 +345,21 @@ obf_status_t launch_basis_stats(const Dims& m, const Workspace& w, char* ws, con
                                 void* V_out /*nullable*/, hipStream_t st);
 // What of the back-fill the caller has already enqueued: nothing; the bases, on `aux`; the bases and the statistics, on `st`.
 enum class Begun { nothing, bases, statistics };
+// The index lists of a token window, which have to move by `by` once nothing of the call reads them any more; launch_backfill sets `done` if its last
+// kernel does that (one launch less: 2 to 3 us).
+struct IdxShift { int32_t* idx; int32_t by; bool done; };
 obf_status_t launch_backfill(const Dims& m, const Workspace& w, char* ws, const void* V, const float* scores,
                              const int32_t* idx, const int32_t* n_keep, int32_t max_budget, int32_t rank,
                              void* V_out, float* delta_out, obf_diag_t* diag, hipStream_t st, hipStream_t aux /*nullable*/,
                              const double* fro_part = nullptr,
                              Begun begun = Begun::nothing, int32_t min_budget = -1 /*smallest per-head budget if known*/,
-                             Variant var = Variant());
+                             Variant var = Variant(), IdxShift* shift = nullptr);
 
 // Rank rule with at most kLeadMaxRank directions: everything after the statistics pass (backfill_lead.hip), App. H's fast path included.
 constexpr int kLeadMaxRank = 16;
+// shift (nullable): its lists move once they have been read.
 obf_status_t launch_backfill_lead(const Dims& m, const Workspace& w, char* ws, const float* scores, const int32_t* idx, int32_t max_budget,
                                   int32_t rank, void* V_out /*nullable*/, float* delta_out, obf_diag_t* diag, hipStream_t st, int vflags,
-                                  int iters);
+                                  int iters, IdxShift* shift);
 
 }  // namespace obf

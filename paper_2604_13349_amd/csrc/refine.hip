@@ -170,27 +170,32 @@ __global__ __launch_bounds__(NT) void k_refine_layer_part(const T* __restrict__ 
                            nband, part + (size_t)head * kBandCap, sh.rescore);
 }
 
-// Second launch: one workgroup per layer finds the band again, adds the heads' exact masses in head order and
-// re-decides the band.
+// Second launch: every head's workgroup finds the layer's band again, adds the heads' exact masses in head order, re-decides the band and writes
+// the head's copy of the shared list: the same steps and so the same list in every workgroup of the layer.  (36 layers of 8
+// heads, 333 tokens: 6.7 us; one workgroup per layer took 5.8, but the launch that copied its list 3.2 and 2 more around it.)
 template <int NT>
 __global__ __launch_bounds__(NT) void k_refine_layer_apply(const float* __restrict__ layer_scores, int N, int H,
-                                                           int max_budget, int32_t* __restrict__ idx_layer,
+                                                           int max_budget, const int32_t* __restrict__ idx_layer,
                                                            const int32_t* __restrict__ n_keep_layer,
-                                                           const double* __restrict__ part) {
+                                                           const double* __restrict__ part, int32_t* __restrict__ idx,
+                                                           int32_t* __restrict__ n_keep) {
   __shared__ RfShared<NT> sh;
-  const int l = blockIdx.x;
+  const int head = blockIdx.x, l = head / H;
   const int n = n_keep_layer[l];
+  const int32_t* shared = idx_layer + (size_t)l * max_budget;
+  int32_t* out = idx + (size_t)head * max_budget;
+  for (int i = threadIdx.x; i < max_budget; i += NT) out[i] = shared[i];
+  if (threadIdx.x == 0) n_keep[head] = n;
   if (n <= 0 || n >= N) return;
-  int32_t* out = idx_layer + (size_t)l * max_budget;
   int nband, nkb, kb;
-  if (!rf_find_band<NT>(sh, layer_scores + (size_t)l * N, out, n, N, nband, nkb, kb)) return;
+  if (!rf_find_band<NT>(sh, layer_scores + (size_t)l * N, shared, n, N, nband, nkb, kb)) return;
   if ((int)threadIdx.x < nband) {
     double s = 0.0;
     for (int h = 0; h < H; ++h) s += part[((size_t)l * H + h) * kBandCap + threadIdx.x];
     sh.band_score[threadIdx.x] = s;
   }
   __syncthreads();
-  rf_apply<NT>(sh, out, N, nband, nkb, kb);
+  rf_apply<NT>(sh, out, N, nband, nkb, kb);              // over the copy: its writes come after the barriers above
 }
 
 obf_status_t launch_refine(const Dims& m, const Workspace& w, char* ws, const void* K, const void* Q,
@@ -208,10 +213,10 @@ obf_status_t launch_refine(const Dims& m, const Workspace& w, char* ws, const vo
 }
 
 // The same re-decision for selections shared by the heads of a layer: scores, idx and n_keep are per layer;
-// part is scratch for the heads' exact masses of the band tokens ([L*H][kBandCap] doubles).
+// part is scratch for the heads' exact masses of the band tokens ([L*H][kBandCap] doubles).  Every head gets the list that results.
 obf_status_t launch_refine_layers(const Dims& m, const void* K, const void* Q, const float* layer_scores,
-                                  const double* row_lse, int32_t max_budget, int32_t* idx_layer,
-                                  const int32_t* n_keep_layer, double* part, hipStream_t st) {
+                                  const double* row_lse, int32_t max_budget, const int32_t* idx_layer,
+                                  const int32_t* n_keep_layer, double* part, int32_t* idx, int32_t* n_keep, hipStream_t st) {
   ProfScope prof_(ST_REFINE, st);
   if (m.dtype == OBF_BF16)
     hipLaunchKernelGGL((k_refine_layer_part<uint16_t, RF_THREADS>), dim3(m.heads), dim3(RF_THREADS), 0, st,
@@ -222,8 +227,8 @@ obf_status_t launch_refine_layers(const Dims& m, const void* K, const void* Q, c
                        (const float*)K, (const float*)Q, layer_scores, row_lse, m.N, m.d, m.R, m.H, max_budget,
                        idx_layer, n_keep_layer, part, m.kvs);
   if (check_launch("refine (layerwise, exact masses)") != OBF_OK) return OBF_ERR_HIP;
-  hipLaunchKernelGGL((k_refine_layer_apply<RF_THREADS>), dim3(m.L), dim3(RF_THREADS), 0, st, layer_scores, m.N, m.H,
-                     max_budget, idx_layer, n_keep_layer, part);
+  hipLaunchKernelGGL((k_refine_layer_apply<RF_THREADS>), dim3(m.heads), dim3(RF_THREADS), 0, st, layer_scores, m.N, m.H,
+                     max_budget, idx_layer, n_keep_layer, part, idx, n_keep);
   return check_launch("refine (layerwise)");
 }
 

@@ -1633,6 +1633,32 @@ def test_bases_statistics_and_gather_in_one_launch(gpu, dtype, d, N, sink):
         assert torch.equal(a[k].view(torch.uint8), b[k][:, :, :most].contiguous().view(torch.uint8)), k
 
 
+@pytest.mark.parametrize("rank,layerwise,variant,heads,N,most", [
+    (2, False, None, 4, 130, 96), (16, True, None, 4, 1026, 100), (4, True, O.Variant(per_token=True), 4, 333, 40), (17, False, None, 4, 333, 40),
+    (2, False, None, 32, 2400, 2100)])     # moved by the last kernel; after the per-slot one; without it; while K rows are still copied by the lists
+def test_index_lists_behind_a_sink(gpu, rank, layerwise, variant, heads, N, most):
+    """The lists that the back-fill's last kernel moves to the heads' own numbers against those of a call without back-fill, and the rows they name."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    sink, L = 3, 2
+    cfg = si.RelayConfig("sinkidx", 61, L, heads // L, 2, 64, N, 8, 0, 3, "bf16", "structured", outlier_frac=0.01)
+    K, V, Q = (gpu.to_dev(x, "bf16") for x in si.make_cache(cfg, 0))
+    n = L if layerwise else heads
+    bud = np.array([0, most, min(most, 33), 1] * n, np.int32)[:n] if most < 2000 else np.full(n, most, np.int32)
+    if layerwise:
+        bud = bud[::-1].copy() if variant else np.array([most, 0], np.int32)
+    kw = dict(budgets=bud, layerwise=layerwise, max_budget=most, sink=sink, n_tokens=N - 2)
+    a = Bd.compress_relay(K, V, Q, rank=rank, variant=None if variant is None else _gpu_variant(variant), **kw)
+    b = Bd.compress_relay(K, V, Q, rank=0, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(a["n_keep"], b["n_keep"]) and torch.equal(a["idx"], b["idx"])
+    live = torch.arange(most, device="cuda") < a["n_keep"][..., None]
+    assert bool(((a["idx"] >= sink) & (a["idx"] < N - 2) == live).all()) and bool((a["idx"][~live] == -1).all())
+    if variant is None:
+        rows = torch.gather(K, 2, a["idx"].clamp(min=0).long()[..., None].expand(-1, -1, -1, 64))
+        assert torch.equal(rows[live], a["K_out"][live])
+
+
 @pytest.mark.parametrize("R", [161, 192, 193, 384])          # 192 rows at once (the last block shared by two waves), 256 of which one is used, two groups
 @pytest.mark.parametrize("L,N", [(1, 1), (1, 63), (1, 64), (2, 65), (1, 96), (40, 1025)])     # steps of 64 tokens, their two tiles, heads over two ranges
 def test_scores_of_tall_row_groups(gpu, R, L, N):

@@ -276,7 +276,8 @@ obf_status_t obf_append_message(int32_t n_heads, int32_t head_dim, int32_t dtype
  * compress it alone.  obf_workspace_bytes_batch() returns room for up to three samples in flight (one slot each; with
  * n_samples = 1 it returns the size of one slot): sample s then runs in lane s mod 3, lane 0 being `stream` and the others
  * streams of the library's own (forked off `stream` and joined back before the call returns, so that all work is ordered
- * on `stream` for the caller); a workspace of one or two slots is accepted too and gives that many lanes, and under stream
+ * on `stream` for the caller).  With max_budget at most 96 (below head_dim) and at most 16 directions the same three slots
+ * hold four lanes where that saves a round of samples; a workspace of one or two slots is accepted too and gives that many lanes, and under stream
  * capture or stage profiling the samples are simply enqueued one after the other on `stream`.  Results do not depend on
  * the number of lanes.  diag nullable.  Errors as
  * obf_compress_relay; nothing is enqueued on a host-side error. */

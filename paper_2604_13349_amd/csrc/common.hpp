@@ -87,11 +87,12 @@ struct Workspace {
   size_t layer_scores; // float   [L][N]        attention mass summed over the heads of a layer (layerwise selector)
   size_t layer_idx;    // int32   [L][max_budget], then int32 [L]: the shared index lists and their lengths
   size_t fro_part;     // double  [heads][ceil(max_budget/16)]   per-gather-block sums of squares of the retained V rows
-  size_t rot;          // float   [heads][kJacobiSweeps][d-1][d/2]  rotation tangents of the Jacobi iteration (max_budget < d only)
   size_t keep_gram;    // double  [kKeepGramSlots][kKeepGramChunks][d*d]  partial Gram matrices (max_budget >= kKeepGramMinBudget)
+  size_t rot;          // float   [heads][kJacobiSweeps][d-1][d/2]  rotation tangents of the Jacobi iteration (max_budget < d only)
   size_t inv_norm;     // float   [heads][max_budget]     reciprocal norms of the retained keys (cache merging)
   size_t route;        // int32   [heads][N]              retained slot of every deleted token (cache merging, when not an output)
   size_t total;
+  size_t lead_total;   // what a fused call needs whose back-fill takes at most kLeadMaxRank directions by the rank rule: all but the three regions before
   int nchunk;          // most chunks per head of the double-precision score path
   int rgroups, tiles_per_head, tiles_per_range, nranges;       // matrix-core score partition (tiles of 32 tokens, or steps of 64 with tall row groups)
   bool narrow_stats;   // tall row groups, but the first pass takes 128 rows at a time, on a partition of its own:
@@ -184,8 +185,9 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.layer_scores = take(sizeof(float) * (size_t)m.L * m.N);
   w.layer_idx = take(sizeof(int32_t) * ((size_t)m.L * (max_budget > 0 ? max_budget : 0) + m.L));
   w.fro_part = take(sizeof(double) * (size_t)m.heads * ((max_budget > 0 ? max_budget : 0) / kGatherRows + 1));
-  w.rot = take((max_budget < m.d && rank > 0) ? sizeof(float) * (size_t)m.heads * kJacobiSweeps * (m.d - 1) * (m.d / 2) : 0);
   w.keep_gram = take(max_budget >= kKeepGramMinBudget ? sizeof(double) * kKeepGramSlots * kKeepGramChunks * (size_t)m.d * m.d : 0);
+  w.lead_total = off;
+  w.rot = take((max_budget < m.d && rank > 0) ? sizeof(float) * (size_t)m.heads * kJacobiSweeps * (m.d - 1) * (m.d / 2) : 0);
   w.inv_norm = take(sizeof(float) * (size_t)m.heads * (max_budget > 0 ? max_budget : 0));
   w.route = take(sizeof(int32_t) * (size_t)m.heads * m.N);
   w.total = off;
@@ -322,10 +324,11 @@ obf_status_t launch_idx_offset(int32_t* idx, size_t n, int32_t offset, hipStream
 // The library's own streams: kAuxStreams per host thread and device, default priority, created on first use and kept.
 // aux_stream returns nullptr when none is available (creation failed, or the thread is in single-stream mode): the
 // launchers then keep everything on the caller's stream.
-constexpr int kBatchLanes = 3;                                   // samples of a batch in flight at a time: with lane 0's
+constexpr int kBatchLanes = 3;                                   // workspace slots of a batch, and samples in flight at a time: with lane 0's
                                                                   // inner fork that makes four streams, one per hardware queue (12 samples of
-                                                                  // 165 to 340 tokens, ms a sample: one lane 0.161, two 0.100, three 0.085)
+                                                                  // 165 to 340 tokens, ms a sample: one lane 0.131, two 0.084, three 0.075)
 constexpr int kAuxStreams = kBatchLanes;                          // the library's own streams per device and thread
+constexpr int kMostLanes = kAuxStreams + 1;                       // where no sample forks
 hipStream_t aux_stream(int which /*0 .. kAuxStreams-1*/);
 // While on (per host thread), no stream or event is created or used by the library.
 void set_single_stream(bool on);

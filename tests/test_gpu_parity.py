@@ -1659,6 +1659,33 @@ def test_index_lists_behind_a_sink(gpu, rank, layerwise, variant, heads, N, most
         assert torch.equal(rows[live], a["K_out"][live])
 
 
+@pytest.mark.parametrize("S,rank,dtype,d,stride", [(4, 2, "bf16", 128, 130), (7, 16, "bf16", 64, 1026), (8, 1, "f32", 64, 130), (4, 17, "bf16", 128, 130)])
+def test_batch_with_four_samples_in_flight(gpu, S, rank, dtype, d, stride):
+    """Four lanes on a workspace of three slots (three with more than 16 directions) against one sample after the other: the same bits, also on a
+    repeated call, and nothing past the workspace."""
+    import torch
+    from paper_2604_13349_amd import binding as Bd
+    cfg = si.RelayConfig("lanes", 71, 2, 4, 2, d, stride, 8, 0, rank, dtype, "structured", outlier_frac=0.01)
+    K, V, Q = (gpu.to_dev(np.stack(x), dtype) for x in zip(*(si.make_cache(cfg, 30 + i) for i in range(S))))
+    lens = [stride - 9 * i for i in range(S)]
+    buds = [(17, 48, 1, 0)[i % 4] for i in range(S)]
+    kw = dict(budgets=buds, rank=rank, sink=2, want_diag=True)
+    one = Bd.compress_relay_batch(K, V, Q, lens, lanes=1, **kw)
+    o = Bd.compress_relay_batch(K, V, Q, lens, **kw)
+    size = o["ws"].numel()
+    held = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    o["ws"] = held[:size]
+    torch.cuda.synchronize()
+    for again in range(3):
+        for k in ("K_out", "V_out", "idx", "n_keep"):
+            o[k].view(torch.uint8).fill_(0x33)
+        Bd.compress_relay_batch(K, V, Q, lens, out=o, **kw)
+        torch.cuda.synchronize()
+        for k in ("K_out", "V_out", "idx", "n_keep", "diag"):
+            assert torch.equal(o[k].view(torch.uint8), one[k].view(torch.uint8)), (k, again)
+        assert bool((held[size:] == 0x5A).all())
+
+
 @pytest.mark.parametrize("R", [161, 192, 193, 384])          # 192 rows at once (the last block shared by two waves), 256 of which one is used, two groups
 @pytest.mark.parametrize("L,N", [(1, 1), (1, 63), (1, 64), (2, 65), (1, 96), (40, 1025)])     # steps of 64 tokens, their two tiles, heads over two ranges
 def test_scores_of_tall_row_groups(gpu, R, L, N):

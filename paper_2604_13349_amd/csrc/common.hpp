@@ -124,16 +124,24 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.nstat = (m.N + kStatChunk - 1) / kStatChunk;
   // matrix-core score path: the flattened (head, 32-token tile) space is cut into one range per
   // persistent workgroup; a head is covered by at most nslot ranges
-  const int tall = score_tall_rows(m.R);
+  const int tall = m.dtype == OBF_BF16 && m.d == 128 ? score_tall_rows(m.R) : 0;
   const int group_rows = tall ? tall : score_rows_per_group(m.R);
   w.rgroups = (m.R + group_rows - 1) / group_rows;
   w.narrow_stats = false;
   auto slots = [](int per_head, int per_range) { return (per_head + per_range - 1) / per_range + 1; };
+  int held = w.nchunk;                                          // slots that stats_part has room for
   if (tall) {                                                   // two workgroups per compute unit
+    // Few heads are cut into more ranges than 128 rows at a time would be.  What their partials need beyond the room for those lies in the bases,
+    // statistics and matrices of the back-fill, which are written after the scores; ranges grow where that is not enough either.
+    const int tiles = (m.N + 31) / 32, per_old = score_tiles_per_range((long)m.heads * tiles, (m.R + score_rows_per_group(m.R) - 1) / score_rows_per_group(m.R));
+    held = slots(tiles, per_old) > held ? slots(tiles, per_old) : held;
+    const size_t spare = sizeof(float) * (4 * (size_t)m.d * m.d + w.nstat * gram_stride(m.d)) / (2 * sizeof(double) * (size_t)m.R);   // per head
+    const int most = spare > (size_t)held ? (int)spare : held;
     w.tiles_per_head = (m.N + kScoreTallStep - 1) / kScoreTallStep;
     const long TT = (long)m.heads * w.tiles_per_head;
     const int per_xcd = (2 * kNumCU / 8) / w.rgroups > 0 ? (2 * kNumCU / 8) / w.rgroups : 1;
     w.tiles_per_range = (int)((TT + 8 * per_xcd - 1) / (8 * per_xcd));
+    while (slots(w.tiles_per_head, w.tiles_per_range) > most) ++w.tiles_per_range;
     w.nranges = (int)((TT + w.tiles_per_range - 1) / w.tiles_per_range);
     // First pass over 256 rows at once or 128 at a time (us): 288 heads of 2048, 4096, 8192, 32768 tokens 53 - 61, 97 - 105, 198 - 197, 763 - 729: where each
     // workgroup has thousands of tokens both are bound by the card's power limit, and operands from LDS cost more than a second pass over K
@@ -145,6 +153,7 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
       const long ST = (long)m.heads * w.stats_tiles_per_head;
       w.stats_tiles_per_range = score_tiles_per_range(ST, w.stats_rgroups);
       w.stats_nranges = (int)((ST + w.stats_tiles_per_range - 1) / w.stats_tiles_per_range);
+      w.narrow_stats = slots(w.stats_tiles_per_head, w.stats_tiles_per_range) <= most;
     }
   } else {
     w.tiles_per_head = (m.N + 31) / 32;
@@ -167,9 +176,10 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
     w.stats_rgroups = w.rgroups; w.stats_tiles_per_head = w.tiles_per_head; w.stats_tiles_per_range = w.tiles_per_range; w.stats_nranges = w.nranges;
   }
   if (tall) w.nslot = slots(w.stats_tiles_per_head, w.stats_tiles_per_range);
+  else held = w.nchunk > w.nslot ? w.nchunk : w.nslot;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
-  w.stats_part = take(sizeof(double) * 2 * (size_t)m.heads * (w.nchunk > w.nslot ? w.nchunk : w.nslot) * m.R);
+  w.stats_part = take(sizeof(double) * 2 * (size_t)m.heads * held * m.R);
   w.row_lse = take(sizeof(double) * (size_t)m.heads * m.R);
   w.scores = take(sizeof(float) * (size_t)m.heads * m.N);
   // a single group, and the double-precision path, write their sums to the scores
@@ -179,6 +189,7 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.basis = take(sizeof(float) * (size_t)m.heads * m.d * m.d);
   w.gram_part = take(sizeof(float) * (size_t)m.heads * w.nstat * gram_stride(m.d));
   w.mats = take(sizeof(float) * (size_t)m.heads * 3 * m.d * m.d);
+  if (w.nslot > held) w.stats_part = w.basis;                    // (basis, gram_part and mats follow each other)
   w.delta = take(sizeof(float) * (size_t)m.heads * m.d);
   w.sel_flags = take(sizeof(int32_t) * (size_t)m.heads);
   w.band = take(16 * (size_t)m.heads * kBandCap);

@@ -11,7 +11,7 @@
 //
 // Bound by energy where there are thousands of tokens per workgroup (the clock falls to 1.7 to 2.0 GHz of 2.4 under the card's power limit), else by
 // the loads and the waits at the steps.  Both passes, us, pairs of 128-row groups (192 rows padded to them) and this:
-//   256 rows  288 heads of 2048, 8192 tokens 122 - 104, 388 - 380    96 of 9000 153 - 141    8 of 2048 29 - 19    192 rows  288 heads of 2048 113 - 85
+//   256 rows  288 heads of 2048, 8192 tokens 119 - 101, 397 - 379    96 of 9000 153 - 141    8 of 2048 29 - 19    192 rows  288 heads of 2048 114 - 87
 // Carrying the first product of a step across its barrier was no faster, sums against a reference that moves only when outgrown neither
 // (most tiles of a cache with outlier tokens outgrow it in some lane), 320 rows this way (160 operand registers a lane) slower.
 // Errors against 64 bits, rms, pairs and this, 64 heads of 2048 tokens, 256 rows: normalisers 2.4e-8 - 1.7e-8, scores 5.9e-8 - 5.7e-8 relative; with tokens

@@ -222,3 +222,13 @@ def test_workspace_holds_column_sums_of_the_second_pass_groups_only(lib, window,
         assert extra <= rest
     else:
         assert 4 * heads * N * sums <= extra <= 4 * heads * N * sums + rest
+
+
+@pytest.mark.parametrize("window", [161, 192, 256])
+@pytest.mark.parametrize("heads", [1, 2, 8])
+def test_workspace_of_tall_row_groups_keeps_partials_of_four_tiles(lib, heads, window):
+    """Row groups of 192 and 256 rows cut few heads into finer ranges than the others, at least one step of 64 tokens each; the workspace
+    still holds a row's partials for ranges of four tiles of 32 tokens (16 bytes each), the rest lies in regions that are idle then."""
+    N = 8192
+    size = lambda w: B.workspace_bytes(B.make_shape(1, heads, 1, 128, N, w, "bf16"), 64, 2)
+    assert size(window) - size(1) <= heads * window * (16 * (N // 128 + 1) + 8) + 2 * 256

@@ -273,7 +273,7 @@ def main() -> int:
                               "value": round(scfg.n_heads * scfg.n_tokens / (rr["elapsed"] / args.steps), 1), "unit": "head-tokens/s",
                               "path": path_s, "roofline": roof_s})
             c["shadow"] = (scfg, sb, holder["o"])
-        # a batch of paper-shape samples through the batch entry point (three samples in flight on streams of the library)
+        # a batch of paper-shape samples through the batch entry point (several samples in flight on streams of the library)
         nb = 12
         if not args.layers:
             trip = [si.make_cache(pc, args.seed + 100 + j, threads=threads) for j in range(nb)]

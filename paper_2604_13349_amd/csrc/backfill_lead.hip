@@ -816,11 +816,13 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
             x = product(x);
             y = product(x);
             const int full = min(min(P, m - found), st.n_del - found);              // most independent columns the block can have
-            bool last = false;
+            bool last = false, again = false;                    // again: the block as it is, its small problem solved to the end
             float rn_before = INFINITY;
             int kc = 0;                                          // directions of the group that can be resolved against its first
             for (int round = 0;; ++round) {
-              // Rayleigh-Ritz: each wave's share of X^T X and X^T Y, one wave solves the small problem
+              // Rayleigh-Ritz: each wave's share of X^T X and X^T Y, one wave solves the small problem.  Far from the end a sweep does, what it
+              // leaves goes with the next; a group ends on vectors that a sweep has left only where their own residual is at the products' rounding.
+              const bool exact = last || again || rn_before < 1e-2f;                // uniform
               float4* xb = xbuf + wave * LE_XTILE;
               float4* yb = xbuf + (NT + wave) * LE_XTILE;
               const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -838,8 +840,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
                 f32x4 S;
                 float theta;
                 int place;
-                // Far from the end a sweep does, what it leaves goes with the next; where the residual decides, the vectors have to be exact.
-                small_ritz<P>(M, H, 1e-5f, 3e-4f, last || rn_before < 1e-2f ? 8 : 1, S, theta, place);
+                small_ritz<P>(M, H, 1e-5f, 3e-4f, exact ? 8 : 1, S, theta, place);
                 s_rot[q * 16 + place] = make_float4(S[0], S[1], S[2], S[3]);
                 if (q == 0) s_th[place] = theta;
               }
@@ -868,14 +869,24 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
                 if (lane == 0) red[wave] = rr;
               }
               lds_barrier();
-              if (kc == 0) break;                                // nothing (more) above the resolution of the matrix
+              if (kc == 0) {                                     // nothing (more) above the resolution of the matrix
+                if (exact) break;
+                again = true;
+                continue;
+              }
               float rn = 0.f;
 #pragma unroll
               for (int w = 0; w < NT; ++w) rn += red[w];
               rn = uniform(sqrtf(rn) / th1);                     // residual of the wanted directions, relative to the spectrum
               // done: at the rounding of the products; there by the polynomial's own estimate; or no longer falling, and then near enough for the
               // last wanted direction, or at the rounding that P G P brought along (of G, 1 / rcr times its own trace)
-              if (rn <= 3e-7f || (last && rn <= 1e-6f) || (rn > 0.5f * rn_before && (rn * th1 <= 1e-5f * s_th[kc - 1] || rn * th1 * rcr <= 3e-8f))) break;
+              if (rn <= 3e-7f || (last && rn <= 1e-6f)) break;
+              if (rn > 0.5f * rn_before && (rn * th1 <= 1e-5f * s_th[kc - 1] || rn * th1 * rcr <= 3e-8f)) {
+                if (exact) break;
+                again = true;
+                continue;
+              }
+              again = false;
               rn_before = rn;
               // columns that depended on the others make room for new ones (a steep spectrum hides all but its leading directions from
               // the first products), unless the matrix has no more directions

@@ -820,9 +820,12 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
             float rn_before = INFINITY;
             int kc = 0;                                          // directions of the group that can be resolved against its first
             for (int round = 0;; ++round) {
-              // Rayleigh-Ritz: each wave's share of X^T X and X^T Y, one wave solves the small problem.  Far from the end a sweep does, what it
-              // leaves goes with the next; a group ends on vectors that a sweep has left only where their own residual is at the products' rounding.
-              const bool exact = last || again || rn_before < 1e-2f;                // uniform
+              // Rayleigh-Ritz: each wave's share of X^T X and X^T Y, one wave solves the small problem.  With eight columns a sweep does far from
+              // the end, what it leaves goes with the next round; with sixteen that costs rounds, and two sweeps in the first and up to eight in the
+              // others, to a looser tolerance, are faster (288 heads of 300 tokens, 16 kept, four strong directions, the kernel with 5, 6, 8 and 16
+              // directions: 115, 129, 141, 227 us; with one sweep 137, 155, 165, 247; 144 calls of 5 to 16 directions 0.97 of the time).
+              // That a residual has come down to the rounding of P G P is believed only of a problem that was solved to the end.
+              const bool exact = last || again || (P == 8 && (group > 0 || rn_before < 1e-2f));       // uniform
               float4* xb = xbuf + wave * LE_XTILE;
               float4* yb = xbuf + (NT + wave) * LE_XTILE;
               const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -840,7 +843,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
                 f32x4 S;
                 float theta;
                 int place;
-                small_ritz<P>(M, H, 1e-5f, 3e-4f, exact ? 8 : 1, S, theta, place);
+                small_ritz<P>(M, H, 1e-5f, P == 8 || exact ? 3e-4f : 0.1f, exact ? 8 : P == 8 ? 1 : round == 0 ? 2 : 8, S, theta, place);
                 s_rot[q * 16 + place] = make_float4(S[0], S[1], S[2], S[3]);
                 if (q == 0) s_th[place] = theta;
               }
@@ -869,24 +872,16 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
                 if (lane == 0) red[wave] = rr;
               }
               lds_barrier();
-              if (kc == 0) {                                     // nothing (more) above the resolution of the matrix
-                if (exact) break;
-                again = true;
-                continue;
-              }
+              if (kc == 0) break;                                // nothing (more) above the resolution of the matrix
               float rn = 0.f;
 #pragma unroll
               for (int w = 0; w < NT; ++w) rn += red[w];
               rn = uniform(sqrtf(rn) / th1);                     // residual of the wanted directions, relative to the spectrum
               // done: at the rounding of the products; there by the polynomial's own estimate; or no longer falling, and then near enough for the
               // last wanted direction, or at the rounding that P G P brought along (of G, 1 / rcr times its own trace)
-              if (rn <= 3e-7f || (last && rn <= 1e-6f)) break;
-              if (rn > 0.5f * rn_before && (rn * th1 <= 1e-5f * s_th[kc - 1] || rn * th1 * rcr <= 3e-8f)) {
-                if (exact) break;
-                again = true;
-                continue;
-              }
-              again = false;
+              const bool stuck = rn > 0.5f * rn_before;
+              again = stuck && rn * th1 * rcr <= 3e-8f;
+              if (rn <= 3e-7f || (last && rn <= 1e-6f) || (stuck && rn * th1 <= 1e-5f * s_th[kc - 1]) || (again && exact)) break;
               rn_before = rn;
               // columns that depended on the others make room for new ones (a steep spectrum hides all but its leading directions from
               // the first products), unless the matrix has no more directions
@@ -902,7 +897,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
               };
               const float gk = growth(thk), g1 = growth(th1);
               const float need = ceilf(__builtin_amdgcn_logf(fmaxf(rn * 5e7f, 10.f)) / gk);
-              if (!(need <= (float)kBlockReach) || round + 1 >= kBlockRounds) { direct = true; break; }
+              if (!again && (!(need <= (float)kBlockReach) || round + 1 >= kBlockRounds)) { direct = true; break; }
               // caps: what single precision can tell apart after the columns have grown so differently (guards against the leading
               // one, then the wanted ones among themselves, less what still mixes them)
               const float c1 = __builtin_amdgcn_logf(round == 0 ? 1e3f : 3e6f) / g1;

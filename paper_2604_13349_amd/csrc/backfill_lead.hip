@@ -532,20 +532,22 @@ __device__ __forceinline__ float uniform(const float v) {
 // FAST selects the fast path of App. H: `iters` steps of C <- orth(C P G P) from a fixed orthonormal start; the exact directions are
 // then only found when diagnostics are wanted, to report how far the fast path's Delta is from theirs.  (A kernel of its own: the calls
 // to the orthogonalisation push six values of each of its products to scratch.  The compiler reports 37 to 41 registers that go to scratch
-// somewhere in the plain kernels of head_dim 128, 116 in this one and 93 in the THIN ones; at head_dim 64 none, 89 and 13.)
+// somewhere in the plain kernels of head_dim 128, 116 in this one and 89 to 94 in the THIN ones; at head_dim 64 none, 90 to 94 and 13 to 16.)
 // THIN: some heads may retain so many directions that their complement is no wider than a block (kThinWidth).  P G P is not formed for
 // those (Q has more rows than there would be products): products with G are followed by a projection of the block, and the block's Ritz
 // values give the trace; see lead_thin.  (288 heads of 1024 tokens, 112, 120 and 126 kept, whole call, 8 directions: 302, 316 and 313 us
 // with that in here, where its operands pushed the matrix to scratch; 293, 305 and 303 as a function.)
-// NARROW: at most four directions, which take a block of eight columns; sixteen otherwise.
-template <typename T, int D, bool FAST, bool THIN, bool NARROW>
+// COLS: the columns of a block, 8 for at most four directions, 16 for more; 0: by what a head has to give, where some may have no more than four deleted
+// rows (288 heads of 66 and 99 tokens, 64 and 96 kept, 8 directions: 66 and 85 us, 83 and 97 with sixteen columns).
+template <typename T, int D, bool FAST, bool THIN, int COLS>
 __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, HeadState* __restrict__ state,
                                                           const float* __restrict__ basis, const float* __restrict__ gram_part,
                                                           float* __restrict__ mats, float* __restrict__ delta,
                                                           float* __restrict__ delta_out, obf_diag_t* __restrict__ diag,
                                                           T* __restrict__ V_out, int max_budget, const float* __restrict__ scores,
                                                           const int32_t* idx, int32_t* moved, int shift, int vflags, int scs, int iters) {
-  constexpr int NT = D / 16, P = NARROW ? 8 : 16;
+  constexpr int NT = D / 16;
+  constexpr bool NARROW = COLS == 8;
   extern __shared__ __attribute__((aligned(16))) float sm[];
   __shared__ float uvec[128], svec[128], coef[128], part[TE_THREADS], dvec[2][16], dex[128];
   __shared__ double dred[TE_WAVES];
@@ -698,6 +700,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
       const float srel = (float)max(st.n_del, D) * (float)kRankEps;
       const float floor_rel = fmaxf(srel * srel, kEigFloor);
       const int kq = min(rank, m), kmax = min(kq, st.n_del);
+      const int P = COLS ? COLS : kmax <= 4 ? 8 : 16;
 
       const BlockLds<D> lds(sm);
       bf16x4* sbuf = lds.sbuf;
@@ -816,6 +819,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
             x = product(x);
             y = product(x);
             const int full = min(min(P, m - found), st.n_del - found);              // most independent columns the block can have
+            const bool loose = P == 16 && full == P;             // how the small problems are solved far from the end
             bool last = false, again = false;                    // again: the block as it is, its small problem solved to the end
             float rn_before = INFINITY;
             int kc = 0;                                          // directions of the group that can be resolved against its first
@@ -823,9 +827,10 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
               // Rayleigh-Ritz: each wave's share of X^T X and X^T Y, one wave solves the small problem.  With eight columns a sweep does far from
               // the end, what it leaves goes with the next round; with sixteen that costs rounds, and two sweeps in the first and up to eight in the
               // others, to a looser tolerance, are faster (288 heads of 300 tokens, 16 kept, four strong directions, the kernel with 5, 6, 8 and 16
-              // directions: 115, 129, 141, 227 us; with one sweep 137, 155, 165, 247; 144 calls of 5 to 16 directions 0.97 of the time).
+              // directions: 115, 129, 141, 227 us; with one sweep 137, 155, 165, 247; 144 calls of 5 to 16 directions 0.97 of the time), but
+              // not where the matrix has fewer directions than that (40 tokens, 32 kept, 8 directions, fp32 at head_dim 64: 53, the other way 80).
               // That a residual has come down to the rounding of P G P is believed only of a problem that was solved to the end.
-              const bool exact = last || again || (P == 8 && (group > 0 || rn_before < 1e-2f));       // uniform
+              const bool exact = last || again || (!loose && (group > 0 || rn_before < 1e-2f));       // uniform
               float4* xb = xbuf + wave * LE_XTILE;
               float4* yb = xbuf + (NT + wave) * LE_XTILE;
               const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -843,7 +848,10 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
                 f32x4 S;
                 float theta;
                 int place;
-                small_ritz<P>(M, H, 1e-5f, P == 8 || exact ? 3e-4f : 0.1f, exact ? 8 : P == 8 ? 1 : round == 0 ? 2 : 8, S, theta, place);
+                const float tol = exact || !loose ? 3e-4f : 0.1f;
+                const int sweeps = exact ? 8 : !loose ? 1 : round == 0 ? 2 : 8;
+                if (P == 8) small_ritz<8>(M, H, 1e-5f, tol, sweeps, S, theta, place);
+                else small_ritz<16>(M, H, 1e-5f, tol, sweeps, S, theta, place);
                 s_rot[q * 16 + place] = make_float4(S[0], S[1], S[2], S[3]);
                 if (q == 0) s_th[place] = theta;
               }
@@ -1031,7 +1039,7 @@ __global__ __launch_bounds__(TE_THREADS, 4) void k_bf_lead(int nstat, int rank, 
         for (int it = 0; it < iters && kk > 0; ++it) {         // uniform
           images();
           if (wave == solver) {
-            const int nk = lead_orth<NARROW ? 4 : TE_MAXK, D>((int)(Ya - sm), (int)(Yb - sm), kk);
+            const int nk = NARROW || (COLS == 0 && kk <= 4) ? lead_orth<4, D>((int)(Ya - sm), (int)(Yb - sm), kk) : lead_orth<TE_MAXK, D>((int)(Ya - sm), (int)(Yb - sm), kk);
             if (lane == 0) s_k = nk;
           }
           __syncthreads();
@@ -1103,9 +1111,9 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const float
   static uint64_t attr_seen = 0;
   once_per_device(attr_mu, attr_seen, [] {
     const int most = (int)(sizeof(float) * lead_lds_floats(D, TE_MAXK));
-    for (const void* k : {(const void*)k_bf_lead<T, D, false, false, false>, (const void*)k_bf_lead<T, D, false, true, false>,
-                          (const void*)k_bf_lead<T, D, true, false, false>, (const void*)k_bf_lead<T, D, false, false, true>,
-                          (const void*)k_bf_lead<T, D, false, true, true>, (const void*)k_bf_lead<T, D, true, false, true>})
+    for (const void* k : {(const void*)k_bf_lead<T, D, false, false, 8>, (const void*)k_bf_lead<T, D, false, false, 16>, (const void*)k_bf_lead<T, D, false, false, 0>,
+                          (const void*)k_bf_lead<T, D, false, true, 8>, (const void*)k_bf_lead<T, D, false, true, 16>, (const void*)k_bf_lead<T, D, false, true, 0>,
+                          (const void*)k_bf_lead<T, D, true, false, 8>, (const void*)k_bf_lead<T, D, true, false, 16>, (const void*)k_bf_lead<T, D, true, false, 0>})
       (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
   });
   const size_t lds = sizeof(float) * lead_lds_floats(D, rank);
@@ -1118,9 +1126,10 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const float
                        delta_out, diag, (T*)V_out, max_budget, scores, idx, moved, by, vflags, m.scs, iters);
   };
   const bool thin = max_budget >= D - kThinWidth && !(vflags & VF_NO_PROJECTION);       // no head can be otherwise
-  if (iters > 0) { if (rank <= 4) go(k_bf_lead<T, D, true, false, true>); else go(k_bf_lead<T, D, true, false, false>); }
-  else if (thin) { if (rank <= 4) go(k_bf_lead<T, D, false, true, true>); else go(k_bf_lead<T, D, false, true, false>); }
-  else { if (rank <= 4) go(k_bf_lead<T, D, false, false, true>); else go(k_bf_lead<T, D, false, false, false>); }
+  auto by_cols = [&](auto k8, auto k16, auto k0) { if (rank <= 4) go(k8); else if (m.N - max_budget > 4) go(k16); else go(k0); };
+  if (iters > 0) by_cols(k_bf_lead<T, D, true, false, 8>, k_bf_lead<T, D, true, false, 16>, k_bf_lead<T, D, true, false, 0>);
+  else if (thin) by_cols(k_bf_lead<T, D, false, true, 8>, k_bf_lead<T, D, false, true, 16>, k_bf_lead<T, D, false, true, 0>);
+  else by_cols(k_bf_lead<T, D, false, false, 8>, k_bf_lead<T, D, false, false, 16>, k_bf_lead<T, D, false, false, 0>);
   return check_launch("backfill leading directions");
 }
 

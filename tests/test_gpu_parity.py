@@ -1278,6 +1278,14 @@ def test_directions_of_a_flat_spectrum_under_the_rounding_of_the_matrix(gpu, ran
     assert float(err.max()) <= 0.1, err.max()
 
 
+@pytest.mark.parametrize("dtype,d,keep", [("bf16", 128, 64), ("f32", 64, 32), ("bf16", 128, 125)])
+@pytest.mark.parametrize("deleted,iters", [(1, 0), (4, 0), (5, 0), (4, 3)])          # the block's width by the head; one row too many for that
+def test_heads_with_few_deleted_rows_under_a_larger_rank(gpu, dtype, d, keep, deleted, iters):
+    """Eight directions asked for where few rows were deleted, beside heads that have more to give."""
+    cfg = si.RelayConfig("fewdel", 83, 1, 4, 2, d, keep + deleted, 8, keep, 8, dtype, "structured")
+    _check_cfg(gpu, cfg, budgets=[keep, keep, keep - 3, 17], variant=O.Variant(subspace_iters=iters) if iters else None)
+
+
 def test_complement_projector_with_coinciding_columns(gpu):
     """Every seventh token carries a multiple of e_0 - e_1 as its value row and no other row touches those two
     coordinates: e_0 - e_1 lies in the retained span, e_0 + e_1 in its complement, so columns 0 and 1 of the projector

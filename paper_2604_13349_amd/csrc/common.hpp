@@ -142,7 +142,21 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
     const int per_xcd = (2 * kNumCU / 8) / w.rgroups > 0 ? (2 * kNumCU / 8) / w.rgroups : 1;
     w.tiles_per_range = (int)((TT + 8 * per_xcd - 1) / (8 * per_xcd));
     while (slots(w.tiles_per_head, w.tiles_per_range) > most) ++w.tiles_per_range;
-    w.nranges = (int)((TT + w.tiles_per_range - 1) / w.tiles_per_range);
+    // Every workgroup of the second pass folds all partials of its head, 0.3 us each, and again where its range goes on into the next head; a step
+    // costs both passes 3 us.  So few heads are cut into no more than 4 sqrt(steps) ranges each, and ranges end with their head (whose last one is the
+    // shorter) where that makes them at most two steps longer, with one of them to a compute unit in place of two where that costs four more at
+    // most.  Both passes, 192 rows (us), before, ranges of equal length that fill the card, and with this: 2 heads of 16384 and 32768 tokens 72, 73 - 27, 35;
+    // 4 of 8192 44 - 23; 8 of 4096 and 16384 30, 39 - 19, 32; 24 of 4096 38 - 27; 96 of 1300 37 - 31; 160 of 2048 56 - 52; 288 of 256 31 - 26.
+    const int SH = w.tiles_per_head, fit = 8 * per_xcd / m.heads;
+    while (16L * w.tiles_per_range * w.tiles_per_range < SH) ++w.tiles_per_range;
+    if (fit >= 1) {
+      const int parts = (SH + w.tiles_per_range - 1) / w.tiles_per_range;
+      auto steps = [&](int most_parts) { const int n = parts < most_parts ? parts : most_parts; return n < 1 ? SH : (SH + n - 1) / n; };
+      const int full = steps(fit), half = steps(fit / 2);
+      const int own = half <= full + 4 ? half : full;
+      if (full <= w.tiles_per_range + 2) { w.tiles_per_range = own; w.tiles_per_head = (SH + own - 1) / own * own; }
+    }
+    w.nranges = (int)(((long)m.heads * w.tiles_per_head + w.tiles_per_range - 1) / w.tiles_per_range);
     // First pass over 256 rows at once or 128 at a time (us): 288 heads of 2048, 4096, 8192, 32768 tokens 53 - 61, 97 - 105, 198 - 197, 763 - 729: where each
     // workgroup has thousands of tokens both are bound by the card's power limit, and operands from LDS cost more than a second pass over K
     // through the first-level cache.  The second pass is ahead throughout (50 - 61, 94 - 103, 183 - 192, 678 - 691), so is 192 rows at once.

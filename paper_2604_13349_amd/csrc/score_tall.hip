@@ -33,7 +33,7 @@ constexpr int TA_LOADS = TA_STEP / 16;   // 16-byte loads of a lane per step
 constexpr int TA_BYTES = TA_STEP * TA_D * 2;
 
 struct TallPart {
-  int SH;        // steps per head
+  int SH;        // steps per head; more than its tokens make where ranges end with their head, whose last range is then the shorter
   int T;         // steps per range
   long TT;       // heads * SH
   long kstride;  // elements between consecutive heads of K
@@ -135,6 +135,12 @@ __device__ __forceinline__ TallPlace tall_place(const int RG) {
   return TallPlace{group * 8 + (in & 7), in >> 3};
 }
 
+// Steps of the range that starts at gs, `pos` steps into a head.
+__device__ __forceinline__ int tall_steps(const TallPart& pt, const long gs, const int pos, const int N) {
+  const int n = (int)(min(pt.TT, gs + pt.T) - gs), own = (N + TA_STEP - 1) / TA_STEP;
+  return own < pt.SH ? min(n, own - pos) : n;
+}
+
 // Pass A: leaves one partial (max, sum-exp) per query row and segment (the part of a head inside a range), as k_score_stats_mfma.
 template <int F, int H>
 __global__ __launch_bounds__(TA_THREADS, 2) void k_score_stats_tall(const uint16_t* __restrict__ K, const uint16_t* __restrict__ Q,
@@ -145,12 +151,12 @@ __global__ __launch_bounds__(TA_THREADS, 2) void k_score_stats_tall(const uint16
   const TallPlace at = tall_place(RG);
   const long gs = (long)at.range * pt.T;
   if (gs >= pt.TT) return;
-  const int n = (int)(min(pt.TT, gs + pt.T) - gs);
+  int head = (int)(gs / pt.SH), pos = (int)(gs - (long)head * pt.SH);
+  const int n = tall_steps(pt, gs, pos, N);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row0 = at.rg * ROWS;
   const float a2 = 1.4426950408889634f / sqrtf((float)TA_D);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)sm.k;
-  int head = (int)(gs / pt.SH), pos = (int)(gs - (long)head * pt.SH);
   int ih = head, ip = pos;                                     // what is loaded next
   auto feed = [&](const int b) {
     fill_step(sm.k + b * TA_BYTES, lds0 + b * TA_BYTES, K + (size_t)ih * pt.kstride + (size_t)ip * TA_STEP * TA_D, N - 1 - ip * TA_STEP, wave, lane, aligned != 0);
@@ -241,8 +247,8 @@ __global__ __launch_bounds__(TA_THREADS, 2) void k_score_mass_tall(const uint16_
   const TallPlace at = tall_place(RG);
   const long gs = (long)at.range * pt.T;
   if (gs >= pt.TT) return;
-  const long ge = min(pt.TT, gs + pt.T);
-  const int n = (int)(ge - gs);
+  const int n = tall_steps(pt, gs, (int)(gs % pt.SH), N);
+  const long ge = gs + n;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row0 = at.rg * ROWS;
   const float a2 = 1.4426950408889634f / sqrtf((float)TA_D);

@@ -1771,7 +1771,14 @@ def test_scores_of_tall_row_groups(gpu, R, L, N):
     _check_masses(gpu, R, L, N, sorted({0, L // 2, L - 1}))
 
 
-@pytest.mark.parametrize("R,off", [(256, 0), (192, 0), (192, 1)])
+@pytest.mark.parametrize("R", [161, 192, 256, 384, 512])
+@pytest.mark.parametrize("L,N", [(1, 20000), (2, 4100), (7, 700), (24, 4100), (60, 1300), (250, 200)])     # few ranges to a head; the last one shorter
+def test_scores_of_tall_row_groups_whose_ranges_end_with_their_head(gpu, R, L, N):
+    """Heads that are cut into ranges of their own."""
+    _check_masses(gpu, R, L, N, sorted({0, L // 2, L - 1}))
+
+
+@pytest.mark.parametrize("R,off", [(256, 0), (192, 0), (192, 1), (225, 0), (256, 1), (384, 0), (352, 1), (512, 0), (450, 1), (512, 1)])
 def test_scores_of_tall_row_groups_over_many_ranges(gpu, R, off):
     """Enough tokens that the first pass over 256 rows goes back to 128 at a time, on a partition of its own; keys off a 16-byte boundary."""
     import torch

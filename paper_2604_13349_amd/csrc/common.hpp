@@ -75,7 +75,7 @@ struct Workspace {
   size_t stats_part;   // double2 [heads][nchunk][R]      partial (max, sum-exp) per score chunk
   size_t row_lse;      // double  [heads][R]
   size_t scores;       // float   [heads][N]              (fused call without scores_out)
-  size_t score_part;   // float   [rgroups][heads][N] per-row-group column sums where there are several
+  size_t score_part;   // float   [rgroups - 1][heads][N] column sums of all row groups but the last, whose lie where the scores will
   size_t head_state;   // HeadState [heads]
   size_t decided;      // int32   [heads]                 1: the fast full-rank test settled the head
   size_t basis;        // float   [heads][d][d]           orthonormal basis of the retained span (columns)
@@ -94,6 +94,7 @@ struct Workspace {
   size_t total;
   size_t lead_total;   // what a fused call needs whose back-fill takes at most kLeadMaxRank directions by the rank rule: all but the three regions before
   int nchunk;          // most chunks per head of the double-precision score path
+  int tall_rows;       // 192 or 256: scores with row groups of that many; 0: others
   int rgroups, tiles_per_head, tiles_per_range, nranges;       // matrix-core score partition (tiles of 32 tokens, or steps of 64 with tall row groups)
   bool narrow_stats;   // tall row groups, but the first pass takes 128 rows at a time, on a partition of its own:
   int stats_rgroups, stats_tiles_per_head, stats_tiles_per_range, stats_nranges;
@@ -124,7 +125,12 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.nstat = (m.N + kStatChunk - 1) / kStatChunk;
   // matrix-core score path: the flattened (head, 32-token tile) space is cut into one range per
   // persistent workgroup; a head is covered by at most nslot ranges
-  const int tall = m.dtype == OBF_BF16 && m.d == 128 ? score_tall_rows(m.R) : 0;
+  int tall = m.dtype == OBF_BF16 && m.d == 128 ? score_tall_rows(m.R) : 0;
+  // Two groups of 192 rows for three of 128 pad nothing less.  They are ahead by their shorter way from head to head; where a workgroup has
+  // thousands of tokens of long heads, three are (both passes, 384 rows, us, three and two: 64 heads of 4096, 8192, 24000 tokens 81 - 72, 130 - 127,
+  // 349 - 376; 288 of 2048, 4096, 8192, 20000 tokens 176 - 147, 302 - 284, 573 - 588, 1358 - 1440).
+  if (tall == 192 && m.R > 320 && m.R <= 384 && m.N >= 8192 && (long)m.heads * m.N >= 4096L * kNumCU) tall = 0;
+  w.tall_rows = tall;
   const int group_rows = tall ? tall : score_rows_per_group(m.R);
   w.rgroups = (m.R + group_rows - 1) / group_rows;
   w.narrow_stats = false;
@@ -197,7 +203,7 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.row_lse = take(sizeof(double) * (size_t)m.heads * m.R);
   w.scores = take(sizeof(float) * (size_t)m.heads * m.N);
   // a single group, and the double-precision path, write their sums to the scores
-  w.score_part = take(w.rgroups > 1 && m.dtype == OBF_BF16 && m.d == 128 ? sizeof(float) * (size_t)w.rgroups * m.heads * m.N : 0);
+  w.score_part = take(w.rgroups > 1 && m.dtype == OBF_BF16 && m.d == 128 ? sizeof(float) * (size_t)(w.rgroups - 1) * m.heads * m.N : 0);
   w.head_state = take(sizeof(HeadState) * (size_t)m.heads);
   w.decided = take(sizeof(int32_t) * (size_t)m.heads);
   w.basis = take(sizeof(float) * (size_t)m.heads * m.d * m.d);
@@ -260,10 +266,10 @@ template <> struct Elem<uint16_t> {
 obf_status_t launch_score_generic(const Dims& m, const Workspace& w, char* ws, const void* K, const void* Q,
                                   float* scores, double* row_lse, hipStream_t st);
 bool mfma_score_supported(const Dims& m);
-// Both passes with row groups of 192 or 256 rows (the first only where w.narrow_stats does not leave it to the other kernel); part: the scores, or a
-// group's sums each.
-obf_status_t launch_score_tall(const Dims& m, const Workspace& w, double* stats_part, const void* K, const void* Q, float* part, double* row_lse,
-                               hipStream_t st);
+// Both passes with row groups of 192 or 256 rows (the first only where w.narrow_stats does not leave it to the other kernel).  The last group's sums go
+// to `scores`, the others' to `part`.
+obf_status_t launch_score_tall(const Dims& m, const Workspace& w, double* stats_part, const void* K, const void* Q, float* part, float* scores,
+                               double* row_lse, hipStream_t st);
 obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, const void* K, const void* Q,
                                float* scores, double* row_lse, hipStream_t st);
 obf_status_t launch_select(const Dims& m, const float* scores, const int32_t* budgets_host, int32_t budget,

@@ -314,13 +314,13 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_stats_mfma(const uint16
 // ------------------------------------------------------------------------------------------------
 // Pass B.  Same partition.  First folds the head's partials into log-sum-exp (every workgroup that touches
 // a head computes the same values; the one holding the head's first tile also writes row_lse), then
-// out = scores (RG == 1) or the row group's partial column sums.
+// the row group's column sums, the last group's to `scores`.
 template <int RB, int KBUF>
 __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_t* __restrict__ K,
                                                                    const uint16_t* __restrict__ Q,
                                                                    const double* __restrict__ stats_part,
                                                                    double* __restrict__ row_lse,
-                                                                   float* __restrict__ out, int N, int R, int RG,
+                                                                   float* __restrict__ part, float* __restrict__ scores, int N, int R, int RG,
                                                                    size_t rg_stride, Part pt, int nslot) {
   __shared__ double s_lse[(RB * 32)];
   // Workgroups are dealt to the 8 XCDs round-robin.  The RG workgroups that stream the same K range (one per row
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(SM_THREADS, 1) void k_score_mass_mfma(const uint16_
     const int ta = (int)(cur - hs) * SM_TILE, tb = min(N, (int)(se - hs) * SM_TILE);
     const uint16_t* Kh = K + (size_t)head * pt.kstride;
     const uint16_t* Qh = Q + (size_t)head * R * SM_D;
-    float* dst = out + (size_t)rg * rg_stride + (size_t)head * N;
+    float* dst = (rg == RG - 1 ? scores : part + (size_t)rg * rg_stride) + (size_t)head * N;
 
     __syncthreads();
     for (int rl = threadIdx.x; rl < RB * 32; rl += SM_THREADS) {
@@ -454,14 +454,14 @@ __global__ __launch_bounds__(SM_THREADS, 2) void k_score_head_mfma(const uint16_
   run_tiles<false, RB, KBUF>(Kh, first + (nt - 1) * STEP, -STEP, nt, N, lane, qf, ep);
 }
 
-// scores = sum of the row groups' partial column sums (fixed order)
+// scores = sum of the row groups' partial column sums (fixed order), the last group's of which lie in it
 __global__ void k_score_sum_groups(const float* __restrict__ part, float* __restrict__ scores, size_t n, int RG,
                                    size_t rg_stride) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   float s = 0.f;
-  for (int g = 0; g < RG; ++g) s += part[(size_t)g * rg_stride + i];
-  scores[i] = s;
+  for (int g = 0; g < RG - 1; ++g) s += part[(size_t)g * rg_stride + i];
+  scores[i] = s + scores[i];
 }
 
 bool mfma_score_supported(const Dims& m) {
@@ -473,8 +473,8 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
   double* stats_part = (double*)(ws + w.stats_part);
   const int RG = w.rgroups;
   const size_t rg_stride = (size_t)m.heads * m.N;
-  float* part = (RG > 1) ? (float*)(ws + w.score_part) : scores;
-  if (score_tall_rows(m.R)) {
+  float* part = (float*)(ws + w.score_part);                     // (not used by a single group)
+  if (w.tall_rows) {
     if (w.narrow_stats) {
       ProfScope prof_(ST_SCORE_STATS, st);
       Part pt;
@@ -483,7 +483,7 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
       hipLaunchKernelGGL((k_score_stats_mfma<4, 3>), dim3(((w.stats_nranges + 7) / 8) * 8 * w.stats_rgroups), dim3(SM_THREADS), 0, st, (const uint16_t*)K,
                          (const uint16_t*)Q, stats_part, m.N, m.R, w.stats_rgroups, pt, w.nslot);
     }
-    if (launch_score_tall(m, w, stats_part, K, Q, part, row_lse, st) != OBF_OK) return OBF_ERR_HIP;
+    if (launch_score_tall(m, w, stats_part, K, Q, part, scores, row_lse, st) != OBF_OK) return OBF_ERR_HIP;
   } else {
     Part pt;
     pt.TH = w.tiles_per_head; pt.T = w.tiles_per_range; pt.TT = (long)m.heads * w.tiles_per_head;
@@ -509,7 +509,7 @@ obf_status_t launch_score_mfma(const Dims& m, const Workspace& w, char* ws, cons
     if (check_launch("score stats (mfma)") != OBF_OK) return OBF_ERR_HIP;
     { ProfScope prof_(ST_SCORE_MASS, st);
       auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, (const double*)stats_part, row_lse, part,
+        hipLaunchKernelGGL(kernel, grid, dim3(SM_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, (const double*)stats_part, row_lse, part, scores,
                            m.N, m.R, RG, rg_stride, pt, w.nslot);
       };
       if (five) go(k_score_mass_mfma<5, 2>); else go(k_score_mass_mfma<4, 3>); }

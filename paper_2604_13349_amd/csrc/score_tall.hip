@@ -240,7 +240,7 @@ __global__ __launch_bounds__(TA_THREADS, 2) void k_score_stats_tall(const uint16
 template <int F, int H>
 __global__ __launch_bounds__(TA_THREADS, 2) void k_score_mass_tall(const uint16_t* __restrict__ K, const uint16_t* __restrict__ Q,
                                                                    const double* __restrict__ stats_part, double* __restrict__ row_lse,
-                                                                   float* __restrict__ out, int N, int R, int RG, size_t rg_stride, TallPart pt,
+                                                                   float* __restrict__ part, float* __restrict__ scores, int N, int R, int RG, size_t rg_stride, TallPart pt,
                                                                    TallPart sp /*the first pass's, in its units*/, int nslot, int aligned) {
   constexpr int ROWS = 128 * F + 64 * H, B = F + H, U = 2 * F + H;
   __shared__ struct { __attribute__((aligned(16))) char k[TA_RING * TA_BYTES]; __attribute__((aligned(16))) float b2[ROWS]; float ps[2][4][TA_STEP]; } sm;
@@ -260,6 +260,7 @@ __global__ __launch_bounds__(TA_THREADS, 2) void k_score_mass_tall(const uint16_
     if (--ip < 0) { ip = pt.SH - 1; --ih; }
   };
   for (int a = 0; a < TA_AHEAD; ++a) if (a < n) feed(a);
+  float* out = at.rg == RG - 1 ? scores : part + (size_t)at.rg * rg_stride;
   float* dst = nullptr;                                        // where the last step's sums go
   int dst_n = 0;
   auto flush = [&](const int p) {                              // the four waves' shares
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(TA_THREADS, 2) void k_score_mass_tall(const uint16_
       // lanes below 32 are left with the first tile's sums over both row halves, the others with the second's
       const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
       sm.ps[s & 1][wave][lane] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
-      dst = out + (size_t)at.rg * rg_stride + (size_t)head * N + tok;
+      dst = out + (size_t)head * N + tok;
       dst_n = min(TA_STEP, N - tok);
     }
     pos = pt.SH - 1; --head;
@@ -349,15 +350,15 @@ __global__ __launch_bounds__(TA_THREADS, 2) void k_score_mass_tall(const uint16_
   flush((n - 1) & 1);
 }
 
-obf_status_t launch_score_tall(const Dims& m, const Workspace& w, double* stats_part, const void* K, const void* Q, float* part, double* row_lse,
-                               hipStream_t st) {
+obf_status_t launch_score_tall(const Dims& m, const Workspace& w, double* stats_part, const void* K, const void* Q, float* part, float* scores,
+                               double* row_lse, hipStream_t st) {
   const int RG = w.rgroups;
   const TallPart pt = {w.tiles_per_head, w.tiles_per_range, (long)m.heads * w.tiles_per_head, (long)m.kvs * TA_D};
   const TallPart sp = {w.stats_tiles_per_head, w.stats_tiles_per_range, (long)m.heads * w.stats_tiles_per_head, pt.kstride};
   const dim3 grid((unsigned)((w.nranges + 7) / 8 * 8 * RG));
   const int aligned = ((uintptr_t)K & 15) == 0;
   const size_t rg_stride = (size_t)m.heads * m.N;
-  const bool two = score_tall_rows(m.R) == 256;
+  const bool two = w.tall_rows == 256;
   if (!w.narrow_stats) {
     ProfScope prof_(ST_SCORE_STATS, st);
     auto go = [&](auto kernel) {
@@ -368,7 +369,7 @@ obf_status_t launch_score_tall(const Dims& m, const Workspace& w, double* stats_
   if (check_launch("score stats (row groups of 192 or 256)") != OBF_OK) return OBF_ERR_HIP;
   { ProfScope prof_(ST_SCORE_MASS, st);
     auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, grid, dim3(TA_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, (const double*)stats_part, row_lse, part, m.N, m.R,
+      hipLaunchKernelGGL(kernel, grid, dim3(TA_THREADS), 0, st, (const uint16_t*)K, (const uint16_t*)Q, (const double*)stats_part, row_lse, part, scores, m.N, m.R,
                          RG, rg_stride, pt, sp, w.nslot, aligned);
     };
     if (two) go(k_score_mass_tall<2, 0>); else go(k_score_mass_tall<1, 1>); }

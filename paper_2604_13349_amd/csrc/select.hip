@@ -49,13 +49,14 @@ __device__ __forceinline__ void block_exscan2(int a, int b, int& ea, int& eb, in
 // kernel took 36, 113 and 158 us on 288, 320 and 288 heads of 8192, 16384 and 32768 tokens; it takes 25, 59 to 74 and 98.
 // With REFINE the tokens whose score lies in the relative band around the threshold are re-decided in double from K, Q
 // and the row log-sum-exp before the list is written (same decisions as select followed by the refinement kernel).
-// With 256 threads a lane may have 256 registers, 512 of them would leave room for one workgroup: at 128 the fp32 kernel keeps 45 of its values in
-// scratch memory (96 heads of 2048 tokens 12.9 us; 11.9 without).
+// Waves per SIMD: four, 128 registers a lane.  The fp32 kernel with REFINE keeps 45 of its values in scratch memory then, and six with 168 registers; with
+// 256 threads three workgroups still share a compute unit (head_dim 64, 2048 tokens, 96, 288, 576 heads: four waves 11.2, 12.4, 17.2 us, three 9.3, 9.5,
+// 11.7, two and no scratch 9.4, 9.5, 14.7).  bf16 has fewer to keep and gains nothing by them.
 constexpr int SEL_BINS = 2048;
 constexpr int SEL_LIST = 256;
 
 template <int SEG, int SEL_THREADS, bool REFINE, typename ET>
-__global__ __launch_bounds__(SEL_THREADS, SEL_THREADS == 256 ? 2 : 4) void k_select(const float* __restrict__ scores, int N, int head0,
+__global__ __launch_bounds__(SEL_THREADS, REFINE && sizeof(ET) == 4 && SEL_THREADS == 256 ? 3 : 4) void k_select(const float* __restrict__ scores, int N, int head0,
                                                         int uniform_budget, BudgetBatch per_head, int use_per_head,
                                                         int max_budget, int32_t* __restrict__ idx,
                                                         int32_t* __restrict__ n_keep, const ET* __restrict__ K,

@@ -128,8 +128,16 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   int tall = m.dtype == OBF_BF16 && m.d == 128 ? score_tall_rows(m.R) : 0;
   // Two groups of 192 rows for three of 128 pad nothing less.  They are ahead by their shorter way from head to head; where a workgroup has
   // thousands of tokens of long heads, three are (both passes, 384 rows, us, three and two: 64 heads of 4096, 8192, 24000 tokens 81 - 72, 130 - 127,
-  // 349 - 376; 288 of 2048, 4096, 8192, 20000 tokens 176 - 147, 302 - 284, 573 - 588, 1358 - 1440).
-  if (tall == 192 && m.R > 320 && m.R <= 384 && m.N >= 8192 && (long)m.heads * m.N >= 4096L * kNumCU) tall = 0;
+  // 349 - 376; 288 of 2048, 4096, 8192, 20000 tokens 176 - 147, 302 - 284, 573 - 588, 1358 - 1440), and so nine for six (1152 rows: 64 heads of 2048 and
+  // 96 of 32768 135 - 108, 2066 - 2167).
+  bool sums_aside = false;                                      // the column sums lie in the bases, statistics and matrices, too
+  if (tall == 192) {
+    const int g = (m.R + 191) / 192, g128 = (m.R + 127) / 128;
+    if (g128 * 128 <= g * 192 && m.N >= 8192 && (long)m.heads * m.N >= 4096L * 8 * (g < 64 ? 64 / g : 1)) {
+      const bool more = g128 - 1 > g;                           // sets than six groups' were
+      if (!more || (size_t)(g128 - 1) * m.N <= 4 * (size_t)m.d * m.d + w.nstat * gram_stride(m.d)) { tall = 0; sums_aside = more; }
+    }
+  }
   w.tall_rows = tall;
   const int group_rows = tall ? tall : score_rows_per_group(m.R);
   w.rgroups = (m.R + group_rows - 1) / group_rows;
@@ -203,13 +211,14 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
   w.row_lse = take(sizeof(double) * (size_t)m.heads * m.R);
   w.scores = take(sizeof(float) * (size_t)m.heads * m.N);
   // a single group, and the double-precision path, write their sums to the scores
-  w.score_part = take(w.rgroups > 1 && m.dtype == OBF_BF16 && m.d == 128 ? sizeof(float) * (size_t)(w.rgroups - 1) * m.heads * m.N : 0);
+  w.score_part = take(w.rgroups > 1 && !sums_aside && m.dtype == OBF_BF16 && m.d == 128 ? sizeof(float) * (size_t)(w.rgroups - 1) * m.heads * m.N : 0);
   w.head_state = take(sizeof(HeadState) * (size_t)m.heads);
   w.decided = take(sizeof(int32_t) * (size_t)m.heads);
   w.basis = take(sizeof(float) * (size_t)m.heads * m.d * m.d);
   w.gram_part = take(sizeof(float) * (size_t)m.heads * w.nstat * gram_stride(m.d));
   w.mats = take(sizeof(float) * (size_t)m.heads * 3 * m.d * m.d);
   if (w.nslot > held) w.stats_part = w.basis;                    // (basis, gram_part and mats follow each other)
+  if (sums_aside) w.score_part = w.basis;                        // (with 128 rows at a time the partials are never there)
   w.delta = take(sizeof(float) * (size_t)m.heads * m.d);
   w.sel_flags = take(sizeof(int32_t) * (size_t)m.heads);
   w.band = take(16 * (size_t)m.heads * kBandCap);

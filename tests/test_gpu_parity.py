@@ -1778,9 +1778,10 @@ def test_scores_of_tall_row_groups_whose_ranges_end_with_their_head(gpu, R, L, N
     _check_masses(gpu, R, L, N, sorted({0, L // 2, L - 1}))
 
 
-@pytest.mark.parametrize("R,off", [(256, 0), (192, 0), (192, 1), (225, 0), (256, 1), (384, 0), (352, 1), (512, 0), (450, 1), (512, 1)])
+@pytest.mark.parametrize("R,off", [(256, 0), (192, 0), (192, 1), (225, 0), (256, 1), (384, 0), (352, 1), (512, 0), (450, 1), (512, 1), (1152, 0)])
 def test_scores_of_tall_row_groups_over_many_ranges(gpu, R, off):
-    """Enough tokens that the first pass over 256 rows goes back to 128 at a time, on a partition of its own; keys off a 16-byte boundary."""
+    """Enough tokens that the first pass over 256 rows goes back to 128 at a time, on a partition of its own, and both where groups of 192 pad nothing less;
+    keys off a 16-byte boundary."""
     import torch
     from paper_2604_13349_amd import binding as Bd
     heads, N = 130, 16411

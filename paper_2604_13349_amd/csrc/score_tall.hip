@@ -39,10 +39,16 @@ struct TallPart {
   long kstride;  // elements between consecutive heads of K
 };
 
-// 16 bytes per lane from base + off to LDS at `lds` + 16 lane, without registers between; complete when vmcnt says so.  (The builtin would have the compiler
-// wait for the youngest of these loads before every read of LDS.  Nothing else in here uses m0.)
-__device__ __forceinline__ void load_to_lds(const uint32_t lds, const uint32_t off, const void* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+// Four times 16 bytes per lane from base + off to LDS at `lds` + 16 lane and 4096 further each time, without registers between; complete when vmcnt says
+// so.  (The builtin would have the compiler wait for the youngest of these loads before every read of LDS.)  m0 is left as it was: the compiler reserves
+// it and would not be told by a clobber.
+__device__ __forceinline__ void load_to_lds(const uint32_t lds, const uint32_t (&off)[4], const void* base) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %6\n\t"
+               "s_add_u32 m0, m0, 0x1000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %6\n\t"
+               "s_add_u32 m0, m0, 0x1000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %6\n\t"
+               "s_add_u32 m0, m0, 0x1000\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %6\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0) : "s"(lds), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory", "scc");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
@@ -53,11 +59,15 @@ __device__ __forceinline__ void fill_step(char* ring, const uint32_t lds, const 
                                           const bool aligned) {
   const int r0 = wave * 4 + (lane >> 4);
   const uint32_t piece = (uint32_t)(((lane & 15) ^ r0) << 4);
+  static_assert(TA_LOADS == 4, "loads of load_to_lds");
+  uint32_t off[TA_LOADS];
 #pragma unroll
-  for (int i = 0; i < TA_LOADS; ++i) {
-    const uint32_t off = (uint32_t)(min(i * 16 + r0, last) << 8) + piece, at = (uint32_t)((i * 16 + wave * 4) * 256);
-    if (aligned) load_to_lds(lds + at, off, Kt);
-    else *(uint4*)(ring + at + lane * 16) = *(const uint4*)((const char*)Kt + off);
+  for (int i = 0; i < TA_LOADS; ++i) off[i] = (uint32_t)(min(i * 16 + r0, last) << 8) + piece;
+  if (aligned) {
+    load_to_lds(lds + wave * 1024, off, Kt);
+  } else {
+#pragma unroll
+    for (int i = 0; i < TA_LOADS; ++i) *(uint4*)(ring + i * 4096 + wave * 1024 + lane * 16) = *(const uint4*)((const char*)Kt + off[i]);
   }
 }
 

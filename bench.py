@@ -51,6 +51,8 @@ def stage_bytes(stage: str, cfg, budgets, active_heads: int) -> float:
         return 4 * kept * d * es
     if stage == "del_stats":
         return active_heads * N * d * es
+    if stage == "basis_stats":            # the statistics' pass over V with the scores, and the gathered rows: K read, both written
+        return active_heads * N * d * es + heads * N * 4 + 3 * kept * d * es
     if stage in ("keep_basis", "keep_cert"):
         return kept * d * es + heads * N * 4
     if stage == "select":
@@ -233,6 +235,9 @@ def main() -> int:
         if r["dominant"] in ("keep_basis", "finalize", "select", "keep_cert"):
             roof["note"] = ("a per-head sequential factorisation or selection: bound by the latency of its dependent steps, "
                             "the HBM fraction only says how far from streaming it is")
+        elif r["dominant"] == "basis_stats":
+            roof["note"] = ("one launch of the statistics' pass over V, the gathered rows and the per-head factorisations of the bases, whose "
+                            "latency holds part of the compute units")
         path = {"bytes": pb, "GBps": round(pb / step_s / 1e9, 2), "frac": round(pb / step_s / 1e9 / HBM_PEAK_GBS, 4),
                 "target_frac": 0.60, "unit": "GB/s of algorithmic bytes (K, Q once; retained rows read and written; V where the back-fill is active)"}
         return roof, path

@@ -343,7 +343,9 @@ obf_status_t obf_compress_relay_static(const obf_shape_t* shape, const void* K, 
  * internal stage's kernel with a pair of events; stage -1 switches it off.  obf_profile_read
  * waits for the recorded events, returns the summed elapsed milliseconds and the number of
  * launches since the last read, and resets both.  Stage ids run 0 .. obf_profile_stage_count()-1;
- * obf_profile_stage_name gives the kernel family each one covers. */
+ * obf_profile_stage_name gives the kernel family each one covers.  Calls whose budgets are at most 96 (below head_dim) launch
+ * the bases, the statistics and, unless staged, the gather as one kernel, the stage "basis_stats"; "gather", "keep_basis" and
+ * "del_stats" have no launch of theirs then. */
 obf_status_t obf_profile_enable(int32_t stage);
 obf_status_t obf_profile_read(double* total_ms, int32_t* launches);
 int32_t obf_profile_stage_count(void);

@@ -4,7 +4,9 @@
 // latency on few workgroups; the longest, the bases, come first in the grid.
 // As three launches on two streams the bases ran beside the others too, but the fork and the join cost 7 and 11 us: 288 heads of 256 tokens, 32 kept,
 // the whole call 154 -> 132 us; two fp32 heads of 512 tokens 92 -> 70; 12 short samples 1007 -> 936; 288 heads of 8192 tokens, 96 kept, 629 -> 611.
-// Budgets above 96 rows stay apart: their basis kernel takes twice the registers, which would halve the waves of the statistics beside it.
+// Budgets above 96 rows stay apart: their basis kernel takes twice the registers, which would halve the waves of the statistics beside it.  fp32 at
+// head_dim 128 has twice the registers here already (its statistics need them), and at 96 rows LDS for one workgroup to a compute unit; apart it is slower
+// all the same: 2 heads of 300 tokens, 96 kept, 157 - 126 us, 288 of 4096 1079 - 1050, 640 of 1024 782 - 747, 288 of 8192 1931 - 1909.
 #include "del_stats_generic.hpp"
 #include "del_stats_mfma.hpp"
 #include "gather.hpp"
@@ -14,7 +16,7 @@ namespace obf {
 
 constexpr int BS_THREADS = KS_THREADS;
 static_assert(BS_THREADS == DM_THREADS && BS_THREADS == DG_THREADS, "the parts of the grid share a workgroup size");
-constexpr int BS_MAX_ROWS = 96;          // retained rows of the basis code that runs four waves per SIMD
+constexpr int BS_MAX_ROWS = 96;          // retained rows of the basis code without the wider registers
 
 struct BsGather { const uint4 *K, *V; uint4 *K_out, *V_out; int blocks /*per head; 0: nothing is gathered*/; };
 
@@ -61,7 +63,7 @@ static obf_status_t run(const Dims& m, const Workspace& w, char* ws, const void*
   });
   BsGather g = {(const uint4*)K, (const uint4*)V, (uint4*)K_out, (uint4*)V_out, K_out ? ga_blocks<BS_THREADS>(max_budget, D * (int)sizeof(T)) : 0};
   const long blocks = (long)m.heads * (1 + w.nstat + g.blocks);
-  ProfScope prof_(ST_DEL_STATS, st);
+  ProfScope prof_(ST_BASIS_STATS, st);
   hipLaunchKernelGGL((k_bf_basis_stats<T, D>), dim3((unsigned)blocks), dim3(BS_THREADS), lds_of(max_budget), st, (const T*)V, scores, idx, n_keep, m.N,
                      max_budget, rank, m.heads, w.nstat, (HeadState*)(ws + w.head_state), (float*)(ws + w.basis), (float*)(ws + w.gram_part), m.scs,
                      m.kvs, g);

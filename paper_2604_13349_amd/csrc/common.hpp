@@ -236,7 +236,7 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
 
 enum Stage {
   ST_SCORE_STATS = 0, ST_SCORE_LSE, ST_SCORE_MASS, ST_SELECT, ST_REFINE, ST_GATHER, ST_KEEP_CERT, ST_KEEP_BASIS, ST_DEL_STATS,
-  ST_FINALIZE, ST_COUNT
+  ST_FINALIZE, ST_BASIS_STATS, ST_COUNT
 };
 
 // Brackets one kernel launch with HIP events when profiling of that stage is enabled.

@@ -18,14 +18,14 @@
 // cores and LDS in turn, and so 288 heads on 256 compute units take 73 where 256 take 54.  With the middle parts in the block's free columns, a sweep
 // for the early small problems and the parts by conversion instructions 288 such heads went from 80 us to 73.  The kernel took the place
 // of a basis of the complement, the tridiagonalisation of its m x m matrix and inverse iteration (68 + 148 us for 288 heads of 256 tokens with 32
-// kept, 2 directions; 73 now, the whole call 299 -> 128; twelve samples 2060 -> 894), and the offset's error against double
+// kept, 2 directions; 73 now, the whole call 299 -> 128; twelve samples, four in flight, 2060 -> 857), and the offset's error against double
 // precision fell from 8.6e-7 to 3.3e-7 (2000 tokens with 96 kept, 8 directions: 4.0e-6 to 5.0e-7).
 //
-// What it depends on: this kernel, as it was before the blocks of eight columns had a kernel of their own, against those before it (us, 288 heads), and the whole call
-//   256 tokens, 32 kept    2, 8, 12, 16 directions   210 223 272 282 -> 79 97 125 164    299 312 360 369 -> 155 173 201 241
-//   1024 tokens, 80 kept                             165 172 199 207 -> 107 127 152 200  331 338 365 373 -> 244 263 286 330
-//   2000 tokens, 96 kept                             130 136 156 163 -> 117 133 156 198  366 371 390 395 -> 311 327 353 391
-//   1024 tokens, 112 kept                             99 103 118 123 -> 101 100 100 101  316 320 336 340 -> 299 301 301 300
+// What it depends on: this kernel against those before it (us, 288 heads), and the whole call when it took their place
+//   256 tokens, 32 kept    2, 8, 12, 16 directions   210 223 272 282 -> 73 96 129 166    299 312 360 369 -> 155 173 201 241
+//   1024 tokens, 80 kept                             165 172 199 207 -> 101 125 154 193  331 338 365 373 -> 244 263 286 330
+//   2000 tokens, 96 kept                             130 136 156 163 -> 105 128 149 187  366 371 390 395 -> 311 327 353 391
+//   1024 tokens, 112 kept                             99 103 118 123 -> 94 93 93 93      316 320 336 340 -> 299 301 301 300
 // A narrow complement costs as much as a wide one here, the kernels before it worked in its own coordinates: at 32 columns they are ahead from
 // thirteen directions on, and where the direct route takes over after the first products (eigenvalues closer than the block can tell
 // apart, 2 directions: complements 96, 64, 32 and 20 wide 308 300 267 275 -> 355 338 315 327).

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(MB_THREADS) void k_mg_bucket(const int32_t* __restr
 // Merge.  A wave per retained slot takes the slot's tokens in ascending order and adds their weighted value rows into a running
 // sum in registers (a lane owns D / 64 columns): the order of the additions is fixed, so the result is the same on every run.  A list of
 // up to MG_LIST tokens is put in order first (every entry counts the smaller ones); a longer one is not: the head's routes are scanned
-// instead, which finds the slot's tokens in order.  Sixteen rows are in flight at a time.  Slots that received nothing are left as the
+// instead, which finds the slot's tokens in order.  Eight rows are in flight at a time, sixteen where the list is longer.  Slots that received nothing are left as the
 // bit copies the gather wrote.  Bound by a wave's instructions per token and its chain offsets - list - rows (nine tokens a
 // slot here; the offsets' read does not wait for n_keep, nor the store for the slot's own value), then by the pass over V: 55 us on 288
 // heads x 2048 tokens x 205 slots, and 9 for the lists; 63 with sixteen loads for every list, 78 and 7 with the weights worked out here, 99 with eight rows ahead and every lane

@@ -172,7 +172,7 @@ __global__ __launch_bounds__(NT) void k_refine_layer_part(const T* __restrict__ 
 
 // Second launch: every head's workgroup finds the layer's band again, adds the heads' exact masses in head order, re-decides the band and writes
 // the head's copy of the shared list: the same steps and so the same list in every workgroup of the layer.  (36 layers of 8
-// heads, 333 tokens: 6.7 us; one workgroup per layer took 5.8, but the launch that copied its list 3.2 and 2 more around it.)
+// heads of 333, 2048 and 8192 tokens: 5.2, 7.1, 13.1 us; one workgroup per layer took 5.0, 6.8, 13.9, but the launch that copied its list 4 to 5.)
 template <int NT>
 __global__ __launch_bounds__(NT) void k_refine_layer_apply(const float* __restrict__ layer_scores, int N, int H,
                                                            int max_budget, const int32_t* __restrict__ idx_layer,

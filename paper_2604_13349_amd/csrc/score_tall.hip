@@ -9,13 +9,16 @@
 // one instruction stream, the operands are picked by LDS address.  The product of the next (block, tile) is issued beside the vector work of the
 // present one; while a wave waits at a step's barrier the other workgroup's on the same SIMD goes on.
 //
-// Bound by energy where there are thousands of tokens per workgroup (the clock falls to 1.7 to 2.0 GHz of 2.4 under the card's power limit), else by
-// the loads and the waits at the steps.  Both passes, us, pairs of 128-row groups (192 rows padded to them) and this:
-//   256 rows  288 heads of 2048, 8192 tokens 119 - 101, 397 - 379    96 of 9000 153 - 141    8 of 2048 29 - 19    192 rows  288 heads of 2048 114 - 87
+// Where there are thousands of tokens per workgroup: K from memory and the products beside each other, at a clock that falls with the power drawn (second
+// pass, 288 heads of 32768 tokens: K once, 1.33 million cycles, the matrix pipe busy in 0.44 of them; 666 us at 2.0 GHz after a pause, 727 at 1.8 in a
+// row of calls).  Else the loads, the waits at the steps and, with few heads, the fold of the partials.  Both passes, us, pairs of 128-row groups (192
+// rows padded to them) and this:
+//   256 rows  288 heads of 128, 2048, 8192 tokens 45 - 19, 113 - 98, 394 - 390    96 of 9000 147 - 133    8 of 2048 28 - 16
+//   192 rows  288 heads of 2048, 4001 tokens 109 - 84, 200 - 156
 // Carrying the first product of a step across its barrier was no faster, sums against a reference that moves only when outgrown neither
 // (most tiles of a cache with outlier tokens outgrow it in some lane), 320 rows this way (160 operand registers a lane) slower.
-// Errors against 64 bits, rms, pairs and this, 64 heads of 2048 tokens, 256 rows: normalisers 2.4e-8 - 1.7e-8, scores 5.9e-8 - 5.7e-8 relative; with tokens
-// of eight times the size 1.21e-6 - 1.11e-6 and 2.0e-7 - 1.9e-7.
+// Errors against 64 bits, six draws of each of eleven shapes of 161 to 512 rows, with and without tokens of eight times the size: rms of scores 0.95 and of
+// normalisers 0.83 of the pairs' (geometric means; 0.85 to 0.99 and 0.52 to 0.93), largest errors 0.98 and 0.91 (0.83 to 1.20 and 0.72 to 1.11).
 #include "score_parts.hpp"
 #include "wave_ops.hpp"
 

@@ -1779,12 +1779,12 @@ def test_scores_of_tall_row_groups_whose_ranges_end_with_their_head(gpu, R, L, N
 
 
 @pytest.mark.parametrize("R,off", [(256, 0), (192, 0), (192, 1), (225, 0), (256, 1), (384, 0), (352, 1), (512, 0), (450, 1), (512, 1), (1152, 0)])
-def test_scores_of_tall_row_groups_over_many_ranges(gpu, R, off):
-    """Enough tokens that the first pass over 256 rows goes back to 128 at a time, on a partition of its own, and both where groups of 192 pad nothing less;
-    keys off a 16-byte boundary."""
+@pytest.mark.parametrize("heads,N", [(130, 16411), (88, 24001)])
+def test_scores_of_tall_row_groups_over_many_ranges(gpu, heads, N, R, off):
+    """Enough tokens that both passes go back to 128 rows at a time where groups of 192 pad nothing less, and in the longer heads the first pass over 256
+    rows, on a partition of its own; keys off a 16-byte boundary."""
     import torch
     from paper_2604_13349_amd import binding as Bd
-    heads, N = 130, 16411
     g = torch.Generator(device="cuda").manual_seed(7)
     held = torch.randn(heads * N * 128 + 8, generator=g, device="cuda").bfloat16()
     held[: 128 * 5] *= 8
@@ -1792,7 +1792,7 @@ def test_scores_of_tall_row_groups_over_many_ranges(gpu, R, off):
     Q = torch.randn((heads, 1, R, 128), generator=g, device="cuda").bfloat16()
     sc, lse = Bd.score(K, Q)
     torch.cuda.synchronize()
-    for h in (0, 63, 129):
+    for h in (0, 63, heads - 1):
         k, q = K[h, 0].double(), Q[h, 0].double()
         x = torch.matmul(q, k.t().contiguous()) / 128 ** 0.5
         want = torch.logsumexp(x, 1)

@@ -12,7 +12,7 @@
 //   4. rbar, Delta, delta and Eq. 7.
 //
 // What bounds it is latency: chains of small products with a barrier each (1600 cycles, of which the matrix cores work 500 for eight columns, 800 for
-// sixteen) and the small problems on one wave (6500 cycles a step for eight columns, 10000 for sixteen, a sweep of rotations 2000 and 4500 of them).
+// sixteen) and the small problems on one wave (6500 cycles a step for eight columns, 14000 for sixteen, a sweep of rotations 2000 and 4500 of them).
 // At m = 96, k = 2 a workgroup alone on its compute unit takes 50 us: G 4, the projection 8, sixteen products 12, four small problems 12 with 5 around
 // them, the rest loads and the tail; two that share one take 73, most of the difference in the projection (14), which fills the vector ALU, the matrix
 // cores and LDS in turn, and so 288 heads on 256 compute units take 73 where 256 take 54.  With the middle parts in the block's free columns, a sweep

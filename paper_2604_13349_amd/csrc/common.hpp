@@ -171,11 +171,11 @@ inline Workspace carve(const Dims& m, int max_budget, int rank) {
       if (full <= w.tiles_per_range + 2) { w.tiles_per_range = own; w.tiles_per_head = (SH + own - 1) / own * own; }
     }
     w.nranges = (int)(((long)m.heads * w.tiles_per_head + w.tiles_per_range - 1) / w.tiles_per_range);
-    // First pass over 256 rows at once or 128 at a time: for the longest heads, and thousands of tokens to a workgroup, operands from LDS cost a little
-    // more than a second pass over K through the first-level cache.  Both passes, us, at once and in parts, 256 rows, 288 heads of 4096, 8192, 12000, 20000, 24000,
-    // 32768 tokens 194 - 200, 382 - 387, 558 - 566, 932 - 930, 1120 - 1106, 1527 - 1505; 512 heads of 4096 331 - 353; 96 of 12000, 32768 184 - 186, 508 - 508; 512 rows,
-    // 512 of 2048 322 - 353, 288 of 8192, 20000 704 - 715, 1714 - 1714, 144 of 32768 1393 - 1389; 768 rows, 288 of 20000 2528 - 2550, 96 of 32768 1368 - 1359.  The second
-    // pass is ahead throughout, and so is 192 rows at once.
+    // First pass over 256 rows at once or 128 at a time: for the longest heads, and thousands of tokens to a workgroup, operands from LDS cost a
+    // little more than a second pass over K through the first-level cache.  Both passes, us, at once and in parts: 256 rows, 288 heads of 4096, 8192,
+    // 12000, 20000, 24000, 32768 tokens 194 - 200, 382 - 387, 558 - 566, 932 - 930, 1120 - 1106, 1527 - 1505; 512 heads of 4096 331 - 353; 96 of 12000, 32768
+    // 184 - 186, 508 - 508; 512 rows, 512 heads of 2048 322 - 353, 288 of 8192, 20000 704 - 715, 1714 - 1714, 144 of 32768 1393 - 1389; 768 rows, 288 of 20000
+    // 2528 - 2550, 96 of 32768 1368 - 1359.  The second pass is ahead throughout, and so is 192 rows at once.
     w.narrow_stats = tall == 256 && m.N >= 24000 && (long)w.tiles_per_range * kScoreTallStep >= 4096;
     if (w.narrow_stats) {
       w.stats_rgroups = (m.R + 127) / 128;

@@ -10,7 +10,7 @@
 // present one; while a wave waits at a step's barrier the other workgroup's on the same SIMD goes on.
 //
 // Where there are thousands of tokens per workgroup: K from memory and the products beside each other, at a clock that falls with the power drawn (second
-// pass, 288 heads of 32768 tokens: K once, 1.33 million cycles, the matrix pipe busy in 0.44 of them; 666 us at 2.0 GHz after a pause, 727 at 1.8 in a
+// pass, 288 heads of 32768 tokens: K once, 1.3 million cycles, the matrix pipe busy in 0.45 of them; 690 us at 1.9 GHz after a pause, 740 at 1.8 in a
 // row of calls).  Else the loads, the waits at the steps and, with few heads, the fold of the partials.  Both passes, us, pairs of 128-row groups (192
 // rows padded to them) and this:
 //   256 rows  288 heads of 128, 2048, 8192 tokens 45 - 19, 113 - 98, 394 - 390    96 of 9000 147 - 133    8 of 2048 28 - 16
